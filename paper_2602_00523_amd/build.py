@@ -1,4 +1,4 @@
-"""Build libsage_hip.so (HIP, gfx950 only) in-tree with hipcc.  `python -m paper_2602_00523_amd.build`."""
+"""Build libsage_hip.so (HIP, gfx950 only) and the native argument binding in-tree.  `python -m paper_2602_00523_amd.build`."""
 from __future__ import annotations
 
 import os
@@ -11,6 +11,7 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libsage_hip.so")
+BINDING = os.path.join(HERE, "_binding.so")
 
 SOURCES = ["entropy_topk.hip", "build_tree.hip", "tree_attention.hip", "tree_attention_f32.hip",
            "tree_attention_bf16.hip", "verify_accept.hip", "commit_history.hip", "lm_head_topk.hip", "fused_steps.hip"]
@@ -84,10 +85,27 @@ def _check_no_scratch(src: str, lines: list, kernels: tuple) -> list:
     return rest
 
 
+def _build_binding() -> None:
+    """The Python side of the ABI: a plain C++ extension module against torch's headers (no device code in it)."""
+    import sysconfig
+    import torch
+    from torch.utils.cpp_extension import include_paths
+    torch_lib = os.path.join(os.path.dirname(torch.__file__), "lib")
+    inc = [os.path.join(ROOT, "include"), sysconfig.get_paths()["include"], "/opt/rocm/include", *include_paths()]
+    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
+           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", *(f"-I{p}" for p in inc),
+           os.path.join(CSRC, "python_binding.cpp"), "-o", BINDING, f"-L{torch_lib}", "-ltorch_python", "-ltorch_cpu", "-lc10", "-lc10_hip"]
+    res = subprocess.run(cmd, capture_output=True, text=True)
+    if res.returncode != 0:
+        raise RuntimeError(f"g++ failed for python_binding.cpp:\n{res.stderr}")
+
+
 def build(verbose: bool = False) -> str:
     os.makedirs(OBJ, exist_ok=True)
     with ThreadPoolExecutor(max_workers=6) as ex:
+        binding = ex.submit(_build_binding)
         objs = list(ex.map(lambda s: _compile(s, verbose), SOURCES))
+        binding.result()
     subprocess.check_call([hipcc(), "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB, *objs])
     return LIB
 

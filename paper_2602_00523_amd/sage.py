@@ -1,4 +1,4 @@
-"""Thin ctypes binding of libsage_hip.so (include/sage.h): same names, argument marshalling only.
+"""Thin binding of libsage_hip.so (include/sage.h): same names, argument marshalling only.
 
 Tensors are torch CUDA(HIP) tensors used as device buffers; nothing here computes anything.  The library is
 loaded on first use and a missing library is an error (there is no fallback path of any kind).
@@ -8,10 +8,11 @@ from __future__ import annotations
 import ctypes
 import os
 
-import torch
+import torch  # noqa: F401  (its libraries have to be loaded before the binding's)
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.environ.get("SAGE_HIP_LIBRARY") or os.path.join(_HERE, "libsage_hip.so")   # the in-tree build unless told otherwise
+BINDING_PATH = os.path.join(_HERE, "_binding.so")           # argument marshalling in native code (csrc/python_binding.cpp)
 MAX_NODES = 64
 F32, BF16 = 0, 1
 STATUS = {0: "OK", 1: "INVALID_ARG", 2: "UNSUPPORTED", 3: "WORKSPACE_TOO_SMALL", 4: "LAUNCH_FAILED"}
@@ -92,28 +93,6 @@ def lib():
     return _lib
 
 
-def _ptr(t):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
-
-
-def _stream(stream=None):
-    s = torch.cuda.current_stream() if stream is None else stream
-    return ctypes.c_void_p(s.cuda_stream)
-
-
-def _dtype_code(t: torch.Tensor) -> int:
-    if t.dtype == torch.float32:
-        return F32
-    if t.dtype == torch.bfloat16:
-        return BF16
-    raise TypeError("float32 or bfloat16 expected")
-
-
-def _check(call: str, rc: int):
-    if rc != 0:
-        raise SageError(call, rc)
-
-
 def tree_params(d_min, d_max, w_min, w_max, k, n_max) -> TreeParams:
     return TreeParams(d_min, d_max, w_min, w_max, k, n_max)
 
@@ -130,251 +109,131 @@ def sage_tree_attention_workspace_bytes(dtype_code: int, B: int, Hq: int, Hkv: i
     return int(lib().sage_tree_attention_workspace_bytes(dtype_code, B, Hq, Hkv, d, max_kv_len))
 
 
-def _nbytes(t) -> int:
-    return 0 if t is None else t.numel() * t.element_size()
+# ---- the calls: Python parameters, and where each C argument comes from ------------------------------------
+# Items of the second string, one per C argument in the order of include/sage.h: ptr (a tensor's address; None = null),
+# nbytes, dtype (float32 / bfloat16), sizeN / strideN of a tensor, int, float, struct, stream (None = the current one);
+# dimN, unitN, sameN and sametype only check.  csrc/python_binding.cpp turns them into native calls.
+
+_ATT = "Q Kc Vc Kt Vt O kv_start kv_len max_kv_len kv_token_stride kv_head_stride anc_mask n_nodes scale"
+_ATT_HEAD = ("dim4:Q ptr:Q ptr:Kc ptr:Vc ptr:Kt ptr:Vt ptr:O dtype:Q size0:Q size2:Q size2:Kt size3:Q ptr:kv_start ptr:kv_len "
+             "int:max_kv_len int:kv_token_stride int:kv_head_stride ptr:anc_mask ptr:n_nodes ")
+_ROW = "entropy topk_idx topk_prob topk_renorm topk_entropy alpha"
+_ROW_PTRS = " ".join(f"ptr:{n}" for n in _ROW.split()) + " "
+_TREE = "n_nodes parent depth rank anc_mask cum_prob=None"
+_TREE_PTRS = "ptr:n_nodes ptr:parent ptr:depth ptr:rank ptr:anc_mask ptr:cum_prob ptr:node_token "
+_CACHE = "Kt Vt Kc Vc kv_start kv_len kv_capacity kv_token_stride kv_head_stride"
+_CACHE_PTRS = "ptr:Kt ptr:Vt ptr:Kc ptr:Vc dtype:Kt "
+_CACHE_POS = "ptr:kv_start ptr:kv_len int:kv_capacity int:kv_token_stride int:kv_head_stride "
+_ACC_PTRS = "ptr:accept_len ptr:best_node ptr:path_nodes ptr:out_tokens "
+_SLICES_VERIFY = ("slices vocab token parent depth anc_mask n_nodes path_cap entropy target_argmax accept_len best_node path_nodes "
+                  "out_tokens")
+_SLICES_VERIFY_PTRS = ("ptr:slices int:vocab ptr:token ptr:parent ptr:depth ptr:anc_mask ptr:n_nodes size0:n_nodes int:path_cap "
+                       "ptr:entropy ptr:target_argmax " + _ACC_PTRS)
+_HISTORY_TAIL = "ptr:hist ptr:count ptr:d_max_in ptr:d_max_out ptr:avg_out stream:stream"
+_LOGITS = "dim2:logits unit1:logits ptr:logits dtype:logits size0:logits size1:logits stride0:logits int:k "
+
+_CALLS = {
+    "sage_entropy_topk": (
+        f"logits k {_ROW} workspace n_valid=None rows_per_group=1 stream=None",
+        _LOGITS + "ptr:n_valid int:rows_per_group " + _ROW_PTRS + "ptr:workspace nbytes:workspace stream:stream"),
+    "sage_entropy_topk_slices": (
+        "logits k workspace n_valid=None rows_per_group=1 stream=None",
+        _LOGITS + "ptr:n_valid int:rows_per_group ptr:workspace nbytes:workspace stream:stream"),
+    "sage_entropy_topk_slices_pair": (
+        "logits_a n_valid_a rows_per_group_a workspace_a logits_b k_b workspace_b stream=None",
+        "dim2:logits_a dim2:logits_b same1:logits_a,logits_b sametype:logits_a,logits_b unit1:logits_a unit1:logits_b "
+        "ptr:logits_a size0:logits_a stride0:logits_a ptr:n_valid_a int:rows_per_group_a ptr:workspace_a nbytes:workspace_a "
+        "ptr:logits_b size0:logits_b stride0:logits_b int:k_b ptr:workspace_b nbytes:workspace_b dtype:logits_a size1:logits_a "
+        "stream:stream"),
+    "sage_build_tree": (
+        f"topk_renorm alpha params {_TREE} topk_idx=None node_token=None stream=None d_max_seq=None",
+        "dim2:topk_renorm ptr:topk_renorm ptr:alpha ptr:topk_idx size0:topk_renorm size1:topk_renorm struct:params ptr:d_max_seq "
+        + _TREE_PTRS + "stream:stream"),
+    "sage_build_tree_from_slices": (
+        f"slices vocab params {_ROW} {_TREE} node_token=None stream=None d_max_seq=None",
+        "dim2:topk_idx ptr:slices int:vocab size0:topk_idx size1:topk_idx struct:params ptr:d_max_seq " + _ROW_PTRS + _TREE_PTRS
+        + "stream:stream"),
+    "sage_tree_attention": (
+        f"{_ATT} workspace stream=None first_node=None",
+        _ATT_HEAD + "ptr:first_node float:scale ptr:workspace nbytes:workspace stream:stream"),
+    "sage_tree_attention_static": (f"{_ATT} stream=None", _ATT_HEAD + "float:scale stream:stream"),
+    "sage_tree_attention_with_plan": (                     # one draft row per sequence: the batch size travels once
+        f"{_ATT} workspace slices vocab params {_ROW} next_n_nodes next_parent next_depth next_rank next_anc_mask next_cum_prob=None "
+        "next_node_token=None stream=None d_max_seq=None",
+        _ATT_HEAD + "float:scale ptr:workspace nbytes:workspace dim2:topk_idx same0:Q,topk_idx ptr:slices int:vocab size1:topk_idx "
+        "struct:params ptr:d_max_seq " + _ROW_PTRS + "ptr:next_n_nodes ptr:next_parent ptr:next_depth ptr:next_rank "
+        "ptr:next_anc_mask ptr:next_cum_prob ptr:next_node_token stream:stream"),
+    "sage_verify_accept": (
+        "token target_argmax parent depth anc_mask n_nodes path_cap accept_len best_node path_nodes out_tokens stream=None",
+        "ptr:token ptr:target_argmax ptr:parent ptr:depth ptr:anc_mask ptr:n_nodes size0:n_nodes int:path_cap " + _ACC_PTRS
+        + "stream:stream"),
+    "sage_verify_accept_from_slices": (f"{_SLICES_VERIFY} stream=None", _SLICES_VERIFY_PTRS + "stream:stream"),
+    "sage_verify_accept_close_from_slices": (
+        f"{_SLICES_VERIFY} {_CACHE} hist count d_max_in d_max_out lo hi d_floor d_cap avg_out=None stream=None",
+        _SLICES_VERIFY_PTRS + "dim4:Kt dim2:hist " + _CACHE_PTRS + "size2:Kt size3:Kt " + _CACHE_POS
+        + "size1:hist float:lo float:hi int:d_floor int:d_cap " + _HISTORY_TAIL),
+    "sage_commit_path": (
+        f"{_CACHE} path_nodes accept_len stream=None",
+        "dim4:Kt " + _CACHE_PTRS + "size0:Kt size2:Kt size3:Kt " + _CACHE_POS + "ptr:path_nodes ptr:accept_len size1:path_nodes "
+        "stream:stream"),
+    "sage_advance_kv_len": (
+        "kv_len accept_len kv_capacity stream=None",
+        "ptr:kv_len ptr:accept_len size0:kv_len int:kv_capacity stream:stream"),
+    "sage_update_history": (
+        "accept_len hist count d_max lo hi d_floor d_cap avg_out=None stream=None",
+        "dim2:hist ptr:accept_len size0:hist size1:hist float:lo float:hi int:d_floor int:d_cap ptr:hist ptr:count ptr:d_max "
+        "ptr:avg_out stream:stream"),
+    "sage_close_step": (
+        f"{_CACHE} path_nodes accept_len hist count d_max_in d_max_out lo hi d_floor d_cap avg_out=None stream=None",
+        "dim4:Kt dim2:hist " + _CACHE_PTRS + "size0:Kt size2:Kt size3:Kt " + _CACHE_POS + "ptr:path_nodes ptr:accept_len "
+        "size1:path_nodes size1:hist float:lo float:hi int:d_floor int:d_cap " + _HISTORY_TAIL),
+    "sage_lm_head_topk": (
+        f"hidden weight k {_ROW} workspace n_valid=None rows_per_group=1 stream=None",
+        "dim2:hidden ptr:hidden ptr:weight dtype:hidden size0:hidden size1:hidden size0:weight stride0:hidden stride0:weight int:k "
+        "ptr:n_valid int:rows_per_group " + _ROW_PTRS + "ptr:workspace nbytes:workspace stream:stream"),
+}
+
+_native = {}
 
 
-# ---- argument marshalling: tensors -> the C argument list of each call -----------------------------------
-
-def _args_entropy_topk(logits, k, entropy, topk_idx, topk_prob, topk_renorm, topk_entropy, alpha, workspace,
-                       n_valid=None, rows_per_group=1, stream=None):
-    rows, vocab = logits.shape
-    assert logits.stride(1) == 1
-    return [_ptr(logits), _dtype_code(logits), rows, vocab, logits.stride(0), k, _ptr(n_valid), rows_per_group,
-            _ptr(entropy), _ptr(topk_idx), _ptr(topk_prob), _ptr(topk_renorm), _ptr(topk_entropy), _ptr(alpha),
-            _ptr(workspace), _nbytes(workspace), _stream(stream)]
-
-
-def _args_build_tree(topk_renorm, alpha, params: TreeParams, n_nodes, parent, depth, rank, anc_mask, cum_prob=None,
-                     topk_idx=None, node_token=None, stream=None, d_max_seq=None):
-    B, k = topk_renorm.shape
-    return [_ptr(topk_renorm), _ptr(alpha), _ptr(topk_idx), B, k, ctypes.byref(params), _ptr(d_max_seq), _ptr(n_nodes),
-            _ptr(parent), _ptr(depth), _ptr(rank), _ptr(anc_mask), _ptr(cum_prob), _ptr(node_token), _stream(stream)]
+def _load_native(name: str):
+    """The native call `name` (all of them are made on first use, then stand in this module under their own names)."""
+    if not _native:
+        if not os.path.exists(BINDING_PATH):
+            raise SageError(f"{BINDING_PATH} is missing: run `python -m paper_2602_00523_amd.build`", -1)
+        from . import _binding
+        L = lib()
+        made = {n: _binding.make(n, ctypes.cast(getattr(L, n), ctypes.c_void_p).value, params, args, SageError)
+                for n, (params, args) in _CALLS.items()}
+        globals().update(made)
+        _native.update(made)
+    return _native[name]
 
 
-def _args_attention_common(Q, Kc, Vc, Kt, Vt, O, kv_start, kv_len, max_kv_len, kv_token_stride, kv_head_stride, anc_mask,
-                           n_nodes, scale, workspace, stream):
-    """The argument list the three attention entry points share (without first_node, which only the plain call has)."""
-    B, _, Hq, d = Q.shape
-    Hkv = Kt.shape[2]
-    return [_ptr(Q), _ptr(Kc), _ptr(Vc), _ptr(Kt), _ptr(Vt), _ptr(O), _dtype_code(Q), B, Hq, Hkv, d, _ptr(kv_start),
-            _ptr(kv_len), max_kv_len, kv_token_stride, kv_head_stride, _ptr(anc_mask), _ptr(n_nodes), scale,
-            _ptr(workspace), _nbytes(workspace), _stream(stream)]
+def _first_use(name: str):
+    def call(*a, **kw):
+        return _load_native(name)(*a, **kw)
+    call.__name__ = call.__qualname__ = name
+    call.__doc__ = f"{name}({', '.join(_CALLS[name][0].split())}): see include/sage.h"
+    return call
 
 
-def _args_tree_attention(Q, Kc, Vc, Kt, Vt, O, kv_start, kv_len, max_kv_len, kv_token_stride, kv_head_stride, anc_mask,
-                         n_nodes, scale, workspace, stream=None, first_node=None):
-    att = _args_attention_common(Q, Kc, Vc, Kt, Vt, O, kv_start, kv_len, max_kv_len, kv_token_stride, kv_head_stride, anc_mask,
-                                 n_nodes, scale, workspace, stream)
-    return att[:18] + [_ptr(first_node)] + att[18:]    # first_node follows n_nodes
-
-
-def _args_tree_attention_static(Q, Kc, Vc, Kt, Vt, O, kv_start, kv_len, max_kv_len, kv_token_stride, kv_head_stride, anc_mask,
-                                n_nodes, scale, stream=None):
-    att = _args_attention_common(Q, Kc, Vc, Kt, Vt, O, kv_start, kv_len, max_kv_len, kv_token_stride, kv_head_stride, anc_mask,
-                                 n_nodes, scale, None, stream)
-    return att[:-3] + att[-1:]                         # no workspace pair
-
-
-def _args_tree_attention_with_plan(Q, Kc, Vc, Kt, Vt, O, kv_start, kv_len, max_kv_len, kv_token_stride, kv_head_stride, anc_mask,
-                                   n_nodes, scale, workspace, slices, vocab, params: TreeParams, entropy, topk_idx, topk_prob,
-                                   topk_renorm, topk_entropy, alpha, next_n_nodes, next_parent, next_depth, next_rank,
-                                   next_anc_mask, next_cum_prob=None, next_node_token=None, stream=None, d_max_seq=None):
-    att = _args_attention_common(Q, Kc, Vc, Kt, Vt, O, kv_start, kv_len, max_kv_len, kv_token_stride, kv_head_stride, anc_mask,
-                                 n_nodes, scale, workspace, stream)
-    plan = _args_build_tree_from_slices(slices, vocab, params, entropy, topk_idx, topk_prob, topk_renorm, topk_entropy, alpha,
-                                        next_n_nodes, next_parent, next_depth, next_rank, next_anc_mask, next_cum_prob,
-                                        next_node_token, stream, d_max_seq)
-    assert plan[2] == att[7], "one draft row per sequence"
-    return att[:-1] + plan[:2] + plan[3:]              # the batch size travels once
-
-
-def _args_verify_accept(token, target_argmax, parent, depth, anc_mask, n_nodes, path_cap, accept_len, best_node,
-                        path_nodes, out_tokens, stream=None):
-    B = n_nodes.shape[0]
-    return [_ptr(token), _ptr(target_argmax), _ptr(parent), _ptr(depth), _ptr(anc_mask), _ptr(n_nodes), B, path_cap,
-            _ptr(accept_len), _ptr(best_node), _ptr(path_nodes), _ptr(out_tokens), _stream(stream)]
-
-
-def _args_commit_path(Kt, Vt, Kc, Vc, kv_start, kv_len, kv_capacity, kv_token_stride, kv_head_stride, path_nodes,
-                      accept_len, stream=None):
-    B, _, Hkv, d = Kt.shape
-    return [_ptr(Kt), _ptr(Vt), _ptr(Kc), _ptr(Vc), _dtype_code(Kt), B, Hkv, d, _ptr(kv_start), _ptr(kv_len), kv_capacity,
-            kv_token_stride, kv_head_stride, _ptr(path_nodes), _ptr(accept_len), path_nodes.shape[1], _stream(stream)]
-
-
-def _args_advance_kv_len(kv_len, accept_len, kv_capacity, stream=None):
-    return [_ptr(kv_len), _ptr(accept_len), kv_len.shape[0], kv_capacity, _stream(stream)]
-
-
-def _args_update_history(accept_len, hist, count, d_max, lo, hi, d_floor, d_cap, avg_out=None, stream=None):
-    B, window = hist.shape
-    return [_ptr(accept_len), B, window, lo, hi, d_floor, d_cap, _ptr(hist), _ptr(count), _ptr(d_max), _ptr(avg_out),
-            _stream(stream)]
-
-
-def _args_lm_head_topk(hidden, weight, k, entropy, topk_idx, topk_prob, topk_renorm, topk_entropy, alpha, workspace,
-                       n_valid=None, rows_per_group=1, stream=None):
-    rows, dim = hidden.shape
-    vocab = weight.shape[0]
-    return [_ptr(hidden), _ptr(weight), _dtype_code(hidden), rows, dim, vocab, hidden.stride(0), weight.stride(0), k,
-            _ptr(n_valid), rows_per_group, _ptr(entropy), _ptr(topk_idx), _ptr(topk_prob), _ptr(topk_renorm),
-            _ptr(topk_entropy), _ptr(alpha), _ptr(workspace), _nbytes(workspace), _stream(stream)]
-
-
-def _args_entropy_topk_slices(logits, k, workspace, n_valid=None, rows_per_group=1, stream=None):
-    rows, vocab = logits.shape
-    assert logits.stride(1) == 1
-    return [_ptr(logits), _dtype_code(logits), rows, vocab, logits.stride(0), k, _ptr(n_valid), rows_per_group,
-            _ptr(workspace), _nbytes(workspace), _stream(stream)]
-
-
-def _args_entropy_topk_slices_pair(logits_a, n_valid_a, rows_per_group_a, workspace_a, logits_b, k_b, workspace_b, stream=None):
-    rows_a, vocab = logits_a.shape
-    rows_b, vocab_b = logits_b.shape
-    assert vocab_b == vocab and logits_a.dtype == logits_b.dtype and logits_a.stride(1) == 1 and logits_b.stride(1) == 1
-    return [_ptr(logits_a), rows_a, logits_a.stride(0), _ptr(n_valid_a), rows_per_group_a, _ptr(workspace_a), _nbytes(workspace_a),
-            _ptr(logits_b), rows_b, logits_b.stride(0), k_b, _ptr(workspace_b), _nbytes(workspace_b), _dtype_code(logits_a),
-            vocab, _stream(stream)]
-
-
-def _args_build_tree_from_slices(slices, vocab, params: TreeParams, entropy, topk_idx, topk_prob, topk_renorm, topk_entropy,
-                                 alpha, n_nodes, parent, depth, rank, anc_mask, cum_prob=None, node_token=None, stream=None,
-                                 d_max_seq=None):
-    B, k = topk_idx.shape
-    return [_ptr(slices), vocab, B, k, ctypes.byref(params), _ptr(d_max_seq), _ptr(entropy), _ptr(topk_idx), _ptr(topk_prob),
-            _ptr(topk_renorm), _ptr(topk_entropy), _ptr(alpha), _ptr(n_nodes), _ptr(parent), _ptr(depth), _ptr(rank),
-            _ptr(anc_mask), _ptr(cum_prob), _ptr(node_token), _stream(stream)]
-
-
-def _args_verify_accept_from_slices(slices, vocab, token, parent, depth, anc_mask, n_nodes, path_cap, entropy, target_argmax,
-                                    accept_len, best_node, path_nodes, out_tokens, stream=None):
-    B = n_nodes.shape[0]
-    return [_ptr(slices), vocab, _ptr(token), _ptr(parent), _ptr(depth), _ptr(anc_mask), _ptr(n_nodes), B, path_cap,
-            _ptr(entropy), _ptr(target_argmax), _ptr(accept_len), _ptr(best_node), _ptr(path_nodes), _ptr(out_tokens),
-            _stream(stream)]
-
-
-def _args_close_step(Kt, Vt, Kc, Vc, kv_start, kv_len, kv_capacity, kv_token_stride, kv_head_stride, path_nodes, accept_len,
-                     hist, count, d_max_in, d_max_out, lo, hi, d_floor, d_cap, avg_out=None, stream=None):
-    B, _, Hkv, d = Kt.shape
-    return [_ptr(Kt), _ptr(Vt), _ptr(Kc), _ptr(Vc), _dtype_code(Kt), B, Hkv, d, _ptr(kv_start), _ptr(kv_len), kv_capacity,
-            kv_token_stride, kv_head_stride, _ptr(path_nodes), _ptr(accept_len), path_nodes.shape[1], hist.shape[1], lo, hi,
-            d_floor, d_cap, _ptr(hist), _ptr(count), _ptr(d_max_in), _ptr(d_max_out), _ptr(avg_out), _stream(stream)]
-
-
-def _args_verify_accept_close_from_slices(slices, vocab, token, parent, depth, anc_mask, n_nodes, path_cap, entropy, target_argmax,
-                                          accept_len, best_node, path_nodes, out_tokens, Kt, Vt, Kc, Vc, kv_start, kv_len,
-                                          kv_capacity, kv_token_stride, kv_head_stride, hist, count, d_max_in, d_max_out, lo, hi,
-                                          d_floor, d_cap, avg_out=None, stream=None):
-    B = n_nodes.shape[0]
-    _, _, Hkv, d = Kt.shape
-    return [_ptr(slices), vocab, _ptr(token), _ptr(parent), _ptr(depth), _ptr(anc_mask), _ptr(n_nodes), B, path_cap,
-            _ptr(entropy), _ptr(target_argmax), _ptr(accept_len), _ptr(best_node), _ptr(path_nodes), _ptr(out_tokens),
-            _ptr(Kt), _ptr(Vt), _ptr(Kc), _ptr(Vc), _dtype_code(Kt), Hkv, d, _ptr(kv_start), _ptr(kv_len), kv_capacity,
-            kv_token_stride, kv_head_stride, hist.shape[1], lo, hi, d_floor, d_cap, _ptr(hist), _ptr(count), _ptr(d_max_in),
-            _ptr(d_max_out), _ptr(avg_out), _stream(stream)]
-
-
-_MARSHAL = {"sage_close_step": _args_close_step,
-            "sage_tree_attention_with_plan": _args_tree_attention_with_plan,
-            "sage_verify_accept_close_from_slices": _args_verify_accept_close_from_slices,
-            "sage_entropy_topk_slices": _args_entropy_topk_slices,
-            "sage_entropy_topk_slices_pair": _args_entropy_topk_slices_pair,
-            "sage_build_tree_from_slices": _args_build_tree_from_slices,
-            "sage_verify_accept_from_slices": _args_verify_accept_from_slices,
-            "sage_entropy_topk": _args_entropy_topk, "sage_build_tree": _args_build_tree,
-            "sage_tree_attention": _args_tree_attention, "sage_tree_attention_static": _args_tree_attention_static,
-            "sage_verify_accept": _args_verify_accept,
-            "sage_commit_path": _args_commit_path, "sage_advance_kv_len": _args_advance_kv_len,
-            "sage_update_history": _args_update_history, "sage_lm_head_topk": _args_lm_head_topk}
-
-
-def sage_entropy_topk(*a, **kw):
-    _check("sage_entropy_topk", lib().sage_entropy_topk(*_args_entropy_topk(*a, **kw)))
-
-
-def sage_build_tree(*a, **kw):
-    _check("sage_build_tree", lib().sage_build_tree(*_args_build_tree(*a, **kw)))
-
-
-def sage_tree_attention(*a, **kw):
-    _check("sage_tree_attention", lib().sage_tree_attention(*_args_tree_attention(*a, **kw)))
-
-
-def sage_tree_attention_static(*a, **kw):
-    _check("sage_tree_attention_static", lib().sage_tree_attention_static(*_args_tree_attention_static(*a, **kw)))
+for _name in _CALLS:
+    globals()[_name] = _first_use(_name)
+del _name
 
 
 def sage_tree_attention_static_scratch_bytes() -> int:
     return int(lib().sage_tree_attention_static_scratch_bytes())
 
 
-def sage_tree_attention_with_plan(*a, **kw):
-    _check("sage_tree_attention_with_plan", lib().sage_tree_attention_with_plan(*_args_tree_attention_with_plan(*a, **kw)))
-
-
-def sage_verify_accept(*a, **kw):
-    _check("sage_verify_accept", lib().sage_verify_accept(*_args_verify_accept(*a, **kw)))
-
-
-def sage_commit_path(*a, **kw):
-    _check("sage_commit_path", lib().sage_commit_path(*_args_commit_path(*a, **kw)))
-
-
-def sage_advance_kv_len(*a, **kw):
-    _check("sage_advance_kv_len", lib().sage_advance_kv_len(*_args_advance_kv_len(*a, **kw)))
-
-
-def sage_update_history(*a, **kw):
-    _check("sage_update_history", lib().sage_update_history(*_args_update_history(*a, **kw)))
-
-
-def sage_verify_accept_close_from_slices(*a, **kw):
-    _check("sage_verify_accept_close_from_slices",
-           lib().sage_verify_accept_close_from_slices(*_args_verify_accept_close_from_slices(*a, **kw)))
-
-
-def sage_close_step(*a, **kw):
-    _check("sage_close_step", lib().sage_close_step(*_args_close_step(*a, **kw)))
-
-
-def sage_lm_head_topk(*a, **kw):
-    _check("sage_lm_head_topk", lib().sage_lm_head_topk(*_args_lm_head_topk(*a, **kw)))
-
-
-def sage_entropy_topk_slices(*a, **kw):
-    _check("sage_entropy_topk_slices", lib().sage_entropy_topk_slices(*_args_entropy_topk_slices(*a, **kw)))
-
-
-def sage_entropy_topk_slices_pair(*a, **kw):
-    _check("sage_entropy_topk_slices_pair", lib().sage_entropy_topk_slices_pair(*_args_entropy_topk_slices_pair(*a, **kw)))
-
-
-def sage_build_tree_from_slices(*a, **kw):
-    _check("sage_build_tree_from_slices", lib().sage_build_tree_from_slices(*_args_build_tree_from_slices(*a, **kw)))
-
-
-def sage_verify_accept_from_slices(*a, **kw):
-    _check("sage_verify_accept_from_slices",
-           lib().sage_verify_accept_from_slices(*_args_verify_accept_from_slices(*a, **kw)))
-
-
 def prepare(name: str, *a, **kw):
     """Marshal the arguments of call `name` once and return a zero-argument callable that enqueues it.
 
-    For loops that issue the same call on the same buffers and stream many times: the per-call cost drops to
-    one foreign-function call.  The tensors (and the TreeParams object) must outlive the callable.
+    For loops that issue the same call on the same buffers and stream many times: what is left per call is the launch.
+    The callable keeps its arguments alive.
     """
-    fn = getattr(lib(), name)
-    args = _MARSHAL[name](*a, **kw)
-    keep = (a, kw)
-
-    def call(_fn=fn, _args=args, _name=name, _keep=keep):
-        rc = _fn(*_args)
-        if rc != 0:
-            raise SageError(_name, rc)
-    return call
+    return _load_native(name).bind(*a, **kw)
 
 
 def sage_build_info() -> str:
