@@ -14,7 +14,8 @@ LIB = os.path.join(HERE, "libsage_hip.so")
 BINDING = os.path.join(HERE, "_binding.so")
 
 SOURCES = ["entropy_topk.hip", "build_tree.hip", "tree_attention.hip", "tree_attention_f32.hip",
-           "tree_attention_bf16.hip", "verify_accept.hip", "commit_history.hip", "lm_head_topk.hip", "fused_steps.hip"]
+           "tree_attention_bf16.hip", "verify_accept.hip", "commit_history.hip", "lm_head_topk.hip", "lm_head_rows.hip",
+           "fused_steps.hip"]
 # packed-fp32 instructions are switched off for every translation unit; the tree rule additionally forbids
 # contraction so that its fp32 decisions are reproducible bit for bit.
 COMMON = ["--offload-arch=gfx950", "-O3", "-std=c++20", "-fPIC", "-Xclang", "-target-feature", "-Xclang",
@@ -27,7 +28,7 @@ EXTRA = {"build_tree.hip": ["-ffp-contract=off"]}
 # a register spill adds scratch loads and stores to that counter and silently breaks the count, so these translation
 # units are compiled with the resource-usage remarks on and the build fails if any of their kernels uses scratch memory.
 NO_SCRATCH = {"tree_attention_bf16.hip": ("tree_attention_bf16_kernel", "tree_attention_plan_kernel"),
-              "lm_head_topk.hip": ("lm_head_kernel",)}
+              "lm_head_topk.hip": ("lm_head_kernel",), "lm_head_rows.hip": ("lm_head_rows_kernel",)}
 
 
 def hipcc() -> str:

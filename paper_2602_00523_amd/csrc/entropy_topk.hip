@@ -416,6 +416,7 @@ inline size_t stats_bytes(int rows, int vocab) {
 namespace sage {
 
 int topk_max_units() { return 64 * MAX_OWN; }
+int topk_merge_max_units() { return 64 * MERGE_MAX_OWN; }
 
 // Pass 2 for `rows` rows whose `nunits` slices each left UnitStats and k sorted keys in stats / keys ([row][unit]).
 void topk_merge(int rows, int k, const int* n_valid, int rows_per_group, int nunits, const UnitStats* stats,
@@ -424,8 +425,11 @@ void topk_merge(int rows, int k, const int* n_valid, int rows_per_group, int nun
     if (nunits <= 256)
         hipLaunchKernelGGL(merge_kernel<4>, dim3(rows), dim3(MERGE_THREADS), 0, s, k, n_valid, rows_per_group, nunits, stats, keys,
                            entropy, topk_idx, topk_prob, topk_renorm, topk_entropy, alpha);
-    else
+    else if (nunits <= 64 * MAX_OWN)
         hipLaunchKernelGGL(merge_kernel<MAX_OWN>, dim3(rows), dim3(MERGE_THREADS), 0, s, k, n_valid, rows_per_group, nunits, stats,
+                           keys, entropy, topk_idx, topk_prob, topk_renorm, topk_entropy, alpha);
+    else
+        hipLaunchKernelGGL(merge_kernel<MERGE_MAX_OWN>, dim3(rows), dim3(MERGE_THREADS), 0, s, k, n_valid, rows_per_group, nunits, stats,
                            keys, entropy, topk_idx, topk_prob, topk_renorm, topk_entropy, alpha);
 }
 

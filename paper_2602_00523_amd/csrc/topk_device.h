@@ -10,6 +10,7 @@ namespace topk {
 constexpr int MERGE_THREADS = 256;
 constexpr int MERGE_LDS_KEYS = 6144;     // lists are staged in LDS when they fit (48 KB)
 constexpr int MAX_OWN = 16;              // lists per lane in the second pass: up to 1024 slices = 1M logits
+constexpr int MERGE_MAX_OWN = 32;        // ... in the second pass as a launch of its own (projections cut the vocabulary finer)
 
 // The wave-wide reductions of sage_internal.h, under this namespace's names.
 using sage::wave_max;

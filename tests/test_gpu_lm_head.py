@@ -99,6 +99,18 @@ def test_more_rows_than_one_block(gu, rows, rpg, n_valid):
         assert packed["entropy"][live[-1]] == alone["entropy"][0]
 
 
+@pytest.mark.parametrize("rows,dim,vocab", [
+    (65, 128, 64), (128, 128, 63),            # one tile, two steps: the shortest pass, a block of 128 slots
+    (193, 384, 2113), (257, 256, 8209),       # a last row in a block of its own; units of one and of several tiles
+    (256, 128, 66000), (70, 128, 300000)])    # units of four tiles and fewer; more slices per row than 1024
+def test_row_block_and_unit_edges(gu, rows, dim, vocab):
+    """Row blocks of 64 to 256 slots and units of one to four vocabulary tiles, at their remainders."""
+    h = wl.gaussian(rows + 1, (rows, dim), "bf16", 1.0)
+    w = wl.gaussian(vocab + 2, (vocab, dim), "bf16", 3.0 / np.sqrt(dim))
+    exact, n = check(gu, h, w, rows_checked=sorted({0, 31, 32, 63, 64, rows // 2, rows - 2, rows - 1}))
+    assert exact >= n - 1
+
+
 def test_planted_winner_and_ties(gu):
     """One vocabulary row is the hidden row itself scaled up: it must win; two identical weight rows tie exactly
     (same products, same order of accumulation), and the lower index must be reported."""
