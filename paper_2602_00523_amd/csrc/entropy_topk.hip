@@ -172,13 +172,13 @@ __global__ __launch_bounds__(THREADS) void slice_rows_kernel(const T* __restrict
 // kept as short as they can be): the same decomposition as the generic kernel below, but the rounds run on ONE
 // 32-bit word per candidate, (16-bit value code << 16) | (1024 - position in the slice), whose order is the total
 // order (value descending, index ascending) inside a slice; 0 = no candidate.  Each wave selects the k best of its
-// 256 logits, wave 0 then selects the k best of the 4k survivors held one per lane.
+// 256 logits, wave 0 then ranks the 4k survivors by counting.
 constexpr int FAST_MAX_K = 16;
 __device__ __forceinline__ void slice_topk_bf16_block(const uint16_t* __restrict__ logits, int vocab, long row_stride, int k,
                                                       const int* __restrict__ n_valid, int rows_per_group, int nunits,
                                                       UnitStats* __restrict__ stats, uint64_t* __restrict__ keys, int unit,
                                                       int row) {
-    __shared__ uint32_t s_list[WAVES * FAST_MAX_K];
+    __shared__ __align__(16) uint32_t s_list[WAVES * FAST_MAX_K];
     __shared__ float s_red[3][WAVES];
     if (!row_is_valid(row, n_valid, rows_per_group)) return;
     const int lane = threadIdx.x & 63;
@@ -210,6 +210,7 @@ __device__ __forceinline__ void slice_topk_bf16_block(const uint16_t* __restrict
         if (lane == round) mine = g;
     }
     if (lane < k) s_list[wave * k + lane] = mine;
+    else if (wave == WAVES - 1 && WAVES * k + lane - k < ((WAVES * k + 15) & ~15)) s_list[WAVES * k + lane - k] = 0;
     // a bf16 value's 32-bit code is its 16-bit code followed by sixteen zeros (non-negative) or ones (negative)
     auto full_code = [](uint32_t key) { return (key & 0xFFFF0000u) | ((key & 0x80000000u) ? 0u : 0xFFFFu); };
     const float wmax = top ? unsortable(full_code(top)) : -INFINITY;
@@ -229,18 +230,32 @@ __device__ __forceinline__ void slice_topk_bf16_block(const uint16_t* __restrict
     __syncthreads();
     if (wave != 0) return;
 
-    uint32_t key = lane < WAVES * k ? s_list[lane] : 0u;
-    uint32_t out = 0;
-    for (int round = 0; round < k; ++round) {
-        const uint32_t g = wave_max_u32(key);
-        key = (key == g) ? 0u : key;
-        if (lane == round) out = g;
+    // ---- wave 0: a lane per survivor finds its place in the slice's list (distinct words, 0 = none), by counting the survivors
+    // above it (about 600 cycles) or, for very short lists, by k rounds of a maximum (about 110 each)
+    const uint32_t key = lane < WAVES * k ? s_list[lane] : 0u;
+    int above = 0;
+    if (k <= 5) {
+        uint32_t rest = key;
+        above = k;
+        for (int round = 0; round < k; ++round) {
+            const uint32_t g = wave_max_u32(rest);
+            if (rest == g) { above = round; rest = 0u; }
+        }
+    } else {
+        for (int o = 0; o < WAVES * k; o += 16) {            // (the list is padded with zeros to whole pieces of 16)
+            uint4 q[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) q[u] = *reinterpret_cast<const uint4*>(s_list + o + 4 * u);
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+                above += (q[u].x > key ? 1 : 0) + (q[u].y > key ? 1 : 0) + (q[u].z > key ? 1 : 0) + (q[u].w > key ? 1 : 0);
+        }
     }
-    if (lane < k) {
-        const Key full = out ? Key{full_code(out), 0xFFFFFFFFu - static_cast<uint32_t>(unit * UNIT + UNIT - static_cast<int>(out & 0xFFFFu))}
-                             : Key{0, 0};
-        keys[(static_cast<long>(row) * nunits + unit) * k + lane] = key_pack(full);
-    }
+    uint64_t* const kout = keys + (static_cast<long>(row) * nunits + unit) * k;
+    if (key != 0 && above < k)
+        kout[above] = key_pack(Key{full_code(key), 0xFFFFFFFFu - static_cast<uint32_t>(unit * UNIT + UNIT - static_cast<int>(key & 0xFFFFu))});
+    const int present = vocab - unit * UNIT;                 // a short last slice has no more candidates than logits
+    if (lane < k && lane >= present) kout[lane] = 0;
     if (lane == 0) {
         float m = fmaxf(fmaxf(s_red[0][0], s_red[0][1]), fmaxf(s_red[0][2], s_red[0][3]));
         float z = 0.f, t = 0.f;
@@ -263,13 +278,18 @@ __global__ __launch_bounds__(THREADS) void slice_topk_bf16_kernel(const uint16_t
     slice_topk_bf16_block(logits, vocab, row_stride, k, n_valid, rows_per_group, nunits, stats, keys, blockIdx.x, blockIdx.y);
 }
 
-// Pass 1 for k > 1 (few rows, latency matters more than bandwidth): one WORKGROUP per slice, 4 logits per lane.
-// Each wave extracts the k best of its 256 logits; wave 0 then merges the four sorted lists.
+// Pass 1 for k > 1 in general (few rows, latency matters more than bandwidth): one WORKGROUP per slice, 4 logits per lane.
+// Each wave finds the value that exactly k of its 256 logits reach, for short lists by stepping down from the maximum, for
+// long ones bit by bit from the top, each bit one ballot per logit (about 20 of the 32 bits on Gaussian logits).  Equal
+// values at the threshold are admitted lowest index first.  The survivors of the four waves, in any order, are then ranked
+// by counting.
+// Selecting by k rounds of a wave-wide maximum of 64-bit keys, some 60 instructions each, made this pass arithmetic-bound:
+// 8 rows of 152064 fp32 logits took 11.6 us at k = 10, one row 36 us at k = 64.
 template <typename T>
 __device__ __forceinline__ void slice_topk_block(const T* __restrict__ logits, int vocab, long row_stride, int k,
                                                  const int* __restrict__ n_valid, int rows_per_group, int nunits,
                                                  UnitStats* __restrict__ stats, uint64_t* __restrict__ keys, int unit, int row) {
-    __shared__ uint64_t s_list[WAVES][SAGE_MAX_TOPK];
+    __shared__ __align__(16) uint64_t s_list[WAVES * SAGE_MAX_TOPK];
     __shared__ float s_red[3][WAVES];
     if (!row_is_valid(row, n_valid, rows_per_group)) return;
     const int lane = threadIdx.x & 63;
@@ -291,26 +311,81 @@ __device__ __forceinline__ void slice_topk_block(const T* __restrict__ logits, i
 #pragma unroll
         for (int e = 0; e < 4; ++e) v[e] = (e0 + e < vocab) ? Loader<T>::one(rowp + e0 + e) : -INFINITY;
     }
-    Key cand[4];
+    // What the search runs on: the value's code, which for bf16 leaves 16 bits for the (inverted) position in the slice, so
+    // that equal values differ.  0 = no candidate.
+    uint32_t code[4];
 #pragma unroll
-    for (int e = 0; e < 4; ++e) cand[e] = (e0 + e < vocab) ? make_key(v[e], e0 + e) : Key{0, 0};
-
-    Key mine = Key{0, 0};                            // lane j keeps the wave's winner of round j
-    Key top = Key{0, 0};
-    for (int round = 0; round < k; ++round) {
-        const Key best = key_max(key_max(cand[0], cand[1]), key_max(cand[2], cand[3]));
-        const Key g = wave_max_key(best);
-        if (round == 0) top = g;
-        if (!key_none(g)) {
-#pragma unroll
-            for (int e = 0; e < 4; ++e)
-                if (key_equal(cand[e], g)) cand[e] = Key{0, 0};
-        }
-        if (lane == round) mine = g;
+    for (int e = 0; e < 4; ++e) {
+        const uint32_t full = sortable(v[e]);
+        code[e] = e0 + e >= vocab ? 0u : sizeof(T) == 4 ? full : ((full & 0xFFFF0000u) | static_cast<uint32_t>(UNIT - (static_cast<int>(threadIdx.x) * 4 + e)));
     }
-    if (lane < k) s_list[wave][lane] = key_pack(mine);
+    auto reach = [&](uint32_t t) __attribute__((always_inline)) {     // how many of the wave's logits reach t (uniform)
+        return __builtin_popcountll(__ballot(code[0] >= t)) + __builtin_popcountll(__ballot(code[1] >= t)) +
+               __builtin_popcountll(__ballot(code[2] >= t)) + __builtin_popcountll(__ballot(code[3] >= t));
+    };
+    const int present = reach(1u);
+    const int want = min(k, present);
+    uint32_t thr = 1u;
+    int got = present;
+    if (got > want && k <= 8) {                      // the next smaller value, round by round (about 400 cycles each)
+        thr = 0xFFFFFFFFu;
+        got = 0;
+        while (got < want) {
+            uint32_t best = 0;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) best = max(best, code[e] < thr ? code[e] : 0u);
+            thr = __builtin_amdgcn_readfirstlane(wave_max_u32(best));
+            if (thr == 0u) break;                    // (NaNs only)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) got += __builtin_popcountll(__ballot(code[e] == thr));
+        }
+    } else if (got > want) {                         // the threshold bit by bit (about 170 cycles each, 20 of them)
+        thr = 0u;
+        for (uint32_t bit = 0x80000000u; bit != 0; bit >>= 1) {
+            const int n = reach(thr | bit);
+            if (n >= want) {
+                thr |= bit;
+                got = n;
+                if (n == want) break;
+            }
+        }
+    }
+    bool in[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) in[e] = code[e] >= thr;
+    auto below_me = [&](const bool (&f)[4]) __attribute__((always_inline)) {   // flags set in lower lanes
+        int n = 0;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const uint64_t b = __ballot(f[e]);
+            n += static_cast<int>(__builtin_amdgcn_mbcnt_hi(static_cast<uint32_t>(b >> 32), __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(b), 0u)));
+        }
+        return n;
+    };
+    if (got > want) {                                // (uniform) several logits equal the threshold: the lowest indices of them
+        bool eq[4];
+        int above = 0;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            eq[e] = code[e] == thr;
+            above += __builtin_popcountll(__ballot(code[e] > thr));
+        }
+        int nth = below_me(eq);                      // indices ascend with the lane, then with e
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            in[e] = code[e] > thr || (eq[e] && nth < want - above);
+            nth += eq[e] ? 1 : 0;
+        }
+    }
+    int at = below_me(in);
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+        if (in[e]) s_list[wave * k + at++] = key_pack(make_key(v[e], e0 + e));
+    if (lane >= want && lane < k) s_list[wave * k + lane] = 0;
+    if (wave == WAVES - 1 && WAVES * k + lane < ((WAVES * k + 15) & ~15)) s_list[WAVES * k + lane] = 0;
+    const uint32_t top = wave_max_u32(max(max(sortable(v[0]), sortable(v[1])), max(sortable(v[2]), sortable(v[3]))));
     // softmax statistics relative to the wave's maximum, combined across the four waves below
-    const float wmax = key_none(top) ? -INFINITY : key_value(top);
+    const float wmax = unsortable(top);              // (-inf where the wave has no logit)
     float Z = 0.f, Tm = 0.f;
     if (wmax > -INFINITY) {
 #pragma unroll
@@ -325,21 +400,16 @@ __device__ __forceinline__ void slice_topk_block(const T* __restrict__ logits, i
     Tm = wave_sum(Tm);
     if (lane == 0) { s_red[0][wave] = wmax; s_red[1][wave] = Z; s_red[2][wave] = Tm; }
     __syncthreads();
-    if (wave != 0) return;
-
-    // ---- wave 0: merge the four sorted lists (lane w < 4 owns list w) and the four statistics
-    int cursor = 0;
-    Key head = lane < WAVES ? key_unpack(s_list[lane][0]) : Key{0, 0};
-    Key out = Key{0, 0};
-    for (int round = 0; round < k; ++round) {
-        const Key g = wave_max_key(head);
-        if (lane == round) out = g;
-        if (lane < WAVES && !key_none(g) && key_equal(head, g)) {
-            ++cursor;
-            head = cursor < k ? key_unpack(s_list[lane][cursor]) : Key{0, 0};
-        }
+    // ---- a thread per survivor counts the survivors above it: its place in the slice's list
+    uint64_t* const kout = keys + (static_cast<long>(row) * nunits + unit) * k;
+    const int tid = threadIdx.x;
+    if (tid < WAVES * k) {
+        const uint64_t mine = s_list[tid];
+        const int above = count_above(s_list, (WAVES * k + 15) & ~15, mine);
+        if (mine != 0 && above < k) kout[above] = mine;
     }
-    if (lane < k) keys[(static_cast<long>(row) * nunits + unit) * k + lane] = key_pack(out);
+    if (tid < k && tid >= vocab - unit * UNIT) kout[tid] = 0;    // a short last slice has no more candidates than logits
+    if (wave != 0) return;
     if (lane == 0) {
         float m = fmaxf(fmaxf(s_red[0][0], s_red[0][1]), fmaxf(s_red[0][2], s_red[0][3]));
         float z = 0.f, t = 0.f;
@@ -391,6 +461,38 @@ __global__ __launch_bounds__(THREADS) void slice_pair_kernel(const T* __restrict
                         blockIdx.y, gridDim.y, static_cast<int>(blockIdx.z) - slabs_b);
 }
 
+// Pass 2 for k = 1 (the target rows): a wave per row, no LDS and no barrier.  Statistics and candidates of the row's slices
+// are requested together (one memory round trip) and reduced in registers, OWN slices per lane at a time.
+template <int OWN>
+__global__ __launch_bounds__(MERGE_THREADS) void merge_one_kernel(const int* __restrict__ n_valid, int rows_per_group, int rows, int nunits,
+                                                                  const UnitStats* __restrict__ stats, const uint64_t* __restrict__ keys,
+                                                                  float* __restrict__ entropy, int* __restrict__ topk_idx,
+                                                                  float* __restrict__ topk_prob, float* __restrict__ topk_renorm,
+                                                                  float* __restrict__ topk_entropy, float* __restrict__ alpha) {
+    const int row = blockIdx.x * (MERGE_THREADS / 64) + (threadIdx.x >> 6);
+    if (row >= rows || !row_is_valid(row, n_valid, rows_per_group)) return;
+    const int lane = threadIdx.x & 63;
+    const UnitStats* st = stats + static_cast<long>(row) * nunits;
+    const uint64_t* kk = keys + static_cast<long>(row) * nunits;
+    UnitStats u[OWN];
+    uint64_t key[OWN];
+#pragma unroll
+    for (int i = 0; i < OWN; ++i) {
+        const bool live = lane + 64 * i < nunits;
+        u[i] = live ? st[lane + 64 * i] : UnitStats{-INFINITY, 0.f, 0.f, 0.f};
+        key[i] = live ? kk[lane + 64 * i] : 0ull;
+    }
+    float m, Z, Tm;
+    combine_unit_stats<OWN>(u, lane, nunits, m, Z, Tm);
+    uint64_t best = key[0];
+#pragma unroll
+    for (int i = 1; i < OWN; ++i) best = max(best, key[i]);
+    const Key g = wave_max_key(key_unpack(best));
+    if (lane == 0 && entropy) entropy[row] = logf(Z) + Tm / Z;
+    MergedRow r;
+    finish_row(row, 1, lane, g, m, Z, topk_idx, topk_prob, topk_renorm, topk_entropy, alpha, r);
+}
+
 // Pass 2 as a launch of its own: one workgroup per row (see merge_row).
 template <int OWN>
 __global__ __launch_bounds__(MERGE_THREADS) void merge_kernel(int k, const int* __restrict__ n_valid, int rows_per_group, int nunits,
@@ -416,20 +518,28 @@ inline size_t stats_bytes(int rows, int vocab) {
 namespace sage {
 
 int topk_max_units() { return 64 * MAX_OWN; }
-int topk_merge_max_units() { return 64 * MERGE_MAX_OWN; }
+int topk_merge_max_units(int k) { return 64 * (k == 1 ? MERGE_MAX_OWN : MAX_OWN); }
 
 // Pass 2 for `rows` rows whose `nunits` slices each left UnitStats and k sorted keys in stats / keys ([row][unit]).
 void topk_merge(int rows, int k, const int* n_valid, int rows_per_group, int nunits, const UnitStats* stats,
                 const uint64_t* keys, float* entropy, int* topk_idx, float* topk_prob, float* topk_renorm,
                 float* topk_entropy, float* alpha, hipStream_t s) {
-    if (nunits <= 256)
+    if (k == 1) {
+        const dim3 grid((rows + MERGE_THREADS / 64 - 1) / (MERGE_THREADS / 64)), block(MERGE_THREADS);
+        if (nunits <= 256)
+            hipLaunchKernelGGL(merge_one_kernel<4>, grid, block, 0, s, n_valid, rows_per_group, rows, nunits, stats, keys, entropy, topk_idx,
+                               topk_prob, topk_renorm, topk_entropy, alpha);
+        else if (nunits <= 64 * MAX_OWN)
+            hipLaunchKernelGGL(merge_one_kernel<MAX_OWN>, grid, block, 0, s, n_valid, rows_per_group, rows, nunits, stats, keys, entropy,
+                               topk_idx, topk_prob, topk_renorm, topk_entropy, alpha);
+        else
+            hipLaunchKernelGGL(merge_one_kernel<MERGE_MAX_OWN>, grid, block, 0, s, n_valid, rows_per_group, rows, nunits, stats, keys,
+                               entropy, topk_idx, topk_prob, topk_renorm, topk_entropy, alpha);
+    } else if (nunits <= 64 * 4)
         hipLaunchKernelGGL(merge_kernel<4>, dim3(rows), dim3(MERGE_THREADS), 0, s, k, n_valid, rows_per_group, nunits, stats, keys,
                            entropy, topk_idx, topk_prob, topk_renorm, topk_entropy, alpha);
-    else if (nunits <= 64 * MAX_OWN)
-        hipLaunchKernelGGL(merge_kernel<MAX_OWN>, dim3(rows), dim3(MERGE_THREADS), 0, s, k, n_valid, rows_per_group, nunits, stats,
-                           keys, entropy, topk_idx, topk_prob, topk_renorm, topk_entropy, alpha);
     else
-        hipLaunchKernelGGL(merge_kernel<MERGE_MAX_OWN>, dim3(rows), dim3(MERGE_THREADS), 0, s, k, n_valid, rows_per_group, nunits, stats,
+        hipLaunchKernelGGL(merge_kernel<MAX_OWN>, dim3(rows), dim3(MERGE_THREADS), 0, s, k, n_valid, rows_per_group, nunits, stats,
                            keys, entropy, topk_idx, topk_prob, topk_renorm, topk_entropy, alpha);
 }
 

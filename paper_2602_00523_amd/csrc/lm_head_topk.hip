@@ -366,7 +366,7 @@ extern "C" int sage_lm_head_topk(const void* hidden, const void* weight, int dty
     if (workspace_bytes < sage_lm_head_topk_workspace_bytes(rows, vocab, k)) return SAGE_WORKSPACE_TOO_SMALL;
     if (rows == 0) return SAGE_OK;
     const int nunits = slices_of(vocab, rows);
-    if (nunits > sage::topk_merge_max_units()) return SAGE_UNSUPPORTED;
+    if (nunits > sage::topk_merge_max_units(k)) return SAGE_UNSUPPORTED;
     UnitStats* stats = static_cast<UnitStats*>(workspace);
     uint64_t* keys = reinterpret_cast<uint64_t*>(static_cast<char*>(workspace) +
                                                  align256(static_cast<size_t>(rows) * nunits * sizeof(UnitStats)));

@@ -10,7 +10,7 @@ namespace topk {
 constexpr int MERGE_THREADS = 256;
 constexpr int MERGE_LDS_KEYS = 6144;     // lists are staged in LDS when they fit (48 KB)
 constexpr int MAX_OWN = 16;              // lists per lane in the second pass: up to 1024 slices = 1M logits
-constexpr int MERGE_MAX_OWN = 32;        // ... in the second pass as a launch of its own (projections cut the vocabulary finer)
+constexpr int MERGE_MAX_OWN = 32;        // ... in the second pass of k = 1 as a launch of its own (projections cut the vocabulary finer)
 
 // The wave-wide reductions of sage_internal.h, under this namespace's names.
 using sage::wave_max;
@@ -58,25 +58,35 @@ __device__ __forceinline__ void combine_unit_stats(const UnitStats (&u)[OWN], in
     Tm = wave_sum(Tm);
 }
 
-// LDS of one merging workgroup.  merge_row takes any type with these members (keys, stats, row_m, row_Z; LDS_KEYS =
-// how many keys fit), so a kernel with another LDS budget can bring a smaller one.
+// LDS of one merging workgroup.  merge_row takes any type with these members (keys, pick, row_m, row_Z; LDS_KEYS = how many
+// keys fit), so a kernel with another LDS budget can bring a smaller one.
+constexpr int PICK_CANDS = 512;          // candidates that the counting selection takes
+constexpr int PICK_LISTS = 256;          // lists that they may come from
+struct PickShared {
+    alignas(16) uint64_t cand[PICK_CANDS];   // candidates for the row's k winners, any order
+    uint64_t win[SAGE_MAX_TOPK];             // the winners, in order
+    uint16_t lists[PICK_LISTS];              // the lists that hold them
+    int nlists, ncand, nkept;
+    uint32_t floor;                          // value code below which no candidate lies
+};
 template <int OWN> struct MergeShared {
     static constexpr int LDS_KEYS = MERGE_LDS_KEYS;
     uint64_t keys[MERGE_LDS_KEYS];
-    UnitStats stats[64 * OWN];
+    PickShared pick;
     float row_m, row_Z;                  // the row's maximum and sum, from the wave that combines the statistics
 };
 
-// Short form of candidate `pos` of list `unit`: 16-bit value code, then the candidate's place among all lists, inverted.
-// It orders candidates exactly like the full key when every value is a widened bf16 (the low half of such a value's
-// code is all zeros or all ones, a function of the sign) and lists are in index order with at most 16 entries each:
-// equal values then rank by (list, position in the list), which is index order.  0 = no candidate.
-constexpr int SHORT_MAX_K = 16;
-__device__ __forceinline__ bool key_is_widened_bf16(Key k) {
-    return key_none(k) || (k.hi & 0xFFFFu) == ((k.hi & 0x80000000u) ? 0u : 0xFFFFu);
-}
-__device__ __forceinline__ uint32_t short_key(Key k, int unit, int pos) {
-    return key_none(k) ? 0u : ((k.hi & 0xFFFF0000u) | (0xFFFFu - static_cast<uint32_t>(unit * SHORT_MAX_K + pos)));
+// How many of keys[0 .. n) (n a multiple of 16, LDS, 16-byte aligned) are above `mine`: broadcast reads, eight in flight.
+__device__ __forceinline__ int count_above(const uint64_t* keys, int n, uint64_t mine) {
+    int above = 0;
+    for (int o = 0; o < n; o += 16) {
+        ulonglong2 h[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) h[u] = *reinterpret_cast<const ulonglong2*>(keys + o + 2 * u);
+#pragma unroll
+        for (int u = 0; u < 8; ++u) above += (h[u].x > mine ? 1 : 0) + (h[u].y > mine ? 1 : 0);
+    }
+    return above;
 }
 
 // What wave 0 holds once a row is merged: lane j < k owns winner j (token index, probability, renormalised probability);
@@ -86,132 +96,11 @@ struct MergedRow {
     float p, q, alpha;
 };
 
-// Second pass for one row, called by all WG_THREADS threads of a workgroup (at least two waves): combine the slice
-// statistics, k-way merge of the per-slice sorted key lists, Eq. 7-9.  OWN = lists per lane (lane owns lists lane,
-// lane+64, ...); the head of every owned list stays in registers and only the lane whose list wins a round fetches its
-// next entry.  Writes the row's outputs (null pointers are skipped) and returns true in wave 0, whose lanes receive
-// `out`; the other waves only help staging and return false.  Every thread passes the same two workgroup barriers.
-template <int OWN, int WG_THREADS = MERGE_THREADS, class Shared>
-__device__ __forceinline__ bool merge_row(int row, int k, int nunits, const UnitStats* __restrict__ stats,
-                                          const uint64_t* __restrict__ keys, Shared& sh, float* __restrict__ entropy,
-                                          int* __restrict__ topk_idx, float* __restrict__ topk_prob,
-                                          float* __restrict__ topk_renorm, float* __restrict__ topk_entropy,
-                                          float* __restrict__ alpha, MergedRow& out) {
-    constexpr int THREADS = WG_THREADS;
-    uint64_t* s_keys = sh.keys;
-    UnitStats* s_stats = sh.stats;
-    const int tid = threadIdx.x;
-    const UnitStats* st = stats + static_cast<long>(row) * nunits;
-    const uint64_t* kk = keys + static_cast<long>(row) * nunits * k;
-    const int total = nunits * k;
-    const bool in_lds = total <= Shared::LDS_KEYS;
-    // ---- the whole workgroup stages statistics and lists in LDS, eight independent loads per thread at a time; while
-    //      doing so it finds out whether the short form of the keys may be used for the selection rounds
-    const bool short_possible = in_lds && k <= SHORT_MAX_K && nunits * SHORT_MAX_K < 0x10000;
-    int all_bf16 = 1;
-    for (int c = tid; c < nunits; c += THREADS) s_stats[c] = st[c];
-    if (in_lds) {
-        for (int i0 = tid; i0 < total; i0 += THREADS * 8) {
-            uint64_t tmp[8];
-#pragma unroll
-            for (int j = 0; j < 8; ++j) tmp[j] = (i0 + j * THREADS < total) ? kk[i0 + j * THREADS] : 0;
-#pragma unroll
-            for (int j = 0; j < 8; ++j) {
-                const int at = i0 + j * THREADS;
-                if (at < total) {
-                    s_keys[at] = tmp[j];
-                    all_bf16 &= key_is_widened_bf16(key_unpack(tmp[j])) ? 1 : 0;
-                }
-            }
-        }
-    }
-    const bool use_short = __syncthreads_and(all_bf16) != 0 && short_possible;
-    // Two serial chains that do not depend on each other run side by side: wave 1 combines the slice statistics (and
-    // stores the row's entropy), wave 0 selects the k winners; they meet before Eq. 7-9, which wave 0 evaluates.
-    const int lane = tid & 63;
-    if (tid >= 64) {
-        if (tid < 128) {
-            UnitStats mine_stats[OWN];
-#pragma unroll
-            for (int i = 0; i < OWN; ++i)
-                mine_stats[i] = lane + 64 * i < nunits ? s_stats[lane + 64 * i] : UnitStats{-INFINITY, 0.f, 0.f, 0.f};
-            float m, Z, Tm;
-            combine_unit_stats<OWN>(mine_stats, lane, nunits, m, Z, Tm);
-            if (lane == 0) {
-                sh.row_m = m;
-                sh.row_Z = Z;
-                if (entropy) entropy[row] = logf(Z) + Tm / Z;
-            }
-        }
-        __syncthreads();
-        return false;                                // wave 0 finishes the row
-    }
-
-    Key mine = Key{0, 0};                            // lane j keeps winner j
-    if (use_short) {
-        // the same tournament on the 32-bit form: one wave reduction per round, the next entry of every list already
-        // in a register when its head wins
-        uint32_t h[OWN], nx[OWN];
-        int cur[OWN];
-#pragma unroll
-        for (int i = 0; i < OWN; ++i) {
-            const int c = lane + 64 * i;
-            h[i] = c < nunits ? short_key(key_unpack(s_keys[c * k]), c, 0) : 0u;
-            nx[i] = (c < nunits && k > 1) ? short_key(key_unpack(s_keys[c * k + 1]), c, 1) : 0u;
-            cur[i] = 0;
-        }
-        uint32_t mine_short = 0;
-        for (int round = 0; round < k; ++round) {
-            uint32_t best = h[0];
-#pragma unroll
-            for (int i = 1; i < OWN; ++i) best = max(best, h[i]);
-            const uint32_t g = wave_max_u32(best);
-            if (lane == round) mine_short = g;
-            if (g != 0 && best == g && round + 1 < k) {
-#pragma unroll
-                for (int i = 0; i < OWN; ++i) {
-                    if (h[i] == g) {
-                        h[i] = nx[i];
-                        const int after = ++cur[i] + 1;
-                        nx[i] = after < k ? short_key(key_unpack(s_keys[(lane + 64 * i) * k + after]), lane + 64 * i, after) : 0u;
-                    }
-                }
-            }
-        }
-        if (mine_short != 0) {
-            const int place = static_cast<int>(0xFFFFu - (mine_short & 0xFFFFu));
-            mine = key_unpack(s_keys[(place / SHORT_MAX_K) * k + place % SHORT_MAX_K]);
-        }
-    } else {
-        Key head[OWN];
-        int cursor[OWN];
-#pragma unroll
-        for (int i = 0; i < OWN; ++i) {
-            const int c = lane + 64 * i;
-            head[i] = c < nunits ? key_unpack(in_lds ? s_keys[c * k] : kk[static_cast<long>(c) * k]) : Key{0, 0};
-            cursor[i] = 0;
-        }
-        for (int round = 0; round < k; ++round) {
-            Key best = head[0];
-#pragma unroll
-            for (int i = 1; i < OWN; ++i) best = key_max(best, head[i]);
-            const Key g = wave_max_key(best);
-            if (lane == round) mine = g;
-            if (!key_none(g) && key_equal(best, g) && round + 1 < k) {   // the owning lane advances the winning list
-#pragma unroll
-                for (int i = 0; i < OWN; ++i) {
-                    if (key_equal(head[i], g)) {
-                        const int nxt = ++cursor[i];
-                        const long at = static_cast<long>(lane + 64 * i) * k + nxt;
-                        head[i] = nxt < k ? key_unpack(in_lds ? s_keys[at] : kk[at]) : Key{0, 0};
-                    }
-                }
-            }
-        }
-    }
-
-    __syncthreads();                                 // the statistics are combined
-    const float m = sh.row_m, Z = sh.row_Z;
+// Eq. 7-9 on the winners that the lanes of one wave hold (lane j < k: winner j), given the row's maximum and sum.  Writes the
+// row's outputs (null pointers are skipped).
+__device__ __forceinline__ void finish_row(int row, int k, int lane, Key mine, float m, float Z, int* __restrict__ topk_idx,
+                                           float* __restrict__ topk_prob, float* __restrict__ topk_renorm,
+                                           float* __restrict__ topk_entropy, float* __restrict__ alpha, MergedRow& out) {
     const bool have = lane < k;
     const float x = have ? key_value(mine) : -INFINITY;
     const float p = have ? expf(x - m) / Z : 0.f;
@@ -234,6 +123,278 @@ __device__ __forceinline__ bool merge_row(int row, int k, int nunits, const Unit
     out.p = p;
     out.q = q;
     out.alpha = a;
+}
+
+// Of the N values that every lane of a wave holds (those with have[i]), mark in in[i] at least the `want` and at most the
+// `most` largest (want <= how many there are, want <= most).  A threshold that at least `want` values reach is built bit by
+// bit, a ballot per value and bit, from the first bit in which the largest and the smallest value differ until no more
+// than `most` reach it: about six bits of 80 cycles on ordinary values when `most` leaves some room.  Only when too many
+// values equal the threshold are those admitted one by one, in order of (i, lane).  Returns the threshold.
+template <int N>
+__device__ __forceinline__ uint32_t wave_pick(const uint32_t (&code)[N], const bool (&have)[N], int want, int most, bool (&in)[N]) {
+    uint32_t hi = 0, lo = 0xFFFFFFFFu;
+    int got = 0;
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+        hi = max(hi, have[i] ? code[i] : 0u);
+        lo = min(lo, have[i] ? code[i] : 0xFFFFFFFFu);
+        got += __builtin_popcountll(__ballot(have[i]));
+    }
+    uint32_t thr = 0;
+    int above = 0;
+    if (got > most) {                                // (uniform)
+        hi = __builtin_amdgcn_readfirstlane(wave_max_u32(hi));
+        lo = __builtin_amdgcn_readfirstlane(~wave_max_u32(~lo));
+        auto reach = [&](uint32_t t) __attribute__((always_inline)) {
+            int n = 0;
+#pragma unroll
+            for (int i = 0; i < N; ++i) n += __builtin_popcountll(__ballot(have[i] && code[i] >= t));
+            return n;
+        };
+        uint32_t bit = hi == lo ? 0u : 0x80000000u >> __builtin_clz(hi ^ lo);
+        thr = bit ? hi & ~(2u * bit - 1u) : hi;      // what all values have in common (2 bit wraps to 0: nothing)
+        for (; bit != 0 && got > most; bit >>= 1) {
+            const int n = reach(thr | bit);
+            if (n >= want) {
+                thr |= bit;
+                got = n;
+            }
+        }
+        if (got > most) above = reach(thr + 1u);     // (thr + 1 wraps for NaNs only, which then are not admitted)
+    }
+    int left = want - above;                         // how many equal ones are admitted
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+        in[i] = have[i] && code[i] >= thr;
+        if (got > most) {
+            const bool eq = in[i] && code[i] == thr;
+            const uint64_t b = __ballot(eq);
+            const int before = static_cast<int>(__builtin_amdgcn_mbcnt_hi(static_cast<uint32_t>(b >> 32), __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(b), 0u)));
+            in[i] = in[i] && (!eq || before < left);
+            left -= __builtin_popcountll(b);
+        }
+    }
+    return thr;
+}
+
+// Second pass for one row, called by all WG_THREADS threads of a workgroup (at least two waves): combine the slice
+// statistics, merge the per-slice sorted key lists, Eq. 7-9.  OWN = lists per lane of one wave (lane owns lists lane,
+// lane+64, ...).  Writes the row's outputs (null pointers are skipped) and returns true in wave 0, whose lanes receive `out`;
+// the other waves help and return false.  Every thread passes the same workgroup barriers.
+//
+// This is pure latency (a few KB of data, one workgroup per row), so what counts is the length of its dependent chain, and
+// k rounds of a wave-wide maximum and the advance of one list (about 250 ns each; more when the lists do not fit LDS)
+// were most of it: 2.5 us at k = 10, 26 us at k = 64.  Instead: (1) wave 0 finds a value that at least k candidates reach
+// and not many more: the p-th largest of the lists' entries at depth d, p (d + 1) >= k, d chosen so that p is a small
+// part of the lists; (2) the entries that reach it are gathered from the lists whose heads do; (3) a thread per candidate
+// counts the candidates above it, which is its place.  Rows with too many candidates (long runs of equal values) take the
+// k rounds, over the k lists with the largest heads, a lane per list.
+template <int OWN, int WG_THREADS = MERGE_THREADS, class Shared>
+__device__ __forceinline__ bool merge_row(int row, int k, int nunits, const UnitStats* __restrict__ stats,
+                                          const uint64_t* __restrict__ keys, Shared& sh, float* __restrict__ entropy,
+                                          int* __restrict__ topk_idx, float* __restrict__ topk_prob,
+                                          float* __restrict__ topk_renorm, float* __restrict__ topk_entropy,
+                                          float* __restrict__ alpha, MergedRow& out) {
+    constexpr int THREADS = WG_THREADS;
+    static_assert(THREADS >= 192, "a wave for the pick, one for the statistics, others to stage");
+    PickShared& pk = sh.pick;
+    const int tid = threadIdx.x;
+    const int lane = tid & 63;
+    const uint64_t* kk = keys + static_cast<long>(row) * nunits * k;
+    const int total = nunits * k;
+    // Short lists are staged in LDS while wave 0 picks; of long ones only the picked lists are fetched, afterwards.
+    const bool in_lds = k <= 16 && total <= Shared::LDS_KEYS;
+    auto stage = [&](int t0, int step) __attribute__((always_inline)) {   // eight independent loads per thread at a time
+        for (int i0 = t0; i0 < total; i0 += step * 8) {
+            uint64_t tmp[8];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) tmp[j] = (i0 + j * step < total) ? kk[i0 + j * step] : 0;
+#pragma unroll
+            for (int j = 0; j < 8; ++j)
+                if (i0 + j * step < total) sh.keys[i0 + j * step] = tmp[j];
+        }
+    };
+    if (tid < 64) {
+        const int depth = min(k - 1, (4 * k + nunits - 1) / nunits - 1);   // k / (depth + 1) is at most a quarter of the lists
+        uint32_t code[OWN], head[OWN];
+        bool have[OWN], in[OWN];
+        int deep = 0;
+#pragma unroll
+        for (int i = 0; i < OWN; ++i) {
+            const int c = lane + 64 * i;
+            const Key h = c < nunits ? key_unpack(kk[static_cast<long>(c) * k]) : Key{0, 0};
+            const Key e = c < nunits ? key_unpack(kk[static_cast<long>(c) * k + depth]) : Key{0, 0};
+            head[i] = h.hi;
+            code[i] = e.hi;
+            have[i] = !key_none(e);
+        }
+        if (lane == 0) pk.ncand = 0;
+        pk.win[lane] = 0;
+#pragma unroll
+        for (int i = 0; i < OWN; ++i) deep += __builtin_popcountll(__ballot(have[i]));
+        const int want = (k + depth) / (depth + 1);
+        // (too few lists that deep: everything is a candidate)
+        const uint32_t thr = deep < want ? 0u : wave_pick<OWN>(code, have, want, want + want / 2 + 2, in);
+        int at = 0;
+#pragma unroll
+        for (int i = 0; i < OWN; ++i) {
+            const bool use = lane + 64 * i < nunits && head[i] >= thr;
+            const uint64_t b = __ballot(use);
+            const int to = at + static_cast<int>(__builtin_amdgcn_mbcnt_hi(static_cast<uint32_t>(b >> 32), __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(b), 0u)));
+            if (use && to < PICK_LISTS) pk.lists[to] = static_cast<uint16_t>(lane + 64 * i);
+            at += __builtin_popcountll(b);
+        }
+        if (lane == 0) {
+            pk.nlists = at;
+            pk.floor = thr;
+        }
+    } else if (tid < 128) {                          // wave 1 combines the slice statistics (and stores the row's entropy)
+        const UnitStats* st = stats + static_cast<long>(row) * nunits;
+        UnitStats mine_stats[OWN];
+#pragma unroll
+        for (int i = 0; i < OWN; ++i)
+            mine_stats[i] = lane + 64 * i < nunits ? st[lane + 64 * i] : UnitStats{-INFINITY, 0.f, 0.f, 0.f};
+        float m, Z, Tm;
+        combine_unit_stats<OWN>(mine_stats, lane, nunits, m, Z, Tm);
+        if (lane == 0) {
+            sh.row_m = m;
+            sh.row_Z = Z;
+            if (entropy) entropy[row] = logf(Z) + Tm / Z;
+        }
+    } else if (in_lds) {
+        stage(tid - 128, THREADS - 128);
+    }
+    __syncthreads();
+    auto entry = [&](int list, int j) __attribute__((always_inline)) {
+        return in_lds ? sh.keys[list * k + j] : kk[static_cast<long>(list) * k + j];
+    };
+    // ---- candidates: a thread per entry of the picked lists; of lists that are not staged only the first eight entries, then
+    // eight more while some list's last one fetched still is a candidate (lists are sorted)
+    const int nl = pk.nlists <= PICK_LISTS ? pk.nlists : 0;
+    const uint32_t floor = pk.floor;
+    auto gather = [&](int j0, int width) __attribute__((always_inline)) {   // entries j0 .. j0 + width - 1 of every picked list
+        const int entries = nl * width;
+        const unsigned inv = (65536u + width - 1) / width;       // (at * inv) >> 16 == at / width for at < 4096, width <= 64
+        bool more = false;
+        for (int at0 = 0; at0 < entries; at0 += THREADS) {
+            const int at = at0 + tid;
+            const int r = static_cast<int>((static_cast<unsigned>(at) * inv) >> 16), j = j0 + at - r * width;
+            const uint64_t e = at < entries && j < k ? entry(pk.lists[r], j) : 0;
+            const bool cand = e != 0 && static_cast<uint32_t>(e >> 32) >= floor;
+            more = more || (cand && at - r * width == width - 1);
+            const uint64_t b = __ballot(cand);
+            if (b != 0) {
+                int base = 0;
+                if (lane == 0) base = atomicAdd(&pk.ncand, static_cast<int>(__builtin_popcountll(b)));
+                base = __builtin_amdgcn_readfirstlane(base);
+                const int to = base + static_cast<int>(__builtin_amdgcn_mbcnt_hi(static_cast<uint32_t>(b >> 32), __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(b), 0u)));
+                if (cand && to < PICK_CANDS) pk.cand[to] = e;
+            }
+        }
+        return more;
+    };
+    if (in_lds) {
+        gather(0, k);
+        __syncthreads();
+    } else {
+        for (int j0 = 0; __syncthreads_or(gather(j0, 8) ? 1 : 0) != 0 && j0 + 8 < k; j0 += 8) {}
+    }
+    int nc = pk.nlists <= PICK_LISTS ? pk.ncand : PICK_CANDS + 1;
+    if (nc <= PICK_CANDS) {                          // (uniform)
+        if (nc > 2 * SAGE_MAX_TOPK) {                // wave 0 picks again among them, k or a few more
+            if (tid < 64) {
+                constexpr int N = PICK_CANDS / 64;
+                uint64_t key[N];
+                uint32_t code[N];
+                bool have[N], in[N];
+#pragma unroll
+                for (int i = 0; i < N; ++i) {
+                    have[i] = lane + 64 * i < nc;
+                    key[i] = have[i] ? pk.cand[lane + 64 * i] : 0;
+                    code[i] = static_cast<uint32_t>(key[i] >> 32);
+                }
+                const int want = min(k, nc), most = min(2 * SAGE_MAX_TOPK, k + k / 2 + 2);
+                const uint32_t thr = wave_pick<N>(code, have, want, most, in);
+                int equal = 0, admitted = 0, at = 0;
+#pragma unroll
+                for (int i = 0; i < N; ++i) {
+                    equal += __builtin_popcountll(__ballot(have[i] && code[i] == thr));
+                    admitted += __builtin_popcountll(__ballot(in[i] && code[i] == thr));
+                }
+                if (admitted != equal) {             // of equal values the lowest indices: the largest lower words
+                    bool eq[N], pick[N];
+#pragma unroll
+                    for (int i = 0; i < N; ++i) {
+                        eq[i] = have[i] && code[i] == thr;
+                        code[i] = eq[i] ? static_cast<uint32_t>(key[i]) : code[i];
+                    }
+                    wave_pick<N>(code, eq, admitted, admitted, pick);
+#pragma unroll
+                    for (int i = 0; i < N; ++i) in[i] = eq[i] ? pick[i] : in[i];
+                }
+#pragma unroll
+                for (int i = 0; i < N; ++i) {
+                    const uint64_t b = __ballot(in[i]);
+                    if (in[i]) pk.cand[at + static_cast<int>(__builtin_amdgcn_mbcnt_hi(static_cast<uint32_t>(b >> 32), __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(b), 0u)))] = key[i];
+                    at += __builtin_popcountll(b);
+                }
+                if (lane == 0) pk.nkept = at;
+            }
+            __syncthreads();
+            nc = pk.nkept;
+        }
+    }
+    if (nc <= PICK_CANDS) {                          // a thread per candidate
+        for (int c = tid; c < nc; c += THREADS) {
+            const uint64_t mine = pk.cand[c];
+            int above = 0;
+            for (int o = 0; o < nc; o += 8) {        // broadcast reads, eight keys at a time; entries past nc are not counted
+                ulonglong2 h[4];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) h[u] = *reinterpret_cast<const ulonglong2*>(pk.cand + o + 2 * u);
+#pragma unroll
+                for (int u = 0; u < 4; ++u)
+                    above += (o + 2 * u < nc && h[u].x > mine ? 1 : 0) + (o + 2 * u + 1 < nc && h[u].y > mine ? 1 : 0);
+            }
+            if (above < k) pk.win[above] = mine;
+        }
+    } else if (tid < 64) {                           // k rounds over the k lists with the largest heads, a lane per list
+        uint32_t code[OWN];
+        bool have[OWN], in[OWN];
+        int nonempty = 0, nl2 = 0;
+#pragma unroll
+        for (int i = 0; i < OWN; ++i) {
+            const Key h = lane + 64 * i < nunits ? key_unpack(entry(lane + 64 * i, 0)) : Key{0, 0};
+            code[i] = h.hi;
+            have[i] = !key_none(h);
+            nonempty += __builtin_popcountll(__ballot(have[i]));
+        }
+        wave_pick<OWN>(code, have, min(k, nonempty), min(k, nonempty), in);   // (i, lane) is list order, which is index order
+#pragma unroll
+        for (int i = 0; i < OWN; ++i) {
+            const uint64_t b = __ballot(in[i]);
+            if (in[i]) pk.lists[nl2 + static_cast<int>(__builtin_amdgcn_mbcnt_hi(static_cast<uint32_t>(b >> 32), __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(b), 0u)))] = static_cast<uint16_t>(lane + 64 * i);
+            nl2 += __builtin_popcountll(b);
+        }
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        const int list = lane < nl2 ? pk.lists[lane] : 0;
+        int cursor = 0;
+        Key head = lane < nl2 ? key_unpack(entry(list, 0)) : Key{0, 0};
+        for (int round = 0; round < k; ++round) {
+            const Key g = wave_max_key(head);
+            if (lane == round) pk.win[round] = key_pack(g);
+            if (!key_none(g) && key_equal(head, g)) {
+                ++cursor;
+                head = cursor < k ? key_unpack(entry(list, cursor)) : Key{0, 0};
+            }
+        }
+    }
+    __syncthreads();
+    if (tid >= 64) return false;                     // wave 0 finishes the row
+    finish_row(row, k, lane, lane < k ? key_unpack(pk.win[lane]) : Key{0, 0}, sh.row_m, sh.row_Z, topk_idx, topk_prob, topk_renorm,
+               topk_entropy, alpha, out);
     return true;
 }
 

@@ -131,7 +131,7 @@ extern "C" int sage_tree_attention_with_plan(
     if (dtype == SAGE_BF16 && sage::attention_bf16_can_carry_plan(pl))
         return sage::tree_attention_bf16(Q, Kc, Vc, Kt, Vt, O, B, Hq, Hkv, d, kv_start, kv_len, max_kv_len, kv_token_stride,
                                          kv_head_stride, anc_mask, n_nodes, nullptr, scale, workspace, workspace_bytes, s, &pl);
-    // fp32, or candidate lists too long for the planning workgroup's LDS: the two launches one after the other
+    // fp32, or more slices than the planning workgroup takes: the two launches one after the other
     rc = dtype == SAGE_F32 ? sage::tree_attention_f32(Q, Kc, Vc, Kt, Vt, O, B, Hq, Hkv, d, kv_start, kv_len, kv_token_stride,
                                                       kv_head_stride, anc_mask, n_nodes, nullptr, scale, s)
                            : sage::tree_attention_bf16(Q, Kc, Vc, Kt, Vt, O, B, Hq, Hkv, d, kv_start, kv_len, max_kv_len,

@@ -182,14 +182,14 @@ __device__ __forceinline__ void attention_workgroup(const int* __restrict__ kv_l
                                                     const int64_t* __restrict__ kv_start_arg, int nslot_arg, int min_tps_arg,
                                                     int G_arg, const Params& prm, const int first_slab) {
     // one LDS object per stage and operand (see header)
-    __shared__ __align__(1024) unsigned char sK0[K_STAGE_B];
-    __shared__ __align__(1024) unsigned char sK1[K_STAGE_B];
-    __shared__ __align__(1024) unsigned char sK2[K_STAGE_B];
-    __shared__ __align__(1024) unsigned char sK3[K_STAGE_B];
-    __shared__ __align__(1024) unsigned char sV0[V_STAGE_B];
-    __shared__ __align__(1024) unsigned char sV1[V_STAGE_B];
-    __shared__ __align__(1024) unsigned char sV2[V_STAGE_B];
-    __shared__ __align__(1024) unsigned char sV3[V_STAGE_B];
+    __shared__ __align__(256) unsigned char sK0[K_STAGE_B];
+    __shared__ __align__(256) unsigned char sK1[K_STAGE_B];
+    __shared__ __align__(256) unsigned char sK2[K_STAGE_B];
+    __shared__ __align__(256) unsigned char sK3[K_STAGE_B];
+    __shared__ __align__(256) unsigned char sV0[V_STAGE_B];
+    __shared__ __align__(256) unsigned char sV1[V_STAGE_B];
+    __shared__ __align__(256) unsigned char sV2[V_STAGE_B];
+    __shared__ __align__(256) unsigned char sV3[V_STAGE_B];
     __shared__ uint64_t s_mask[ROWS_PER_WG];
 #define SK(i) ((i) == 0 ? sK0 : (i) == 1 ? sK1 : (i) == 2 ? sK2 : sK3)
 #define SV(i) ((i) == 0 ? sV0 : (i) == 1 ? sV1 : (i) == 2 ? sV2 : sV3)
@@ -650,12 +650,12 @@ __global__ __launch_bounds__(THREADS) void tree_attention_bf16_kernel(const int*
 // when the attention's own workgroups fill every CU, the one that has to wait for a free CU is then the attention's
 // last (a sequence's final split, seldom a full one), and it waits for the short planning workgroup, not the other
 // way round.
-constexpr int PLAN_LDS_KEYS = 2400;     // what the 160 KB of a CU leave beside the attention's stages (k = 16 at 152064 tokens: 2384)
+constexpr int PLAN_LDS_KEYS = 2400;     // short lists staged beside the attention's stages (k = 16 at 152064 tokens: 2384)
 constexpr int PLAN_OWN = 4;              // slices per lane: up to 256 slices per draft row
 struct PlanShared {
     static constexpr int LDS_KEYS = PLAN_LDS_KEYS;
     uint64_t* keys;
-    sage::topk::UnitStats* stats;
+    sage::topk::PickShared& pick;
     float& row_m;
     float& row_Z;
 };
@@ -667,13 +667,13 @@ __global__ __launch_bounds__(THREADS) void tree_attention_plan_kernel(const int*
                                                                       const Params prm, const sage::PlanArgs pl) {
     if (static_cast<int>(blockIdx.y) < plan_slabs) {        // workgroup-uniform
         __shared__ uint64_t p_keys[PLAN_LDS_KEYS];
-        __shared__ sage::topk::UnitStats p_stats[64 * PLAN_OWN];
+        __shared__ sage::topk::PickShared p_pick;
         __shared__ float p_row[2];
         // one sequence per launch slot: the slab's first workgroup of sequence blockIdx.z; batches: slab workgroups in turn
         const int b = BATCH ? static_cast<int>(blockIdx.y * gridDim.x + blockIdx.x)
                             : (blockIdx.x == 0 ? static_cast<int>(blockIdx.z) : prm.B);
         if (b >= prm.B) return;
-        PlanShared sh{p_keys, p_stats, p_row[0], p_row[1]};
+        PlanShared sh{p_keys, p_pick, p_row[0], p_row[1]};
         sage::plan_sequence<PLAN_OWN, THREADS>(b, pl, sh);
         return;
     }
@@ -848,11 +848,8 @@ size_t attention_bf16_workspace_bytes(int B, int Hkv, int G, int max_kv_len) {
     return (sh.batch ? static_cast<size_t>(1) : static_cast<size_t>(B)) * Hkv * sh.nslot * static_cast<size_t>(PART_SLOT_B);
 }
 
-// Whether the attention launch can carry this planning along: the lists of a draft row must fit the LDS the planning
-// workgroup has, and a lane holds at most PLAN_OWN slices.
-bool attention_bf16_can_carry_plan(const PlanArgs& pl) {
-    return pl.nunits <= 64 * PLAN_OWN && pl.nunits * pl.k <= PLAN_LDS_KEYS;
-}
+// Whether the attention launch can carry this planning along: a lane holds at most PLAN_OWN slices.
+bool attention_bf16_can_carry_plan(const PlanArgs& pl) { return pl.nunits <= 64 * PLAN_OWN; }
 
 // plan == nullptr: the attention alone.  Otherwise the caller has checked attention_bf16_can_carry_plan(*plan).
 int tree_attention_bf16(const void* Q, const void* Kc, const void* Vc, const void* Kt, const void* Vt, void* O, int B,

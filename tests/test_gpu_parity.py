@@ -92,6 +92,38 @@ def test_entropy_topk_row_groups_k1(gu):
     assert (g["alpha"][:9] == 1.0).all()
 
 
+def selection_rows(kind, vocab, dtype):
+    """Rows whose winners sit where a selection can go wrong."""
+    g = wl.rng(4200 + vocab)
+    x = g.standard_normal((2, vocab)).astype(np.float32)
+    if kind == "equal":                                  # every logit the same: the lowest indices win
+        x[:] = 1.5
+    elif kind == "levels":                               # a handful of values: long runs of ties at the threshold
+        x[:] = g.integers(0, 3, size=x.shape)
+    elif kind == "one slice":                            # all winners in one stretch of 1024 logits, and in its last ones
+        x[0, 1024:2048] += 50.0
+        x[1, vocab - 70:] += 50.0
+    elif kind == "few finite":                           # fewer finite logits than k
+        x[:] = -np.inf
+        x[0, [5, vocab // 2, vocab - 1]] = [1.0, 2.0, 2.0]
+        x[1, vocab - 1] = 0.25
+    buf = wl.to_storage(np.pad(x, ((0, 0), (0, -vocab % 16))), dtype)      # (rows are 16-byte aligned)
+    return buf[:, :vocab]
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("kind,vocab,k", [
+    ("equal", 3000, 64), ("equal", 300000, 16), ("levels", 40000, 64), ("levels", 152064, 10), ("one slice", 5000, 64),
+    ("one slice", 152064, 16), ("gaussian", 40000, 64), ("gaussian", 70001, 40), ("gaussian", 1025, 17), ("gaussian", 2049, 2),
+    ("few finite", 3000, 10), ("few finite", 9000, 40)])
+def test_topk_selection_edges(gu, dtype, kind, vocab, k):
+    """Ties at the threshold, concentrated winners, a last slice of one logit, fewer candidates than k: indices exact."""
+    x = selection_rows(kind, vocab, dtype)
+    g1, o1 = gu.gpu_entropy_topk(x, k), oracle.entropy_topk(x, k)
+    assert (g1["topk_idx"] == o1["topk_idx"]).all()
+    np.testing.assert_allclose(g1["topk_prob"], o1["topk_prob"], rtol=1e-5, atol=1e-7)
+
+
 @pytest.mark.parametrize("rows,rpg,n_valid,vocab,dtype", [
     (150, 64, [64, 33, 22], 5000, "f32"),            # a short last group (22 rows): every one of its rows counts
     (150, 64, [17, 0, 99], 70008, "bf16"),           # n_valid beyond the group's rows is clamped
