@@ -695,7 +695,7 @@ __global__ __launch_bounds__(64 * ROWS) void tree_attention_merge_kernel(const i
                                                                          const int* __restrict__ n_nodes_arg, int nslot_arg,
                                                                          int min_tps_arg, int G_arg, int phases_arg,
                                                                          const Params prm) {
-    static_assert(MAXS <= 32, "one split per lane, one register per split");
+    static_assert(MAXS <= 64, "one split per lane, one register per split");
     // As in the main kernel, a KV head's blocks are congruent modulo the KV-head count, so with 8 KV heads they run on
     // the XCD whose L2 still holds that head's partials.  Rows of a KV head are numbered as there: node * G + head-in-group.
     const int lane = threadIdx.x & 63;
@@ -801,11 +801,15 @@ namespace sage {
 // Launch shape.  A single sequence (and batches of more than 64): slots = workgroups per (sequence, KV head); a slot is
 // (KV split, column group); the sequence is cut into about one 8-wave workgroup per CU (one round, no tail).
 // Batches of 2..64 sequences: the tile list of all sequences is cut into `nrange` ranges per KV head, about one
-// workgroup per CU in total whatever the lengths turn out to be on the device; a range is at least MIN_RANGE_TILES
-// tiles (every pass pays a few microseconds of prologue and epilogue), and the partial slots of a KV head are one per
-// range plus one per (sequence, column group), the most that range and segment boundaries can produce together.
+// workgroup per CU in total whatever the lengths turn out to be on the device, and the partial slots of a KV head are one
+// per range plus one per (sequence, column group), the most that range and segment boundaries can produce together.
+// A range is at least MIN_RANGE_TILES positions: as long as CUs are idle, shorter ranges end sooner, until they are about
+// as long as the prologue and epilogue of the pass that a range pays anyway (3 sequences of 301-1999 tokens, four layers
+// and a step's other launches: 101 us at 8, 91.4 at 5, 88.5 at 4, 88.2 at 3 and 2; 2 of 212-613 tokens, six layers: 118,
+// 105, 97, 97).  CAP_RANGE_TILES bounds the ranges, and with them the workspace, by the longest lengths allowed.
 constexpr int MAX_BATCH_LANES = 64;      // a lane per sequence in make_batch_shape
-constexpr int MIN_RANGE_TILES = 8;      // positions of the line, pass cost included
+constexpr int MIN_RANGE_TILES = SEG_COST_TILES;   // positions of the line, pass cost included
+constexpr int CAP_RANGE_TILES = 8;
 struct LaunchShape { int nslot, min_tiles_per_split, nrange; bool batch; };
 LaunchShape attention_bf16_shape(int B, int Hkv, int G, int max_kv_len) {
     const int max_groups = (SAGE_MAX_NODES * G + ROWS_PER_WG - 1) / ROWS_PER_WG;
@@ -816,7 +820,7 @@ LaunchShape attention_bf16_shape(int B, int Hkv, int G, int max_kv_len) {
     if (sh.batch) {
         long want = 256 / Hkv;
         if (want < 1) want = 1;
-        const long cap = (static_cast<long>(B) * (tiles + SEG_COST_TILES) * max_groups + MIN_RANGE_TILES - 1) / MIN_RANGE_TILES;
+        const long cap = (static_cast<long>(B) * (tiles + SEG_COST_TILES) * max_groups + CAP_RANGE_TILES - 1) / CAP_RANGE_TILES;
         if (want > cap) want = cap;
         sh.nrange = static_cast<int>(want);
         sh.min_tiles_per_split = MIN_RANGE_TILES;
@@ -911,8 +915,9 @@ int tree_attention_bf16(const void* Q, const void* Kc, const void* Vc, const voi
     const int max_tiles = (max_kv_len + TILE - 1) / TILE + 1;
     int most = sh.batch ? p.nrange : p.nslot;         // upper bound of the splits of a row: no more than slots, or tiles
     if (most > max_tiles) most = max_tiles;
-    // more than 32 splits take several passes of 32: 64 register pairs per lane cost more in resident waves than the
-    // second round trip does
+    // Batches: more than 32 splits (seldom: a sequence with nearly the whole batch's tokens) take several passes of 32, which
+    // keeps more waves resident.  A single sequence has few waves to keep, and a second pass is a second round trip to
+    // memory: up to 64 splits in one (41 splits of 7 to 21 rows x 4 KV heads: 4.6 -> 4.1 us).
     if (sh.batch) {
         if (most <= 8) hipLaunchKernelGGL((tree_attention_merge_kernel<8, true, MERGE_ROWS_BATCH>), mgrid, mblock, 0, stream, kv_len, n_nodes, p.nslot,
                                p.min_tiles_per_split, G, p.merge_phases, p);
@@ -925,7 +930,11 @@ int tree_attention_bf16(const void* Q, const void* Kc, const void* Vc, const voi
                                p.min_tiles_per_split, G, p.merge_phases, p);
         else if (most <= 16) hipLaunchKernelGGL((tree_attention_merge_kernel<16, false, MERGE_ROWS_SINGLE>), mgrid, mblock, 0, stream, kv_len, n_nodes, p.nslot,
                                p.min_tiles_per_split, G, p.merge_phases, p);
-        else hipLaunchKernelGGL((tree_attention_merge_kernel<32, false, MERGE_ROWS_SINGLE>), mgrid, mblock, 0, stream, kv_len, n_nodes, p.nslot,
+        else if (most <= 32) hipLaunchKernelGGL((tree_attention_merge_kernel<32, false, MERGE_ROWS_SINGLE>), mgrid, mblock, 0, stream, kv_len, n_nodes, p.nslot,
+                               p.min_tiles_per_split, G, p.merge_phases, p);
+        else if (most <= 48) hipLaunchKernelGGL((tree_attention_merge_kernel<48, false, MERGE_ROWS_SINGLE>), mgrid, mblock, 0, stream, kv_len, n_nodes, p.nslot,
+                               p.min_tiles_per_split, G, p.merge_phases, p);
+        else hipLaunchKernelGGL((tree_attention_merge_kernel<64, false, MERGE_ROWS_SINGLE>), mgrid, mblock, 0, stream, kv_len, n_nodes, p.nslot,
                                p.min_tiles_per_split, G, p.merge_phases, p);
     }
     return launch_status();

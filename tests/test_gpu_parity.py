@@ -360,6 +360,13 @@ def test_attention_bf16_many_sequences(gu, B, Hq, Hkv, max_len, seed):
     run_attention_case(gu, 3000 + seed, "bf16", B, Hq, Hkv, 128, lens, sizes)
 
 
+@pytest.mark.parametrize("tiles", [32, 33, 48, 49, 64, 65, 128, 129])
+def test_attention_bf16_split_counts(gu, tiles):
+    """One sequence and two KV heads: a split per 64-token tile up to 128, so the merge takes every one of its widths at its
+    last count, the next one's first, and several passes of the widest."""
+    run_attention_case(gu, 4000 + tiles, "bf16", 1, 4, 2, 128, [64 * (tiles - 1) - 3], sizes=[3])
+
+
 def test_attention_is_deterministic(gu):
     inp = wl.attention_inputs(3, 1, 64, 8, 128, [2000], "bf16")
     mask, nn = tree_batch(wl.rng(3), 1, [40])
