@@ -216,3 +216,14 @@ def test_candidate_lists_with_row_groups(gu):
             assert abs(g["alpha"][r] - o["alpha"][r]) <= 2e-3
         else:
             assert (g["topk_idx"][r] == -1).all() and np.isnan(g["entropy"][r])
+
+
+@pytest.mark.parametrize("rows,vocab,k", [(40, 700, 16), (3, 152064, 10), (64, 81930, 2)])
+def test_candidate_lists_of_equal_logits(gu, rows, vocab, k):
+    """Every logit of a row is the same: whatever the unit and the half of the rows, the lowest indices in order."""
+    dim = 128
+    h = wl.gaussian(rows + 3, (rows, dim), "bf16", 1.0)
+    w = np.repeat(wl.gaussian(9, (1, dim), "bf16", 1.0), vocab, axis=0)
+    g = gu.gpu_lm_head_topk(h, w, k)
+    np.testing.assert_array_equal(g["topk_idx"], np.tile(np.arange(k, dtype=np.int32), (rows, 1)))
+    np.testing.assert_allclose(g["topk_renorm"], 1.0 / k, rtol=1e-5)
