@@ -42,7 +42,9 @@ __device__ __forceinline__ Fold fold_logits(int v0, int stride, int v_end, Logit
 #pragma unroll
         for (int i = 0; i < 16; ++i) {
             // capped where exp is below 2^-125: a masked entry then adds about 1e-38 instead of 0 to a sum that is >= 1
-            const float dlt = fminf(best - logit(a, i, left), 87.0f);
+            // (the minimum that keeps a NaN: a NaN or +inf logit makes the row's statistics NaN; the best candidate is the
+            // best of the numbers)
+            const float dlt = __builtin_elementwise_minimum(best - logit(a, i, left), 87.0f);
             const float e = __builtin_amdgcn_exp2f(dlt * -1.4426950408889634f);
             Z += e;
             Tm = fmaf(e, dlt, Tm);

@@ -227,3 +227,18 @@ def test_candidate_lists_of_equal_logits(gu, rows, vocab, k):
     g = gu.gpu_lm_head_topk(h, w, k)
     np.testing.assert_array_equal(g["topk_idx"], np.tile(np.arange(k, dtype=np.int32), (rows, 1)))
     np.testing.assert_allclose(g["topk_renorm"], 1.0 / k, rtol=1e-5)
+
+
+@pytest.mark.parametrize("rows,value", [(5, np.nan), (5, np.inf), (70, np.nan), (70, np.inf)])
+def test_logits_that_are_not_finite(gu, rows, value):
+    """A NaN or infinite logit makes the row's entropy NaN; +inf is the greedy token, a NaN is passed over."""
+    dim, vocab = 128, 2000
+    h = np.abs(wl.bf16_bits_to_f32(wl.gaussian(1, (rows, dim), "bf16", 1.0))) + 0.5
+    h = (h.view(np.uint32) >> 16).astype(np.uint16)
+    w = wl.gaussian(2, (vocab, dim), "bf16", 0.1)
+    clean = gu.gpu_lm_head_topk(h, w, 1)["topk_idx"][:, 0]
+    assert (clean != 1234).all()
+    w[1234, 5] = np.array([value], np.float32).view(np.uint32)[0] >> 16
+    g = gu.gpu_lm_head_topk(h, w, 1)
+    assert np.isnan(g["entropy"]).all()
+    np.testing.assert_array_equal(g["topk_idx"][:, 0], clean if np.isnan(value) else np.full(rows, 1234))
