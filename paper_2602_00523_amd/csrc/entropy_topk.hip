@@ -2,13 +2,14 @@
 // (Sec. 3.1: Eq. 7 renormalised top-k, Eq. 8 its entropy, Eq. 9 confidence; Eq. 1 softmax) and, with k = 1,
 // the target's greedy token per tree node (Sec. 2.2 / Def. 4.1).
 //
-// HBM-bound: every logit is read exactly once with 16-byte loads.  Pass 1: each WAVE owns a slice of UNIT
-// logits of one row, held in registers; it extracts the slice's k best entries under the total order (value
-// descending, index ascending) by k rounds of a wave-wide maximum on a 64-bit composite key, done with DPP row
-// rotations and the 16/32-lane swaps (no LDS, no workgroup barrier), and reduces the slice's softmax statistics
+// HBM-bound: every logit is read exactly once with 16-byte loads.  Candidates are ordered by a 64-bit composite key (value
+// descending, index ascending).  Pass 1 cuts a row into slices of UNIT logits: with k = 1 each WAVE owns a slice and takes
+// its maximum, done with DPP row rotations and the 16/32-lane swaps (no LDS, no workgroup barrier); with k > 1 a workgroup
+// owns it, each wave finds what its k best logits reach and the survivors are ranked by counting.  Either reduces the
+// slice's softmax statistics
 //   Z = sum exp(x - m),  T = sum exp(x - m) (m - x)   so that   H = ln Z + T / Z   (both terms >= 0).
-// Pass 2 (one wave per row) combines the slice statistics by log-sum-exp, merges the sorted per-slice lists with
-// a k-round tournament over the list heads (lists staged in LDS), and evaluates Eq. 7-9 on the k winners.
+// Pass 2 combines the slice statistics by log-sum-exp, finds the k winners of the sorted per-slice lists (k = 1: a wave per
+// row; k > 1: a workgroup per row, merge_row in topk_device.h) and evaluates Eq. 7-9 on them.
 #include "sage_internal.h"
 #include "topk_common.h"
 #include "topk_device.h"
@@ -316,7 +317,8 @@ __device__ __forceinline__ void slice_topk_block(const T* __restrict__ logits, i
     uint32_t code[4];
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
-        const uint32_t full = sortable(v[e]);
+        // (NaNs of the extreme codes move by one: 0 marks no candidate, and the rounds below start under 0xFFFFFFFF)
+        const uint32_t full = min(max(sortable(v[e]), 1u), 0xFFFFFFFEu);
         code[e] = e0 + e >= vocab ? 0u : sizeof(T) == 4 ? full : ((full & 0xFFFF0000u) | static_cast<uint32_t>(UNIT - (static_cast<int>(threadIdx.x) * 4 + e)));
     }
     auto reach = [&](uint32_t t) __attribute__((always_inline)) {     // how many of the wave's logits reach t (uniform)
@@ -335,7 +337,6 @@ __device__ __forceinline__ void slice_topk_block(const T* __restrict__ logits, i
 #pragma unroll
             for (int e = 0; e < 4; ++e) best = max(best, code[e] < thr ? code[e] : 0u);
             thr = __builtin_amdgcn_readfirstlane(wave_max_u32(best));
-            if (thr == 0u) break;                    // (NaNs only)
 #pragma unroll
             for (int e = 0; e < 4; ++e) got += __builtin_popcountll(__ballot(code[e] == thr));
         }

@@ -160,7 +160,7 @@ __device__ __forceinline__ uint32_t wave_pick(const uint32_t (&code)[N], const b
                 got = n;
             }
         }
-        if (got > most) above = reach(thr + 1u);     // (thr + 1 wraps for NaNs only, which then are not admitted)
+        if (got > most && thr != 0xFFFFFFFFu) above = reach(thr + 1u);   // (nothing is above the largest code)
     }
     int left = want - above;                         // how many equal ones are admitted
 #pragma unroll

@@ -135,6 +135,19 @@ def test_entropy_topk_row_groups_k1_shapes(gu, rows, rpg, n_valid, vocab, dtype)
     check_entropy(gu, wl.to_storage(z, dtype), 1, np.array(n_valid, np.int32), rpg)
 
 
+@pytest.mark.parametrize("k", [4, 8, 9, 40])
+@pytest.mark.parametrize("bits", [0x7FFFFFFF, 0xFFFFFFFF])
+def test_topk_of_extreme_nans(gu, bits, k):
+    """Rows of the NaNs whose codes are the largest and the smallest word: k tokens of the row (equal values: the first k)."""
+    vocab = 5000
+    x = np.full((2, vocab), bits, np.uint32).view(np.float32)
+    x[1, 1030:1060] = 1.0                            # fewer numbers in a slice than k = 40, more than the others
+    g = gu.gpu_entropy_topk(x, k)
+    np.testing.assert_array_equal(g["topk_idx"][0], np.arange(k))
+    idx = g["topk_idx"][1]
+    assert ((0 <= idx) & (idx < vocab)).all() and len(set(idx.tolist())) == k
+
+
 # ------------------------------------------------------------------ a2
 
 def test_build_tree_bit_exact(gu):
