@@ -105,7 +105,7 @@ bool take_parameters(const Program& p, PyObject* const* args, size_t npos, PyObj
     return true;
 }
 
-bool marshal(const Program& p, PyObject* const* slot, Value* out) {
+bool fill(const Program& p, PyObject* const* slot, Value* out) {
     for (const Op& op : p.ops) {
         PyObject* o = slot[op.a];
         switch (op.kind) {
@@ -149,12 +149,7 @@ bool marshal(const Program& p, PyObject* const* slot, Value* out) {
             }
             case STREAM: {
                 if (o == Py_None) {
-                    try {
-                        (out++)->i = static_cast<int64_t>(reinterpret_cast<uintptr_t>(c10::hip::getCurrentHIPStream().stream()));
-                    } catch (const std::exception& e) {
-                        PyErr_SetString(PyExc_RuntimeError, e.what());
-                        return false;
-                    }
+                    (out++)->i = static_cast<int64_t>(reinterpret_cast<uintptr_t>(c10::hip::getCurrentHIPStream().stream()));
                     break;
                 }
                 PyObject* h = PyObject_GetAttrString(o, "cuda_stream");
@@ -204,6 +199,19 @@ bool marshal(const Program& p, PyObject* const* slot, Value* out) {
         }
     }
     return true;
+}
+
+// torch throws for what it cannot give (the address or a stride of a sparse or batched tensor, a stream without a device):
+// a Python error, since no C++ exception may leave through the interpreter.
+bool marshal(const Program& p, PyObject* const* slot, Value* out) {
+    try {
+        return fill(p, slot, out);
+    } catch (const c10::Error& e) {
+        PyErr_SetString(PyExc_RuntimeError, e.what_without_backtrace());
+    } catch (const std::exception& e) {
+        PyErr_SetString(PyExc_RuntimeError, e.what());
+    }
+    return false;
 }
 
 PyObject* jump(const Program& p, const Value* v) {

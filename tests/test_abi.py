@@ -241,3 +241,19 @@ def test_attention_with_plan_validates_on_the_host(lib):
     assert call(next_nn=one) == INVALID and call(next_mask=one) == INVALID      # the planned tree aliases the verified one
     assert call(ws=null) == INVALID and call(ws=null, dtype=0) == 0             # fp32 needs no workspace
     assert call(vocab=2_000_000) == UNSUPPORTED and call(B=70000) == UNSUPPORTED
+
+
+def test_tensors_without_an_address_are_python_errors():
+    """Tensors of a function transform or without strides: an exception as from torch itself, and the process lives."""
+    import torch
+    from paper_2602_00523_amd import sage
+
+    def call(x):
+        sage.sage_entropy_topk(x, 1, None, None, None, None, None, None, None)
+        return x
+    with pytest.raises(RuntimeError, match="storage"):
+        torch.vmap(call)(torch.zeros(2, 4, 8))
+    with pytest.raises((RuntimeError, AssertionError)):
+        call(torch.eye(4).to_sparse())
+    with pytest.raises(TypeError):
+        call([1.0, 2.0])
