@@ -23,7 +23,7 @@
 // first, so that the workgroups go through units of one size at a time and the chip finishes together (152064 x 512 rows:
 // 18-19 tiles per pair of CUs = 5 units of 3 or 4, 4.75 rounds of work in place of the 5 that equal units of 4 would
 // need).  Only blocks of live rows are items; a block is 64, 128, 192 or 256 rows deep.  Row blocks of one unit are
-// consecutive items of one XCD and share the unit's weights through that XCD's L2 as far as they stay together (1.7 fetches
+// consecutive items of one XCD and share the unit's weights through that XCD's L2 as far as they stay together (1.21 fetches
 // of the matrix at 512 rows).
 //
 // Measured (hidden 8192, vocabulary 152064; before = 4 waves on 320 vocabulary rows x 128 hidden rows): 512 live rows
