@@ -240,7 +240,8 @@ __device__ __forceinline__ void slice_topk_bf16_block(const uint16_t* __restrict
         above = k;
         for (int round = 0; round < k; ++round) {
             const uint32_t g = wave_max_u32(rest);
-            if (rest == g) { above = round; rest = 0u; }
+            // (0 marks the lanes without a candidate and those ranked already: fewer than k candidates are not matched again)
+            if (g != 0 && rest == g) { above = round; rest = 0u; }
         }
     } else {
         for (int o = 0; o < WAVES * k; o += 16) {            // (the list is padded with zeros to whole pieces of 16)

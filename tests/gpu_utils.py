@@ -26,6 +26,12 @@ def to_host(t: torch.Tensor) -> np.ndarray:
     return t.cpu().numpy()
 
 
+def workspace(nbytes: int) -> torch.Tensor:
+    """A workspace as an earlier call may have left it: all ones are the largest candidate keys and NaN statistics, so that
+    an entry which a kernel reads without having written it shows."""
+    return torch.full((nbytes,), 0xFF, device=DEV, dtype=torch.uint8)
+
+
 def widen(a: np.ndarray) -> np.ndarray:
     return a.astype(np.float64) if a.dtype != np.uint16 else wl.bf16_bits_to_f32(a).astype(np.float64)
 
@@ -41,7 +47,7 @@ def gpu_entropy_topk(logits_np, k, n_valid=None, rows_per_group=1):
     f = lambda *s: torch.full(s, float("nan"), device=DEV, dtype=torch.float32)
     out = dict(entropy=f(rows), topk_idx=torch.full((rows, k), -1, device=DEV, dtype=torch.int32), topk_prob=f(rows, k),
                topk_renorm=f(rows, k), topk_entropy=f(rows), alpha=f(rows))
-    ws = torch.empty(sage.sage_entropy_topk_workspace_bytes(rows, vocab, k), device=DEV, dtype=torch.uint8)
+    ws = workspace(sage.sage_entropy_topk_workspace_bytes(rows, vocab, k))
     nv = None if n_valid is None else to_dev(np.asarray(n_valid, np.int32))
     sage.sage_entropy_topk(x, k, out["entropy"], out["topk_idx"], out["topk_prob"], out["topk_renorm"],
                            out["topk_entropy"], out["alpha"], ws, nv, rows_per_group)
@@ -78,7 +84,7 @@ def gpu_tree_attention(inp: dict, anc_mask_np, n_nodes_np, Hq, Hkv, d, scale=Non
     mask, nn = to_dev(np.ascontiguousarray(anc_mask_np, np.uint64)), to_dev(np.asarray(n_nodes_np, np.int32))
     max_len = int(np.max(inp["kv_len"])) if B else 0
     code = sage.F32 if Q.dtype == torch.float32 else sage.BF16
-    ws = torch.empty(sage.sage_tree_attention_workspace_bytes(code, B, Hq, Hkv, d, max_len), device=DEV, dtype=torch.uint8)
+    ws = workspace(sage.sage_tree_attention_workspace_bytes(code, B, Hq, Hkv, d, max_len))
     if scale is None:
         scale = 1.0 / float(np.sqrt(d))
     first = None if first_node_np is None else to_dev(np.asarray(first_node_np, np.int32))
@@ -146,7 +152,7 @@ def gpu_lm_head_topk(hidden_np, weight_np, k, n_valid=None, rows_per_group=1):
     f = lambda *s: torch.full(s, float("nan"), device=DEV, dtype=torch.float32)
     out = dict(entropy=f(rows), topk_idx=torch.full((rows, k), -1, device=DEV, dtype=torch.int32), topk_prob=f(rows, k),
                topk_renorm=f(rows, k), topk_entropy=f(rows), alpha=f(rows))
-    ws = torch.empty(sage.sage_lm_head_topk_workspace_bytes(rows, vocab, k), device=DEV, dtype=torch.uint8)
+    ws = workspace(sage.sage_lm_head_topk_workspace_bytes(rows, vocab, k))
     nv = None if n_valid is None else to_dev(np.asarray(n_valid, np.int32))
     sage.sage_lm_head_topk(h, w, k, out["entropy"], out["topk_idx"], out["topk_prob"], out["topk_renorm"],
                            out["topk_entropy"], out["alpha"], ws, nv, rows_per_group)
@@ -165,7 +171,7 @@ def gpu_plan_from_slices(logits_np, k, prm: dict, d_max_seq_np=None):
     a2 = dict(n_nodes=torch.zeros(B, device=DEV, dtype=torch.int32), parent=i32(-2), depth=i32(-2), rank=i32(-2),
               anc_mask=torch.zeros((B, MAX_NODES), device=DEV, dtype=torch.int64),
               cum_prob=torch.full((B, MAX_NODES), float("nan"), device=DEV, dtype=torch.float32), node_token=i32(-2))
-    ws = torch.empty(sage.sage_entropy_topk_workspace_bytes(B, vocab, k), device=DEV, dtype=torch.uint8)
+    ws = workspace(sage.sage_entropy_topk_workspace_bytes(B, vocab, k))
     dm = None if d_max_seq_np is None else to_dev(np.ascontiguousarray(d_max_seq_np, np.int32))
     sage.sage_entropy_topk_slices(x, k, ws)
     sage.sage_build_tree_from_slices(ws, vocab, sage.tree_params(**prm), a1["entropy"], a1["topk_idx"], a1["topk_prob"],
@@ -188,7 +194,7 @@ def gpu_attention_with_plan(inp: dict, anc_mask_np, n_nodes_np, Hq, Hkv, d, logi
     mask, nn = to_dev(np.ascontiguousarray(anc_mask_np, np.uint64)), to_dev(np.asarray(n_nodes_np, np.int32))
     max_len = int(np.max(inp["kv_len"])) if B else 0
     code = sage.F32 if Q.dtype == torch.float32 else sage.BF16
-    ws3 = torch.empty(sage.sage_tree_attention_workspace_bytes(code, B, Hq, Hkv, d, max_len), device=DEV, dtype=torch.uint8)
+    ws3 = workspace(sage.sage_tree_attention_workspace_bytes(code, B, Hq, Hkv, d, max_len))
     x = to_dev(logits_np)
     assert x.shape[0] == B
     vocab = x.shape[1]
@@ -199,7 +205,7 @@ def gpu_attention_with_plan(inp: dict, anc_mask_np, n_nodes_np, Hq, Hkv, d, logi
     a2 = dict(n_nodes=torch.zeros(B, device=DEV, dtype=torch.int32), parent=i32(-2), depth=i32(-2), rank=i32(-2),
               anc_mask=torch.zeros((B, MAX_NODES), device=DEV, dtype=torch.int64),
               cum_prob=torch.full((B, MAX_NODES), float("nan"), device=DEV, dtype=torch.float32), node_token=i32(-2))
-    ws1 = torch.empty(sage.sage_entropy_topk_workspace_bytes(B, vocab, k), device=DEV, dtype=torch.uint8)
+    ws1 = workspace(sage.sage_entropy_topk_workspace_bytes(B, vocab, k))
     dm = None if d_max_seq_np is None else to_dev(np.ascontiguousarray(d_max_seq_np, np.int32))
     sage.sage_entropy_topk_slices(x, k, ws1)
     sage.sage_tree_attention_with_plan(Q, Kc, Vc, Kt, Vt, O, kv_start, kv_len, max_len, inp["kv_token_stride"],
@@ -228,7 +234,7 @@ def gpu_accept_from_slices(target_logits_np, token, parent, depth, anc_mask, n_n
                best_node=torch.full((B,), -9, device=DEV, dtype=torch.int32),
                path_nodes=torch.full((B, path_cap), -9, device=DEV, dtype=torch.int32),
                out_tokens=torch.full((B, path_cap), -9, device=DEV, dtype=torch.int32))
-    ws = torch.empty(sage.sage_entropy_topk_workspace_bytes(rows, vocab, 1), device=DEV, dtype=torch.uint8)
+    ws = workspace(sage.sage_entropy_topk_workspace_bytes(rows, vocab, 1))
     sage.sage_entropy_topk_slices(x, 1, ws, nn, MAX_NODES)
     sage.sage_verify_accept_from_slices(ws, vocab, args[0], args[1], args[2], mask, nn, path_cap, out["entropy"],
                                         out["target_argmax"], out["accept_len"], out["best_node"], out["path_nodes"],

@@ -124,6 +124,35 @@ def test_topk_selection_edges(gu, dtype, kind, vocab, k):
     np.testing.assert_allclose(g1["topk_prob"], o1["topk_prob"], rtol=1e-5, atol=1e-7)
 
 
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("k", [2, 3, 4, 5, 6, 17])
+def test_topk_short_last_slice(gu, dtype, k):
+    """A last slice of 1024 with fewer logits than k, about k, and the winners of a row among them; in one call, and through
+    the pair of slice passes and the planning call."""
+    import torch
+    from paper_2602_00523_amd import sage
+    prm = dict(d_min=1, d_max=4, w_min=1, w_max=k, k=k, n_max=16)
+    for vocab in [1024 * m + r for m in (1, 3) for r in sorted({1, k - 1, k, k + 1})]:
+        tail = vocab % 1024
+        x = wl.rng(vocab * 64 + k).standard_normal((3, vocab)).astype(np.float32)
+        x[0, -tail:] += 20.0                             # row 0: all of the last slice wins; row 1: none of it
+        x[1, -tail:] -= 20.0
+        x[2, 7] = x[2, -1] = 30.0                        # row 2: an equal pair, the second in the last slice
+        x = wl.to_storage(np.pad(x, ((0, 0), (0, -vocab % 16))), dtype)[:, :vocab]
+        want = oracle.entropy_topk(x, k)["topk_idx"]
+        np.testing.assert_array_equal(gu.gpu_entropy_topk(x, k)["topk_idx"], want, err_msg=f"vocab {vocab}")
+        dev = gu.to_dev(x.base)[:, :vocab]
+        ws_a, ws_b = (gu.workspace(sage.sage_entropy_topk_workspace_bytes(3, vocab, n)) for n in (1, k))
+        sage.sage_entropy_topk_slices_pair(dev, torch.tensor([3], device=dev.device, dtype=torch.int32), 3, ws_a, dev, k, ws_b)
+        f = lambda *s: torch.zeros(*s, device=dev.device)  # noqa: E731
+        i32 = lambda *s: torch.zeros(*s, device=dev.device, dtype=torch.int32)  # noqa: E731
+        idx, alpha = i32(3, k), f(3)
+        sage.sage_build_tree_from_slices(ws_b, vocab, sage.tree_params(**prm), None, idx, None, f(3, k), None, alpha, i32(3),
+                                         i32(3, MAX_NODES), i32(3, MAX_NODES), i32(3, MAX_NODES),
+                                         torch.zeros(3, MAX_NODES, device=dev.device, dtype=torch.int64))
+        np.testing.assert_array_equal(idx.cpu().numpy(), want, err_msg=f"vocab {vocab}, pair")
+
+
 @pytest.mark.parametrize("rows,rpg,n_valid,vocab,dtype", [
     (150, 64, [64, 33, 22], 5000, "f32"),            # a short last group (22 rows): every one of its rows counts
     (150, 64, [17, 0, 99], 70008, "bf16"),           # n_valid beyond the group's rows is clamped
