@@ -351,6 +351,17 @@ int lm_head_rows_units(int vocab, int rows) {
     return sh.ranges * sh.units_per_range;
 }
 
+// Most slices per row that any call with up to `rows` (> 64) rows uses: more row blocks mean fewer ranges and, by rounding,
+// sometimes fewer units (152064 tokens: 768 with one block, 640 with two), and a workspace for `rows` rows has to do for fewer.
+int lm_head_rows_most_units(int vocab, int rows) {
+    int most = 0;
+    for (int r = BLOCK_ROWS; ; r += BLOCK_ROWS) {            // a row count of each number of blocks; past CUS blocks nothing changes
+        const int n = lm_head_rows_units(vocab, r);
+        most = n > most ? n : most;
+        if (r >= rows || r >= CUS * BLOCK_ROWS) return most;
+    }
+}
+
 int launch_lm_head_rows(const void* hidden, const void* weight, int rows, int dim, int vocab, long hidden_stride,
                         long weight_stride, const int* n_valid, int rows_per_group, UnitStats* stats, uint64_t* keys, hipStream_t s) {
     const Shape sh = launch_shape(vocab, rows);

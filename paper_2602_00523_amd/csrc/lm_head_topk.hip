@@ -30,6 +30,7 @@ using namespace sage::topk;
 
 namespace sage {
 int lm_head_rows_units(int vocab, int rows);
+int lm_head_rows_most_units(int vocab, int rows);
 int launch_lm_head_rows(const void*, const void*, int, int, int, long, long, const int*, int, UnitStats*, uint64_t*, hipStream_t);
 }  // namespace sage
 
@@ -388,7 +389,8 @@ inline int slices_of(int vocab, int rows) { return rows > TILE_R ? sage::lm_head
 
 extern "C" size_t sage_lm_head_topk_workspace_bytes(int rows, int vocab, int k) {
     if (rows < 0 || vocab < 1 || k < 1) return 0;
-    const int n = slices_of(vocab, rows);
+    // (no smaller than for any smaller number of rows: a workspace for the largest batch does for every batch)
+    const int n = rows > TILE_R ? sage::lm_head_rows_most_units(vocab, rows) : slices_of(vocab, rows);
     return align256(static_cast<size_t>(rows) * n * sizeof(UnitStats)) + static_cast<size_t>(rows) * n * k * sizeof(uint64_t) + 256;
 }
 

@@ -49,6 +49,21 @@ def test_workspace_sizes_are_pure_host_functions(lib):
     assert 0 < w1 <= w2 < (1 << 28)
 
 
+@pytest.mark.parametrize("vocab", [1, 63, 5000, 32000, 50257, 65536, 152064, 200000, 655360])
+def test_workspace_for_a_batch_does_for_a_smaller_one(lib, vocab):
+    """A program allocates once, for its largest batch: the size never falls when rows, k or the vocabulary grow."""
+    for name in ("sage_lm_head_topk_workspace_bytes", "sage_entropy_topk_workspace_bytes"):
+        size = getattr(lib, name)
+        size.restype = ctypes.c_size_t
+        for k in (1, 16):
+            last = 0
+            for rows in sorted({*range(0, 1100), *range(1100, 70000, 97), 1 << 20}):
+                now = size(rows, vocab, k)
+                assert last <= now, (name, rows, k)
+                assert now <= size(rows, vocab + 64, k) and now <= size(rows, vocab, k + 1)
+                last = now
+
+
 def test_invalid_arguments_are_rejected_on_the_host(lib):
     INVALID = 1
     null = ctypes.c_void_p(0)
