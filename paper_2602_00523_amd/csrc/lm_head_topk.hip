@@ -48,6 +48,7 @@ constexpr int CHUNK = 128;               // hidden elements per stage
 constexpr int ROW_B = CHUNK * 2;         // bytes of one row of a stage
 constexpr int THREADS = 256;
 constexpr int MAX_K = 16;                // largest candidate list per row
+constexpr int MAX_VOCAB = 655360;        // 1024 units of 10 tiles
 constexpr int CUS = 256;                 // compute units of the MI355X: workgroups of a launch that stay resident
 constexpr int STAGES = 8;                // weight ring: all but one stage in flight per workgroup
 // stage layout: row t at (t % 16) * GROUP + (t / 16) * ROW_B; a group is the 1 KB one wave-level LDS-direct load
@@ -413,7 +414,8 @@ extern "C" int sage_lm_head_topk(const void* hidden, const void* weight, int dty
     if (workspace_bytes < sage_lm_head_topk_workspace_bytes(rows, vocab, k)) return SAGE_WORKSPACE_TOO_SMALL;
     if (rows == 0) return SAGE_OK;
     const int nunits = slices_of(vocab, rows);
-    if (nunits > sage::topk_merge_max_units(k)) return SAGE_UNSUPPORTED;
+    // (one limit for every number of rows; the second pass takes what either kernel cuts such a vocabulary into)
+    if (vocab > MAX_VOCAB || nunits > sage::topk_merge_max_units(k)) return SAGE_UNSUPPORTED;
     UnitStats* stats = static_cast<UnitStats*>(workspace);
     uint64_t* keys = reinterpret_cast<uint64_t*>(static_cast<char*>(workspace) +
                                                  align256(static_cast<size_t>(rows) * nunits * sizeof(UnitStats)));

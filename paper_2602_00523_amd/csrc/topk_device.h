@@ -10,7 +10,9 @@ namespace topk {
 constexpr int MERGE_THREADS = 256;
 constexpr int MERGE_LDS_KEYS = 6144;     // lists are staged in LDS when they fit (48 KB)
 constexpr int MAX_OWN = 16;              // lists per lane in the second pass: up to 1024 slices = 1M logits
-constexpr int MERGE_MAX_OWN = 32;        // ... in the second pass of k = 1 as a launch of its own (projections cut the vocabulary finer)
+// ... in the second pass of k = 1 as a launch of its own: projections of more than 64 rows cut the vocabulary into units of at
+// most 256, up to 2635 of them at the 655360 tokens that they take
+constexpr int MERGE_MAX_OWN = 42;
 
 // The wave-wide reductions of sage_internal.h, under this namespace's names.
 using sage::wave_max;

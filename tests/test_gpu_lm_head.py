@@ -242,3 +242,21 @@ def test_logits_that_are_not_finite(gu, rows, value):
     g = gu.gpu_lm_head_topk(h, w, 1)
     assert np.isnan(g["entropy"]).all()
     np.testing.assert_array_equal(g["topk_idx"][:, 0], clean if np.isnan(value) else np.full(rows, 1234))
+
+
+@pytest.mark.parametrize("rows", [3, 70, 600])
+def test_largest_vocabulary(gu, rows):
+    """The same limit for every number of rows: 655360 tokens are taken (70 and 600 rows: more than 2048 slices per row), one
+    more is refused."""
+    import torch
+    from paper_2602_00523_amd import sage
+    dim, vocab = 128, 655360
+    w = wl.gaussian(21, (vocab + 1, dim), "bf16", 3.0 / np.sqrt(dim))
+    h = wl.gaussian(22, (rows, dim), "bf16", 1.0)
+    w[vocab - 1] = h[rows - 1]                           # the last row's winner is the last token
+    exact, n = check(gu, h, w[:vocab], rows_checked=sorted({0, rows // 2, rows - 1}))
+    assert exact == n
+    hd, wd = gu.to_dev(h), gu.to_dev(w)
+    out, ws = torch.zeros(rows, 1, device=hd.device, dtype=torch.int32), gu.workspace(1 << 28)
+    with pytest.raises(sage.SageError, match="UNSUPPORTED"):
+        sage.sage_lm_head_topk(hd, wd, 1, None, out, None, None, None, None, ws)
