@@ -88,12 +88,17 @@ __device__ __forceinline__ void stage_barrier() {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// TOPK: k candidates per (row, unit) instead of one (the draft side of Sec. 3.1, whose rows are few): after the fold, the
-// unit's logits of 32 rows at a time are laid out in the idle ring and a wave per row finds a value that at least k and at
-// most 64 of them reach (about nine bits of a threshold, a ballot per 64 logits and bit), then ranks those by counting: about a
-// microsecond a row.  k rounds over the logits in registers, which this replaced, took 2 to 3 us each whatever the rows,
-// at the end of every workgroup's only unit, when no loads are in flight (16 rows, hidden 3584, vocabulary 152064, k = 10:
-// 230 -> 216 us, of which the stream of the weights takes about 190).
+// TOPK: k candidates per (row, unit) instead of one (the draft side of Sec. 3.1, whose rows are few), after the fold, at the
+// end of every workgroup's only unit, when no loads are in flight.  Two ways, by the number of live rows and k:
+//   counting: the unit's logits of 32 rows at a time are laid out in the idle ring and a wave per row finds a value that at
+//     least k and at most 64 of them reach (about nine bits of a threshold, a ballot per 64 logits and bit), then ranks those
+//     by counting, four rows side by side: 1.0 us a live row (T = 10; T = 5: 0.3 to 0.45), whatever k;
+//   rounds: every lane scans its 16 T logits for the best one after the previous winner, the four lanes of a row are combined
+//     (lane halves by a swap, vocabulary halves through LDS): 3.1 us each (T = 5: 1.6), whatever the rows.
+// LIST_ROWS_PER_K live rows per candidate is where the two meet, within 1 us of it for every k (us of the call, counting /
+// rounds; vocabulary 152064, hidden 1024, T = 10: 16 rows k = 4 80.8 / 77.3 and k = 8 81.2 / 89.1, 32 rows k = 8 96.5 / 89.2
+// and k = 12 97.0 / 101.0, 64 rows k = 16 132 / 114; vocabulary 32000, hidden 3584, T = 5: 16 rows k = 3 72.1 / 68.3 and k = 6
+// 72.6 / 73.5, 64 rows k = 16 92.6 / 90.6).
 template <int T, bool TOPK>
 __global__ __launch_bounds__(THREADS) void lm_head_kernel(const Params prm) {
     // The ring position of a step must be a compile-time constant (every stage is its own LDS object, so that loads
@@ -103,6 +108,7 @@ __global__ __launch_bounds__(THREADS) void lm_head_kernel(const Params prm) {
     constexpr int UNROLL = (T % 8 == 0) ? 1 : (T % 4 == 0) ? 2 : (T % 2 == 0) ? 4 : 8;
     static_assert((UNROLL * T) % STAGES == 0, "ring positions must be static");
     constexpr int ROWS = TILE_R;                             // hidden rows of this workgroup
+    constexpr int LIST_ROWS_PER_K = T > 5 ? 3 : 4;           // candidate lists: see above
     __shared__ __align__(16) unsigned char sW0[STAGE_B];
     __shared__ __align__(16) unsigned char sW1[STAGE_B];
     __shared__ __align__(16) unsigned char sW2[STAGE_B];
@@ -117,11 +123,12 @@ __global__ __launch_bounds__(THREADS) void lm_head_kernel(const Params prm) {
     __shared__ int s_row[ROWS];                              // hidden row behind each of this block's slots, -1 = none
     __shared__ int s_cnt[THREADS];
     __shared__ __align__(16) uint64_t s_cand[TOPK ? THREADS / 64 : 1][TOPK ? 64 : 1];   // candidate lists: what a wave ranks
+    __shared__ uint64_t s_sel[TOPK ? 2 : 1][TOPK ? TILE_R : 1][2];   // candidate rounds: a row's winner per vocabulary half
 #define SW(i) ((i) == 0 ? sW0 : (i) == 1 ? sW1 : (i) == 2 ? sW2 : (i) == 3 ? sW3 : (i) == 4 ? sW4 : (i) == 5 ? sW5 : (i) == 6 ? sW6 : sW7)
 
     const int tid = threadIdx.x;
-    // ---- the rows: slot j is live row number j, counted over the groups in order.  Fills s_row and returns whether any row
-    // is live (the same in every thread).
+    // ---- the rows: slot j is live row number j, counted over the groups in order.  Fills s_row and returns how many
+    // are live (the same in every thread).
     auto map_rows = [&]() __attribute__((always_inline)) {
         int live = prm.rows;
         if (prm.n_valid == nullptr) {
@@ -140,9 +147,10 @@ __global__ __launch_bounds__(THREADS) void lm_head_kernel(const Params prm) {
             live = before;
         }
         __syncthreads();
-        return live > 0;
+        return live;
     };
-    if (!map_rows()) return;
+    const int live = __builtin_amdgcn_readfirstlane(map_rows());
+    if (live <= 0) return;
     // candidate lists: the codes of one hidden row (of 32) lie in the ring, CODE_ROWS rows per stage; the four words between
     // rows put the 16-byte writes of 16 consecutive rows on all 64 banks once
     constexpr int CODE_PITCH = T * TILE_V + 4, CODE_ROWS = 6;
@@ -295,73 +303,120 @@ __global__ __launch_bounds__(THREADS) void lm_head_kernel(const Params prm) {
         sage::lmhead::combine_folds(&s_part[tid][0][0], s_key[tid], prm.stats + o, TOPK ? nullptr : prm.keys + o);
     }
     if constexpr (TOPK) {
-        // The statistics are done: the logits' order-preserving codes (0 = not a candidate: past the unit's end, or -inf) of 32
-        // hidden rows go into the idle ring, row by row in vocabulary order, and a wave selects from one row at a time.
-#pragma unroll 1
-        for (int batch = 0; batch < TILE_R / 32; ++batch) {
-            if (s_row[batch * 32] < 0) break;                // (live rows come first)
+        if (live >= LIST_ROWS_PER_K * prm.k) {               // (uniform) rounds
             // (made opaque, or what depends on the thread index alone would be kept alive across the main loop)
             int lane = threadIdx.x & 63;
             asm volatile("" : "+v"(lane));
-            if (rt == batch) {
-                const int half = lane >> 5;
-                LDS_AS uint32_t* const mine = code_row(lane & 31) + 32 * vt + 4 * half;
+            const int half = lane >> 5;
+            const int hr = rt * 32 + (lane & 31);
+            const int row = s_row[hr];
+            // the statistics are done: the logits give way, in place, to their order-preserving codes (0 = not a candidate: past
+            // the unit's end, or -inf), so that a round costs one 64-bit compare pair per logit
+#pragma unroll
+            for (int t = 0; t < T; ++t) {
+                int left = v_end - ((tile_begin + t) * TILE_V + 32 * vt + 4 * half);
+                asm volatile("" : "+v"(left));               // (or the fold's comparison masks would be kept for this loop)
+#pragma unroll
+                for (int i = 0; i < 16; ++i) {
+                    const float x = acc[t][i];
+                    acc[t][i] = __uint_as_float((8 * (i >> 2) + (i & 3) < left && x > -INFINITY) ? sortable(x) : 0u);
+                }
+            }
+            uint64_t prev = ~0ull;                           // the previous winner: candidates come after it in the order
+            for (int j = 0; j < prm.k; ++j) {
+                uint64_t best = 0xFFFFFFFFull;               // (code 0, lowest index word): below every candidate
 #pragma unroll
                 for (int t = 0; t < T; ++t) {
-                    int left = v_end - ((tile_begin + t) * TILE_V + 32 * vt + 4 * half);
-                    asm volatile("" : "+v"(left));           // (or the fold's comparison masks would be kept for this loop)
+                    uint32_t lo0 = 0xFFFFFFFFu - static_cast<uint32_t>((tile_begin + t) * TILE_V + 32 * vt + 4 * half);
+                    asm volatile("" : "+v"(lo0));            // (or 16 T index words would be kept for all rounds)
 #pragma unroll
-                    for (int i0 = 0; i0 < 16; i0 += 4) {
-                        uint32_t code[4];
-#pragma unroll
-                        for (int i = 0; i < 4; ++i) {
-                            const float x = acc[t][i0 + i];
-                            code[i] = (2 * i0 + i < left && x > -INFINITY) ? sortable(x) : 0u;
-                        }
-                        *(LDS_AS u32x4*)(mine + t * TILE_V + 2 * i0) = u32x4{code[0], code[1], code[2], code[3]};
+                    for (int i = 0; i < 16; ++i) {
+                        const uint64_t key = (static_cast<uint64_t>(__float_as_uint(acc[t][i])) << 32) | (lo0 - (8 * (i >> 2) + (i & 3)));
+                        best = (key < prev && key > best) ? key : best;
                     }
-                    __builtin_amdgcn_sched_barrier(0);
                 }
+                Key mine = (best >> 32) == 0 ? Key{0, 0} : key_unpack(best);
+                {                                            // the other lane half of this row
+                    const auto hi = __builtin_amdgcn_permlane32_swap(mine.hi, mine.hi, false, false);
+                    const auto lo = __builtin_amdgcn_permlane32_swap(mine.lo, mine.lo, false, false);
+                    mine = key_max(Key{hi[0], lo[0]}, Key{hi[1], lo[1]});
+                }
+                if (half == 0) s_sel[j & 1][hr][vt] = key_pack(mine);
+                __syncthreads();                             // (rounds alternate between two buffers: one barrier per round)
+                const Key w = key_max(key_unpack(s_sel[j & 1][hr][0]), key_unpack(s_sel[j & 1][hr][1]));
+                if (vt == 0 && half == 0 && row >= 0)
+                    prm.keys[(static_cast<long>(row) * prm.nunits + unit) * prm.k + j] = key_pack(w);
+                prev = key_none(w) ? 0ull : key_pack(w);     // an exhausted unit: nothing comes after
             }
-            __syncthreads();
+        } else {
+            // The statistics are done: the logits' order-preserving codes (0 = not a candidate: past the unit's end, or -inf) of 32
+            // hidden rows go into the idle ring, row by row in vocabulary order, and a wave selects from one row at a time.
 #pragma unroll 1
-            for (int q = wave; q < 32; q += THREADS / 64) {
-                const int row = __builtin_amdgcn_readfirstlane(s_row[batch * 32 + q]);
-                if (row < 0) break;
-                const LDS_AS uint32_t* const codes = code_row(q);
-                uint32_t code[T];
-                bool have[T], in[T];
-                int present = 0;
+            for (int batch = 0; batch < TILE_R / 32; ++batch) {
+                if (s_row[batch * 32] < 0) break;                // (live rows come first)
+                // (made opaque, or what depends on the thread index alone would be kept alive across the main loop)
+                int lane = threadIdx.x & 63;
+                asm volatile("" : "+v"(lane));
+                if (rt == batch) {
+                    const int half = lane >> 5;
+                    LDS_AS uint32_t* const mine = code_row(lane & 31) + 32 * vt + 4 * half;
 #pragma unroll
-                for (int i = 0; i < T; ++i) code[i] = codes[i * 64 + lane];
+                    for (int t = 0; t < T; ++t) {
+                        int left = v_end - ((tile_begin + t) * TILE_V + 32 * vt + 4 * half);
+                        asm volatile("" : "+v"(left));           // (or the fold's comparison masks would be kept for this loop)
 #pragma unroll
-                for (int i = 0; i < T; ++i) {
-                    have[i] = code[i] != 0;
-                    present += __builtin_popcountll(__ballot(have[i]));
+                        for (int i0 = 0; i0 < 16; i0 += 4) {
+                            uint32_t code[4];
+#pragma unroll
+                            for (int i = 0; i < 4; ++i) {
+                                const float x = acc[t][i0 + i];
+                                code[i] = (2 * i0 + i < left && x > -INFINITY) ? sortable(x) : 0u;
+                            }
+                            *(LDS_AS u32x4*)(mine + t * TILE_V + 2 * i0) = u32x4{code[0], code[1], code[2], code[3]};
+                        }
+                        __builtin_amdgcn_sched_barrier(0);
+                    }
                 }
-                // at least k candidates and no more than a lane can take each; of equal values the lowest indices
-                wave_pick<T>(code, have, min(prm.k, present), 64, in);
-                int n = 0;
+                __syncthreads();
+#pragma unroll 1
+                for (int q = wave; q < 32; q += THREADS / 64) {
+                    const int row = __builtin_amdgcn_readfirstlane(s_row[batch * 32 + q]);
+                    if (row < 0) break;
+                    const LDS_AS uint32_t* const codes = code_row(q);
+                    uint32_t code[T];
+                    bool have[T], in[T];
+                    int present = 0;
 #pragma unroll
-                for (int i = 0; i < T; ++i) {
-                    const uint64_t b = __ballot(in[i]);
-                    if (in[i])
-                        s_cand[wave][n + static_cast<int>(__builtin_amdgcn_mbcnt_hi(static_cast<uint32_t>(b >> 32), __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(b), 0u)))] =
-                            key_pack(Key{code[i], 0xFFFFFFFFu - static_cast<uint32_t>(tile_begin * TILE_V + i * 64 + lane)});
-                    n += __builtin_popcountll(b);
+                    for (int i = 0; i < T; ++i) code[i] = codes[i * 64 + lane];
+#pragma unroll
+                    for (int i = 0; i < T; ++i) {
+                        have[i] = code[i] != 0;
+                        present += __builtin_popcountll(__ballot(have[i]));
+                    }
+                    // at least k candidates and no more than a lane can take each; of equal values the lowest indices
+                    wave_pick<T>(code, have, min(prm.k, present), 64, in);
+                    int n = 0;
+#pragma unroll
+                    for (int i = 0; i < T; ++i) {
+                        const uint64_t b = __ballot(in[i]);
+                        if (in[i])
+                            s_cand[wave][n + static_cast<int>(__builtin_amdgcn_mbcnt_hi(static_cast<uint32_t>(b >> 32), __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(b), 0u)))] =
+                                key_pack(Key{code[i], 0xFFFFFFFFu - static_cast<uint32_t>(tile_begin * TILE_V + i * 64 + lane)});
+                        n += __builtin_popcountll(b);
+                    }
+                    if (lane >= n && lane < ((n + 15) & ~15)) s_cand[wave][lane] = 0;   // whole pieces of 16 to count in
+                    // (a wave's LDS operations complete in order; the fence keeps the compiler from reading ahead of the writes)
+                    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+                    __builtin_amdgcn_wave_barrier();
+                    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+                    uint64_t* const out = prm.keys + (static_cast<long>(row) * prm.nunits + unit) * prm.k;
+                    const uint64_t key = lane < n ? s_cand[wave][lane] : 0;
+                    const int above = count_above(s_cand[wave], (n + 15) & ~15, key);
+                    if (lane < n && above < prm.k) out[above] = key;
+                    if (lane >= n && lane < prm.k) out[lane] = 0;   // fewer candidates than k
                 }
-                if (lane >= n && lane < ((n + 15) & ~15)) s_cand[wave][lane] = 0;   // whole pieces of 16 to count in
-                // (a wave's LDS operations complete in order; the fence keeps the compiler from reading ahead of the writes)
-                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-                __builtin_amdgcn_wave_barrier();
-                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-                uint64_t* const out = prm.keys + (static_cast<long>(row) * prm.nunits + unit) * prm.k;
-                const uint64_t key = lane < n ? s_cand[wave][lane] : 0;
-                const int above = count_above(s_cand[wave], (n + 15) & ~15, key);
-                if (lane < n && above < prm.k) out[above] = key;
-                if (lane >= n && lane < prm.k) out[lane] = 0;   // fewer candidates than k
+                __syncthreads();                                 // the next batch's codes go over these
             }
-            __syncthreads();                                 // the next batch's codes go over these
         }
     }
     __syncthreads();                                         // the next unit rewrites s_part

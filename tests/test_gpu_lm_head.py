@@ -229,6 +229,28 @@ def test_candidate_lists_of_equal_logits(gu, rows, vocab, k):
     np.testing.assert_allclose(g["topk_renorm"], 1.0 / k, rtol=1e-5)
 
 
+@pytest.mark.parametrize("vocab,per_k", [(2100, 4), (82000, 3)])
+@pytest.mark.parametrize("k", [2, 7, 16])
+def test_candidate_lists_by_rounds_and_by_counting(gu, vocab, per_k, k):
+    """A list is selected by rounds from per_k k live rows on, below by counting (one row alone: by counting): the same
+    tokens and probabilities, with equal logits, -inf logits and a row that has fewer candidates than k in some units."""
+    dim = 128
+    h = np.abs(wl.bf16_bits_to_f32(wl.gaussian(61, (64, dim), "bf16", 1.0)))
+    h = (h.view(np.uint32) >> 16).astype(np.uint16)
+    w = wl.gaussian(62 + vocab, (vocab, dim), "bf16", 0.1)
+    w[100:160] = w[1900]                                        # equal logits across tiles, and across units of the larger one
+    minus_inf = np.array([-np.inf], np.float32).view(np.uint32)[0] >> 16
+    w[500:1500, 3] = minus_inf                                  # whole tiles without a candidate
+    rows = [0, 1, 31, 32, 40, 63]
+    alone = {r: gu.gpu_lm_head_topk(h[r:r + 1], w, k) for r in rows}
+    for live in sorted({min(64, per_k * k - 1), min(64, per_k * k), 64}):
+        g = gu.gpu_lm_head_topk(h, w, k, np.array([live], np.int32), 64)
+        for r in rows:
+            for key in ("topk_idx", "topk_prob", "topk_renorm", "topk_entropy", "alpha", "entropy"):
+                if r < live:
+                    np.testing.assert_array_equal(g[key][r], alone[r][key][0], err_msg=f"{live} live, row {r}: {key}")
+
+
 @pytest.mark.parametrize("rows,value", [(5, np.nan), (5, np.inf), (70, np.nan), (70, np.inf)])
 def test_logits_that_are_not_finite(gu, rows, value):
     """A NaN or infinite logit makes the row's entropy NaN; +inf is the greedy token, a NaN is passed over."""
