@@ -464,15 +464,26 @@ __global__ __launch_bounds__(THREADS) void slice_pair_kernel(const T* __restrict
 }
 
 // Pass 2 for k = 1 (the target rows): a wave per row, no LDS and no barrier.  Statistics and candidates of the row's slices
-// are requested together (one memory round trip) and reduced in registers, OWN slices per lane at a time.
+// are requested together (one memory round trip) and reduced in registers, OWN slices per lane at a time.  units_used (nullable)
+// is the number of slices where the device has decided it, at most `nunits`; it is requested together with the row's validity,
+// so that it costs no round trip.
 template <int OWN>
 __global__ __launch_bounds__(MERGE_THREADS) void merge_one_kernel(const int* __restrict__ n_valid, int rows_per_group, int rows, int nunits,
+                                                                  const int* __restrict__ units_used,
                                                                   const UnitStats* __restrict__ stats, const uint64_t* __restrict__ keys,
                                                                   float* __restrict__ entropy, int* __restrict__ topk_idx,
                                                                   float* __restrict__ topk_prob, float* __restrict__ topk_renorm,
                                                                   float* __restrict__ topk_entropy, float* __restrict__ alpha) {
     const int row = blockIdx.x * (MERGE_THREADS / 64) + (threadIdx.x >> 6);
-    if (row >= rows || !row_is_valid(row, n_valid, rows_per_group)) return;
+    if (row >= rows) return;
+    if (units_used) {                                // (with n_valid only)
+        int used = *units_used, valid = n_valid[row / rows_per_group];
+        asm volatile("" : "+v"(used), "+v"(valid));  // both loads before the branch
+        if (row % rows_per_group >= valid) return;
+        nunits = min(__builtin_amdgcn_readfirstlane(used), nunits);
+    } else if (!row_is_valid(row, n_valid, rows_per_group)) {
+        return;
+    }
     const int lane = threadIdx.x & 63;
     const UnitStats* st = stats + static_cast<long>(row) * nunits;
     const uint64_t* kk = keys + static_cast<long>(row) * nunits;
@@ -523,19 +534,20 @@ int topk_max_units() { return 64 * MAX_OWN; }
 int topk_merge_max_units(int k) { return 64 * (k == 1 ? MERGE_MAX_OWN : MAX_OWN); }
 
 // Pass 2 for `rows` rows whose `nunits` slices each left UnitStats and k sorted keys in stats / keys ([row][unit]).
+// units_used (k = 1 only, nullable): the number of slices where the device has decided it; then `nunits` is the most it can be.
 void topk_merge(int rows, int k, const int* n_valid, int rows_per_group, int nunits, const UnitStats* stats,
                 const uint64_t* keys, float* entropy, int* topk_idx, float* topk_prob, float* topk_renorm,
-                float* topk_entropy, float* alpha, hipStream_t s) {
+                float* topk_entropy, float* alpha, hipStream_t s, const int* units_used) {
     if (k == 1) {
         const dim3 grid((rows + MERGE_THREADS / 64 - 1) / (MERGE_THREADS / 64)), block(MERGE_THREADS);
         if (nunits <= 256)
-            hipLaunchKernelGGL(merge_one_kernel<4>, grid, block, 0, s, n_valid, rows_per_group, rows, nunits, stats, keys, entropy, topk_idx,
+            hipLaunchKernelGGL(merge_one_kernel<4>, grid, block, 0, s, n_valid, rows_per_group, rows, nunits, units_used, stats, keys, entropy, topk_idx,
                                topk_prob, topk_renorm, topk_entropy, alpha);
         else if (nunits <= 64 * MAX_OWN)
-            hipLaunchKernelGGL(merge_one_kernel<MAX_OWN>, grid, block, 0, s, n_valid, rows_per_group, rows, nunits, stats, keys, entropy,
+            hipLaunchKernelGGL(merge_one_kernel<MAX_OWN>, grid, block, 0, s, n_valid, rows_per_group, rows, nunits, units_used, stats, keys, entropy,
                                topk_idx, topk_prob, topk_renorm, topk_entropy, alpha);
         else
-            hipLaunchKernelGGL(merge_one_kernel<MERGE_MAX_OWN>, grid, block, 0, s, n_valid, rows_per_group, rows, nunits, stats, keys,
+            hipLaunchKernelGGL(merge_one_kernel<MERGE_MAX_OWN>, grid, block, 0, s, n_valid, rows_per_group, rows, nunits, units_used, stats, keys,
                                entropy, topk_idx, topk_prob, topk_renorm, topk_entropy, alpha);
     } else if (nunits <= 64 * 4)
         hipLaunchKernelGGL(merge_kernel<4>, dim3(rows), dim3(MERGE_THREADS), 0, s, k, n_valid, rows_per_group, nunits, stats, keys,

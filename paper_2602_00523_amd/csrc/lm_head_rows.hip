@@ -24,7 +24,10 @@
 // 18-19 tiles per pair of CUs = 5 units of 3 or 4, 4.75 rounds of work in place of the 5 that equal units of 4 would
 // need).  Only blocks of live rows are items; a block is 64, 128, 192 or 256 rows deep.  Row blocks of one unit are
 // consecutive items of one XCD and share the unit's weights through that XCD's L2 as far as they stay together (1.21 fetches
-// of the matrix at 512 rows).
+// of the matrix at 512 rows).  Up to 128 live rows the weight stream is the bound, and what counts is that every CU has the same
+// share of it: the cut for one block, three units of at most 4 tiles on each of 256 CUs (152064 tokens), whatever the number of
+// rows; cut for the blocks of 1024 rows, 64 live ones take 459 us instead of 446, 128 of 512 470 instead of 456.  With more
+// live rows the larger units of the rows' own cut are as good or better (256 of 512: 622 us, 645 with the cut for one block).
 //
 // Measured (hidden 8192, vocabulary 152064; before = 4 waves on 320 vocabulary rows x 128 hidden rows): 512 live rows
 // 1690 -> 1080 us (1.18 PFLOP/s), 256 live 870 -> 620, 160 live 920 -> 500, 128 live 500 -> 466, 1024 live 3140 -> 1970.
@@ -51,14 +54,20 @@ constexpr int TILE_V = 64;               // vocabulary rows of a tile: a strip f
 constexpr int MAX_TILES = 4;             // tiles of a unit
 constexpr int BLOCK_ROWS = 256;          // hidden rows of a full block
 constexpr int STEP_B = 128;              // bytes of one row per step (64 elements)
+constexpr int FEW_LIVE = 128;            // up to so many live rows of any number: the vocabulary is cut as for one block
 constexpr int LDS_B = 160 * 1024;
+
+// How the vocabulary is cut; see the top of the file.
+struct Cut { int ranges, units_per_range; };
 
 struct Params {
     const unsigned char* hidden; const unsigned char* weight;
     long hidden_stride_b, weight_stride_b;
-    int rows, vocab, nsteps, ranges, units_per_range, ntiles;
+    int rows, vocab, nsteps, ntiles;
+    Cut few, all;                        // for up to FEW_LIVE live rows; for more
     const int* n_valid; int rows_per_group;
-    UnitStats* stats; uint64_t* keys;    // [rows][ranges * units_per_range]
+    UnitStats* stats; uint64_t* keys;    // [rows][units]
+    int* units_used;                     // receives the number of units, which follows from the live rows
 };
 
 template <int N> __device__ __forceinline__ void wait_vm() {
@@ -74,7 +83,7 @@ __device__ __forceinline__ void bare_barrier() {
 // One unit x row block: NV tiles = 2 NV strips of vocabulary rows (those at or past v_end repeat the last one and are masked) times
 // 64 NR hidden rows.  s_row[0 .. 64 NR) at the start of LDS holds the hidden row behind each slot (-1 = none).
 template <int NV, int NR>
-__device__ __forceinline__ void pass(const Params& prm, unsigned char* lds, int unit, int v_begin, int v_end) {
+__device__ __forceinline__ void pass(const Params& prm, unsigned char* lds, int units, int unit, int v_begin, int v_end) {
     // Stages of the weight and of the hidden ring: as many as fit (small units would otherwise have too little in flight),
     // the same number unless only two hidden stages fit beside three weight stages.
     constexpr int FIT = LDS_B / ((NV + NR) * TILE_V * STEP_B);
@@ -259,7 +268,7 @@ __device__ __forceinline__ void pass(const Params& prm, unsigned char* lds, int 
     }
     __syncthreads();
     if (my_row >= 0) {
-        const long o = static_cast<long>(my_row) * (prm.ranges * prm.units_per_range) + unit;
+        const long o = static_cast<long>(my_row) * units + unit;
         sage::lmhead::combine_folds(s_part + tid * 12, s_key + tid * 4, prm.stats + o, prm.keys + o);
     }
 }
@@ -298,25 +307,28 @@ __global__ __launch_bounds__(THREADS) void lm_head_rows_kernel(const Params prm)
         return live;
     };
     const int live = __builtin_amdgcn_readfirstlane(map_rows(0));
+    if (live <= 0) return;
     const int blocks = (live + BLOCK_ROWS - 1) / BLOCK_ROWS;
-    const int units = prm.ranges * prm.units_per_range;
+    const Cut cut = live <= FEW_LIVE ? prm.few : prm.all;
+    const int units = cut.ranges * cut.units_per_range;
+    if (prm.units_used && blockIdx.x == 0 && tid == 0) *prm.units_used = units;
     const int items = ((units + 7) / 8) * 8 * blocks;
     for (int item = blockIdx.x; item < items; item += gridDim.x) {
         const int slot = item >> 3;
         const int u = (slot / blocks) * 8 + (item & 7);      // first units of all ranges, then second ones, ...
         const int rb = slot % blocks;
         if (u >= units) continue;                            // (uniform)
-        const int range = u % prm.ranges, j = u / prm.ranges;
-        const int r_begin = static_cast<int>(static_cast<long>(range) * prm.ntiles / prm.ranges);
-        const int r_tiles = static_cast<int>(static_cast<long>(range + 1) * prm.ntiles / prm.ranges) - r_begin;   // >= units_per_range
-        const int t_begin = r_begin + j * r_tiles / prm.units_per_range;                // even shares: 1 to MAX_TILES
-        const int t_end = r_begin + (j + 1) * r_tiles / prm.units_per_range;
+        const int range = u % cut.ranges, j = u / cut.ranges;
+        const int r_begin = static_cast<int>(static_cast<long>(range) * prm.ntiles / cut.ranges);
+        const int r_tiles = static_cast<int>(static_cast<long>(range + 1) * prm.ntiles / cut.ranges) - r_begin;   // >= units_per_range
+        const int t_begin = r_begin + j * r_tiles / cut.units_per_range;                // even shares: 1 to MAX_TILES
+        const int t_end = r_begin + (j + 1) * r_tiles / cut.units_per_range;
         const int rows_here = min(BLOCK_ROWS, live - rb * BLOCK_ROWS);
         __syncthreads();                                     // the previous item has left LDS
         map_rows(rb);
         const int v_begin = t_begin * TILE_V, v_end = min(prm.vocab, t_end * TILE_V);
         const int nv = t_end - t_begin, nr = (rows_here + 63) / 64;
-#define SAGE_PASS(V, R) pass<V, R>(prm, lds, u, v_begin, v_end)
+#define SAGE_PASS(V, R) pass<V, R>(prm, lds, units, u, v_begin, v_end)
         if (nv == 4) {
             if (nr == 4) SAGE_PASS(4, 4); else if (nr == 3) SAGE_PASS(4, 3); else if (nr == 2) SAGE_PASS(4, 2); else SAGE_PASS(4, 1);
         } else if (nv == 3) {
@@ -330,51 +342,53 @@ __global__ __launch_bounds__(THREADS) void lm_head_rows_kernel(const Params prm)
     }
 }
 
-struct Shape { int ranges, units_per_range, ntiles; };
-inline Shape launch_shape(int vocab, int rows) {
-    Shape sh;
-    sh.ntiles = (vocab + TILE_V - 1) / TILE_V;
-    const int blocks = (rows + BLOCK_ROWS - 1) / BLOCK_ROWS;
-    sh.ranges = CUS / blocks > 1 ? CUS / blocks : 1;
-    if (sh.ranges > sh.ntiles) sh.ranges = sh.ntiles;
-    const int most = (sh.ntiles + sh.ranges - 1) / sh.ranges;
-    sh.units_per_range = (most + MAX_TILES - 1) / MAX_TILES;
-    return sh;
-}
-
 }  // namespace
 
 namespace sage {
 
-int lm_head_rows_units(int vocab, int rows) {
-    const Shape sh = launch_shape(vocab, rows);
-    return sh.ranges * sh.units_per_range;
+static Cut cut_vocabulary(int vocab, int rows) {
+    const int ntiles = (vocab + TILE_V - 1) / TILE_V, blocks = (rows + BLOCK_ROWS - 1) / BLOCK_ROWS;
+    Cut c;
+    c.ranges = CUS / blocks > 1 ? CUS / blocks : 1;
+    if (c.ranges > ntiles) c.ranges = ntiles;
+    const int most = (ntiles + c.ranges - 1) / c.ranges;
+    c.units_per_range = (most + MAX_TILES - 1) / MAX_TILES;
+    return c;
 }
 
-// Most slices per row that any call with up to `rows` (> 64) rows uses: more row blocks mean fewer ranges and, by rounding,
-// sometimes fewer units (152064 tokens: 768 with one block, 640 with two), and a workspace for `rows` rows has to do for fewer.
-int lm_head_rows_most_units(int vocab, int rows) {
+// Slices per row when more than FEW_LIVE of the rows are live.
+int lm_head_rows_units(int vocab, int rows) {
+    const Cut c = cut_vocabulary(vocab, rows);
+    return c.ranges * c.units_per_range;
+}
+
+// Slices that a row has room for: the most of any number of rows up to `rows`, since few live rows are cut for as one block and
+// a workspace has to do for fewer rows.  More row blocks mean fewer ranges and, by rounding, sometimes fewer units (152064
+// tokens: 768 with one block, 640 with two).
+int lm_head_rows_slots(int vocab, int rows) {
     int most = 0;
-    for (int r = BLOCK_ROWS; ; r += BLOCK_ROWS) {            // a row count of each number of blocks; past CUS blocks nothing changes
+    for (int r = BLOCK_ROWS; ; r += BLOCK_ROWS) {            // past CUS blocks nothing changes
         const int n = lm_head_rows_units(vocab, r);
         most = n > most ? n : most;
         if (r >= rows || r >= CUS * BLOCK_ROWS) return most;
     }
 }
 
+// units_used: receives the number of slices per row, which the live rows decide (nullable: nobody needs to know).
 int launch_lm_head_rows(const void* hidden, const void* weight, int rows, int dim, int vocab, long hidden_stride,
-                        long weight_stride, const int* n_valid, int rows_per_group, UnitStats* stats, uint64_t* keys, hipStream_t s) {
-    const Shape sh = launch_shape(vocab, rows);
+                        long weight_stride, const int* n_valid, int rows_per_group, UnitStats* stats, uint64_t* keys, int* units_used, hipStream_t s) {
     Params p;
     p.hidden = static_cast<const unsigned char*>(hidden);
     p.weight = static_cast<const unsigned char*>(weight);
     p.hidden_stride_b = hidden_stride * 2;
     p.weight_stride_b = weight_stride * 2;
     p.rows = rows; p.vocab = vocab; p.nsteps = dim / 64;
-    p.ranges = sh.ranges; p.units_per_range = sh.units_per_range; p.ntiles = sh.ntiles;
+    p.ntiles = (vocab + TILE_V - 1) / TILE_V;
+    p.few = cut_vocabulary(vocab, n_valid ? 1 : rows);
+    p.all = cut_vocabulary(vocab, rows);
     p.n_valid = n_valid; p.rows_per_group = rows_per_group;
-    p.stats = stats; p.keys = keys;
-    const long most = static_cast<long>((sh.ranges * sh.units_per_range + 7) / 8) * 8 * ((rows + BLOCK_ROWS - 1) / BLOCK_ROWS);
+    p.stats = stats; p.keys = keys; p.units_used = units_used;
+    const long most = static_cast<long>((lm_head_rows_slots(vocab, rows) + 7) / 8) * 8 * ((rows + BLOCK_ROWS - 1) / BLOCK_ROWS);
     hipLaunchKernelGGL(lm_head_rows_kernel, dim3(most < CUS ? static_cast<unsigned>(most) : CUS), dim3(THREADS), 0, s, p);
     return launch_status();
 }

@@ -30,8 +30,8 @@ using namespace sage::topk;
 
 namespace sage {
 int lm_head_rows_units(int vocab, int rows);
-int lm_head_rows_most_units(int vocab, int rows);
-int launch_lm_head_rows(const void*, const void*, int, int, int, long, long, const int*, int, UnitStats*, uint64_t*, hipStream_t);
+int lm_head_rows_slots(int vocab, int rows);
+int launch_lm_head_rows(const void*, const void*, int, int, int, long, long, const int*, int, UnitStats*, uint64_t*, int*, hipStream_t);
 }  // namespace sage
 
 namespace {
@@ -438,15 +438,15 @@ inline Shape launch_shape(int vocab) {
     sh.nunits = need > 256 ? need : (sh.ntiles < 256 ? sh.ntiles : 256);
     return sh;
 }
-// slices ("units") per row, whichever kernel fills them
-inline int slices_of(int vocab, int rows) { return rows > TILE_R ? sage::lm_head_rows_units(vocab, rows) : launch_shape(vocab).nunits; }
+// slices ("units") that a row has room for, whichever kernel fills them; never fewer than for a smaller number of rows, so that
+// a workspace for the largest batch does for every batch
+inline int slices_of(int vocab, int rows) { return rows > TILE_R ? sage::lm_head_rows_slots(vocab, rows) : launch_shape(vocab).nunits; }
 
 }  // namespace
 
 extern "C" size_t sage_lm_head_topk_workspace_bytes(int rows, int vocab, int k) {
     if (rows < 0 || vocab < 1 || k < 1) return 0;
-    // (no smaller than for any smaller number of rows: a workspace for the largest batch does for every batch)
-    const int n = rows > TILE_R ? sage::lm_head_rows_most_units(vocab, rows) : slices_of(vocab, rows);
+    const int n = slices_of(vocab, rows);
     return align256(static_cast<size_t>(rows) * n * sizeof(UnitStats)) + static_cast<size_t>(rows) * n * k * sizeof(uint64_t) + 256;
 }
 
@@ -468,16 +468,23 @@ extern "C" int sage_lm_head_topk(const void* hidden, const void* weight, int dty
     if (rows > (1 << 20)) return SAGE_UNSUPPORTED;                                            // grid size
     if (workspace_bytes < sage_lm_head_topk_workspace_bytes(rows, vocab, k)) return SAGE_WORKSPACE_TOO_SMALL;
     if (rows == 0) return SAGE_OK;
-    const int nunits = slices_of(vocab, rows);
+    int nunits = slices_of(vocab, rows);
     // (one limit for every number of rows; the second pass takes what either kernel cuts such a vocabulary into)
     if (vocab > MAX_VOCAB || nunits > sage::topk_merge_max_units(k)) return SAGE_UNSUPPORTED;
     UnitStats* stats = static_cast<UnitStats*>(workspace);
     uint64_t* keys = reinterpret_cast<uint64_t*>(static_cast<char*>(workspace) +
                                                  align256(static_cast<size_t>(rows) * nunits * sizeof(UnitStats)));
+    int* units_used = nullptr;
     hipStream_t s = sage::as_stream(stream);
     if (rows > TILE_R) {
+        // with n_valid there are one of two numbers of slices, and the device says which behind the keys, in the last 256
+        // bytes of the size; without, or when the two are the same, it is known here
+        if (n_valid && sage::lm_head_rows_units(vocab, 1) != sage::lm_head_rows_units(vocab, rows))
+            units_used = reinterpret_cast<int*>(keys + static_cast<size_t>(rows) * nunits * k);
+        else
+            nunits = sage::lm_head_rows_units(vocab, rows);
         const int rc = sage::launch_lm_head_rows(hidden, weight, rows, dim, vocab, hidden_stride, weight_stride, n_valid, rows_per_group,
-                                                 stats, keys, s);
+                                                 stats, keys, units_used, s);
         if (rc != SAGE_OK) return rc;
     } else {
         const Shape sh = launch_shape(vocab);
@@ -497,6 +504,6 @@ extern "C" int sage_lm_head_topk(const void* hidden, const void* weight, int dty
         if (hipGetLastError() != hipSuccess) return SAGE_LAUNCH_FAILED;
     }
     sage::topk_merge(rows, k, n_valid, rows_per_group, nunits, stats, keys, entropy, topk_idx, topk_prob, topk_renorm,
-                     topk_entropy, alpha, s);
+                     topk_entropy, alpha, s, units_used);
     return sage::launch_status();
 }

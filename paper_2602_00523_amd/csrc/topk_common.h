@@ -39,6 +39,6 @@ int topk_merge_max_units(int k);        // most slices per row that topk_merge t
 void topk_workspace_layout(int rows, int vocab, void* workspace, topk::UnitStats** stats, uint64_t** keys, int* nunits);
 void topk_merge(int rows, int k, const int* n_valid, int rows_per_group, int nunits, const topk::UnitStats* stats,
                 const uint64_t* keys, float* entropy, int* topk_idx, float* topk_prob, float* topk_renorm,
-                float* topk_entropy, float* alpha, hipStream_t s);
+                float* topk_entropy, float* alpha, hipStream_t s, const int* units_used = nullptr);
 
 }  // namespace sage

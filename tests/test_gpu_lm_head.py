@@ -111,6 +111,25 @@ def test_row_block_and_unit_edges(gu, rows, dim, vocab):
     assert exact >= n - 1
 
 
+@pytest.mark.parametrize("vocab", [40000, 70001])
+@pytest.mark.parametrize("per_group", [0, 1, 12, 13, 26, 60])
+def test_cut_follows_the_live_rows(gu, vocab, per_group):
+    """Ten groups of 60: up to 128 live rows the vocabulary is cut for one block of rows, otherwise for the three of 600 rows,
+    and the second pass has to know (40000 tokens: 256 slices per row or 170).  Counts on both sides of the line."""
+    rows, rpg, dim = 600, 60, 128
+    h = wl.gaussian(31, (rows, dim), "bf16", 1.0)
+    w = wl.gaussian(32 + vocab, (vocab, dim), "bf16", 3.0 / np.sqrt(dim))
+    w[vocab - 1] = h[540]                                # (a token of the last unit must win)
+    n_valid = np.full(10, per_group, np.int32)
+    if per_group == 12:
+        n_valid[:8] += 1                                 # exactly 128 live rows
+    live = [r for r in range(rows) if r % rpg < n_valid[r // rpg]]
+    assert len(live) in (0, 10, 128, 130, 260, 600)
+    check(gu, h, w, n_valid, rpg, rows_checked=sorted({live[0], live[len(live) // 2], live[-1]}) if live else None)
+    if live:
+        assert gu.gpu_lm_head_topk(h, w, 1, n_valid, rpg)["topk_idx"][540, 0] == vocab - 1
+
+
 def test_planted_winner_and_ties(gu):
     """One vocabulary row is the hidden row itself scaled up: it must win; two identical weight rows tie exactly
     (same products, same order of accumulation), and the lower index must be reported."""
