@@ -62,6 +62,7 @@ struct Program {
     std::vector<PyObject*> defaults;     // for optional parameters
     std::vector<Op> ops;
     PyObject* error;                     // exception class: error(call, status)
+    PyObject *module, *doc, *signature;  // what the call shows as __module__, __doc__ and __signature__
 };
 
 const at::Tensor* tensor_of(const Program& p, PyObject* o, int param) {
@@ -290,6 +291,9 @@ void call_dealloc(PyObject* self) {
         for (PyObject* o : c->program->names) Py_DECREF(o);
         for (PyObject* o : c->program->defaults) Py_XDECREF(o);
         Py_XDECREF(c->program->error);
+        Py_XDECREF(c->program->module);
+        Py_XDECREF(c->program->doc);
+        Py_XDECREF(c->program->signature);
         delete c->program;
     }
     PyTypeObject* t = Py_TYPE(self);
@@ -305,7 +309,22 @@ void bound_dealloc(PyObject* self) {
     Py_DECREF(t);
 }
 
+// A call stands in for a function of its module: it has that one's names, docstring and signature and is pickled by name.
+PyObject* call_name(PyObject* self, void*) { return PyUnicode_FromString(reinterpret_cast<CallObject*>(self)->program->entry->name); }
+template <PyObject* Program::*WHAT> PyObject* call_get(PyObject* self, void*) {
+    PyObject* o = reinterpret_cast<CallObject*>(self)->program->*WHAT;
+    Py_INCREF(o);
+    return o;
+}
+PyObject* call_reduce(PyObject* self, PyObject*) { return call_name(self, nullptr); }
+
+PyGetSetDef call_getset[] = {{"__name__", call_name, nullptr, nullptr, nullptr}, {"__qualname__", call_name, nullptr, nullptr, nullptr},
+                             {"__module__", call_get<&Program::module>, nullptr, nullptr, nullptr},
+                             {"__doc__", call_get<&Program::doc>, nullptr, nullptr, nullptr},
+                             {"__signature__", call_get<&Program::signature>, nullptr, nullptr, nullptr},
+                             {nullptr, nullptr, nullptr, nullptr, nullptr}};
 PyMethodDef call_methods[] = {
+    {"__reduce__", call_reduce, METH_NOARGS, nullptr},
     {"bind", reinterpret_cast<PyCFunction>(reinterpret_cast<void (*)(void)>(call_bind)), METH_FASTCALL | METH_KEYWORDS,
      "bind(*args, **kwargs): the call with these arguments, as a callable without any"},
     {nullptr, nullptr, 0, nullptr}};
@@ -314,7 +333,7 @@ PyMemberDef call_members[] = {{"__vectorcalloffset__", T_PYSSIZET, offsetof(Call
 PyMemberDef bound_members[] = {{"__vectorcalloffset__", T_PYSSIZET, offsetof(BoundObject, vectorcall), READONLY, nullptr},
                                {nullptr, 0, 0, 0, nullptr}};
 PyType_Slot call_slots[] = {{Py_tp_dealloc, reinterpret_cast<void*>(call_dealloc)}, {Py_tp_call, reinterpret_cast<void*>(PyVectorcall_Call)},
-                            {Py_tp_methods, call_methods}, {Py_tp_members, call_members}, {0, nullptr}};
+                            {Py_tp_methods, call_methods}, {Py_tp_getset, call_getset}, {Py_tp_members, call_members}, {0, nullptr}};
 PyType_Slot bound_slots[] = {{Py_tp_dealloc, reinterpret_cast<void*>(bound_dealloc)},
                              {Py_tp_call, reinterpret_cast<void*>(PyVectorcall_Call)}, {Py_tp_members, bound_members}, {0, nullptr}};
 PyType_Spec call_spec = {"paper_2602_00523_amd._binding.Call", sizeof(CallObject), 0, Py_TPFLAGS_DEFAULT | Py_TPFLAGS_HAVE_VECTORCALL,
@@ -335,13 +354,13 @@ std::vector<std::string> words(const char* text) {
     return out;
 }
 
-// make(name, address, params, args, error): params = "logits k ... n_valid=None rows=1", args = "ptr:logits dtype:logits ...".
+// make(name, address, params, args, error, module, doc, signature): params = "logits k ... n_valid=None rows=1", args = "ptr:logits dtype:logits ...".
 // Raises ValueError when the description does not fit the function's declaration.
 PyObject* make(PyObject*, PyObject* args) {
     const char *name, *params, *cargs;
     unsigned long long address;
-    PyObject* error;
-    if (!PyArg_ParseTuple(args, "sKssO", &name, &address, &params, &cargs, &error)) return nullptr;
+    PyObject *error, *module, *doc, *signature;
+    if (!PyArg_ParseTuple(args, "sKssOUUO", &name, &address, &params, &cargs, &error, &module, &doc, &signature)) return nullptr;
     auto* c = PyObject_New(CallObject, call_type);
     if (!c) return nullptr;
     c->vectorcall = call_vectorcall;
@@ -359,6 +378,12 @@ PyObject* make(PyObject*, PyObject* args) {
     p.fn = reinterpret_cast<void*>(static_cast<uintptr_t>(address));
     Py_INCREF(error);
     p.error = error;
+    Py_INCREF(module);
+    p.module = module;
+    Py_INCREF(doc);
+    p.doc = doc;
+    Py_INCREF(signature);
+    p.signature = signature;
     std::vector<std::string> names;
     for (const std::string& w : words(params)) {
         const size_t eq = w.find('=');
@@ -412,7 +437,7 @@ PyObject* make(PyObject*, PyObject* args) {
     return reinterpret_cast<PyObject*>(c);
 }
 
-PyMethodDef module_methods[] = {{"make", make, METH_VARARGS, "make(name, address, params, args, error): a call"}, {nullptr, nullptr, 0, nullptr}};
+PyMethodDef module_methods[] = {{"make", make, METH_VARARGS, "make(name, address, params, args, error, module, doc, signature): a call"}, {nullptr, nullptr, 0, nullptr}};
 PyModuleDef module_def = {PyModuleDef_HEAD_INIT, "_binding", "Calls of libsage_hip.so with torch tensors, marshalled natively.", -1,
                           module_methods};
 

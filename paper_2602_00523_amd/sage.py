@@ -6,6 +6,7 @@ loaded on first use and a missing library is an error (there is no fallback path
 from __future__ import annotations
 
 import ctypes
+import inspect
 import os
 
 import torch  # noqa: F401  (its libraries have to be loaded before the binding's)
@@ -196,6 +197,18 @@ _CALLS = {
 _native = {}
 
 
+def _doc(name: str) -> str:
+    return f"{name}({', '.join(_CALLS[name][0].split())}): see include/sage.h"
+
+
+def _signature(name: str) -> inspect.Signature:
+    def parameter(word: str) -> inspect.Parameter:
+        n, _, default = word.partition("=")
+        default = inspect.Parameter.empty if not default else None if default == "None" else int(default)
+        return inspect.Parameter(n, inspect.Parameter.POSITIONAL_OR_KEYWORD, default=default)
+    return inspect.Signature([parameter(w) for w in _CALLS[name][0].split()])
+
+
 def _load_native(name: str):
     """The native call `name` (all of them are made on first use, then stand in this module under their own names)."""
     if not _native:
@@ -203,7 +216,7 @@ def _load_native(name: str):
             raise SageError(f"{BINDING_PATH} is missing: run `python -m paper_2602_00523_amd.build`", -1)
         from . import _binding
         L = lib()
-        made = {n: _binding.make(n, ctypes.cast(getattr(L, n), ctypes.c_void_p).value, params, args, SageError)
+        made = {n: _binding.make(n, ctypes.cast(getattr(L, n), ctypes.c_void_p).value, params, args, SageError, __name__, _doc(n), _signature(n))
                 for n, (params, args) in _CALLS.items()}
         globals().update(made)
         _native.update(made)
@@ -214,7 +227,8 @@ def _first_use(name: str):
     def call(*a, **kw):
         return _load_native(name)(*a, **kw)
     call.__name__ = call.__qualname__ = name
-    call.__doc__ = f"{name}({', '.join(_CALLS[name][0].split())}): see include/sage.h"
+    call.__doc__ = _doc(name)
+    call.__signature__ = _signature(name)
     return call
 
 
