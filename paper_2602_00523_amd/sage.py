@@ -218,7 +218,8 @@ def _load_native(name: str):
         L = lib()
         made = {n: _binding.make(n, ctypes.cast(getattr(L, n), ctypes.c_void_p).value, params, args, SageError, __name__, _doc(n), _signature(n))
                 for n, (params, args) in _CALLS.items()}
-        globals().update(made)
+        # (a name that the program has given to something else in the meantime, a wrapper say, stays with that)
+        globals().update({n: call for n, call in made.items() if globals().get(n) is _first[n]})
         _native.update(made)
     return _native[name]
 
@@ -232,9 +233,8 @@ def _first_use(name: str):
     return call
 
 
-for _name in _CALLS:
-    globals()[_name] = _first_use(_name)
-del _name
+_first = {_name: _first_use(_name) for _name in _CALLS}
+globals().update(_first)
 
 
 def sage_tree_attention_static_scratch_bytes() -> int:

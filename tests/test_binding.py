@@ -1,12 +1,17 @@
 """The Python side of the calls (csrc/python_binding.cpp) without a GPU: what it accepts and hands on.  No call here reaches a
 device: either the arguments say that there is nothing to do, or they are refused on the host."""
 import inspect
+import os
 import pickle
+import subprocess
+import sys
 
 import pytest
 import torch
 
 from paper_2602_00523_amd import sage
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 
 class Stream:
@@ -27,3 +32,16 @@ def test_native_calls_keep_their_names():
     assert call.__doc__ == "sage_advance_kv_len(kv_len, accept_len, kv_capacity, stream=None): see include/sage.h"
     assert pickle.loads(pickle.dumps(call)) is call
     assert str(inspect.signature(call)) == "(kv_len, accept_len, kv_capacity, stream=None)"
+
+
+def test_first_use_leaves_replaced_functions_alone():
+    """What a program has put in place of a call (a wrapper, a mock) stays when the native calls are loaded; the others are
+    replaced."""
+    program = """
+from paper_2602_00523_amd import sage
+def counted(*a, **kw): pass
+plain, sage.sage_build_tree = sage.sage_commit_path, counted
+sage._load_native("sage_commit_path")
+assert sage.sage_build_tree is counted and sage.sage_commit_path is not plain
+"""
+    subprocess.run([sys.executable, "-c", program], check=True, cwd=ROOT)
