@@ -247,6 +247,8 @@ def prepare(name: str, *a, **kw):
     For loops that issue the same call on the same buffers and stream many times: what is left per call is the launch.
     The callable keeps its arguments alive.
     """
+    if name not in _CALLS:
+        raise AttributeError(f"the library has no call {name!r}")
     return _load_native(name).bind(*a, **kw)
 
 

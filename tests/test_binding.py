@@ -45,3 +45,8 @@ sage._load_native("sage_commit_path")
 assert sage.sage_build_tree is counted and sage.sage_commit_path is not plain
 """
     subprocess.run([sys.executable, "-c", program], check=True, cwd=ROOT)
+
+
+def test_prepare_of_an_unknown_call():
+    with pytest.raises(AttributeError, match="sage_no_such_call"):
+        sage.prepare("sage_no_such_call")
