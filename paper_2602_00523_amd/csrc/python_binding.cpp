@@ -7,6 +7,7 @@
 // that says where the argument comes from.  Both are parsed once, into a flat list of operations; calling it fills the C
 // arguments from the tensors and numbers and jumps to the library.  `bind` does the same but stops before the jump and
 // returns a callable that makes it (sage.prepare).  Nothing here computes anything or knows a device.
+#include <torch/csrc/Dtype.h>
 #include <torch/csrc/autograd/python_variable.h>
 
 #include <c10/hip/HIPStream.h>
@@ -65,11 +66,74 @@ struct Program {
     PyObject *module, *doc, *signature;  // what the call shows as __module__, __doc__ and __signature__
 };
 
-const at::Tensor* tensor_of(const Program& p, PyObject* o, int param) {
-    if (THPVariable_Check(o)) return &THPVariable_Unpack(o);
-    PyErr_Format(PyExc_TypeError, "%s: %U must be a tensor, not %s", p.entry->name, p.names[param], Py_TYPE(o)->tp_name);
-    return nullptr;
+struct PythonError {};                   // thrown while arguments are read: the Python error is set
+struct Reference {                       // owns one
+    PyObject* o;
+    explicit Reference(PyObject* given) : o(given) { if (!o) throw PythonError{}; }
+    ~Reference() { Py_DECREF(o); }
+    Reference(const Reference&) = delete;
+    Reference& operator=(const Reference&) = delete;
+};
+int64_t integer(PyObject* o) {
+    const long long v = PyLong_AsLongLong(o);
+    if (v == -1 && PyErr_Occurred()) throw PythonError{};
+    return v;
 }
+
+// What the operations read of a tensor argument.  A torch.Tensor (or Parameter) is read directly; anything else that has a
+// tensor's methods, a subclass that overrides them among it, through these; an object without them is a TypeError.
+class TensorArgument {
+public:
+    TensorArgument(const Program& p, int param, PyObject* o) : program(p), index(param), object(o) {
+        if (THPVariable_CheckExact(o)) tensor = &THPVariable_Unpack(o);
+    }
+    uint64_t address() const {
+        if (tensor) return reinterpret_cast<uintptr_t>(tensor->data_ptr());
+        const Reference v(PyObject_CallNoArgs(attribute("data_ptr").o));
+        const unsigned long long a = PyLong_AsUnsignedLongLongMask(v.o);
+        if (PyErr_Occurred()) throw PythonError{};
+        return a;
+    }
+    int64_t nbytes() const {
+        if (tensor) return tensor->numel() * static_cast<int64_t>(tensor->element_size());
+        const Reference n(PyObject_CallNoArgs(attribute("numel").o)), each(PyObject_CallNoArgs(attribute("element_size").o));
+        return integer(n.o) * integer(each.o);
+    }
+    int64_t dim() const {
+        if (tensor) return tensor->dim();
+        const Py_ssize_t n = PySequence_Size(attribute("shape").o);
+        if (n < 0) throw PythonError{};
+        return n;
+    }
+    int64_t size(int i) const {
+        if (tensor) return tensor->size(i);
+        const Reference n(PySequence_GetItem(attribute("shape").o, i));
+        return integer(n.o);
+    }
+    int64_t stride(int i) const {
+        if (tensor) return tensor->stride(i);
+        const Reference n(PyObject_CallFunction(attribute("stride").o, "i", i));
+        return integer(n.o);
+    }
+    at::ScalarType dtype() const {
+        if (tensor) return tensor->scalar_type();
+        const Reference d = attribute("dtype");
+        return THPDtype_Check(d.o) ? reinterpret_cast<THPDtype*>(d.o)->scalar_type : at::ScalarType::Undefined;
+    }
+
+private:
+    Reference attribute(const char* name) const {
+        PyObject* a = PyObject_GetAttrString(object, name);
+        if (!a && PyErr_ExceptionMatches(PyExc_AttributeError))
+            PyErr_Format(PyExc_TypeError, "%s: %U must be a tensor, not %s", program.entry->name, program.names[index],
+                         Py_TYPE(object)->tp_name);
+        return Reference(a);
+    }
+    const Program& program;
+    int index;
+    PyObject* object;
+    const at::Tensor* tensor = nullptr;
+};
 
 // The parameters of one call, by position and keyword.  New references are not taken: the caller's objects outlive this.
 bool take_parameters(const Program& p, PyObject* const* args, size_t npos, PyObject* kwnames, PyObject** slot) {
@@ -112,15 +176,11 @@ bool fill(const Program& p, PyObject* const* slot, Value* out) {
         switch (op.kind) {
             case PTR: {
                 if (o == Py_None) { (out++)->i = 0; break; }
-                const at::Tensor* t = tensor_of(p, o, op.a);
-                if (!t) return false;
-                (out++)->i = static_cast<int64_t>(reinterpret_cast<uintptr_t>(t->data_ptr()));
+                (out++)->i = static_cast<int64_t>(TensorArgument(p, op.a, o).address());
                 break;
             }
             case INT: {
-                const long long v = PyLong_AsLongLong(o);
-                if (v == -1 && PyErr_Occurred()) return false;
-                (out++)->i = v;
+                (out++)->i = integer(o);
                 break;
             }
             case FLOAT: {
@@ -131,9 +191,7 @@ bool fill(const Program& p, PyObject* const* slot, Value* out) {
             }
             case NBYTES: {
                 if (o == Py_None) { (out++)->i = 0; break; }
-                const at::Tensor* t = tensor_of(p, o, op.a);
-                if (!t) return false;
-                (out++)->i = t->numel() * static_cast<int64_t>(t->element_size());
+                (out++)->i = TensorArgument(p, op.a, o).nbytes();
                 break;
             }
             case STRUCT: {               // a ctypes structure, by address
@@ -162,36 +220,35 @@ bool fill(const Program& p, PyObject* const* slot, Value* out) {
                 break;
             }
             default: {
-                const at::Tensor* t = tensor_of(p, o, op.a);
-                if (!t) return false;
+                const TensorArgument t(p, op.a, o);
                 if (op.kind == CHECK_DIM) {
-                    if (t->dim() != op.n) {
+                    if (t.dim() != op.n) {
                         PyErr_Format(PyExc_ValueError, "%s: %U must have %d dimensions", p.entry->name, p.names[op.a], op.n);
                         return false;
                     }
                 } else if (op.kind == DTYPE) {
-                    if (t->scalar_type() != at::kFloat && t->scalar_type() != at::kBFloat16) {
+                    const at::ScalarType type = t.dtype();
+                    if (type != at::kFloat && type != at::kBFloat16) {
                         PyErr_SetString(PyExc_TypeError, "float32 or bfloat16 expected");
                         return false;
                     }
-                    (out++)->i = t->scalar_type() == at::kFloat ? SAGE_F32 : SAGE_BF16;
+                    (out++)->i = type == at::kFloat ? SAGE_F32 : SAGE_BF16;
                 } else if (op.kind == CHECK_SIZE || op.kind == CHECK_DTYPE) {
-                    const at::Tensor* u = tensor_of(p, slot[op.b], op.b);
-                    if (!u) return false;
-                    const bool ok = op.kind == CHECK_DTYPE ? t->scalar_type() == u->scalar_type()
-                                                           : op.n < t->dim() && op.n < u->dim() && t->size(op.n) == u->size(op.n);
+                    const TensorArgument u(p, op.b, slot[op.b]);
+                    const bool ok = op.kind == CHECK_DTYPE ? t.dtype() == u.dtype()
+                                                           : op.n < t.dim() && op.n < u.dim() && t.size(op.n) == u.size(op.n);
                     if (!ok) {
                         PyErr_Format(PyExc_AssertionError, "%s: %U and %U do not agree", p.entry->name, p.names[op.a], p.names[op.b]);
                         return false;
                     }
                 } else {                 // SIZE, STRIDE, CHECK_UNIT: one dimension
-                    if (op.n >= t->dim()) {
+                    if (op.n >= t.dim()) {
                         PyErr_Format(PyExc_ValueError, "%s: %U has too few dimensions", p.entry->name, p.names[op.a]);
                         return false;
                     }
-                    if (op.kind == SIZE) (out++)->i = t->size(op.n);
-                    else if (op.kind == STRIDE) (out++)->i = t->stride(op.n);
-                    else if (t->stride(op.n) != 1) {
+                    if (op.kind == SIZE) (out++)->i = t.size(op.n);
+                    else if (op.kind == STRIDE) (out++)->i = t.stride(op.n);
+                    else if (t.stride(op.n) != 1) {
                         PyErr_Format(PyExc_AssertionError, "%s: %U must be contiguous along its last dimension", p.entry->name, p.names[op.a]);
                         return false;
                     }
@@ -207,6 +264,7 @@ bool fill(const Program& p, PyObject* const* slot, Value* out) {
 bool marshal(const Program& p, PyObject* const* slot, Value* out) {
     try {
         return fill(p, slot, out);
+    } catch (const PythonError&) {
     } catch (const c10::Error& e) {
         PyErr_SetString(PyExc_RuntimeError, e.what_without_backtrace());
     } catch (const std::exception& e) {

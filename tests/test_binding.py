@@ -50,3 +50,67 @@ assert sage.sage_build_tree is counted and sage.sage_commit_path is not plain
 def test_prepare_of_an_unknown_call():
     with pytest.raises(AttributeError, match="sage_no_such_call"):
         sage.prepare("sage_no_such_call")
+
+
+class Mimic:
+    """An array with the methods of a tensor that the calls read, as another library's arrays have them."""
+
+    def __init__(self, t):
+        self.t = t
+        self.shape, self.dtype = tuple(t.shape), t.dtype
+
+    def data_ptr(self):
+        return self.t.data_ptr()
+
+    def stride(self, i):
+        return self.t.stride(i)
+
+    def numel(self):
+        return self.t.numel()
+
+    def element_size(self):
+        return self.t.element_size()
+
+
+class Elsewhere(torch.Tensor):
+    """A tensor subclass that says itself where its data is."""
+
+    def data_ptr(self):
+        return 0
+
+
+def outcome(make, x):
+    out, ws = torch.zeros(2, 1, dtype=torch.int32), torch.zeros(8, dtype=torch.uint8)
+    try:
+        sage.sage_entropy_topk(make(x), 1, None, make(out), None, None, None, None, make(ws), stream=Stream())
+    except Exception as e:
+        return type(e), str(e)
+
+
+@pytest.mark.parametrize("x,why", [
+    (torch.zeros(2, 64), "WORKSPACE_TOO_SMALL"),         # read to the end: the eight bytes of the workspace are too few
+    (torch.zeros(2, 64, dtype=torch.bfloat16), "WORKSPACE_TOO_SMALL"),
+    (torch.zeros(2, 66)[:, :60], "INVALID_ARG"),         # the row stride arrives (rows are not 16-byte aligned)
+    (torch.zeros(64, 2).T, "contiguous"),
+    (torch.zeros(2, 3, 64), "2 dimensions"),
+    (torch.zeros(2, 64, dtype=torch.float64), "float32 or bfloat16")])
+def test_arguments_with_the_methods_of_a_tensor(x, why):
+    """What has a tensor's methods is read like a tensor, with the same errors."""
+    tensor = outcome(lambda t: t, x)
+    assert why in tensor[1]
+    assert outcome(Mimic, x) == tensor
+
+
+def test_a_tensor_subclass_is_read_through_its_methods():
+    """An overridden data_ptr is the one that counts: a null one is refused, also where there is nothing to do."""
+    none = Mimic(torch.zeros(1, dtype=torch.int32))
+    none.shape = (0,)                                    # no sequence
+    sage.sage_advance_kv_len(none, torch.zeros(1, dtype=torch.int32), 10, stream=Stream())
+    with pytest.raises(sage.SageError, match="INVALID_ARG"):
+        sage.sage_advance_kv_len(none, torch.zeros(1, dtype=torch.int32).as_subclass(Elsewhere), 10, stream=Stream())
+
+
+def test_arguments_without_them_are_type_errors():
+    for x in (4096, [1.0, 2.0], object()):
+        with pytest.raises(TypeError, match="must be a tensor"):
+            sage.sage_advance_kv_len(torch.zeros(1, dtype=torch.int32), x, 10, stream=Stream())
