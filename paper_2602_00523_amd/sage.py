@@ -171,7 +171,7 @@ _CALLS = {
     "sage_verify_accept_from_slices": (f"{_SLICES_VERIFY} stream=None", _SLICES_VERIFY_PTRS + "stream:stream"),
     "sage_verify_accept_close_from_slices": (
         f"{_SLICES_VERIFY} {_CACHE} hist count d_max_in d_max_out lo hi d_floor d_cap avg_out=None stream=None",
-        _SLICES_VERIFY_PTRS + "dim4:Kt dim2:hist " + _CACHE_PTRS + "size2:Kt size3:Kt " + _CACHE_POS
+        _SLICES_VERIFY_PTRS + "dim4:Kt " + _CACHE_PTRS + "size2:Kt size3:Kt " + _CACHE_POS
         + "size1:hist float:lo float:hi int:d_floor int:d_cap " + _HISTORY_TAIL),
     "sage_commit_path": (
         f"{_CACHE} path_nodes accept_len stream=None",
@@ -186,7 +186,7 @@ _CALLS = {
         "ptr:avg_out stream:stream"),
     "sage_close_step": (
         f"{_CACHE} path_nodes accept_len hist count d_max_in d_max_out lo hi d_floor d_cap avg_out=None stream=None",
-        "dim4:Kt dim2:hist " + _CACHE_PTRS + "size0:Kt size2:Kt size3:Kt " + _CACHE_POS + "ptr:path_nodes ptr:accept_len "
+        "dim4:Kt " + _CACHE_PTRS + "size0:Kt size2:Kt size3:Kt " + _CACHE_POS + "ptr:path_nodes ptr:accept_len "
         "size1:path_nodes size1:hist float:lo float:hi int:d_floor int:d_cap " + _HISTORY_TAIL),
     "sage_lm_head_topk": (
         f"hidden weight k {_ROW} workspace n_valid=None rows_per_group=1 stream=None",

@@ -114,3 +114,20 @@ def test_arguments_without_them_are_type_errors():
     for x in (4096, [1.0, 2.0], object()):
         with pytest.raises(TypeError, match="must be a tensor"):
             sage.sage_advance_kv_len(torch.zeros(1, dtype=torch.int32), x, 10, stream=Stream())
+
+
+def test_closing_calls_take_histories_of_more_dimensions():
+    """The window is the second size of `hist` whatever follows: an empty batch goes through, a window over 64 is refused."""
+    i32 = lambda *s: torch.zeros(*s, dtype=torch.int32)  # noqa: E731
+    kt, full = Mimic(torch.zeros(1, 64, 2, 64)), i32(64)
+    kt.shape = (0, 64, 2, 64)                            # no sequence
+
+    def close(hist):
+        sage.sage_close_step(kt, kt, kt, kt, full, full, 100, 128, 64, i32(1, 9), full, hist, full, full, full, 2.0, 3.0, 3, 8,
+                             stream=Stream())
+    close(i32(1, 10))
+    close(i32(1, 10, 1))
+    with pytest.raises(sage.SageError, match="INVALID_ARG"):
+        close(i32(1, 65, 1))
+    with pytest.raises(ValueError):
+        close(i32(10))
