@@ -64,6 +64,16 @@ __device__ __forceinline__ void combine_unit_stats(const UnitStats (&u)[OWN], in
 // keys fit), so a kernel with another LDS budget can bring a smaller one.
 constexpr int PICK_CANDS = 512;          // candidates that the counting selection takes
 constexpr int PICK_LISTS = 256;          // lists that they may come from
+constexpr int STAGED_MAX_K = 16;         // longer lists are not staged in LDS
+// Entry number `at` of lists of `width` lies in list (at * reciprocal(width)) >> 16: true of what is asked for here, up to
+// PICK_LISTS lists of up to STAGED_MAX_K (it fails at entry 3293 of lists of 27, and at 1448 of lists of 63).
+__host__ __device__ constexpr unsigned reciprocal(unsigned width) { return (65536u + width - 1) / width; }
+constexpr bool reciprocal_holds(unsigned width) {
+    for (unsigned at = 0; at < PICK_LISTS * width; ++at)
+        if ((at * reciprocal(width)) >> 16 != at / width) return false;
+    return true;
+}
+static_assert([] { for (unsigned w = 1; w <= STAGED_MAX_K; ++w) if (!reciprocal_holds(w)) return false; return true; }(), "reciprocal");
 struct PickShared {
     alignas(16) uint64_t cand[PICK_CANDS];   // candidates for the row's k winners, any order
     uint64_t win[SAGE_MAX_TOPK];             // the winners, in order
@@ -205,7 +215,7 @@ __device__ __forceinline__ bool merge_row(int row, int k, int nunits, const Unit
     const uint64_t* kk = keys + static_cast<long>(row) * nunits * k;
     const int total = nunits * k;
     // Short lists are staged in LDS while wave 0 picks; of long ones only the picked lists are fetched, afterwards.
-    const bool in_lds = k <= 16 && total <= Shared::LDS_KEYS;
+    const bool in_lds = k <= STAGED_MAX_K && total <= Shared::LDS_KEYS;
     auto stage = [&](int t0, int step) __attribute__((always_inline)) {   // eight independent loads per thread at a time
         for (int i0 = t0; i0 < total; i0 += step * 8) {
             uint64_t tmp[8];
@@ -274,9 +284,9 @@ __device__ __forceinline__ bool merge_row(int row, int k, int nunits, const Unit
     // eight more while some list's last one fetched still is a candidate (lists are sorted)
     const int nl = pk.nlists <= PICK_LISTS ? pk.nlists : 0;
     const uint32_t floor = pk.floor;
-    auto gather = [&](int j0, int width) __attribute__((always_inline)) {   // entries j0 .. j0 + width - 1 of every picked list
+    auto gather = [&](int j0, int width) __attribute__((always_inline)) {   // entries j0 .. j0 + width - 1 of every picked list; width <= STAGED_MAX_K
         const int entries = nl * width;
-        const unsigned inv = (65536u + width - 1) / width;       // (at * inv) >> 16 == at / width for at < 4096, width <= 64
+        const unsigned inv = reciprocal(width);
         bool more = false;
         for (int at0 = 0; at0 < entries; at0 += THREADS) {
             const int at = at0 + tid;
