@@ -115,7 +115,10 @@ def test_accept_from_slices_equals_separate_calls_and_oracle(gu, vocab, dtype, B
     ("slabs", "bf16", 11, 28, 4, 128, [300] * 11, [5] * 11, 4100, 8, "f32", wl.CONFIGS["toy"]["tree"]),
     # more sequences than the batched decomposition takes: one launch slot per sequence
     ("many", "bf16", 70, 8, 2, 128, [90] * 70, [3] * 70, 2000, 4, "f32", dict(d_min=1, d_max=5, w_min=1, w_max=4, k=4, n_max=20)),
-    # candidate lists too long for the planning workgroup: two launches, same results
+    # the planning rides along, its candidate lists longer than its LDS stages: many slices, and long lists
+    ("slices", "bf16", 2, 64, 8, 128, [700, 90], [20, 9], 200000, 16, "bf16", wl.CONFIGS["c3"]["tree"]),
+    ("lists", "bf16", 1, 64, 8, 128, [1500], [30], 152064, 40, "f32", dict(d_min=2, d_max=12, w_min=2, w_max=40, k=40, n_max=64)),
+    # more slices than the planning workgroup takes: two launches, same results
     ("long", "bf16", 2, 64, 8, 128, [500, 200], [20, 9], 300000, 20, "bf16", dict(d_min=2, d_max=12, w_min=2, w_max=20, k=20, n_max=64)),
     # fp32 attention: two launches, same results
     ("toy", "f32", 2, 4, 1, 64, [256, 100], [16, 7], 1024, 8, "f32", wl.CONFIGS["toy"]["tree"]),

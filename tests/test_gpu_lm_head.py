@@ -130,6 +130,37 @@ def test_cut_follows_the_live_rows(gu, vocab, per_group):
         assert gu.gpu_lm_head_topk(h, w, 1, n_valid, rpg)["topk_idx"][540, 0] == vocab - 1
 
 
+def test_cut_follows_the_live_rows_of_each_replay(gu):
+    """The device decides on the cut: a captured call whose row counts cross the line between replays gives what the plain call
+    gives, in a workspace that still holds the other cut's slices."""
+    import torch
+    from paper_2602_00523_amd import sage
+    rows, rpg, dim, vocab = 600, 60, 128, 40000
+    h = gu.to_dev(wl.gaussian(31, (rows, dim), "bf16", 1.0))
+    w = gu.to_dev(wl.gaussian(33, (vocab, dim), "bf16", 3.0 / np.sqrt(dim)))
+    nv = torch.full((10,), rpg, device=h.device, dtype=torch.int32)
+    ws = gu.workspace(sage.sage_lm_head_topk_workspace_bytes(rows, vocab, 1))
+    ent, idx = torch.zeros(rows, device=h.device), torch.zeros(rows, 1, device=h.device, dtype=torch.int32)
+    side = torch.cuda.Stream()
+    call = sage.prepare("sage_lm_head_topk", h, w, 1, ent, idx, None, None, None, None, ws, nv, rpg, stream=side)
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=side):
+        call()
+    for count in (60, 12, 26, 1, 60, 0, 5):
+        nv.fill_(count)
+        ent.fill_(-1.0)
+        idx.fill_(-1)
+        graph.replay()
+        torch.cuda.synchronize()
+        got = ent.clone(), idx.clone()
+        ent.fill_(-1.0)
+        idx.fill_(-1)
+        sage.sage_lm_head_topk(h, w, 1, ent, idx, None, None, None, None, gu.workspace(ws.numel()), nv, rpg)
+        torch.cuda.synchronize()
+        assert torch.equal(got[0], ent) and torch.equal(got[1], idx)
+        assert int((idx >= 0).sum()) == 10 * count
+
+
 def test_planted_winner_and_ties(gu):
     """One vocabulary row is the hidden row itself scaled up: it must win; two identical weight rows tie exactly
     (same products, same order of accumulation), and the lower index must be reported."""
