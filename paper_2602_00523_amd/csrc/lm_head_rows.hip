@@ -9,8 +9,10 @@
 // dimension: 64 KB of operands for 8.4 MFLOP, against 92 KB for a tile of 128 rows x 320 (the layout this one replaced).
 //
 // Data movement.  Operands go from global memory straight into LDS (16-byte LDS-direct loads, 8 rows x 128 bytes per
-// wave-level load) through two rings, of weight stages and of hidden stages; weights come from HBM and are requested up
-// to three steps ahead, hidden rows come from L2 and follow two ahead when LDS is full (NR >= 3).  A row of a stage is 128
+// wave-level load) through two rings, of WR weight stages and of HR hidden stages.  Weights are requested WR - 1 steps ahead,
+// into the stage that the step before has left, hidden rows HR steps ahead, into the stage that the step itself leaves.  Both
+// rings have as many stages as fit, up to eight; with a unit and block of NV + NR >= 7 only WR = 3 and HR = 2 fit (the
+// weights come from HBM, the hidden rows from L2).  The counted waits follow from these numbers.  A row of a stage is 128
 // bytes; its 16-byte chunk c sits at position c ^ ((row / 2) % 8), which a loading lane achieves by fetching another chunk
 // of its row, and which makes the 16-byte fragment reads of 16 consecutive rows hit all 64 banks once.
 // The fragments of a 16-element block are read while the MFMAs of the block before it run, so a wave that has its SIMD
@@ -30,9 +32,9 @@
 // live rows the larger units of the rows' own cut are as good or better (256 of 512: 622 us, 645 with the cut for one block).
 //
 // Measured (hidden 8192, vocabulary 152064; before = 4 waves on 320 vocabulary rows x 128 hidden rows): 512 live rows
-// 1690 -> 1080 us (1.18 PFLOP/s), 256 live 870 -> 620, 160 live 920 -> 500, 128 live 500 -> 466, 1024 live 3140 -> 1970.
-// At 512 rows the matrix pipe is busy 75 % of the cycles and the chip clocks down to 1.45 GHz: what is left is power
-// (without any operand load the same loop runs at 1.77 GHz and 82 %), so bytes moved per flop are what counts.
+// 1690 -> 1045 us (1.22 PFLOP/s), 256 live 880 -> 620, 160 live 920 -> 500, 128 live 505 -> 453, 1024 live 3140 -> 1975; 64 live
+// of 512 443 -> 442.  At 512 rows the matrix pipe is busy 74 % of the cycles and the chip clocks down to 1.48 GHz (2.19 in the
+// 64-row call): what is left is power, so bytes moved per flop are what counts.
 #include <type_traits>
 
 #include "lm_head_device.h"
