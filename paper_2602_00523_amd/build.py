@@ -23,7 +23,10 @@ COMMON = ["--offload-arch=gfx950", "-O3", "-std=c++20", "-fPIC", "-Xclang", "-ta
           # leading scalar kernel arguments arrive in registers at wave launch instead of through a first memory fetch:
           # these kernels are short and launched in dependent chains, where that round trip is a visible share
           "-mllvm", "-amdgpu-kernarg-preload-count=16"]
-EXTRA = {"build_tree.hip": ["-ffp-contract=off"]}
+EXTRA = {"build_tree.hip": ["-ffp-contract=off"],
+         # MFMA results in ordinary vector registers: the softmax reads scores and rescales accumulators where they lie, and the
+         # operands that only MFMAs read take the accumulation registers
+         "tree_attention_bf16.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"]}
 # Kernels that keep their own count of vector-memory operations in flight (s_waitcnt vmcnt(N) around LDS-direct loads):
 # a register spill adds scratch loads and stores to that counter and silently breaks the count, so these translation
 # units are compiled with the resource-usage remarks on and the build fails if any of their kernels uses scratch memory.

@@ -13,33 +13,39 @@
 // registers of S^T are, as they stand, the B operand of the PV product (the token order inside a 16-token k-block
 // is whatever the accumulator layout says; the V^T reads follow that order).
 //
-// Decomposition (decided on the device from n_nodes/kv_len, so no host round trip): a workgroup of 8 waves owns
-// (sequence, KV head, group of up to 8 column tiles = 256 query rows, KV split); wave w owns column tile w (32 query
-// rows) and processes whole 64-token tiles for it, so nothing is shared between waves but the K/V stages, and a wave's
-// partial result is complete for its rows.  What bounds this kernel is how many bytes per second ONE compute unit can
-// pull in (about 24-32 GB/s when the data comes from HBM, the latency of a miss times what a CU can keep in flight;
-// every workgroup that shares a tile through L2 still waits out the first one's miss), not the matrix pipe: so a tile
-// that has been brought into LDS must serve as many query rows as registers allow, and a tree of up to 32 nodes (G = 8)
-// is one group.  With 2..64 sequences the splits are equal ranges of one list of all sequences' tiles, so ragged lengths
-// leave no CU idle (see the kernel).  The KV head is the fastest grid index, so in launch order the workgroups of one KV
-// head are congruent modulo the KV-head count, which with 8 KV heads pins a head to one XCD and its L2: the two groups
-// of a 64-node tree re-read K/V from that L2, not from HBM.  Each workgroup writes an un-normalised partial (max, sum
-// in fp32, O^T in bf16); a second kernel merges the splits in a fixed order (deterministic, no float atomics) and
-// writes bf16.
+// Decomposition (decided on the device from n_nodes/kv_len, so no host round trip): a workgroup of 4 waves, one per SIMD,
+// owns (sequence, KV head, group of up to 256 query rows, KV split); wave w owns one column tile of 32 rows (groups of up
+// to 128 rows) or two (larger ones) and processes every 32-token block of the split for them, so nothing is shared between
+// waves but the K/V stages, and a wave's partial result is complete for its rows.  A block that has been brought into LDS
+// serves as many query rows as registers allow: what a CU can pull in (about 24 GB/s from HBM) bounds small trees, and a
+// tree of up to 32 nodes (G = 8) is one group.  With two column tiles a fragment read from LDS feeds two MFMAs, which halves
+// the LDS reads of 64-node trees.  With 2..64 sequences the splits are equal ranges of one list of all sequences' blocks, so
+// ragged lengths leave no CU idle (see the kernel).  The KV head is the fastest grid index, so in launch order the workgroups
+// of one KV head are congruent modulo the KV-head count, which with 8 KV heads pins a head to one XCD and its L2: the two
+// groups of a 64-node tree re-read K/V from that L2, not from HBM.  Each workgroup writes an un-normalised partial (max, sum
+// in fp32, O^T in bf16); a second kernel merges the splits in a fixed order (deterministic, no float atomics) and writes bf16.
 //
-// Data movement.  K/V tiles of 64 tokens go from global memory straight into LDS (16-byte LDS-direct loads, no
-// staging registers; issued through inline assembly, see lds_direct_load16) through a 4-stage ring, three tiles
-// ahead of the MFMAs.  A wave-level load writes 1 KB of contiguous LDS; it carries four tokens that are 16 apart,
-// and the 1 KB groups are padded so that consecutive tokens are staggered across the banks (conflict-free reads
-// with compile-time offsets, see the layout constants).  Every stage is its own LDS object, so every stage address
-// is a compile-time constant.  The ancestor masks and the Q rows take the same road ahead of the first tiles, so
-// that no load of the kernel returns into a register and every wait on the vector-memory counter is a counted one
-// (which is also why these kernels must not spill: the build checks that they use no scratch memory).
+// Data movement.  K/V blocks of 32 tokens go from global memory straight into LDS (16-byte LDS-direct loads, no staging
+// registers; issued through inline assembly, see lds_direct_load16) through a ring of four stages.  A wave-level load
+// writes 1 KB of contiguous LDS; it carries four tokens that are 8 apart, and the 1 KB groups are padded so that the reads
+// are free of bank conflicts at compile-time offsets (see the layout constants).  The ancestor masks and the Q rows take
+// the same road ahead of the first blocks, so that no load of the kernel returns into a register and every wait on the
+// vector-memory counter is a counted one (which is also why these kernels must not spill: the build checks that they use no
+// scratch memory).
 //
-// Softmax.  The reference maximum of a row is only moved by rebase(): the usual tile costs no maximum at all.
-// Probabilities are exp2 of the scaled differences to the reference, rounded to bf16 (the B operand of PV); their sum,
-// taken over the rounded values with a two-element dot product, doubles as the overflow check.  The final
+// Softmax.  The reference maximum of a row is only moved by rebase(): the usual block costs one maximum over the scaled
+// differences to the reference, which says whether a probability would pass 2^8.  Probabilities are exp2 of the differences,
+// rounded to bf16 (the B operand of PV); their sum is taken over the rounded values, in fp32, by small MFMAs.  The final
 // normalisation uses the same reference for numerator and denominator, so the result does not depend on it.
+//
+// What bounds it, and against the kernel before this one (8 waves of 32 rows, softmax and MFMAs of a wave one after the
+// other, sums by two-element dot products, which block the matrix pipe for 16 cycles each); whole call, before -> now:
+//   small trees: the stream, and at short contexts launch, two round trips and the merge launch.  12 nodes, 64/8 heads, 4096
+//   positions 14.2 -> 12.6 us, 32768 positions 33.8 -> 32.8; 15 nodes, 16384 positions 24.2 -> 23.4; three sequences of
+//   301 to 1999 positions 15.5 -> 14.4; eight of 2205 to 12133 56.3 -> 55.0; 28/4 heads, 3 new rows of 12, 2560 positions
+//   10.0 -> 9.25.
+//   64 nodes: power.  32768 positions 79 -> 79.5 us (0.92 PFLOP/s at a clock of 2.0 GHz; 2.3 in the short calls), 16384
+//   positions 47.9 -> 47.3; fewer instructions and waits no longer show.
 #include <type_traits>
 
 #include "plan_device.h"
@@ -56,29 +62,89 @@ typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef __attribute__((address_space(3))) unsigned char lds_byte;
 #define LDS_AS __attribute__((address_space(3)))
 
+typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+
+typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+
+typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+
+typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+
+typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+
+typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+
+typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+
+typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+
+typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+
+typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+
+typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+
+typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+
+typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+
+typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+
+typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+
+typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+
+typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+
+typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+
+typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+
+typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+
+typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+
+typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+
+typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+
+typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+
 constexpr int D = 128;                  // head_dim
-constexpr int TILE = 64;                // tokens per LDS stage
-constexpr int THREADS = 512;
-constexpr int CT_PER_WG = 8;            // column tiles (of 32 query rows) per workgroup: one per wave
-constexpr int ROWS_PER_WG = CT_PER_WG * 32;
+constexpr int BLK = 32;                 // tokens per block (one stage of the ring)
+constexpr int THREADS = 256;
+constexpr int WAVES = THREADS / 64;
+constexpr int ROWS_PER_WG = 256;        // query rows of a group: up to 2 column tiles of 32 per wave
 constexpr int ROW_B = 256;              // bytes of one token row (128 bf16)
-// LDS stage layout: token t of a tile sits at (t % 16) * GROUP + (t / 16) * ROW_B, where a group is the 1 KB that
-// one wave-level LDS-direct load writes (tokens t, t+16, t+32, t+48) plus padding.  The padding staggers
-// consecutive tokens across the banks: 16 bytes for K (read 16 consecutive tokens x one 16-byte chunk at a time),
-// 64 bytes for V (read 4 consecutive tokens x 64 bytes at a time).  All per-fragment offsets are compile-time.
-constexpr int K_GROUP = 4 * ROW_B + 16;
+// LDS stage layout: token t of a block sits at (t % 8) * GROUP + (t / 8) * ROW_B, where a group is the 1 KB that one
+// wave-level LDS-direct load writes (tokens t, t+8, t+16, t+24) plus padding.  K is read 16 consecutive tokens x one 16-byte
+// chunk at a time: 32 bytes of padding put eight consecutive tokens on eight different even chunk positions, and the rows
+// with t / 8 odd hold their chunks with the lowest index bit flipped, so that the other eight are on the odd ones.  V is
+// read 4 consecutive tokens x 64 bytes at a time: 64 bytes of padding.  Every fragment offset is a per-lane constant plus
+// a compile-time one, and the reads are conflict-free.
+constexpr int K_GROUP = 4 * ROW_B + 32;
 constexpr int V_GROUP = 4 * ROW_B + 64;
-constexpr int K_STAGE_B = 16 * K_GROUP;
-constexpr int V_STAGE_B = 16 * V_GROUP;
+constexpr int K_STAGE_B = 8 * K_GROUP;
+constexpr int V_STAGE_B = 8 * V_GROUP;
+constexpr int STAGE_B = K_STAGE_B + V_STAGE_B;
+// Four stages: one that is read, one that is free for the next loads, two on their way (K a block ahead of V).  More do not
+// help, they cost: of 4, 5, 6, 7 and 9 stages, 32768 positions under 12 nodes take 32.8, 34.4, 34.3, 35.2 and 36.5 us, 4096
+// positions 12.6, 13.0, 13.2, 13.4 and 13.7 (a call that starts by requesting more waits longer for its first block, and
+// workgroups of different KV heads that run further apart read the cache's rows in smaller pieces); 3 stages take 41.1 and 12.8.
 constexpr int STAGES = 4;
-constexpr int LOADS_PER_TILE = 2 * TILE * ROW_B / (THREADS * 16);   // LDS-direct loads per thread per tile (K and V)
+constexpr int END = STAGES * STAGE_B;
+constexpr int AHEAD = STAGES - 2;       // steps (V block t, K block t + 2) requested ahead
+constexpr int Q_TILE_B = K_STAGE_B;     // 32 query rows in the layout of a K block, behind the ring
+constexpr int RING_B = END + ROWS_PER_WG / 32 * Q_TILE_B;
+constexpr int LOADS = 2;                // LDS-direct loads per thread and operand block
 // A partial: per query row O^T[128] in bf16, then max and sum in fp32.
 constexpr int PART_ROW_B = D * 2 + 16;   // (8 bytes of padding keep the rows 16-byte aligned)
 constexpr int PART_SLOT_B = ROWS_PER_WG * PART_ROW_B;
 constexpr int EPI_ROW_B = PART_ROW_B;    // a parked row of the epilogue has the layout of a partial row
-static_assert(32 * EPI_ROW_B <= K_STAGE_B && 32 * EPI_ROW_B <= V_STAGE_B, "a stage buffer holds a wave's epilogue block");
-constexpr float RAISE_MIN = 4.0f;       // rebase() raises a row's reference maximum only past 2^4 ...
-constexpr float REBASE_SUM = 512.0f;    // ... which bounds a lane's 32 probabilities of a tile by this sum afterwards
+static_assert(ROWS_PER_WG * EPI_ROW_B <= RING_B, "the ring holds the epilogue's rows");
+constexpr float RAISE_MIN = 4.0f;       // rebase() raises a row's reference maximum only past 2^4;
+constexpr float REBASE_PAST = 8.0f;     // it is called when a probability would pass 2^8
+constexpr float NO_REFERENCE = 3e38f;   // stands for -(reference * scale) while a row has none: every admitted key passes 2^8 then
 
 struct Params {
     const uint16_t* Q; const uint16_t* Kc; const uint16_t* Vc; const uint16_t* Kt; const uint16_t* Vt;
@@ -87,46 +153,49 @@ struct Params {
     const int* first_node;               // nullable: rows are computed for nodes first_node[b] .. n_nodes[b] - 1 only
     unsigned char* part;                 // [B][Hkv][nslot] slots of PART_SLOT_B bytes; batched launches: [Hkv][nslot]
     long kv_token_stride, kv_head_stride;
-    int B, Hq, Hkv, G, nslot, min_tiles_per_split;
+    int B, Hq, Hkv, G, nslot, min_blocks_per_split;
     int nrange;                          // batched launches: ranges (workgroups) per KV head
     int merge_phases;                    // merge workgroups per (sequence, KV head)
     float scale_log2e;                   // softmax scale times log2(e): probabilities are exp2 of scaled differences
 };
 
+// blocks of the cache and of the tree's own keys
+__device__ __forceinline__ int blocks_of(int tokens) { return (tokens + BLK - 1) / BLK; }
+
 // How one (sequence, KV head) is cut into workgroups; evaluated identically by both kernels.
 struct Split {
-    int n, first, rows, col_groups, tiles, tiles_per_split, nsplit;
+    int n, first, rows, col_groups, blocks, blocks_per_split, nsplit;
 };
 // the first node whose rows are computed: inside [0, n), so that a call always has a row
 __device__ __forceinline__ int clamp_first(int first, int n) { return first < 0 ? 0 : (first > n - 1 ? n - 1 : first); }
-__device__ __forceinline__ Split make_split(int n_nodes, int first_node, int kv_len, int G, int nslot, int min_tps) {
+__device__ __forceinline__ Split make_split(int n_nodes, int first_node, int kv_len, int G, int nslot, int min_bps) {
     Split s;
     s.n = n_nodes < 1 ? 1 : (n_nodes > SAGE_MAX_NODES ? SAGE_MAX_NODES : n_nodes);
     s.first = clamp_first(first_node, s.n);
     s.rows = (s.n - s.first) * G;
     s.col_groups = (s.rows + ROWS_PER_WG - 1) / ROWS_PER_WG;
     const int L = kv_len > 0 ? kv_len : 0;
-    s.tiles = (L + TILE - 1) / TILE + 1;                    // cache tiles, then one tile holding the tree's keys
+    s.blocks = blocks_of(L) + blocks_of(s.n);               // cache blocks, then one or two with the tree's keys
     int max_split = nslot / s.col_groups;
     if (max_split < 1) max_split = 1;
-    s.tiles_per_split = max(min_tps, (s.tiles + max_split - 1) / max_split);
-    s.nsplit = (s.tiles + s.tiles_per_split - 1) / s.tiles_per_split;
+    s.blocks_per_split = max(min_bps, (s.blocks + max_split - 1) / max_split);
+    s.nsplit = (s.blocks + s.blocks_per_split - 1) / s.blocks_per_split;
     return s;
 }
 
 // Batched decomposition: lane b of a wave holds the shape of sequence b.  Every (sequence, column group) segment
-// occupies SEG_COST_TILES + tiles positions of one line per KV head (the first SEG_COST_TILES stand for the prologue and
-// epilogue a pass costs, about that many tile steps); the line of `total` positions is cut into ranges of q, so a
-// workgroup whose range starts several segments gets fewer tiles.  Evaluated identically by both kernels.
-constexpr int SEG_COST_TILES = 4;
+// occupies SEG_COST + blocks positions of one line per KV head (the first SEG_COST stand for the prologue and
+// epilogue a pass costs, about that many block steps); the line of `total` positions is cut into ranges of q, so a
+// workgroup whose range starts several segments gets fewer blocks.  Evaluated identically by both kernels.
+constexpr int SEG_COST = 8;
 struct BatchShape {
-    int n, first, L, tiles, col_groups, start_lo, start_hi;  // per lane (sequence)
+    int n, first, L, blocks, col_groups, start_lo, start_hi; // per lane (sequence)
     int total, q;                                            // wave-uniform
 };
 __device__ __forceinline__ int wave_sum_i32(int v) { return static_cast<int>(sage::wave_sum_u32(static_cast<uint32_t>(v))); }
 __device__ __forceinline__ BatchShape make_batch_shape(const Params& prm, int lane) {
     BatchShape bs;
-    bs.n = 1; bs.first = 0; bs.L = 0; bs.tiles = 0; bs.col_groups = 0; bs.start_lo = 0; bs.start_hi = 0;
+    bs.n = 1; bs.first = 0; bs.L = 0; bs.blocks = 0; bs.col_groups = 0; bs.start_lo = 0; bs.start_hi = 0;
     if (lane < prm.B) {
         const int nn = prm.n_nodes[lane];
         const int len = prm.kv_len[lane];
@@ -134,13 +203,13 @@ __device__ __forceinline__ BatchShape make_batch_shape(const Params& prm, int la
         bs.n = nn < 1 ? 1 : (nn > SAGE_MAX_NODES ? SAGE_MAX_NODES : nn);
         bs.first = prm.first_node ? clamp_first(prm.first_node[lane], bs.n) : 0;
         bs.L = len > 0 ? len : 0;
-        bs.tiles = (bs.L + TILE - 1) / TILE + 1;             // cache tiles, then one tile holding the tree's keys
+        bs.blocks = blocks_of(bs.L) + blocks_of(bs.n);       // cache blocks, then one or two with the tree's keys
         bs.col_groups = ((bs.n - bs.first) * prm.G + ROWS_PER_WG - 1) / ROWS_PER_WG;
         bs.start_lo = static_cast<int>(static_cast<uint32_t>(st));
         bs.start_hi = static_cast<int>(st >> 32);
     }
-    bs.total = wave_sum_i32((bs.tiles + SEG_COST_TILES) * bs.col_groups);   // tiles = 0 in lanes past the batch, so is col_groups
-    bs.q = max(prm.min_tiles_per_split, (bs.total + prm.nrange - 1) / prm.nrange);
+    bs.total = wave_sum_i32((bs.blocks + SEG_COST) * bs.col_groups);   // blocks = 0 in lanes past the batch, so is col_groups
+    bs.q = max(prm.min_blocks_per_split, (bs.total + prm.nrange - 1) / prm.nrange);
     return bs;
 }
 
@@ -148,16 +217,29 @@ __device__ __forceinline__ BatchShape make_batch_shape(const Params& prm, int la
 template <int N> __device__ __forceinline__ void wait_vm() {
     __builtin_amdgcn_s_waitcnt((N & 15) | (7 << 4) | (15 << 8) | ((N >> 4) << 14));
 }
+// ... until at most n loads are out (n even, wave-uniform)
+__device__ __forceinline__ void wait_vm_upto(int n) {
+    switch (n >> 1) {
+        case 0: wait_vm<0>(); break;
+        case 1: wait_vm<2>(); break;
+        case 2: wait_vm<4>(); break;
+        case 3: wait_vm<6>(); break;
+        case 4: wait_vm<8>(); break;
+        default: wait_vm<10>(); break;
+    }
+}
+static_assert(LOADS * (AHEAD + AHEAD + 1) <= 10, "the largest count that is asked for");
 
 // Workgroup barrier of the stage ring.  __syncthreads() would also fence, and a workgroup-scope release makes the
 // compiler wait for every LDS-direct load still in flight, which is exactly what the ring must not do: each
-// thread has already waited for its own share of the tile (wait_vm), LDS needs no cache maintenance, so the bare
+// thread has already waited for its own share of the block (wait_vm), LDS needs no cache maintenance, so the bare
 // barrier is enough; the wavefront-scope fences only pin the order of memory operations around it.
 __device__ __forceinline__ void stage_barrier() {
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_s_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
+__device__ __forceinline__ void wait_lds() { __builtin_amdgcn_s_waitcnt(0xc07f); }   // lgkmcnt(0)
 
 // max / sum of a value with its partner in the other 32-lane half (both halves receive the result)
 __device__ __forceinline__ float cross_half_max(float v) {
@@ -169,9 +251,463 @@ __device__ __forceinline__ float cross_half_sum(float v) {
     return __uint_as_float(r[0]) + __uint_as_float(r[1]);
 }
 
+// LDS of a workgroup.
+struct Lds {
+    unsigned char ring[RING_B];
+    uint64_t mask[ROWS_PER_WG];          // the rows' ancestor masks
+};
+
+// What one pass works on; every field is wave-uniform.
+struct Segment {
+    int b, g, L, n, node0, rows, cg;     // sequence, KV head, cache length, nodes, first node computed, rows, column group
+    int begin, count, cache_blocks;      // blocks begin .. begin + count - 1 (count >= 1); those from cache_blocks on are the tree's
+    long kv_start;
+    unsigned char* out;                  // the partial
+};
+
+// One pass: the blocks of a segment for one column group; CT = column tiles of 32 rows per wave (wave w owns rows
+// 32 CT w .. of the group).
+//
+// The loop runs over units, a unit being (block, column tile).  While the vector pipe turns the scores of unit u into
+// probabilities, the matrix pipe computes the scores of unit u + 1 and the PV product of unit u - 1: 16 MFMAs that depend on
+// nothing of unit u, one ahead of each of its 16 scores per lane, in program order (scheduling fences), because one wave per
+// SIMD has no other wave to fill its gaps.  Fragments of K and V are read from LDS into a second set of registers a unit
+// (CT = 1) or a block (CT = 2) before they are used; a fragment read serves CT column tiles.
+template <int CT>
+__device__ __forceinline__ void attention_pass(const Params& prm, LDS_AS Lds* lds, const Segment& sg, const int inv_G, const int tid) {
+    constexpr int KA = CT == 2 ? 1 : 2;                      // K is read KA blocks ahead of V
+    LDS_AS unsigned char* const ring = lds->ring;
+    const int lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // wave-uniform, so LDS stage addresses stay scalar
+    const int r32 = lane & 31;           // MFMA row (A) / column (B, C) owned by this lane
+    const int half = lane >> 5;
+    const int group_rows = min(ROWS_PER_WG, sg.rows - sg.cg * ROWS_PER_WG);
+    const int row0 = wave * 32 * CT;     // this wave's first row within the group
+    const bool active = row0 < group_rows;
+    const int H = sg.count;
+
+    // ---- loader: load i of wave w brings tokens t, t+8, t+16, t+24 (t = 2w + i) of a block, 1 KB of LDS: lane l fills
+    // chunk position l % 16 of token t + 8 (l / 16).  Addresses are a wave-uniform block base in scalar registers plus a
+    // 32-bit per-lane offset that is the same for every full block.
+    const int ld_tok = (lane >> 4) * 8 + wave * 2;           // token within the block for i = 0 (i = 1: the next one)
+    const unsigned k_chunk_b = ((lane & 15) ^ ((lane >> 4) & 1)) * 16;
+    const unsigned v_chunk_b = (lane & 15) * 16;
+    const unsigned cache_row_b = static_cast<unsigned>(prm.kv_token_stride) * 2u;   // host: 64 rows fit 32 bits
+    const unsigned tree_row_b = static_cast<unsigned>(prm.Hkv) * D * 2u;
+    const long cache_at = sg.kv_start * prm.kv_token_stride + static_cast<long>(sg.g) * prm.kv_head_stride;
+    const long tree_at = (static_cast<long>(sg.b) * SAGE_MAX_NODES * prm.Hkv + sg.g) * D;
+    const unsigned tok_off = static_cast<unsigned>(ld_tok) * cache_row_b;
+    const int full = min(H, max(0, sg.L / BLK - sg.begin));  // leading blocks that are whole blocks of the cache
+
+    struct Load { const unsigned char* base; unsigned off[2]; LDS_AS unsigned char* dst; int wanted; };
+    // where block h of K or V lies: a uniform base and this lane's offsets for i = 0, 1; wanted = 0 past the last block
+    auto locate = [&](auto is_v, int h, Load& l) __attribute__((always_inline)) {
+        constexpr bool V = decltype(is_v)::value;
+        const unsigned chunk_b = V ? v_chunk_b : k_chunk_b;
+        const int blk = sg.begin + h;
+        const bool is_tree = blk >= sg.cache_blocks;
+        const int tb = is_tree ? blk - sg.cache_blocks : blk;
+        const unsigned row_b = is_tree ? tree_row_b : cache_row_b;
+        l.wanted = __builtin_amdgcn_readfirstlane(max(0, H - h));
+        l.base = reinterpret_cast<const unsigned char*>(is_tree ? (V ? prm.Vt : prm.Kt) + tree_at : (V ? prm.Vc : prm.Kc) + cache_at) +
+                 static_cast<long>(tb) * BLK * row_b;
+        // in a ragged tail and in the tree's keys the rows past the end repeat the last one: they are masked later
+        const int last = (is_tree ? sg.n : sg.L) - 1 - tb * BLK;
+        l.off[0] = static_cast<unsigned>(min(ld_tok, last)) * row_b + chunk_b;
+        l.off[1] = static_cast<unsigned>(min(ld_tok + 1, last)) * row_b + chunk_b;
+    };
+    auto issue = [&](auto is_v, int h) __attribute__((always_inline)) {   // one of the first blocks
+        constexpr bool V = decltype(is_v)::value;
+        constexpr int GROUP = V ? V_GROUP : K_GROUP;
+        if (h >= H) return;
+        LDS_AS unsigned char* dst = ring + (h * STAGE_B + (V ? K_STAGE_B : 0) + wave * 2 * GROUP);   // (h < STAGES)
+        Load l;
+        if (h < full) {
+            l.base = reinterpret_cast<const unsigned char*>((V ? prm.Vc : prm.Kc) + cache_at) + static_cast<long>(sg.begin + h) * BLK * cache_row_b;
+            l.off[0] = tok_off + (V ? v_chunk_b : k_chunk_b);
+            l.off[1] = l.off[0] + cache_row_b;
+        } else {
+            locate(is_v, h, l);
+        }
+        sage::lds_direct_load16(l.base, l.off[0], dst);
+        sage::lds_direct_load16(l.base, l.off[1], dst + GROUP);
+    };
+    using IsK = std::false_type;
+    using IsV = std::true_type;
+    // What block h requests on the way, V block h + AHEAD and K block h + AHEAD + 2, as four loads that its units deal out
+    // between their MFMAs (a load occupies the CU's address path for 16 cycles: 16 of them at once would hold up four waves).
+    Load next_k, next_v;
+    auto request = [&](auto is_v, int i) __attribute__((always_inline)) {
+        constexpr bool V = decltype(is_v)::value;
+        const Load& l = V ? next_v : next_k;
+        sage::lds_direct_load16_if(l.wanted, l.base, l.off[i], l.dst + i * (V ? V_GROUP : K_GROUP));
+    };
+    // The usual step: everything that is out and everything that it requests is a whole block of the cache.  Nothing is
+    // computed for it but two running addresses and the two stages.
+    const int usual_end = full - 2 - AHEAD;
+    const unsigned block_b = BLK * cache_row_b;
+    const unsigned char* k_next = reinterpret_cast<const unsigned char*>(prm.Kc + cache_at) + static_cast<long>(sg.begin + AHEAD + 2) * block_b;
+    const unsigned char* v_next = reinterpret_cast<const unsigned char*>(prm.Vc + cache_at) + static_cast<long>(sg.begin + AHEAD) * block_b;
+    unsigned stage = 0;                                      // offset of block h's stage
+    auto stage_after = [&](int n) __attribute__((always_inline)) {       // ... of block h + n's, 0 <= n < STAGES
+        const unsigned at = stage + static_cast<unsigned>(n) * STAGE_B;
+        return at >= END ? at - END : at;
+    };
+    // Before block h's units: K block h + KA and V block h have landed for every wave, and the stages of K block h and V block
+    // h - 2 are free (an MFMA of block h - 1 has used what was read from them).  Loads complete in order, and what was
+    // requested after the two is out at most.
+    auto arrive = [&](int h) __attribute__((always_inline)) {
+        next_k.dst = ring + (stage + wave * 2 * K_GROUP);
+        next_v.dst = ring + (stage_after(STAGES - 2) + K_STAGE_B + wave * 2 * V_GROUP);
+        if (__builtin_expect(h < usual_end, 1)) {
+            next_k.base = k_next;
+            next_k.off[0] = tok_off + k_chunk_b;
+            next_k.off[1] = next_k.off[0] + cache_row_b;
+            next_v.base = v_next;
+            next_v.off[0] = tok_off + v_chunk_b;
+            next_v.off[1] = next_v.off[0] + cache_row_b;
+            next_k.wanted = next_v.wanted = 1;
+            k_next += block_b;
+            v_next += block_b;
+            wait_vm<LOADS * (AHEAD - 1 + AHEAD + 1 - KA)>();
+        } else {
+            locate(IsK{}, h + AHEAD + 2, next_k);
+            locate(IsV{}, h + AHEAD, next_v);
+            const int r = H - 1 - h;                         // blocks after h
+            wait_vm_upto(LOADS * (min(AHEAD - 1, r) + min(AHEAD + 1 - KA, max(0, r - KA))));
+        }
+        stage_barrier();
+    };
+
+    // Everything the prologue needs from memory goes straight into LDS, requested back to back in this order: the wave's
+    // ancestor masks, its Q rows, the first blocks.  No load of the kernel returns into a
+    // register, so the compiler never waits on the vector-memory counter here and the only waits are the counted ones.
+    // Rows past the group's last one repeat that row (their results are never written).
+    auto row_of = [&](int local) __attribute__((always_inline)) {      // row `local` of this group -> (node, head in group)
+        const int mm = min(sg.cg * ROWS_PER_WG + local, sg.rows - 1);
+        const int nd = (mm * inv_G) >> 16;                               // exact for mm < 64 G, G <= 16
+        return make_int2(sg.node0 + nd, mm - nd * prm.G);
+    };
+    // Q rows as tiles of 32 in the layout of a K block: row q of a tile sits at (q % 8) * K_GROUP + (q / 8) * ROW_B
+    LDS_AS unsigned char* const q_tiles = ring + END + wave * CT * Q_TILE_B;
+    if (active) {
+#pragma unroll
+        for (int c = 0; c < CT; ++c) {                       // both words of the masks of rows 32 c + lane / 2
+            const int2 r = row_of(row0 + 32 * c + (lane >> 1));
+            sage::lds_direct_load4(reinterpret_cast<const unsigned char*>(prm.anc_mask + static_cast<long>(sg.b) * SAGE_MAX_NODES + r.x) + (lane & 1) * 4,
+                                   (LDS_AS unsigned char*)(&lds->mask[row0 + 32 * c]));
+        }
+#pragma unroll
+        for (int c = 0; c < CT; ++c)
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                const int2 r = row_of(row0 + 32 * c + i + 8 * (lane >> 4));
+                const unsigned char* src = reinterpret_cast<const unsigned char*>(
+                    prm.Q + ((static_cast<long>(sg.b) * SAGE_MAX_NODES + r.x) * prm.Hq + sg.g * prm.G + r.y) * D) + k_chunk_b;
+                sage::lds_direct_load16(src, q_tiles + c * Q_TILE_B + i * K_GROUP);
+            }
+    }
+    issue(IsK{}, 0);
+    issue(IsK{}, 1);
+#pragma unroll
+    for (int t = 0; t < AHEAD; ++t) {
+        issue(IsV{}, t);
+        issue(IsK{}, t + 2);
+    }
+    // masks, Q and the first KA blocks of K have landed
+    wait_vm_upto(LOADS * (min(AHEAD, H) + min(AHEAD + 2 - KA, max(0, H - KA))));
+    stage_barrier();                                         // ... everyone's have
+
+    if (!active) {                                           // no rows: this wave only brings its share of the blocks
+        for (int h = 0; h < H; ++h) {
+            arrive(h);
+            stage = stage_after(1);
+            request(IsV{}, 0);
+            request(IsV{}, 1);
+            request(IsK{}, 0);
+            request(IsK{}, 1);
+        }
+        wait_vm<0>();
+        __syncthreads();
+        return;
+    }
+
+    // ---- per-lane LDS read offsets.  K fragment kk: token r32, chunk 2 kk + half -> k_lane + 32 kk.
+    const unsigned k_lane = (r32 & 7) * K_GROUP + (r32 >> 3) * ROW_B + ((half ^ ((r32 >> 3) & 1)) * 16);
+    // V^T fragment (dt, jj, u): k-block jj (16 tokens); the 16-lane group q = lane/16 reads tokens 16jj + 8u + 4(q/2) + s/4
+    // and dims dt*32 + 16(q%2) + 4(s%4) .. +3  (s = lane%16); after the transposing read lane s holds dim dt*32+16(q%2)+s.
+    // Offset: v_lane + (2 jj + u) * ROW_B + dt * 64.
+    unsigned v_lane;
+    {
+        const int q = lane >> 4, s16 = lane & 15;
+        v_lane = K_STAGE_B + (4 * (q >> 1) + (s16 >> 2)) * V_GROUP + (2 * (q & 1) + ((s16 & 3) >> 1)) * 16 + 8 * (s16 & 1);
+    }
+    auto read16 = [&](unsigned at) __attribute__((always_inline)) {
+        return __builtin_bit_cast(bf16x8, *(const LDS_AS u32x4*)(ring + at));
+    };
+
+    bf16x8 qf[CT][8];                                        // this lane's query rows: the B operand of every score MFMA
+#pragma unroll
+    for (int c = 0; c < CT; ++c)
+#pragma unroll
+        for (int kk = 0; kk < 8; ++kk)
+            qf[c][kk] = __builtin_bit_cast(bf16x8, *(const LDS_AS u32x4*)(q_tiles + c * Q_TILE_B + k_lane + kk * 32));
+
+#pragma unroll
+    for (int c = 0; c < CT; ++c)
+#pragma unroll
+        for (int kk = 0; kk < 8; ++kk) asm volatile("" : "+a"(qf[c][kk]));   // only MFMAs read it: in accumulation registers
+
+    f32x16 acc[CT][4];                                       // O^T: 4 tiles of 32 dims x this lane's query rows
+#pragma unroll
+    for (int c = 0; c < CT; ++c)
+#pragma unroll
+        for (int dt = 0; dt < 4; ++dt)
+#pragma unroll
+            for (int i = 0; i < 16; ++i) acc[c][dt][i] = 0.f;
+    float m_ref[CT], neg_mc[CT];                             // reference maximum of raw (unscaled) scores; -(m_ref * c)
+    f32x4 l_run[CT];                                         // this lane's share of the running sum, four times
+#pragma unroll
+    for (int c = 0; c < CT; ++c) {
+        m_ref[c] = -INFINITY;
+        neg_mc[c] = NO_REFERENCE;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) l_run[c][i] = 0.f;
+    }
+    const float c_log2 = prm.scale_log2e;
+    f32x16 sc[2];                                            // scores of the current and of the next unit
+    bf16x8 pf[2][2];                                         // P^T of the current and of the last unit, B operand of PV
+    bf16x8 kf[8], vf[4][2];                                  // fragments of K (by 16 dims) and V^T (by 32 dims and 16 tokens)
+
+    auto read_k = [&](bf16x8& f, unsigned at, int kk) __attribute__((always_inline)) { f = read16(at + kk * 32); };
+    auto read_v = [&](bf16x8& f, unsigned at, int dt, int jj) __attribute__((always_inline)) {
+        LDS_AS unsigned char* p = ring + (at + 2 * jj * ROW_B + dt * 64);
+        const bf16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((LDS_AS bf16x4*)p);
+        const bf16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((LDS_AS bf16x4*)(p + ROW_B));
+        f = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+    };
+    auto qk = [&](f32x16& s, const bf16x8 (&k)[8], const bf16x8 (&q)[8], int kk) __attribute__((always_inline)) {
+        if (kk == 0) {
+#pragma unroll
+            for (int i = 0; i < 16; ++i) s[i] = 0.f;
+        }
+        s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(k[kk], q[kk], s, 0, 0, 0);
+    };
+    // admit keys: cache positions below kv_len; tree nodes in this row's ancestor-or-self mask
+    auto mask_scores = [&](f32x16& s, int h, int c) __attribute__((always_inline)) {
+        const int blk = sg.begin + h;
+        uint32_t admit;
+        if (blk >= sg.cache_blocks) {
+            admit = reinterpret_cast<LDS_AS uint32_t*>(lds->mask)[2 * (row0 + 32 * c + r32) + (blk - sg.cache_blocks)];
+        } else {
+            admit = (1u << (sg.L - blk * BLK)) - 1u;         // 1..31 valid tokens
+        }
+        admit >>= 4 * half;
+        // token of accumulator register i: 8 (i/4) + 4 half + i%4
+#pragma unroll
+        for (int i = 0; i < 16; ++i)
+            if (!((admit >> (8 * (i >> 2) + (i & 3))) & 1u)) s[i] = -INFINITY;
+    };
+    // Move the reference maximum of the rows that need it to the row maximum of the current unit (both 32-lane halves of
+    // a row decide alike) and rescale what has been accumulated so far.
+    auto rebase = [&](const f32x16& s, int c, bool nothing_yet) __attribute__((always_inline)) {
+        float tmax = fmaxf(s[0], s[1]);
+#pragma unroll
+        for (int i = 2; i < 16; ++i) tmax = fmaxf(tmax, s[i]);
+        tmax = cross_half_max(tmax);
+        const bool raise = (m_ref[c] == -INFINITY) ? (tmax > -INFINITY) : ((tmax - m_ref[c]) * c_log2 > RAISE_MIN);
+        const float m_new = raise ? tmax : m_ref[c];
+        const float corr = !raise ? 1.f : (m_ref[c] == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f((m_ref[c] - m_new) * c_log2);
+        m_ref[c] = m_new;
+        neg_mc[c] = m_new == -INFINITY ? NO_REFERENCE : -m_new * c_log2;
+        if (!nothing_yet) {
+            l_run[c][0] *= corr;                             // (the other three are not read)
+#pragma unroll
+            for (int dt = 0; dt < 4; ++dt)
+#pragma unroll
+                for (int i = 0; i < 16; ++i) acc[c][dt][i] *= corr;
+        }
+    };
+    // (the compiler does not move the computation of x past this point)
+#define PIN(x) asm volatile("" : "+v"(x))
+    // two probabilities to bf16 in place i, i + 1 of f
+    auto pack2 = [&](bf16x8& f, int i, float p0, float p1) __attribute__((always_inline)) {
+        const f32x2 pp = {p0, p1};
+        uint32_t u = __builtin_bit_cast(uint32_t, __builtin_convertvector(pp, bf16x2));
+        PIN(u);                                              // (or it would be computed after the branch that follows)
+        const bf16x2 pb = __builtin_bit_cast(bf16x2, u);
+        f[i] = pb[0];
+        f[i + 1] = pb[1];
+    };
+    // The running sums of the rounded probabilities, four of a lane's 16 at a time: of the 16 products of 4 x 4 matrices that
+    // this MFMA does, a lane's four values are one column, and a matrix of ones adds it up.  8 cycles of the matrix pipe; two
+    // two-element dot products block it for 16 each, and unpacking and adding are eight instructions of a full vector pipe.
+    auto add_up = [&](f32x4& l, const bf16x8& p, int j) __attribute__((always_inline)) {
+        typedef short s16x4 __attribute__((ext_vector_type(4)));
+        const s16x4 ones = {0x3F80, 0x3F80, 0x3F80, 0x3F80};
+        const bf16x4 part = j == 0 ? __builtin_shufflevector(p, p, 0, 1, 2, 3) : __builtin_shufflevector(p, p, 4, 5, 6, 7);
+        l = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(ones, __builtin_bit_cast(s16x4, part), l, 0, 0, 0);
+    };
+#define FENCE() __builtin_amdgcn_sched_barrier(0)
+    // Unit (h, C); P = h % 2 when CT = 1.
+    auto unit = [&](auto parity, auto cc, const int h) __attribute__((always_inline)) {
+        constexpr int C = decltype(cc)::value;
+        constexpr int CUR = CT == 2 ? C : decltype(parity)::value;   // which of the two score and probability sets
+        constexpr int OTHER_C = CT == 2 ? 1 - C : 0;         // column tile of the units before and after
+        constexpr bool READ = C == 0;
+        f32x16& s = sc[CUR];
+        if (__builtin_expect(h >= full || h == 0, 0)) {
+            if (h >= full) mask_scores(s, h, C);
+            if (h == 0) rebase(s, C, true);
+        }
+        const unsigned k_at = stage_after(KA) + k_lane, v_at = stage + v_lane;
+        // The softmax of score m takes three steps, each in a later MFMA's shadow than the one before, so that no instruction
+        // waits for the result of the one ahead of it.
+        float x[2], e[4], most = -INFINITY;
+        x[0] = fmaf(s[0], c_log2, neg_mc[C]);
+        x[1] = fmaf(s[1], c_log2, neg_mc[C]);
+        PIN(x[0]);
+        PIN(x[1]);
+        e[0] = __builtin_amdgcn_exp2f(x[0]);
+        PIN(e[0]);
+        bf16x8 (&p)[2] = pf[CUR];
+        bf16x8 (&before)[2] = pf[1 - CUR];                   // the last unit's
+        FENCE();
+#pragma unroll
+        for (int m = 0; m < 16; ++m) {
+            // alternately a score MFMA and a PV MFMA, the last score MFMA third from the end; a fragment's register is
+            // refilled as soon as the last MFMA that needs it has been issued
+            const int mm = m == 13 ? 14 : m == 14 ? 13 : m, i = mm >> 1;
+            if (mm & 1) {
+                acc[OTHER_C][i & 3] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[i & 3][i >> 2], before[i >> 2], acc[OTHER_C][i & 3], 0, 0, 0);
+                if (READ) read_v(vf[i & 3][i >> 2], v_at, i & 3, i >> 2);
+            } else {
+                qk(sc[1 - CUR], kf, qf[OTHER_C], i);
+                if (READ) read_k(kf[i], k_at, i);
+            }
+            if ((m & 3) == 2) add_up(l_run[OTHER_C], before[m >> 3], (m >> 2) & 1);
+            if (CT == 2 ? C == 1 && (m & 3) == 1 : (m & 1) && m < 8) {   // m = 1, 5, 9, 13 or 1, 3, 5, 7: V, V, K, K
+                constexpr int STEP = CT == 2 ? 4 : 2;
+                if (m < 2 * STEP) request(IsV{}, m / STEP);
+                else request(IsK{}, m / STEP - 2);
+            }
+            if (!(m & 1)) {
+                if (m > 0) pack2(p[(m - 2) >> 3], (m - 2) & 7, e[(m - 2) & 3], e[(m - 1) & 3]);
+                most = fmaxf(fmaxf(most, x[0]), x[1]);       // scores m, m + 1
+                PIN(most);
+            }
+            if (m < 15) {
+                e[(m + 1) & 3] = __builtin_amdgcn_exp2f(x[(m + 1) & 1]);
+                PIN(e[(m + 1) & 3]);
+            } else {
+                pack2(p[1], 6, e[2], e[3]);
+            }
+            if (m < 14) {
+                x[m & 1] = fmaf(s[m + 2], c_log2, neg_mc[C]);
+                PIN(x[m & 1]);
+            }
+            FENCE();
+        }
+        // A probability that may have overflowed, or a row's first admitted key.
+        if (__builtin_expect(__any(most > REBASE_PAST), 0)) {
+            rebase(s, C, false);
+            float neg_mc_now = neg_mc[C];
+            PIN(neg_mc_now);                                 // (or the differences above would be kept for the rows that did not move)
+#pragma unroll
+            for (int i = 0; i < 16; i += 2)
+                pack2(p[i >> 3], i & 7, __builtin_amdgcn_exp2f(fmaf(s[i], c_log2, neg_mc_now)),
+                      __builtin_amdgcn_exp2f(fmaf(s[i + 1], c_log2, neg_mc_now)));
+        }
+        if (C == CT - 1) stage = stage_after(1);
+        FENCE();
+    };
+#undef PIN
+    using I0 = std::integral_constant<int, 0>;
+    using I1 = std::integral_constant<int, 1>;
+
+    // The scores of the first unit; what the first unit multiplies as "the last one's" is zero.  With CT = 1 the loop takes two
+    // blocks at a time, for the two sets of scores; of an odd number the first one goes ahead.
+#pragma unroll
+    for (int kk = 0; kk < 8; ++kk) read_k(kf[kk], k_lane, kk);
+#pragma unroll
+    for (int i = 0; i < 8; ++i)
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            vf[i & 3][i >> 2][e] = static_cast<__bf16>(0.0f);
+            pf[i & 1][(i >> 1) & 1][e] = static_cast<__bf16>(0.0f);
+        }
+    auto first_scores = [&](f32x16& s) __attribute__((always_inline)) {
+#pragma unroll
+        for (int kk = 0; kk < 8; ++kk) {
+            qk(s, kf, qf[0], kk);
+            if (CT == 1) read_k(kf[kk], STAGE_B + k_lane, kk);
+        }
+    };
+    int h = 0;
+    if (CT == 1 && (H & 1)) {
+        first_scores(sc[1]);
+        arrive(0);
+        unit(I1{}, I0{}, 0);
+        h = 1;
+    } else {
+        first_scores(sc[0]);
+    }
+    while (h < H) {
+        arrive(h);
+        unit(I0{}, I0{}, h);
+        if (CT == 2) {
+            unit(I0{}, std::integral_constant<int, CT - 1>{}, h);
+        } else {
+            arrive(++h);
+            unit(I1{}, I0{}, h);
+        }
+        ++h;
+    }
+    // PV of the last unit
+#pragma unroll
+    for (int m = 0; m < 8; ++m)
+        acc[CT - 1][m & 3] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[m & 3][m >> 2], pf[1][m >> 2], acc[CT - 1][m & 3], 0, 0, 0);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) add_up(l_run[CT - 1], pf[1][j >> 1], j & 1);
+#undef FENCE
+
+    float l_tot[CT];
+#pragma unroll
+    for (int c = 0; c < CT; ++c) l_tot[c] = cross_half_sum(l_run[c][0]);
+    wait_vm<0>();
+
+    // ---- epilogue: a wave's rows (O^T in bf16, max, sum) are complete.  They go through the wave's own piece of the ring as
+    // rows of EPI_ROW_B bytes, transposed on the way: written 8 bytes (4 dims) at a time from the accumulator layout, read
+    // back and stored to the partial in row order, for the second kernel to merge.
+    __syncthreads();                                         // all stages are idle now
+    LDS_AS unsigned char* const mine = ring + row0 * EPI_ROW_B;
+#pragma unroll
+    for (int c = 0; c < CT; ++c) {
+        LDS_AS unsigned char* row = mine + (32 * c + r32) * EPI_ROW_B;
+#pragma unroll
+        for (int dt = 0; dt < 4; ++dt)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const f32x4 v = {acc[c][dt][4 * q], acc[c][dt][4 * q + 1], acc[c][dt][4 * q + 2], acc[c][dt][4 * q + 3]};
+                *reinterpret_cast<LDS_AS bf16x4*>(row + (dt * 32 + 8 * q + 4 * half) * 2) = __builtin_convertvector(v, bf16x4);
+            }
+        if (half == 0) *reinterpret_cast<LDS_AS f32x2*>(row + D * 2) = f32x2{m_ref[c], l_tot[c]};
+    }
+    // (a wave's LDS operations complete in order, and the reads below wait for them: no barrier inside a wave)
+    // Parked rows and partial rows have the same pitch, so the wave's rows go out as one contiguous copy of 17 chunks of 16
+    // bytes a row (16 of O^T, one of max and sum), 64 chunks per store instruction
+    const int last_chunk = min(32 * CT, group_rows - row0) * (PART_ROW_B / 16);
+    unsigned char* out = sg.out + static_cast<long>(row0) * PART_ROW_B;
+#pragma unroll
+    for (int i = 0; i < (32 * CT * (PART_ROW_B / 16) + 63) / 64; ++i) {
+        const int ch = lane + 64 * i;
+        if (ch < last_chunk) *reinterpret_cast<u32x4*>(out + ch * 16) = *reinterpret_cast<LDS_AS u32x4*>(mine + ch * 16);
+    }
+}
+
 // BATCH = false: one sequence per launch slot, every (sequence, KV head) cut into equal splits (see make_split).
-// BATCH = true (2..64 sequences): the tiles of all sequences form one list per KV head (sequence-major, then column
-// group), cut into prm.nrange equal ranges; a workgroup owns one range and runs one pass (prologue, tile loop,
+// BATCH = true (2..64 sequences): the blocks of all sequences form one list per KV head (sequence-major, then column
+// group), cut into prm.nrange equal ranges; a workgroup owns one range and runs one pass (prologue, block loop,
 // epilogue) per (sequence, column group) segment its range touches, so ragged lengths cannot unbalance the launch.
 // The leading arguments repeat fields of prm: explicit scalar arguments are preloaded into registers at wave launch
 // (the library is built with kernel-argument preloading), so the first thing a workgroup does, fetching its sequence's
@@ -179,403 +715,37 @@ __device__ __forceinline__ float cross_half_sum(float v) {
 template <bool BATCH>
 __device__ __forceinline__ void attention_workgroup(const int* __restrict__ kv_len_arg, const int* __restrict__ n_nodes_arg,
                                                     const int* __restrict__ first_node_arg,
-                                                    const int64_t* __restrict__ kv_start_arg, int nslot_arg, int min_tps_arg,
-                                                    int G_arg, const Params& prm, const int first_slab) {
-    // one LDS object per stage and operand (see header)
-    __shared__ __align__(256) unsigned char sK0[K_STAGE_B];
-    __shared__ __align__(256) unsigned char sK1[K_STAGE_B];
-    __shared__ __align__(256) unsigned char sK2[K_STAGE_B];
-    __shared__ __align__(256) unsigned char sK3[K_STAGE_B];
-    __shared__ __align__(256) unsigned char sV0[V_STAGE_B];
-    __shared__ __align__(256) unsigned char sV1[V_STAGE_B];
-    __shared__ __align__(256) unsigned char sV2[V_STAGE_B];
-    __shared__ __align__(256) unsigned char sV3[V_STAGE_B];
-    __shared__ uint64_t s_mask[ROWS_PER_WG];
-#define SK(i) ((i) == 0 ? sK0 : (i) == 1 ? sK1 : (i) == 2 ? sK2 : sK3)
-#define SV(i) ((i) == 0 ? sV0 : (i) == 1 ? sV1 : (i) == 2 ? sV2 : sV3)
-
-    const int lane = threadIdx.x & 63;   // (run_segment derives its own copies)
-
+                                                    const int64_t* __restrict__ kv_start_arg, int nslot_arg, int min_bps_arg,
+                                                    int G_arg, const Params& prm, const int first_slab, LDS_AS Lds* lds) {
     // grid = (KV head, slot or range, sequence): the KV head is the fastest index of the launch order, and no index
     // costs a division
     const int g = blockIdx.x;
     const int id = static_cast<int>(blockIdx.y) - first_slab;   // slabs before first_slab belong to somebody else
     const int inv_G = (65536 + G_arg - 1) / G_arg;           // (m * inv_G) >> 16 == m / G for the rows of a KV head
 
-    // One pass over tiles [t_begin, t_end) of sequence b for column group cg; the un-normalised partial goes to out_base.
-    // (seq_rows rows, of nodes first_v .. seq_n - 1)
-    auto run_segment = [&](const int b_v, const int L_v, const int seq_n_v, const int first_v, const int seq_rows_v, const int cg_v, const int t_begin_v,
-                           const int t_end_v, const int tree_tile_v, const long kv_start_v, unsigned char* const out_base_v)
-                           __attribute__((always_inline)) {
-    // every argument is wave-uniform; said to the compiler (the batched walk derives them through lane reads), so that
-    // everything computed from them stays in scalar registers
-    auto uni = [](int v) __attribute__((always_inline)) { return __builtin_amdgcn_readfirstlane(v); };
-    auto uni64 = [&](uint64_t v) __attribute__((always_inline)) {
-        return (static_cast<uint64_t>(static_cast<uint32_t>(uni(static_cast<int>(v >> 32)))) << 32) |
-               static_cast<uint32_t>(uni(static_cast<int>(static_cast<uint32_t>(v))));
+    auto run_segment = [&](const Segment& v) __attribute__((always_inline)) {
+        // every field is wave-uniform; said to the compiler (the batched walk derives them through lane reads), so that
+        // everything computed from them stays in scalar registers
+        auto uni = [](int x) __attribute__((always_inline)) { return __builtin_amdgcn_readfirstlane(x); };
+        auto uni64 = [&](uint64_t x) __attribute__((always_inline)) {
+            return (static_cast<uint64_t>(static_cast<uint32_t>(uni(static_cast<int>(x >> 32)))) << 32) |
+                   static_cast<uint32_t>(uni(static_cast<int>(static_cast<uint32_t>(x))));
+        };
+        Segment sg;
+        sg.b = uni(v.b); sg.g = g; sg.L = uni(v.L); sg.n = uni(v.n); sg.node0 = uni(v.node0); sg.rows = uni(v.rows); sg.cg = uni(v.cg);
+        sg.begin = uni(v.begin); sg.count = uni(v.count); sg.cache_blocks = uni(v.cache_blocks);
+        sg.kv_start = static_cast<long>(uni64(static_cast<uint64_t>(v.kv_start)));
+        sg.out = reinterpret_cast<unsigned char*>(uni64(reinterpret_cast<uint64_t>(v.out)));
+        if (BATCH) __syncthreads();                          // the previous segment's epilogue has left the ring
+        // A batched workgroup calls this in a loop.  Everything that depends only on the thread index would be
+        // loop-invariant, and the compiler hoists all of it out of the loop and keeps it alive across the whole pass.
+        // The thread index is therefore made opaque per pass, and its derived values are recomputed.
+        int tid = static_cast<int>(threadIdx.x);
+        if (BATCH) asm volatile("" : "+v"(tid));
+        // up to 128 rows: one column tile per wave, on as many SIMDs as there are tiles; more: two
+        if (sg.rows - sg.cg * ROWS_PER_WG <= WAVES * 32) attention_pass<1>(prm, lds, sg, inv_G, tid);
+        else attention_pass<2>(prm, lds, sg, inv_G, tid);
     };
-    const int b = uni(b_v), L = uni(L_v), seq_n = uni(seq_n_v), seq_rows = uni(seq_rows_v), cg = uni(cg_v);
-    const int node0 = uni(first_v);
-    const int t_begin = uni(t_begin_v), t_end = uni(t_end_v), tree_tile = uni(tree_tile_v);
-    const long kv_start_b = static_cast<long>(uni64(static_cast<uint64_t>(kv_start_v)));
-    unsigned char* const out_base = reinterpret_cast<unsigned char*>(uni64(reinterpret_cast<uint64_t>(out_base_v)));
-    if (BATCH) __syncthreads();                              // the previous segment's epilogue has left the stage buffers
-    // A batched workgroup calls this in a loop.  Everything below that depends only on the thread index would be
-    // loop-invariant, and the compiler hoists all of it out of the loop and keeps it alive across the whole pass (some
-    // fifty registers more than the pass itself needs, which does not fit).  The thread index is therefore made opaque
-    // per pass, and its derived values are recomputed (a handful of instructions).
-    int tid = static_cast<int>(threadIdx.x);
-    if (BATCH) asm volatile("" : "+v"(tid));
-    const int lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // wave-uniform, so LDS stage addresses stay scalar
-    const int r32 = lane & 31;           // MFMA row (A) / column (B, C) owned by this lane
-    const int half = lane >> 5;
-    // ---- wave roles: wave w owns column tile w of the group (32 query rows) and processes whole tiles for it; with up
-    // to four column tiles every computing wave has a SIMD to itself
-    const int group_rows = min(ROWS_PER_WG, seq_rows - cg * ROWS_PER_WG);
-    const int group_ct = (group_rows + 31) / 32;             // 1..8 column tiles in this group
-    const bool wide = group_ct > 4;                          // Q needs two stages of the ring on its way in
-    const bool wave_active = wave < group_ct;
-    const int m_local = wave * 32 + r32;                     // this lane's query row within the group
-
-    // ---- loader: instruction i of wave w copies tokens r, r+16, r+32, r+48 (r = 2w + i) of K and of V, 1 KB of
-    //      LDS each: lane l fills chunk l%16 of token r + 16 (l/16).  Addresses are a wave-uniform tile base in scalar
-    //      registers plus a 32-bit per-lane offset that is the same for every full tile, so a tile costs no vector
-    //      address arithmetic.
-    const int ld_tok = (lane >> 4) * 16 + wave * 2;          // token within the tile for i = 0 (i = 1: the next one)
-    const unsigned ld_chunk_b = (lane & 15) * 16;
-    const unsigned char* k_cache = reinterpret_cast<const unsigned char*>(
-        prm.Kc + kv_start_b * prm.kv_token_stride + static_cast<long>(g) * prm.kv_head_stride);
-    const unsigned char* v_cache = reinterpret_cast<const unsigned char*>(
-        prm.Vc + kv_start_b * prm.kv_token_stride + static_cast<long>(g) * prm.kv_head_stride);
-    const unsigned char* k_tree = reinterpret_cast<const unsigned char*>(
-        prm.Kt + (static_cast<long>(b) * SAGE_MAX_NODES * prm.Hkv + g) * D);
-    const unsigned char* v_tree = reinterpret_cast<const unsigned char*>(
-        prm.Vt + (static_cast<long>(b) * SAGE_MAX_NODES * prm.Hkv + g) * D);
-    const unsigned cache_row_b = static_cast<unsigned>(prm.kv_token_stride) * 2u;   // host: 64 rows fit 32 bits
-    const unsigned tree_row_b = static_cast<unsigned>(prm.Hkv) * D * 2u;
-    const unsigned ld_off0 = static_cast<unsigned>(ld_tok) * cache_row_b + ld_chunk_b;
-    const unsigned ld_off1 = ld_off0 + cache_row_b;
-
-    auto issue_loads = [&](int tile, auto stc) __attribute__((always_inline)) {
-        constexpr int ST = decltype(stc)::value;
-        LDS_AS unsigned char* k_dst = (LDS_AS unsigned char*)(&SK(ST)[wave * 2 * K_GROUP]);
-        LDS_AS unsigned char* v_dst = (LDS_AS unsigned char*)(&SV(ST)[wave * 2 * V_GROUP]);
-        const bool is_tree = (tile == tree_tile);
-        if (tile >= t_end) {
-            // Nothing left to fetch, but every step issues the same number of loads, so the wait for a tile is one fixed
-            // count on every path.  Four loads of one valid 16-byte piece (served by L2) into the free stage.
-            const unsigned char* any = reinterpret_cast<const unsigned char*>(prm.Q);
-            sage::lds_direct_load16(any, 0u, k_dst);
-            sage::lds_direct_load16(any, 0u, v_dst);
-            sage::lds_direct_load16(any, 0u, k_dst + K_GROUP);
-            sage::lds_direct_load16(any, 0u, v_dst + V_GROUP);
-        } else if (!is_tree && tile * TILE + TILE <= L) {    // full cache tile
-            const unsigned char* kb = k_cache + static_cast<long>(tile) * TILE * cache_row_b;
-            const unsigned char* vb = v_cache + static_cast<long>(tile) * TILE * cache_row_b;
-            sage::lds_direct_load16(kb, ld_off0, k_dst);
-            sage::lds_direct_load16(vb, ld_off0, v_dst);
-            sage::lds_direct_load16(kb, ld_off1, k_dst + K_GROUP);
-            sage::lds_direct_load16(vb, ld_off1, v_dst + V_GROUP);
-        } else {                                             // ragged tail or the tree's keys: rows past the end are
-            const unsigned char* kb = is_tree ? k_tree : k_cache + static_cast<long>(tile) * TILE * cache_row_b;   // masked later,
-            const unsigned char* vb = is_tree ? v_tree : v_cache + static_cast<long>(tile) * TILE * cache_row_b;   // reads stay in range
-            const unsigned row_b = is_tree ? tree_row_b : cache_row_b;
-            const int last = is_tree ? seq_n - 1 : L - 1 - tile * TILE;
-            const unsigned o0 = static_cast<unsigned>(min(ld_tok, last)) * row_b + ld_chunk_b;
-            const unsigned o1 = static_cast<unsigned>(min(ld_tok + 1, last)) * row_b + ld_chunk_b;
-            sage::lds_direct_load16(kb, o0, k_dst);
-            sage::lds_direct_load16(vb, o0, v_dst);
-            sage::lds_direct_load16(kb, o1, k_dst + K_GROUP);
-            sage::lds_direct_load16(vb, o1, v_dst + V_GROUP);
-        }
-    };
-    // Everything the prologue needs from memory goes straight into LDS, requested back to back in this order: the rows'
-    // ancestor masks, the Q rows (into the ring's last stage, idle until the first tile step refills it; a group of more
-    // than four column tiles also borrows the third stage, whose tile is then requested one step later), the first
-    // tiles.  No load returns into a register, so the compiler never waits on the vector-memory counter here and the
-    // only waits are the counted ones: loads complete in order, so masks and Q have landed once no more than the tile
-    // loads are outstanding, and the first tile is processed while the following ones are still arriving.
-    // Rows past the group's last one repeat that row (their results are never written).
-    auto row_of = [&](int local) __attribute__((always_inline)) {      // row `local` of this group -> (node, head in group)
-        const int mm = min(cg * ROWS_PER_WG + local, seq_rows - 1);
-        const int nd = (mm * inv_G) >> 16;                               // exact for mm < 64 G, G <= 16
-        return make_int2(node0 + nd, mm - nd * prm.G);
-    };
-    {
-        // wave w brings both words of the masks of its rows 32 w + lane / 2
-        const int2 r = row_of(wave * 32 + (lane >> 1));
-        sage::lds_direct_load4(
-            reinterpret_cast<const unsigned char*>(prm.anc_mask + static_cast<long>(b) * SAGE_MAX_NODES + r.x) + (lane & 1) * 4,
-            (LDS_AS unsigned char*)(&s_mask[wave * 32]));
-    }
-    // Q rows as blocks of 64 in the layout of a K tile (K buffer) and of a V tile (V buffer): row q of a block sits at
-    // (q % 16) * GROUP + (q / 16) * ROW_B.  Blocks 0, 1 -> stage 3; blocks 2, 3 (wide groups only) -> stage 2.
-    auto issue_q = [&](auto blkc) __attribute__((always_inline)) {
-        constexpr int BLK = decltype(blkc)::value;
-#pragma unroll
-        for (int i = 0; i < 2; ++i) {
-            const int2 r = row_of(BLK * 64 + wave * 2 + i + 16 * (lane >> 4));
-            const unsigned char* src = reinterpret_cast<const unsigned char*>(
-                prm.Q + ((static_cast<long>(b) * SAGE_MAX_NODES + r.x) * prm.Hq + g * prm.G + r.y) * D) + ld_chunk_b;
-            unsigned char* buf = BLK == 0 ? sK3 : BLK == 1 ? sV3 : BLK == 2 ? sK2 : sV2;
-            const int group_b = (BLK & 1) ? V_GROUP : K_GROUP;
-            sage::lds_direct_load16(src, (LDS_AS unsigned char*)(&buf[(wave * 2 + i) * group_b]));
-        }
-    };
-    using I0 = std::integral_constant<int, 0>;
-    using I1 = std::integral_constant<int, 1>;
-    using I2 = std::integral_constant<int, 2>;
-    using I3 = std::integral_constant<int, 3>;
-    using I4 = std::integral_constant<int, 4>;
-    issue_q(I0{});
-    issue_q(I1{});
-    if (wide) {
-        issue_q(I2{});
-        issue_q(I3{});
-    }
-    issue_loads(t_begin, I0{});
-    issue_loads(t_begin + 1, I1{});
-    if (wide) {
-        wait_vm<2 * LOADS_PER_TILE>();                       // this thread's mask and Q loads have landed
-    } else {
-        issue_loads(t_begin + 2, I2{});
-        wait_vm<3 * LOADS_PER_TILE>();
-    }
-    stage_barrier();                                         // ... everyone's have
-    bf16x8 qf[8];                                            // this lane's query row: the B operand of every score MFMA
-    {
-        const int q = (wave & 1) * 32 + r32;                 // row within its block of 64
-        const int blk = wave >> 1;
-        const lds_byte* qb = blk == 0 ? (const lds_byte*)sK3 : blk == 1 ? (const lds_byte*)sV3 : blk == 2 ? (const lds_byte*)sK2
-                                                                                                       : (const lds_byte*)sV2;
-        qb += (q & 15) * ((blk & 1) ? V_GROUP : K_GROUP) + (q >> 4) * ROW_B + half * 16;
-#pragma unroll
-        for (int kk = 0; kk < 8; ++kk) qf[kk] = __builtin_bit_cast(bf16x8, *(const LDS_AS uint4*)(qb + kk * 32));
-    }
-    __builtin_amdgcn_s_waitcnt(0xc07f);                      // lgkmcnt(0): Q is in registers before this wave reaches the
-                                                             // barrier after which its stages are refilled
-
-    // ---- per-lane LDS read offsets.  K fragment (sub, kk): token r32 of 32-token half `sub`, chunk 2kk + half
-    //      -> k_lane + sub * 2 * ROW_B + 32 kk.
-    const int k_lane = (r32 & 15) * K_GROUP + (r32 >> 4) * ROW_B + half * 16;
-    // V^T fragment (dt, jj, u): k-block jj (16 tokens); the 16-lane group q = lane/16 reads tokens 16jj + 8u + 4(q/2) + s/4
-    // and dims dt*32 + 16(q%2) + 4(s%4) .. +3  (s = lane%16); after the transposing read lane s holds dim dt*32+16(q%2)+s.
-    // Offset: v_lane + jj * ROW_B + u * 8 * V_GROUP + dt * 64.
-    int v_lane;
-    {
-        const int q = lane >> 4, s16 = lane & 15;
-        v_lane = (4 * (q >> 1) + (s16 >> 2)) * V_GROUP + (2 * (q & 1) + ((s16 & 3) >> 1)) * 16 + 8 * (s16 & 1);
-    }
-
-    f32x16 acc[4];                                           // O^T: 4 tiles of 32 dims x this lane's query row
-#pragma unroll
-    for (int dt = 0; dt < 4; ++dt)
-#pragma unroll
-        for (int i = 0; i < 16; ++i) acc[dt][i] = 0.f;
-    float m_ref = -INFINITY;                                 // reference maximum of raw (unscaled) scores
-    float neg_mc = 0.f;                                      // -m_ref * c, 0 while there is no reference yet
-    float l_run = 0.f;                                       // this lane's share of the running sum
-    const float c = prm.scale_log2e;
-    f32x16 sc[2];                                            // scores of the tile's two 32-token halves
-    bf16x8 pf[4];                                            // P^T of the tile's four 16-token k-blocks, the B operand of PV
-    bf16x8 ka[8], va[2][4];                                  // K fragments of a half tile; V^T fragments of two dim tiles
-
-    // The pieces of a tile step: scores (S^T = K Q^T, MFMA), softmax (VALU), PV (MFMA).  The LDS reads of a piece are
-    // issued in batches ahead of the arithmetic that hides their latency; the scheduling fences keep the compiler from
-    // sinking them back next to their uses, where every MFMA group would wait out a full LDS round trip.
-    auto read_k = [&](const lds_byte* kb, auto subc, auto firstc) __attribute__((always_inline)) {
-        constexpr int SUB = decltype(subc)::value;
-        constexpr int FIRST = decltype(firstc)::value;        // dims FIRST*16 .. FIRST*16 + 63
-#pragma unroll
-        for (int kk = FIRST; kk < FIRST + 4; ++kk)
-            ka[kk] = __builtin_bit_cast(bf16x8, *(const LDS_AS uint4*)(kb + k_lane + SUB * 2 * ROW_B + kk * 32));
-    };
-    auto read_v = [&](const lds_byte* vb, auto dt0c) __attribute__((always_inline)) {
-        constexpr int DT0 = decltype(dt0c)::value;            // dims DT0*32 .. DT0*32 + 63, all four k-blocks
-#pragma unroll
-        for (int dt = DT0; dt < DT0 + 2; ++dt)
-#pragma unroll
-            for (int jj = 0; jj < 4; ++jj) {
-                const lds_byte* p0 = vb + v_lane + jj * ROW_B + dt * 64;
-                const bf16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((LDS_AS bf16x4*)p0);
-                const bf16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((LDS_AS bf16x4*)(p0 + 8 * V_GROUP));
-                va[dt - DT0][jj] = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
-            }
-    };
-    auto score_mfma = [&](auto subc, auto firstc) __attribute__((always_inline)) {
-        constexpr int SUB = decltype(subc)::value;
-        constexpr int FIRST = decltype(firstc)::value;
-        if (FIRST == 0) {
-#pragma unroll
-            for (int i = 0; i < 16; ++i) sc[SUB][i] = 0.f;
-        }
-#pragma unroll
-        for (int kk = FIRST; kk < FIRST + 4; ++kk) sc[SUB] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ka[kk], qf[kk], sc[SUB], 0, 0, 0);
-    };
-    // admit keys: cache positions below kv_len; tree nodes in this row's ancestor-or-self mask
-    auto score_mask = [&](int tile) __attribute__((always_inline)) {
-        const bool is_tree = (tile == tree_tile);
-        if (!(is_tree || tile * TILE + TILE > L)) return;
-        uint64_t admit;
-        if (is_tree) {
-            admit = s_mask[m_local];
-        } else {
-            const int left = L - tile * TILE;                // 1..63 valid tokens
-            admit = (1ull << left) - 1ull;
-        }
-        // token of accumulator register i of half `sub`: 32 sub + 8 (i/4) + 4 half + i%4
-#pragma unroll
-        for (int sub = 0; sub < 2; ++sub) {
-            const uint32_t adm = static_cast<uint32_t>(admit >> (4 * half + 32 * sub));
-#pragma unroll
-            for (int i = 0; i < 16; ++i)
-                if (!((adm >> (8 * (i >> 2) + (i & 3))) & 1u)) sc[sub][i] = -INFINITY;
-        }
-    };
-    // probabilities of k-block JJ: sc[JJ / 2][8 (JJ % 2) .. + 7] -> pf[JJ]; returns sum + the block's rounded probabilities
-    auto probs = [&](auto jjc, float sum) __attribute__((always_inline)) {
-        constexpr int JJ = decltype(jjc)::value;
-        const bf16x2 ones = {static_cast<__bf16>(1.0f), static_cast<__bf16>(1.0f)};
-        bf16x8 frag;
-#pragma unroll
-        for (int e = 0; e < 8; e += 2) {
-            const f32x2 pp = {__builtin_amdgcn_exp2f(fmaf(sc[JJ >> 1][8 * (JJ & 1) + e], c, neg_mc)),
-                              __builtin_amdgcn_exp2f(fmaf(sc[JJ >> 1][8 * (JJ & 1) + e + 1], c, neg_mc))};
-            const bf16x2 pb = __builtin_convertvector(pp, bf16x2);
-            frag[e] = pb[0];
-            frag[e + 1] = pb[1];
-            sum = __builtin_amdgcn_fdot2_f32_bf16(pb, ones, sum, false);
-        }
-        pf[JJ] = frag;
-        return sum;
-    };
-    auto all_probs = [&]() __attribute__((always_inline)) { return probs(I3{}, probs(I2{}, probs(I1{}, probs(I0{}, 0.f)))); };
-    // Move the reference maximum of the rows that need it to the row maximum of the current tile (both 32-lane halves of
-    // a row decide alike) and rescale what has been accumulated so far.
-    auto rebase = [&]() __attribute__((always_inline)) {
-        float tmax = fmaxf(sc[0][0], sc[1][0]);
-#pragma unroll
-        for (int i = 1; i < 16; ++i) tmax = fmaxf(tmax, fmaxf(sc[0][i], sc[1][i]));
-        tmax = cross_half_max(tmax);
-        const bool raise = (m_ref == -INFINITY) ? (tmax > -INFINITY) : ((tmax - m_ref) * c > RAISE_MIN);
-        if (__any(raise)) {
-            const float m_new = raise ? tmax : m_ref;
-            const float corr = !raise ? 1.f : (m_ref == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f((m_ref - m_new) * c);
-            m_ref = m_new;
-            neg_mc = -m_ref * c;                             // raise implies a finite maximum
-            if (!raise && m_ref == -INFINITY) neg_mc = 0.f;
-            l_run *= corr;
-#pragma unroll
-            for (int dt = 0; dt < 4; ++dt)
-#pragma unroll
-                for (int i = 0; i < 16; ++i) acc[dt][i] *= corr;
-        }
-    };
-    // Back to rebase() when a lane's sum says its probabilities may have overflowed, or when a lane has no reference yet:
-    // the pass's first tile, or every key so far was masked for its half of the row.
-    auto overflow = [&](float sum) __attribute__((always_inline)) {
-        return __any(!(sum <= REBASE_SUM) || m_ref == -INFINITY) != 0;
-    };
-    // O^T += V^T P^T for the 64 dims whose fragments are in va (four k-blocks of 16 tokens)
-    auto pv_mfma = [&](auto dt0c) __attribute__((always_inline)) {
-        constexpr int DT0 = decltype(dt0c)::value;
-#pragma unroll
-        for (int jj = 0; jj < 4; ++jj)
-#pragma unroll
-            for (int dt = DT0; dt < DT0 + 2; ++dt)
-                acc[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va[dt - DT0][jj], pf[jj], acc[dt], 0, 0, 0);
-    };
-#define FENCE() __builtin_amdgcn_sched_barrier(0)
-
-    auto process = [&](int tile, int first, auto stc) __attribute__((always_inline)) {
-        constexpr int ST = decltype(stc)::value;
-        if (first && wide) {
-            wait_vm<1 * LOADS_PER_TILE>();                   // (the third tile is not on its way yet)
-            stage_barrier();                                 // tile 0 has landed; everyone has read Q out of stages 2, 3
-            issue_loads(tile + 2, std::integral_constant<int, (ST + 2) % STAGES>{});
-        } else {
-            wait_vm<2 * LOADS_PER_TILE>();                   // this thread's part of `tile` has landed (two tiles may fly)
-            stage_barrier();                                 // ... everyone's has, and the stage read last step is free
-        }
-        issue_loads(tile + 3, std::integral_constant<int, (ST + 3) % STAGES>{});
-        if (!wave_active) return;
-
-        const lds_byte* kst = (const lds_byte*)(SK(ST));
-        const lds_byte* vst = (const lds_byte*)(SV(ST));
-        read_k(kst, I0{}, I0{});
-        read_k(kst, I0{}, I4{});
-        FENCE();
-        score_mfma(I0{}, I0{});
-        FENCE();
-        read_k(kst, I1{}, I0{});                             // the second half's fragments follow the first's through the
-        FENCE();                                             // same registers, one batch of four behind the MFMAs
-        score_mfma(I0{}, I4{});
-        FENCE();
-        read_k(kst, I1{}, I4{});
-        FENCE();
-        score_mfma(I1{}, I0{});
-        FENCE();
-        read_v(vst, I0{});                                   // V reads go out between the score MFMAs and land
-        FENCE();                                             // during the softmax
-        score_mfma(I1{}, I4{});
-        FENCE();
-        score_mask(tile);
-        float sum = all_probs();
-        if (overflow(sum)) {
-            rebase();
-            sum = all_probs();
-        }
-        l_run += sum;
-        pv_mfma(I0{});
-        FENCE();
-        read_v(vst, I2{});
-        FENCE();
-        pv_mfma(I2{});
-    };
-    for (int tile = t_begin; tile < t_end; tile += STAGES) {    // no path reaches a step without the steps before it
-        process(tile, tile == t_begin, I0{});
-        if (tile + 1 >= t_end) break;
-        process(tile + 1, 0, I1{});
-        if (tile + 2 >= t_end) break;
-        process(tile + 2, 0, I2{});
-        if (tile + 3 >= t_end) break;
-        process(tile + 3, 0, I3{});
-    }
-#undef FENCE
-
-    const float l_tot = cross_half_sum(l_run);
-    wait_vm<0>();                                            // the placeholder loads of the last steps have landed too
-
-    // ---- epilogue: a wave's block (O^T in bf16, max, sum) is complete for its 32 rows.  It goes through the wave's own
-    // piece of a stage buffer as [32 rows][EPI_ROW_B bytes], transposed on the way: written 8 bytes (4 dims) at a time from
-    // the accumulator layout, read back and stored to the partial in row order, for the second kernel to merge.
-    __syncthreads();                                         // all stages are idle now
-    if (wave_active) {
-        unsigned char* blk = wave < 4 ? SK(wave) : SV(wave - 4);
-        unsigned char* mine = blk + r32 * EPI_ROW_B;
-#pragma unroll
-        for (int dt = 0; dt < 4; ++dt)
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const f32x4 v = {acc[dt][4 * q], acc[dt][4 * q + 1], acc[dt][4 * q + 2], acc[dt][4 * q + 3]};
-                *reinterpret_cast<bf16x4*>(mine + (dt * 32 + 8 * q + 4 * half) * 2) = __builtin_convertvector(v, bf16x4);
-            }
-        if (half == 0) *reinterpret_cast<float2*>(mine + D * 2) = make_float2(m_ref, l_tot);
-        // (a wave's LDS operations complete in order, and the reads below wait for them: no barrier inside a wave)
-        const int rows_here = min(32, group_rows - wave * 32);
-        unsigned char* out = out_base + static_cast<long>(wave) * 32 * PART_ROW_B;
-        // parked rows and partial rows have the same pitch, so the wave's block goes out as one contiguous copy of
-        // rows_here * 17 chunks of 16 bytes (16 of O^T, one of max and sum), 64 chunks per store instruction
-        const int last_chunk = rows_here * (PART_ROW_B / 16);
-#pragma unroll
-        for (int i = 0; i < 9; ++i) {
-            const int ch = lane + 64 * i;
-            if (ch < last_chunk)
-                *reinterpret_cast<uint4*>(out + ch * 16) = *reinterpret_cast<const uint4*>(blk + ch * 16);
-        }
-    }
-    };   // run_segment
 
     if (!BATCH) {
         const int slot = id;
@@ -591,25 +761,25 @@ __device__ __forceinline__ void attention_workgroup(const int* __restrict__ kv_l
         asm("" : "+s"(len_b), "+s"(n_b), "+s"(start_lo), "+s"(start_hi), "+s"(f_b));
         const long start_b = (static_cast<long>(start_hi) << 32) | static_cast<uint32_t>(start_lo);
         const int L = len_b > 0 ? len_b : 0;
-        const Split sp = make_split(n_b, f_b, L, G_arg, nslot_arg, min_tps_arg);
+        const Split sp = make_split(n_b, f_b, L, G_arg, nslot_arg, min_bps_arg);
         if (sp.col_groups > nslot_arg) return;              // host guarantees nslot >= the largest group count
         const int cg = slot % sp.col_groups;
         const int split = slot / sp.col_groups;
         if (split >= sp.nsplit) return;
-        const int t_begin = split * sp.tiles_per_split;
-        const int t_end = min(sp.tiles, t_begin + sp.tiles_per_split);
-        run_segment(b, L, sp.n, sp.first, sp.rows, cg, t_begin, t_end, sp.tiles - 1, start_b,
-                    prm.part + ((static_cast<long>(b) * prm.Hkv + g) * prm.nslot + slot) * PART_SLOT_B);
+        const int begin = split * sp.blocks_per_split;
+        run_segment(Segment{b, g, L, sp.n, sp.first, sp.rows, cg, begin, min(sp.blocks - begin, sp.blocks_per_split), blocks_of(L),
+                            start_b, prm.part + ((static_cast<long>(b) * prm.Hkv + g) * prm.nslot + slot) * PART_SLOT_B});
     } else {
+        const int lane = threadIdx.x & 63;
         const BatchShape bs = make_batch_shape(prm, lane);  // lane b holds sequence b
-        const int r0 = id * bs.q;                            // this workgroup's range of the tile list
+        const int r0 = id * bs.q;                            // this workgroup's range of the list
         const int r1 = min(bs.total, r0 + bs.q);
         if (r0 >= r1) return;
         int first = 0, groups_before = 0;                    // first position / number of segments of the sequences before b
         for (int b = 0; b < prm.B && first < r1; ++b) {
-            const int tiles_b = __builtin_amdgcn_readlane(bs.tiles, b);
+            const int blocks_b = __builtin_amdgcn_readlane(bs.blocks, b);
             const int cgs_b = __builtin_amdgcn_readlane(bs.col_groups, b);
-            const int seg_len = tiles_b + SEG_COST_TILES;
+            const int seg_len = blocks_b + SEG_COST;
             if (first + seg_len * cgs_b > r0) {
                 const int n_b = __builtin_amdgcn_readlane(bs.n, b);
                 const int f_b = __builtin_amdgcn_readlane(bs.first, b);
@@ -617,19 +787,17 @@ __device__ __forceinline__ void attention_workgroup(const int* __restrict__ kv_l
                 const long start_b = (static_cast<long>(__builtin_amdgcn_readlane(bs.start_hi, b)) << 32) |
                                      static_cast<uint32_t>(__builtin_amdgcn_readlane(bs.start_lo, b));
                 for (int cg = 0; cg < cgs_b; ++cg) {
-                    const int tile0 = first + cg * seg_len + SEG_COST_TILES;      // position of the segment's first tile
-                    const int lo = max(r0, tile0), hi = min(r1, tile0 + tiles_b);
+                    const int block0 = first + cg * seg_len + SEG_COST;      // position of the segment's first block
+                    const int lo = max(r0, block0), hi = min(r1, block0 + blocks_b);
                     if (lo < hi)
-                        run_segment(b, L_b, n_b, f_b, (n_b - f_b) * prm.G, cg, lo - tile0, hi - tile0, tiles_b - 1, start_b,
-                                    prm.part + (static_cast<long>(g) * prm.nslot + id + groups_before + cg) * PART_SLOT_B);
+                        run_segment(Segment{b, g, L_b, n_b, f_b, (n_b - f_b) * prm.G, cg, lo - block0, hi - lo, blocks_of(L_b), start_b,
+                                            prm.part + (static_cast<long>(g) * prm.nslot + id + groups_before + cg) * PART_SLOT_B});
                 }
             }
             first += seg_len * cgs_b;
             groups_before += cgs_b;
         }
     }
-#undef SK
-#undef SV
 }
 
 template <bool BATCH>
@@ -637,8 +805,10 @@ __global__ __launch_bounds__(THREADS) void tree_attention_bf16_kernel(const int*
                                                                       const int* __restrict__ n_nodes_arg,
                                                                       const int* __restrict__ first_node_arg,
                                                                       const int64_t* __restrict__ kv_start_arg, int nslot_arg,
-                                                                      int min_tps_arg, int G_arg, const Params prm) {
-    attention_workgroup<BATCH>(kv_len_arg, n_nodes_arg, first_node_arg, kv_start_arg, nslot_arg, min_tps_arg, G_arg, prm, 0);
+                                                                      int min_bps_arg, int G_arg, const Params prm) {
+    __shared__ __align__(256) Lds lds;
+    attention_workgroup<BATCH>(kv_len_arg, n_nodes_arg, first_node_arg, kv_start_arg, nslot_arg, min_bps_arg, G_arg, prm, 0,
+                               (LDS_AS Lds*)&lds);
 }
 
 // The same launch carrying the planning of the next tree along (sage_tree_attention_with_plan): the grid has extra
@@ -650,8 +820,13 @@ __global__ __launch_bounds__(THREADS) void tree_attention_bf16_kernel(const int*
 // when the attention's own workgroups fill every CU, the one that has to wait for a free CU is then the attention's
 // last (a sequence's final split, seldom a full one), and it waits for the short planning workgroup, not the other
 // way round.
-constexpr int PLAN_LDS_KEYS = 2400;     // short lists staged beside the attention's stages (k = 16 at 152064 tokens: 2384)
+constexpr int PLAN_LDS_KEYS = 2400;     // short lists staged in LDS (k = 16 at 152064 tokens: 2384)
 constexpr int PLAN_OWN = 4;              // slices per lane: up to 256 slices per draft row
+struct PlanLds {                         // (a planning workgroup uses the same LDS as an attention workgroup)
+    uint64_t keys[PLAN_LDS_KEYS];
+    sage::topk::PickShared pick;
+    float row[2];
+};
 struct PlanShared {
     static constexpr int LDS_KEYS = PLAN_LDS_KEYS;
     uint64_t* keys;
@@ -663,21 +838,24 @@ template <bool BATCH>
 __global__ __launch_bounds__(THREADS) void tree_attention_plan_kernel(const int* __restrict__ kv_len_arg,
                                                                       const int* __restrict__ n_nodes_arg,
                                                                       const int64_t* __restrict__ kv_start_arg, int nslot_arg,
-                                                                      int min_tps_arg, int G_arg, int plan_slabs,
+                                                                      int min_bps_arg, int G_arg, int plan_slabs,
                                                                       const Params prm, const sage::PlanArgs pl) {
+    __shared__ __align__(256) union Both {
+        Lds attention;
+        PlanLds plan;
+        __device__ Both() {}
+    } lds;
     if (static_cast<int>(blockIdx.y) < plan_slabs) {        // workgroup-uniform
-        __shared__ uint64_t p_keys[PLAN_LDS_KEYS];
-        __shared__ sage::topk::PickShared p_pick;
-        __shared__ float p_row[2];
         // one sequence per launch slot: the slab's first workgroup of sequence blockIdx.z; batches: slab workgroups in turn
         const int b = BATCH ? static_cast<int>(blockIdx.y * gridDim.x + blockIdx.x)
                             : (blockIdx.x == 0 ? static_cast<int>(blockIdx.z) : prm.B);
         if (b >= prm.B) return;
-        PlanShared sh{p_keys, p_pick, p_row[0], p_row[1]};
+        PlanShared sh{lds.plan.keys, lds.plan.pick, lds.plan.row[0], lds.plan.row[1]};
         sage::plan_sequence<PLAN_OWN, THREADS>(b, pl, sh);
         return;
     }
-    attention_workgroup<BATCH>(kv_len_arg, n_nodes_arg, nullptr, kv_start_arg, nslot_arg, min_tps_arg, G_arg, prm, plan_slabs);   // a verify pass: every node
+    attention_workgroup<BATCH>(kv_len_arg, n_nodes_arg, nullptr, kv_start_arg, nslot_arg, min_bps_arg, G_arg, prm, plan_slabs,
+                               (LDS_AS Lds*)&lds.attention);   // a verify pass: every node
 }
 
 // Merge the splits of one (sequence, node, query head) in split order and write bf16.  One wave per row:
@@ -693,7 +871,7 @@ constexpr int MERGE_PHASES_BATCH = 32;   // batches: workgroups per (sequence, K
 template <int MAXS, bool BATCH, int ROWS>
 __global__ __launch_bounds__(64 * ROWS) void tree_attention_merge_kernel(const int* __restrict__ kv_len_arg,
                                                                          const int* __restrict__ n_nodes_arg, int nslot_arg,
-                                                                         int min_tps_arg, int G_arg, int phases_arg,
+                                                                         int min_bps_arg, int G_arg, int phases_arg,
                                                                          const Params prm) {
     static_assert(MAXS <= 64, "one split per lane, one register per split");
     // As in the main kernel, a KV head's blocks are congruent modulo the KV-head count, so with 8 KV heads they run on
@@ -770,7 +948,7 @@ __global__ __launch_bounds__(64 * ROWS) void tree_attention_merge_kernel(const i
         int f_b = prm.first_node ? __builtin_amdgcn_readfirstlane(prm.first_node[b]) : 0;
         asm("" : "+s"(len_b), "+s"(n_b), "+s"(f_b));
         const int L = len_b > 0 ? len_b : 0;
-        const Split sp = make_split(n_b, f_b, L, G_arg, nslot_arg, min_tps_arg);
+        const Split sp = make_split(n_b, f_b, L, G_arg, nslot_arg, min_bps_arg);
         if (sp.col_groups > nslot_arg) return;
         const unsigned char* base = prm.part + ((static_cast<long>(b) * prm.Hkv + g) * prm.nslot) * PART_SLOT_B;
         for (int m = phase * ROWS + wave; m < sp.rows; m += phases * ROWS)
@@ -780,16 +958,16 @@ __global__ __launch_bounds__(64 * ROWS) void tree_attention_merge_kernel(const i
         const BatchShape bs = make_batch_shape(prm, lane);
         const int first_b = __builtin_amdgcn_readlane(bs.first, b);
         const int live = (__builtin_amdgcn_readlane(bs.n, b) - first_b) * prm.G;
-        const int tiles_b = __builtin_amdgcn_readlane(bs.tiles, b);
-        const int before = wave_sum_i32(lane < b ? (bs.tiles + SEG_COST_TILES) * bs.col_groups : 0);
+        const int blocks_b = __builtin_amdgcn_readlane(bs.blocks, b);
+        const int before = wave_sum_i32(lane < b ? (bs.blocks + SEG_COST) * bs.col_groups : 0);
         const int groups_before = wave_sum_i32(lane < b ? bs.col_groups : 0);
         for (int m = phase * ROWS + wave; m < live; m += phases * ROWS) {
             const int cg = m / ROWS_PER_WG;
-            const int u0 = before + cg * (tiles_b + SEG_COST_TILES) + SEG_COST_TILES;   // first tile of segment (b, cg)
+            const int u0 = before + cg * (blocks_b + SEG_COST) + SEG_COST;   // first block of segment (b, cg)
             const int s_first = u0 / bs.q;
             merge_row(b, first_b + m / prm.G, m % prm.G,
                       prm.part + (static_cast<long>(g) * prm.nslot + s_first + groups_before + cg) * PART_SLOT_B + (m % ROWS_PER_WG) * PART_ROW_B,
-                      static_cast<unsigned>(PART_SLOT_B), (u0 + tiles_b - 1) / bs.q - s_first + 1);
+                      static_cast<unsigned>(PART_SLOT_B), (u0 + blocks_b - 1) / bs.q - s_first + 1);
         }
     }
 }
@@ -808,8 +986,10 @@ namespace sage {
 // and a step's other launches: 101 us at 8, 91.4 at 5, 88.5 at 4, 88.2 at 3 and 2; 2 of 212-613 tokens, six layers: 118,
 // 105, 97, 97).  CAP_RANGE_TILES bounds the ranges, and with them the workspace, by the longest lengths allowed.
 constexpr int MAX_BATCH_LANES = 64;      // a lane per sequence in make_batch_shape
-constexpr int MIN_RANGE_TILES = SEG_COST_TILES;   // positions of the line, pass cost included
+constexpr int TILE = 64;                 // tokens: the unit in which the host counts
+constexpr int MIN_RANGE_TILES = 4;       // 64-token positions of the line, pass cost included
 constexpr int CAP_RANGE_TILES = 8;
+constexpr int SEG_COST_TILES = SEG_COST * BLK / TILE;
 struct LaunchShape { int nslot, min_tiles_per_split, nrange; bool batch; };
 LaunchShape attention_bf16_shape(int B, int Hkv, int G, int max_kv_len) {
     const int max_groups = (SAGE_MAX_NODES * G + ROWS_PER_WG - 1) / ROWS_PER_WG;
@@ -880,7 +1060,7 @@ int tree_attention_bf16(const void* Q, const void* Kc, const void* Vc, const voi
     p.B = B; p.Hq = Hq; p.Hkv = Hkv; p.G = G;
     const LaunchShape sh = attention_bf16_shape(B, Hkv, G, max_kv_len);
     p.nslot = sh.nslot;
-    p.min_tiles_per_split = sh.min_tiles_per_split;
+    p.min_blocks_per_split = sh.min_tiles_per_split * (TILE / BLK);
     p.scale_log2e = scale * 1.4426950408889634f;
 
     p.nrange = sh.nrange;
@@ -893,18 +1073,18 @@ int tree_attention_bf16(const void* Q, const void* Kc, const void* Vc, const voi
         const dim3 grid(Hkv, plan_slabs + own_slabs, sh.batch ? 1 : B);
         if (sh.batch)
             hipLaunchKernelGGL(tree_attention_plan_kernel<true>, grid, block, 0, stream, kv_len, n_nodes, kv_start, p.nslot,
-                               p.min_tiles_per_split, G, plan_slabs, p, *plan);
+                               p.min_blocks_per_split, G, plan_slabs, p, *plan);
         else
             hipLaunchKernelGGL(tree_attention_plan_kernel<false>, grid, block, 0, stream, kv_len, n_nodes, kv_start, p.nslot,
-                               p.min_tiles_per_split, G, plan_slabs, p, *plan);
+                               p.min_blocks_per_split, G, plan_slabs, p, *plan);
     } else {
         const dim3 grid(Hkv, own_slabs, sh.batch ? 1 : B);
         if (sh.batch)
             hipLaunchKernelGGL(tree_attention_bf16_kernel<true>, grid, block, 0, stream, kv_len, n_nodes, first_node, kv_start, p.nslot,
-                               p.min_tiles_per_split, G, p);
+                               p.min_blocks_per_split, G, p);
         else
             hipLaunchKernelGGL(tree_attention_bf16_kernel<false>, grid, block, 0, stream, kv_len, n_nodes, first_node, kv_start, p.nslot,
-                               p.min_tiles_per_split, G, p);
+                               p.min_blocks_per_split, G, p);
     }
     if (hipGetLastError() != hipSuccess) return SAGE_LAUNCH_FAILED;
     const int mrows = sh.batch ? MERGE_ROWS_BATCH : MERGE_ROWS_SINGLE;
@@ -920,22 +1100,22 @@ int tree_attention_bf16(const void* Q, const void* Kc, const void* Vc, const voi
     // memory: up to 64 splits in one (41 splits of 7 to 21 rows x 4 KV heads: 4.6 -> 4.1 us).
     if (sh.batch) {
         if (most <= 8) hipLaunchKernelGGL((tree_attention_merge_kernel<8, true, MERGE_ROWS_BATCH>), mgrid, mblock, 0, stream, kv_len, n_nodes, p.nslot,
-                               p.min_tiles_per_split, G, p.merge_phases, p);
+                               p.min_blocks_per_split, G, p.merge_phases, p);
         else if (most <= 16) hipLaunchKernelGGL((tree_attention_merge_kernel<16, true, MERGE_ROWS_BATCH>), mgrid, mblock, 0, stream, kv_len, n_nodes, p.nslot,
-                               p.min_tiles_per_split, G, p.merge_phases, p);
+                               p.min_blocks_per_split, G, p.merge_phases, p);
         else hipLaunchKernelGGL((tree_attention_merge_kernel<32, true, MERGE_ROWS_BATCH>), mgrid, mblock, 0, stream, kv_len, n_nodes, p.nslot,
-                               p.min_tiles_per_split, G, p.merge_phases, p);
+                               p.min_blocks_per_split, G, p.merge_phases, p);
     } else {
         if (most <= 8) hipLaunchKernelGGL((tree_attention_merge_kernel<8, false, MERGE_ROWS_SINGLE>), mgrid, mblock, 0, stream, kv_len, n_nodes, p.nslot,
-                               p.min_tiles_per_split, G, p.merge_phases, p);
+                               p.min_blocks_per_split, G, p.merge_phases, p);
         else if (most <= 16) hipLaunchKernelGGL((tree_attention_merge_kernel<16, false, MERGE_ROWS_SINGLE>), mgrid, mblock, 0, stream, kv_len, n_nodes, p.nslot,
-                               p.min_tiles_per_split, G, p.merge_phases, p);
+                               p.min_blocks_per_split, G, p.merge_phases, p);
         else if (most <= 32) hipLaunchKernelGGL((tree_attention_merge_kernel<32, false, MERGE_ROWS_SINGLE>), mgrid, mblock, 0, stream, kv_len, n_nodes, p.nslot,
-                               p.min_tiles_per_split, G, p.merge_phases, p);
+                               p.min_blocks_per_split, G, p.merge_phases, p);
         else if (most <= 48) hipLaunchKernelGGL((tree_attention_merge_kernel<48, false, MERGE_ROWS_SINGLE>), mgrid, mblock, 0, stream, kv_len, n_nodes, p.nslot,
-                               p.min_tiles_per_split, G, p.merge_phases, p);
+                               p.min_blocks_per_split, G, p.merge_phases, p);
         else hipLaunchKernelGGL((tree_attention_merge_kernel<64, false, MERGE_ROWS_SINGLE>), mgrid, mblock, 0, stream, kv_len, n_nodes, p.nslot,
-                               p.min_tiles_per_split, G, p.merge_phases, p);
+                               p.min_blocks_per_split, G, p.merge_phases, p);
     }
     return launch_status();
 }

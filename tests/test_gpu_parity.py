@@ -409,6 +409,26 @@ def test_attention_bf16_split_counts(gu, tiles):
     run_attention_case(gu, 4000 + tiles, "bf16", 1, 4, 2, 128, [64 * (tiles - 1) - 3], sizes=[3])
 
 
+@pytest.mark.parametrize("nodes", [4, 16, 17, 32, 33])
+@pytest.mark.parametrize("blocks,tail", [(1, 0), (1, 31), (2, 1), (3, 16), (4, 0), (5, 31), (7, 1)])
+def test_attention_bf16_pass_lengths(gu, nodes, blocks, tail):
+    """One sequence, many KV heads and so few splits: passes of `blocks` 32-token blocks, of which the cache's last holds
+    32 - tail tokens, at the row counts between one and two column tiles per wave and between one and two groups.  Half of the
+    lengths with scores that grow along the cache, so that the reference maximum has to move in every block."""
+    Hq, Hkv = 512, 64                                     # four splits of a KV head (two where there are two groups)
+    splits, tree = (2 if nodes > 32 else 4), (2 if nodes > 32 else 1)
+    L = max(32 * (splits * blocks - tree) - tail, 0)
+    inp = wl.attention_inputs(5000 + nodes + blocks, 1, Hq, Hkv, 128, [L], "bf16", pad_tokens=2)
+    if blocks & 1 and L:
+        ramp = np.linspace(0.5, 24.0, L, dtype=np.float32)[:, None, None]
+        inp["Kc"][:L] = wl.f32_to_bf16_bits(wl.bf16_bits_to_f32(inp["Kc"][:L]) * ramp)
+    mask, nn = tree_batch(wl.rng(blocks), 1, [nodes])
+    ref = oracle.tree_attention(inp["Q"], inp["Kc"], inp["Vc"], inp["Kt"], inp["Vt"], inp["kv_start"], inp["kv_len"],
+                                inp["kv_token_stride"], inp["kv_head_stride"], mask, nn, Hq, Hkv, 128)
+    got, _ = gu.gpu_tree_attention(inp, mask, nn, Hq, Hkv, 128, fill=12345.0)
+    gu.assert_attention_close(got, ref, nn, TOL["bf16"])
+
+
 def test_attention_is_deterministic(gu):
     inp = wl.attention_inputs(3, 1, 64, 8, 128, [2000], "bf16")
     mask, nn = tree_batch(wl.rng(3), 1, [40])
