@@ -2,6 +2,8 @@
 // the kernels that fold it into the step that consumes its result (fused_steps.hip): wave-wide reductions, the per-row
 // merge of slice statistics and candidate lists, Eq. 7-9 on the winners.
 #pragma once
+#include <type_traits>
+
 #include "topk_common.h"
 
 namespace sage {
@@ -199,8 +201,10 @@ __device__ __forceinline__ uint32_t wave_pick(const uint32_t (&code)[N], const b
 // were most of it: 2.5 us at k = 10, 26 us at k = 64.  Instead: (1) wave 0 finds a value that at least k candidates reach
 // and not many more: the p-th largest of the lists' entries at depth d, p (d + 1) >= k, d chosen so that p is a small
 // part of the lists; (2) the entries that reach it are gathered from the lists whose heads do; (3) a thread per candidate
-// counts the candidates above it, which is its place.  Rows with too many candidates (long runs of equal values) take the
-// k rounds, over the k lists with the largest heads, a lane per list.
+// counts the candidates above it, which is its place.  A row of few large logits over a level floor has a threshold that
+// thousands of entries equal: when there are too many candidates, those strictly above the threshold are gathered instead,
+// and do if they are k (64 planted logits over a floor, k = 64, whole call: 35.5 us by the rounds that it took before, 18.4
+// now).  What is left takes the k rounds, over the k lists with the largest heads, a lane per list.
 template <int OWN, int WG_THREADS = MERGE_THREADS, class Shared>
 __device__ __forceinline__ bool merge_row(int row, int k, int nunits, const UnitStats* __restrict__ stats,
                                           const uint64_t* __restrict__ keys, Shared& sh, float* __restrict__ entropy,
@@ -284,34 +288,64 @@ __device__ __forceinline__ bool merge_row(int row, int k, int nunits, const Unit
     // eight more while some list's last one fetched still is a candidate (lists are sorted)
     const int nl = pk.nlists <= PICK_LISTS ? pk.nlists : 0;
     const uint32_t floor = pk.floor;
-    auto gather = [&](int j0, int width) __attribute__((always_inline)) {   // entries j0 .. j0 + width - 1 of every picked list; width <= STAGED_MAX_K
+    // entries j0 .. j0 + width - 1 of every picked list, BATCH of them per thread requested before the first is looked at;
+    // width <= STAGED_MAX_K; returns whether a list's last one fetched was a candidate
+    auto gather = [&](auto batch, int j0, int width, bool strictly) __attribute__((always_inline)) {
+        constexpr int BATCH = decltype(batch)::value;
         const int entries = nl * width;
         const unsigned inv = reciprocal(width);
         bool more = false;
-        for (int at0 = 0; at0 < entries; at0 += THREADS) {
-            const int at = at0 + tid;
-            const int r = static_cast<int>((static_cast<unsigned>(at) * inv) >> 16), j = j0 + at - r * width;
-            const uint64_t e = at < entries && j < k ? entry(pk.lists[r], j) : 0;
-            const bool cand = e != 0 && static_cast<uint32_t>(e >> 32) >= floor;
-            more = more || (cand && at - r * width == width - 1);
-            const uint64_t b = __ballot(cand);
-            if (b != 0) {
-                int base = 0;
-                if (lane == 0) base = atomicAdd(&pk.ncand, static_cast<int>(__builtin_popcountll(b)));
-                base = __builtin_amdgcn_readfirstlane(base);
-                const int to = base + static_cast<int>(__builtin_amdgcn_mbcnt_hi(static_cast<uint32_t>(b >> 32), __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(b), 0u)));
-                if (cand && to < PICK_CANDS) pk.cand[to] = e;
+        for (int at0 = 0; at0 < entries; at0 += BATCH * THREADS) {
+            uint64_t e[BATCH];
+            bool last[BATCH];
+#pragma unroll
+            for (int u = 0; u < BATCH; ++u) {
+                const int at = at0 + u * THREADS + tid;
+                const int r = static_cast<int>((static_cast<unsigned>(at) * inv) >> 16), j = j0 + at - r * width;
+                e[u] = at < entries && j < k ? entry(pk.lists[r], j) : 0;
+                last[u] = at - r * width == width - 1;
+            }
+#pragma unroll
+            for (int u = 0; u < BATCH; ++u) {
+                const uint32_t code = static_cast<uint32_t>(e[u] >> 32);
+                const bool cand = e[u] != 0 && (strictly ? code > floor : code >= floor);
+                more = more || (cand && last[u]);
+                const uint64_t b = __ballot(cand);
+                if (b != 0) {
+                    int base = 0;
+                    if (lane == 0) base = atomicAdd(&pk.ncand, static_cast<int>(__builtin_popcountll(b)));
+                    base = __builtin_amdgcn_readfirstlane(base);
+                    const int to = base + static_cast<int>(__builtin_amdgcn_mbcnt_hi(static_cast<uint32_t>(b >> 32), __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(b), 0u)));
+                    if (cand && to < PICK_CANDS) pk.cand[to] = e[u];
+                }
             }
         }
         return more;
     };
-    if (in_lds) {
-        gather(0, k);
+    // all candidates of the picked lists; returns how many (or that they are too many), after a barrier
+    auto gather_all = [&](bool strictly) __attribute__((always_inline)) {
+        if (in_lds) {
+            gather(std::integral_constant<int, 1>{}, 0, k, strictly);
+            __syncthreads();
+            return pk.ncand;
+        }
+        for (int j0 = 0;; j0 += 8) {
+            const bool more = __syncthreads_or(gather(std::integral_constant<int, 4>{}, j0, 8, strictly) ? 1 : 0) != 0;
+            const int n = pk.ncand;
+            if (!more || j0 + 8 >= k || n > PICK_CANDS) return n;
+            __syncthreads();                         // everyone has read the count before the next round adds to it
+        }
+    };
+    int nc = gather_all(false);
+    if (pk.nlists > PICK_LISTS) {                    // (uniform, like what follows)
+        nc = PICK_CANDS + 1;
+    } else if (nc > PICK_CANDS) {
         __syncthreads();
-    } else {
-        for (int j0 = 0; __syncthreads_or(gather(j0, 8) ? 1 : 0) != 0 && j0 + 8 < k; j0 += 8) {}
+        if (tid == 0) pk.ncand = 0;
+        __syncthreads();
+        nc = gather_all(true);
+        if (nc < k) nc = PICK_CANDS + 1;
     }
-    int nc = pk.nlists <= PICK_LISTS ? pk.ncand : PICK_CANDS + 1;
     if (nc <= PICK_CANDS) {                          // (uniform)
         if (nc > 2 * SAGE_MAX_TOPK) {                // wave 0 picks again among them, k or a few more
             if (tid < 64) {

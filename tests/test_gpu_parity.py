@@ -103,6 +103,10 @@ def selection_rows(kind, vocab, dtype):
     elif kind == "one slice":                            # all winners in one stretch of 1024 logits, and in its last ones
         x[0, 1024:2048] += 50.0
         x[1, vocab - 70:] += 50.0
+    elif kind == "planted":                              # 64 (row 1: 20) distinct large logits over a level floor of equal ones
+        x[:] = -60.0
+        for r, many in enumerate((64, 20)):
+            x[r, g.permutation(vocab)[:many]] = -0.5 * np.arange(many)
     elif kind == "few finite":                           # fewer finite logits than k
         x[:] = -np.inf
         x[0, [5, vocab // 2, vocab - 1]] = [1.0, 2.0, 2.0]
@@ -115,6 +119,7 @@ def selection_rows(kind, vocab, dtype):
 @pytest.mark.parametrize("kind,vocab,k", [
     ("equal", 3000, 64), ("equal", 300000, 16), ("levels", 40000, 64), ("levels", 152064, 10), ("one slice", 5000, 64),
     ("one slice", 152064, 16), ("gaussian", 40000, 64), ("gaussian", 70001, 40), ("gaussian", 1025, 17), ("gaussian", 2049, 2),
+    ("planted", 152064, 64), ("planted", 152064, 16), ("planted", 5000, 33), ("planted", 3000, 21),
     ("few finite", 3000, 10), ("few finite", 9000, 40)])
 def test_topk_selection_edges(gu, dtype, kind, vocab, k):
     """Ties at the threshold, concentrated winners, a last slice of one logit, fewer candidates than k: indices exact."""
