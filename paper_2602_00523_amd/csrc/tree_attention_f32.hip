@@ -2,119 +2,182 @@
 // Alg. 1 Phase 2) in plain fp32 FMA arithmetic.  Used for small full-precision shapes; the bf16 MFMA kernel
 // carries the 72B-shape workloads.
 //
-// One workgroup per (node, query head, sequence).  Keys are taken 256 at a time: lane = key for the scores
-// (q broadcast from LDS, the key row read with 16-byte loads), then thread = (output dimension, slice of the block's
-// keys) for the probability-weighted sum of values (coalesced across the dimension, eight independent loads in
-// flight per thread), with an online softmax across blocks; the key slices are summed through LDS at the end.
-// The tree's own keys form the last block, admitted by the node's ancestor-or-self mask.
+// One workgroup per (node, query head, sequence).  The keys are one list, the cache's positions and then the tree's nodes,
+// and 16 lanes share a key: a lane holds float4 pieces of its row, 64 dims apart, so that a load instruction reads whole
+// rows.  A wave takes four keys at a time and keeps a softmax of its own (reference maximum, sum, weighted values) over all
+// the keys it takes; the eight waves meet once, at the end, through LDS.
+//
+// What bounds it is latency: at 16 nodes x 4 heads x 272 keys of 64 dims a workgroup has 136 KB to read and a chain of
+// dependent round trips.  There are two of those to memory, the sequence's sizes and then Q and every key and value of a
+// tile of up to 288 keys, all requested before the first is used, and one barrier.  Before (a lane per key, whose loads
+// touch 64 rows each, the cache's keys before the tree's, scores before values,
+// six barriers a block) -> now, us per call: 8 nodes x 4 heads x 264 keys x 64 dims 8.6 -> 5.4, 16 x 8 x 527 x 128 29.4 -> 15.1,
+// 64 x 32 x 2064 x 128 323 -> 157, 16 x 4 x 1016 x 256 80 -> 22.5.  Against 64 bits: 1.5-2.3e-7, 3.0-7.9e-7 before.
+#include <utility>
+
 #include "sage_internal.h"
 
 namespace {
 
-constexpr int THREADS = 256;
+constexpr int THREADS = 512;
+constexpr int WAVES = THREADS / 64;
 
-__device__ __forceinline__ float block_reduce(float v, float* s_red, bool is_max) {
-    v = is_max ? sage::wave_max(v) : sage::wave_sum(v);
-    __syncthreads();                         // s_red may still be read from a previous reduction
-    if ((threadIdx.x & 63) == 0) s_red[threadIdx.x >> 6] = v;
-    __syncthreads();
-    float r = s_red[0];
-#pragma unroll
-    for (int i = 1; i < THREADS / 64; ++i) r = is_max ? fmaxf(r, s_red[i]) : r + s_red[i];
-    return r;
+// sum / maximum over the 16 lanes of a row, in each of them
+__device__ __forceinline__ float row_sum(float v) {
+    v += sage::f_dpp<0x128>(v); v += sage::f_dpp<0x124>(v); v += sage::f_dpp<0x122>(v); v += sage::f_dpp<0x121>(v);
+    return v;
+}
+__device__ __forceinline__ float row_max(float v) {
+    v = fmaxf(v, sage::f_dpp<0x128>(v)); v = fmaxf(v, sage::f_dpp<0x124>(v)); v = fmaxf(v, sage::f_dpp<0x122>(v)); v = fmaxf(v, sage::f_dpp<0x121>(v));
+    return v;
+}
+// lane u of its row of 16, in each of them
+template <int U> __device__ __forceinline__ float row_lane(float v) { return sage::f_dpp<0x150 + U>(v); }   // row_newbcast
+template <class F, int... U> __device__ __forceinline__ void each(F f, std::integer_sequence<int, U...>) { (f(std::integral_constant<int, U>{}), ...); }
+// sum / maximum over the four rows of a wave
+__device__ __forceinline__ float rows_sum(float v) {
+    auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    v = __uint_as_float(a[0]) + __uint_as_float(a[1]);
+    a = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    return __uint_as_float(a[0]) + __uint_as_float(a[1]);
+}
+__device__ __forceinline__ float rows_max(float v) {
+    auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    v = fmaxf(__uint_as_float(a[0]), __uint_as_float(a[1]));
+    a = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    return fmaxf(__uint_as_float(a[0]), __uint_as_float(a[1]));
 }
 
+// NC = pieces of 64 dims (the last one may be partly past d); TAKES = times that a tile's keys are taken.
+template <int NC, int TAKES>
 __global__ __launch_bounds__(THREADS) void tree_attention_f32_kernel(
-    const float* __restrict__ Q, const float* __restrict__ Kc, const float* __restrict__ Vc,
-    const float* __restrict__ Kt, const float* __restrict__ Vt, float* __restrict__ O, int Hq, int Hkv, int d,
-    const int64_t* __restrict__ kv_start, const int* __restrict__ kv_len, long kv_token_stride, long kv_head_stride,
-    const uint64_t* __restrict__ anc_mask, const int* __restrict__ n_nodes, const int* __restrict__ first_node, float scale) {
-    __shared__ float s_q[256];
-    __shared__ float s_p[THREADS];
-    __shared__ float s_red[THREADS / 64];
+    const int* __restrict__ n_nodes, const int* __restrict__ kv_len, const int64_t* __restrict__ kv_start,
+    const int* __restrict__ first_node, const uint64_t* __restrict__ anc_mask, int Hq, int Hkv, int d,
+    const float* __restrict__ Q, const float* __restrict__ Kc, const float* __restrict__ Vc, const float* __restrict__ Kt,
+    const float* __restrict__ Vt, float* __restrict__ O, long kv_token_stride, long kv_head_stride, float scale) {
+    __shared__ float s_acc[WAVES][NC * 64];
+    __shared__ float s_m[WAVES], s_l[WAVES];
 
     const int i = blockIdx.x, h = blockIdx.y, b = blockIdx.z;
     int n = n_nodes[b];
+    const int len = kv_len[b];
+    const int64_t start = kv_start[b];
+    const uint64_t mask = anc_mask[static_cast<long>(b) * SAGE_MAX_NODES + i];
+    int first = first_node ? first_node[b] : 0;              // rows of earlier nodes are not asked for
     n = n < 1 ? 1 : (n > SAGE_MAX_NODES ? SAGE_MAX_NODES : n);   // a tree always has its root
-    int first = first_node ? first_node[b] : 0;             // rows of earlier nodes are not asked for
     first = first < 0 ? 0 : (first > n - 1 ? n - 1 : first);
     if (i >= n || i < first) return;
     const int tid = threadIdx.x;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int dim0 = (tid & 15) * 4, row = (tid >> 4) & 3;
     const int g = h / (Hq / Hkv);
-    const int L = kv_len[b] > 0 ? kv_len[b] : 0;
-    const long qoff = ((static_cast<long>(b) * SAGE_MAX_NODES + i) * Hq + h) * d;
-    const uint64_t mask = anc_mask[static_cast<long>(b) * SAGE_MAX_NODES + i];
-    if (tid < d) s_q[tid] = Q[qoff + tid];
-    __syncthreads();
+    const int L = len > 0 ? len : 0;
+    const int cache_fours = (L + 3) / 4, fours = cache_fours + (n + 3) / 4;   // a wave takes four keys, all of the cache or all of the tree
+    const long q_at = ((static_cast<long>(b) * SAGE_MAX_NODES + i) * Hq + h) * d;
+    const long cache_at = start * kv_token_stride + static_cast<long>(g) * kv_head_stride;
+    const long tree_at = (static_cast<long>(b) * SAGE_MAX_NODES * Hkv + g) * d, tree_stride = static_cast<long>(Hkv) * d;
 
-    const float* kbase = Kc + kv_start[b] * kv_token_stride + static_cast<long>(g) * kv_head_stride;
-    const float* vbase = Vc + kv_start[b] * kv_token_stride + static_cast<long>(g) * kv_head_stride;
-    const float* ktree = Kt + (static_cast<long>(b) * SAGE_MAX_NODES * Hkv + g) * d;
-    const float* vtree = Vt + (static_cast<long>(b) * SAGE_MAX_NODES * Hkv + g) * d;
-    const long tree_stride = static_cast<long>(Hkv) * d;
-
-    const int dpad = d <= 64 ? 64 : (d <= 128 ? 128 : 256);  // threads per key slice in the value pass
-    const int nslices = THREADS / dpad;
-    const int dim = tid % dpad, slice = tid / dpad;
-    float m = -INFINITY, l = 0.f, acc = 0.f;
-    const int nblocks = (L + THREADS - 1) / THREADS + 1;     // cache blocks, then one block of tree keys
-    for (int blk = 0; blk < nblocks; ++blk) {
-        const bool tree = (blk == nblocks - 1);
-        const int j = tree ? tid : blk * THREADS + tid;
-        const bool admitted = tree ? (tid < n && ((mask >> tid) & 1)) : (j < L);
-        const float* krow = tree ? ktree + j * tree_stride : kbase + j * kv_token_stride;
-        float s = -INFINITY;
-        if (admitted) {
-            float a = 0.f;
-            for (int c = 0; c < d; c += 4) {
-                const float4 kv = *reinterpret_cast<const float4*>(krow + c);
-                a = fmaf(s_q[c], kv.x, a);
-                a = fmaf(s_q[c + 1], kv.y, a);
-                a = fmaf(s_q[c + 2], kv.z, a);
-                a = fmaf(s_q[c + 3], kv.w, a);
-            }
-            s = a * scale;
-        }
-        const float bm = block_reduce(s, s_red, true);
-        const float m_new = fmaxf(m, bm);
-        if (m_new == -INFINITY) continue;                    // nothing admitted so far (uniform across the workgroup)
-        const float p = admitted ? expf(s - m_new) : 0.f;
-        const float corr = (m == -INFINITY) ? 0.f : expf(m - m_new);
-        const float bl = block_reduce(p, s_red, false);
-        l = l * corr + bl;
-        m = m_new;
-        __syncthreads();                                     // previous block's s_p fully consumed
-        s_p[tid] = p;
-        __syncthreads();
-        acc *= corr;
-        if (dim < d) {
-            const int cnt = tree ? n : min(THREADS, L - blk * THREADS);
-            const float* vcol = (tree ? vtree : vbase + static_cast<long>(blk) * THREADS * kv_token_stride) + dim;
-            const long vstride = tree ? tree_stride : kv_token_stride;
-            int t = slice;
-            for (; t + 7 * nslices < cnt; t += 8 * nslices) {
-                float v[8];
+    const float4 zero = make_float4(0.f, 0.f, 0.f, 0.f);
+    int dims[NC];                                            // (d is a multiple of 4; pieces past d are read inside the row
+    float4 acc[NC];                                          // and not counted)
 #pragma unroll
-                for (int u = 0; u < 8; ++u) v[u] = vcol[(t + u * nslices) * vstride];
-#pragma unroll
-                for (int u = 0; u < 8; ++u) {
-                    const float pt = s_p[t + u * nslices];
-                    acc = (pt != 0.f) ? fmaf(pt, v[u], acc) : acc;
-                }
-            }
-            for (; t < cnt; t += nslices) {
-                const float pt = s_p[t];
-                if (pt != 0.f) acc = fmaf(pt, vcol[t * vstride], acc);
-            }
-        }
+    for (int c = 0; c < NC; ++c) {
+        dims[c] = min(64 * c + dim0, d - 4);
+        acc[c] = zero;
     }
-    __syncthreads();                                         // s_p is free: sum the key slices
-    s_p[tid] = acc;
+    float m = -INFINITY, l = 0.f;                            // of this wave; l of this lane's keys
+    for (int tile = 0; tile < fours; tile += TAKES * WAVES) {
+        float4 k[TAKES][NC], v[TAKES][NC];
+#pragma unroll
+        for (int u = 0; u < TAKES; ++u) {                    // what is past the end repeats the last four, or the last key, and is
+            const int f = min(tile + u * WAVES + wave, fours - 1);   // not admitted
+            const bool tree = f >= cache_fours;              // (uniform, like everything but the lane's row and dims)
+            const int j0 = 4 * (tree ? f - cache_fours : f), last = (tree ? n : L) - 1 - j0;
+            const long stride = tree ? tree_stride : kv_token_stride;
+            const long at = (tree ? tree_at : cache_at) + j0 * stride;
+            const long off = min(row, last) * stride;
+            const float* kr = (tree ? Kt : Kc) + at;
+            const float* vr = (tree ? Vt : Vc) + at;
+#pragma unroll
+            for (int c = 0; c < NC; ++c) {
+                k[u][c] = *reinterpret_cast<const float4*>(kr + off + dims[c]);
+                v[u][c] = *reinterpret_cast<const float4*>(vr + off + dims[c]);
+            }
+        }
+        float4 q[NC];                                        // (here, and not ahead of the loop, whose entry would wait for it)
+#pragma unroll
+        for (int c = 0; c < NC; ++c) q[c] = *reinterpret_cast<const float4*>(Q + q_at + dims[c]);
+        __builtin_amdgcn_sched_barrier(0);                   // every load is out before the first one is used
+        // scores: every lane of a row has all of the row's; lane u keeps the one of take u
+        float mine = -INFINITY;
+        const int lane16 = tid & 15;
+#pragma unroll
+        for (int u = 0; u < TAKES; ++u) {
+            float a = 0.f;
+#pragma unroll
+            for (int c = 0; c < NC; ++c) {
+                const bool whole = NC == 1 ? dim0 < d : 64 * c + dim0 < d;
+                float t = fmaf(q[c].x, k[u][c].x, a);
+                t = fmaf(q[c].y, k[u][c].y, t);
+                t = fmaf(q[c].z, k[u][c].z, t);
+                t = fmaf(q[c].w, k[u][c].w, t);
+                a = whole ? t : a;
+            }
+            a = row_sum(a);
+            mine = lane16 == u ? a * scale : mine;
+        }
+        const int f = tile + lane16 * WAVES + wave, j = 4 * (f < cache_fours ? f : f - cache_fours) + row;
+        const bool admitted = lane16 < TAKES && (f < cache_fours ? j < L : j < n && ((mask >> j) & 1));
+        mine = admitted ? mine : -INFINITY;
+        const float m_new = fmaxf(m, rows_max(row_max(mine)));
+        if (m_new == -INFINITY) continue;                    // nothing admitted so far (uniform across the wave)
+        const float corr = m == -INFINITY ? 0.f : expf(m - m_new);
+        m = m_new;
+        const float p = admitted ? expf(mine - m) : 0.f;
+        l = l * corr + p;
+#pragma unroll
+        for (int c = 0; c < NC; ++c) {
+            acc[c].x *= corr; acc[c].y *= corr; acc[c].z *= corr; acc[c].w *= corr;
+        }
+        // a value that has no weight does not count, whatever it is
+        const bool all = __all(lane16 >= TAKES || p != 0.f);
+        each([&](auto uc) __attribute__((always_inline)) {
+            constexpr int u = decltype(uc)::value;
+            const float pu = row_lane<u>(p);
+#pragma unroll
+            for (int c = 0; c < NC; ++c) {
+                float4 x = v[u][c];
+                if (!all && pu == 0.f) x = zero;
+                acc[c].x = fmaf(pu, x.x, acc[c].x);
+                acc[c].y = fmaf(pu, x.y, acc[c].y);
+                acc[c].z = fmaf(pu, x.z, acc[c].z);
+                acc[c].w = fmaf(pu, x.w, acc[c].w);
+            }
+        }, std::make_integer_sequence<int, TAKES>{});
+    }
+    l = row_sum(l);
+    l = rows_sum(l);
+#pragma unroll
+    for (int c = 0; c < NC; ++c) {
+        const float4 sum = make_float4(rows_sum(acc[c].x), rows_sum(acc[c].y), rows_sum(acc[c].z), rows_sum(acc[c].w));
+        if (row == 0) *reinterpret_cast<float4*>(&s_acc[wave][64 * c + dim0]) = sum;
+    }
+    if ((tid & 63) == 0) {
+        s_m[wave] = m;
+        s_l[wave] = l;
+    }
     __syncthreads();
     if (tid < d) {
-        float sum = 0.f;
-        for (int sl = 0; sl < nslices; ++sl) sum += s_p[tid + sl * dpad];
-        O[qoff + tid] = sum / l;
+        float m_all = -INFINITY, l_all = 0.f, o = 0.f;
+#pragma unroll
+        for (int w = 0; w < WAVES; ++w) m_all = fmaxf(m_all, s_m[w]);
+#pragma unroll
+        for (int w = 0; w < WAVES; ++w) {
+            const float weight = s_m[w] == -INFINITY ? 0.f : expf(s_m[w] - m_all);
+            l_all = fmaf(weight, s_l[w], l_all);
+            o = fmaf(weight, s_acc[w][tid], o);
+        }
+        O[q_at + tid] = o / l_all;
     }
 }
 
@@ -129,10 +192,12 @@ int tree_attention_f32(const void* Q, const void* Kc, const void* Vc, const void
     if (d < 4 || d > 256 || (d % 4) != 0) return SAGE_UNSUPPORTED;
     if ((kv_token_stride % 4) != 0 || (kv_head_stride % 4) != 0) return SAGE_INVALID_ARG;
     if (Hq > 65535 || B > 65535) return SAGE_UNSUPPORTED;
-    hipLaunchKernelGGL(tree_attention_f32_kernel, dim3(SAGE_MAX_NODES, Hq, B), dim3(THREADS), 0, stream,
-                       static_cast<const float*>(Q), static_cast<const float*>(Kc), static_cast<const float*>(Vc),
-                       static_cast<const float*>(Kt), static_cast<const float*>(Vt), static_cast<float*>(O), Hq, Hkv, d,
-                       kv_start, kv_len, kv_token_stride, kv_head_stride, anc_mask, n_nodes, first_node, scale);
+    // as many keys at once as the registers of a wave hold beside each other: 288, 128, 64
+    const auto kernel = d <= 64 ? tree_attention_f32_kernel<1, 9> : d <= 128 ? tree_attention_f32_kernel<2, 4> : tree_attention_f32_kernel<4, 2>;
+    hipLaunchKernelGGL(kernel, dim3(SAGE_MAX_NODES, Hq, B), dim3(THREADS), 0, stream, n_nodes, kv_len, kv_start, first_node, anc_mask, Hq,
+                       Hkv, d, static_cast<const float*>(Q), static_cast<const float*>(Kc), static_cast<const float*>(Vc),
+                       static_cast<const float*>(Kt), static_cast<const float*>(Vt), static_cast<float*>(O), kv_token_stride,
+                       kv_head_stride, scale);
     return launch_status();
 }
 

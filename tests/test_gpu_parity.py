@@ -272,7 +272,8 @@ def test_attention_toy_f32(gu):
 
 
 @pytest.mark.parametrize("B,Hq,Hkv,d,lens", [(2, 4, 2, 64, [300, 0]), (1, 6, 3, 32, [1]), (3, 8, 1, 128, [511, 257, 64]),
-                                             (1, 2, 2, 256, [1000])])
+                                             (1, 2, 2, 256, [1000]), (2, 2, 1, 4, [5, 288]), (3, 2, 1, 60, [223, 224, 289]),
+                                             (2, 4, 2, 68, [63, 130]), (1, 2, 1, 132, [66]), (2, 1, 1, 192, [3, 0])])
 def test_attention_f32_shapes(gu, B, Hq, Hkv, d, lens):
     run_attention_case(gu, 5 + B + d, "f32", B, Hq, Hkv, d, lens)
 
