@@ -329,11 +329,16 @@ __device__ __forceinline__ bool merge_row(int row, int k, int nunits, const Unit
             __syncthreads();
             return pk.ncand;
         }
+        const bool many = nl * 8 > THREADS;          // more than an entry per thread (of few lists one round trip is enough)
         for (int j0 = 0;; j0 += 8) {
-            const bool more = __syncthreads_or(gather(std::integral_constant<int, 4>{}, j0, 8, strictly) ? 1 : 0) != 0;
-            const int n = pk.ncand;
-            if (!more || j0 + 8 >= k || n > PICK_CANDS) return n;
-            __syncthreads();                         // everyone has read the count before the next round adds to it
+            const bool any = many ? gather(std::integral_constant<int, 4>{}, j0, 8, strictly) : gather(std::integral_constant<int, 1>{}, j0, 8, strictly);
+            const bool more = __syncthreads_or(any ? 1 : 0) != 0;
+            if (!more || j0 + 8 >= k) return pk.ncand;
+            if (many) {                              // stop as soon as they are too many
+                const int n = pk.ncand;
+                if (n > PICK_CANDS) return n;
+                __syncthreads();                     // everyone has read the count before the next round adds to it
+            }
         }
     };
     int nc = gather_all(false);

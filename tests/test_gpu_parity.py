@@ -69,6 +69,17 @@ def test_entropy_topk_shapes(gu, vocab, k, dtype):
     check_entropy(gu, buf[:, :vocab], k)
 
 
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("vocab,k", [(64, 64), (700, 8), (1024, 1), (1024, 17), (1025, 1), (2048, 5), (2049, 5), (2050, 64), (4096, 1), (4097, 1)])
+def test_entropy_topk_few_slices(gu, vocab, k, dtype):
+    """Vocabularies up to and just past what one launch takes, with groups of which only some rows count."""
+    rows, rpg, n_valid = 11, 4, np.array([3, 0, 4], np.int32)
+    z = wl.rng(vocab + k).standard_normal((rows, (vocab + 15) // 16 * 16), dtype=np.float32) * 4.0
+    buf = wl.to_storage(z, dtype)[:, :vocab]
+    check_entropy(gu, buf, k)
+    check_entropy(gu, buf, k, n_valid, rpg)
+
+
 def test_entropy_topk_closed_forms_and_ties(gu):
     V = 152064
     x = np.zeros((4, V), np.float32)
