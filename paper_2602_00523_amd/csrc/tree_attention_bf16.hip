@@ -187,7 +187,7 @@ __device__ __forceinline__ Split make_split(int n_nodes, int first_node, int kv_
 // occupies SEG_COST + blocks positions of one line per KV head (the first SEG_COST stand for the prologue and
 // epilogue a pass costs, about that many block steps); the line of `total` positions is cut into ranges of q, so a
 // workgroup whose range starts several segments gets fewer blocks.  Evaluated identically by both kernels.
-constexpr int SEG_COST = 8;
+constexpr int SEG_COST = 6;
 struct BatchShape {
     int n, first, L, blocks, col_groups, start_lo, start_hi; // per lane (sequence)
     int total, q;                                            // wave-uniform
@@ -981,15 +981,17 @@ namespace sage {
 // Batches of 2..64 sequences: the tile list of all sequences is cut into `nrange` ranges per KV head, about one
 // workgroup per CU in total whatever the lengths turn out to be on the device, and the partial slots of a KV head are one
 // per range plus one per (sequence, column group), the most that range and segment boundaries can produce together.
-// A range is at least MIN_RANGE_TILES positions: as long as CUs are idle, shorter ranges end sooner, until they are about
-// as long as the prologue and epilogue of the pass that a range pays anyway (3 sequences of 301-1999 tokens, four layers
-// and a step's other launches: 101 us at 8, 91.4 at 5, 88.5 at 4, 88.2 at 3 and 2; 2 of 212-613 tokens, six layers: 118,
-// 105, 97, 97).  CAP_RANGE_TILES bounds the ranges, and with them the workspace, by the longest lengths allowed.
+// A range is at least MIN_RANGE_TILES positions, the prologue and epilogue of the pass that it pays anyway: as long as CUs are
+// idle, shorter ranges end sooner until they are about that long.  Attention call, us, at (SEG_COST blocks, MIN_RANGE_TILES) = (8, 4),
+// (6, 3), (5, 2), (4, 2): three sequences of 301-1999 tokens 14.7, 14.3, 14.0, 13.6; two of 212 and 613 13.0, 11.5, 11.7, 12.1; eight of
+// 2205-12133 56.0, 53.4, 54.1, 55.3; six of 500-4000 23.3, 23.5, 22.9, 24.0; twelve of 300-5000 with 30 nodes 58.2, 57.7, 59.1, 59.0.
+// The workspace, of which the size stays, counts CAP_SEGMENT_TILES per segment and CAP_RANGE_TILES per range of the longest
+// lengths allowed.
 constexpr int MAX_BATCH_LANES = 64;      // a lane per sequence in make_batch_shape
 constexpr int TILE = 64;                 // tokens: the unit in which the host counts
-constexpr int MIN_RANGE_TILES = 4;       // 64-token positions of the line, pass cost included
+constexpr int MIN_RANGE_TILES = 3;       // 64-token positions of the line, pass cost included
 constexpr int CAP_RANGE_TILES = 8;
-constexpr int SEG_COST_TILES = SEG_COST * BLK / TILE;
+constexpr int CAP_SEGMENT_TILES = 4;
 struct LaunchShape { int nslot, min_tiles_per_split, nrange; bool batch; };
 LaunchShape attention_bf16_shape(int B, int Hkv, int G, int max_kv_len) {
     const int max_groups = (SAGE_MAX_NODES * G + ROWS_PER_WG - 1) / ROWS_PER_WG;
@@ -1000,7 +1002,7 @@ LaunchShape attention_bf16_shape(int B, int Hkv, int G, int max_kv_len) {
     if (sh.batch) {
         long want = 256 / Hkv;
         if (want < 1) want = 1;
-        const long cap = (static_cast<long>(B) * (tiles + SEG_COST_TILES) * max_groups + CAP_RANGE_TILES - 1) / CAP_RANGE_TILES;
+        const long cap = (static_cast<long>(B) * (tiles + CAP_SEGMENT_TILES) * max_groups + CAP_RANGE_TILES - 1) / CAP_RANGE_TILES;
         if (want > cap) want = cap;
         sh.nrange = static_cast<int>(want);
         sh.min_tiles_per_split = MIN_RANGE_TILES;
