@@ -136,7 +136,13 @@ __global__ __launch_bounds__(THREADS) void slice_kernel(const T* __restrict__ lo
 // Rows in groups of which only the first n_valid[group] count (the target rows of a tree): grid (slices / 4, phases,
 // groups).  A workgroup walks the live rows phase, phase + phases, ... of its group, the next row's loads in flight
 // while the current one is reduced, so rows past n_valid cost no workgroup of their own.
-constexpr int ROW_PHASES = 16;
+// Phases: with one or two groups every live row may have its workgroups at once (64 live rows of 152064 in one group, first
+// pass 8.4 -> 6.6 us, 40 in each of two 8.9 -> 7.9; 12 rows 3.1 either way).  With more groups 16 of them fill the chip, and the
+// workgroups of dead rows that more would add show (8 x 12 rows 8.5 us at 16, 9.1 at 32, 9.7 at 64).
+inline int row_phases(int groups, int rows_per_group) {
+    const int phases = groups == 1 ? 64 : groups == 2 ? 32 : 16;
+    return rows_per_group < phases ? rows_per_group : phases;
+}
 template <typename T>
 __device__ __forceinline__ void slice_rows_block(const T* __restrict__ logits, int vocab, long row_stride,
                                                  const int* __restrict__ n_valid, int rows_per_group, int rows, int nunits,
@@ -690,7 +696,7 @@ static int run_first_pass(const void* logits, int dtype, int rows, int vocab, lo
                                vocab, row_stride, nunits, stats, keys);
     } else if (k == 1) {                             // grouped rows: workgroups walk the live rows of their group
         const int groups = (rows + rows_per_group - 1) / rows_per_group;
-        const dim3 grid((nunits + WAVES - 1) / WAVES, rows_per_group < ROW_PHASES ? rows_per_group : ROW_PHASES, groups);
+        const dim3 grid((nunits + WAVES - 1) / WAVES, row_phases(groups, rows_per_group), groups);
         if (dtype == SAGE_F32)
             hipLaunchKernelGGL(slice_rows_kernel<float>, grid, dim3(THREADS), 0, s, static_cast<const float*>(logits), vocab,
                                row_stride, n_valid, rows_per_group, rows, nunits, stats, keys);
@@ -775,7 +781,7 @@ extern "C" int sage_entropy_topk_slices_pair(const void* logits_a, int rows_a, l
     b.stats = static_cast<UnitStats*>(workspace_b);
     b.keys = reinterpret_cast<uint64_t*>(static_cast<char*>(workspace_b) + stats_bytes(rows_b, vocab));
     const int groups = (rows_a + rows_per_group_a - 1) / rows_per_group_a;
-    const int gx = (nunits + WAVES - 1) / WAVES, gy = rows_per_group_a < ROW_PHASES ? rows_per_group_a : ROW_PHASES;
+    const int gx = (nunits + WAVES - 1) / WAVES, gy = row_phases(groups, rows_per_group_a);
     const long blocks_b = static_cast<long>(nunits) * rows_b;
     const long slabs_b = (blocks_b + static_cast<long>(gx) * gy - 1) / (static_cast<long>(gx) * gy);
     if (slabs_b + groups > 65535) return SAGE_UNSUPPORTED;
