@@ -155,6 +155,7 @@ struct Params {
     long kv_token_stride, kv_head_stride;
     int B, Hq, Hkv, G, nslot, min_blocks_per_split;
     int nrange;                          // batched launches: ranges (workgroups) per KV head
+    int inv_G;                           // 65536 / G rounded up: (m * inv_G) >> 16 == m / G for the rows of a KV head
     int merge_phases;                    // merge workgroups per (sequence, KV head)
     float scale_log2e;                   // softmax scale times log2(e): probabilities are exp2 of scaled differences
 };
@@ -162,9 +163,26 @@ struct Params {
 // blocks of the cache and of the tree's own keys
 __device__ __forceinline__ int blocks_of(int tokens) { return (tokens + BLK - 1) / BLK; }
 
+// The sizes go through a few divisions before a kernel can request anything.  A general one is some 25 dependent
+// instructions, and there were five of them in the attention kernel's way to its first load and four in the merge's (whole
+// call of 3 new rows over 41 splits 9.3 -> 8.85 us, of 12 nodes over 4096 positions 12.7 -> 12.35, with the merge's first_node
+// and reciprocal brought by the host).
+// x / y for 0 <= x, 1 <= y: below 2^21, x + 1/2 over y is at least 1/2 / y away from an integer, and two roundings and a
+// reciprocal of one ulp move it by less than (x + 1/2) / y * 2^-22.
+__device__ __forceinline__ int div_floor(int x, int y) {
+    if (x < (1 << 21))                                       // (uniform, and what there is: 67 million positions)
+        return __builtin_amdgcn_readfirstlane(static_cast<int>((static_cast<float>(x) + 0.5f) * __builtin_amdgcn_rcpf(static_cast<float>(y))));
+    return x / y;
+}
+__device__ __forceinline__ int div_ceil(int x, int y) { return div_floor(x + y - 1, y); }
+// x / groups for x <= 256 and up to four column groups
+__device__ __forceinline__ int per_group(int x, int groups) {
+    return groups == 1 ? x : groups == 2 ? x >> 1 : groups == 3 ? (x * 171) >> 9 : x >> 2;
+}
+
 // How one (sequence, KV head) is cut into workgroups; evaluated identically by both kernels.
 struct Split {
-    int n, first, rows, col_groups, blocks, blocks_per_split, nsplit;
+    int n, first, rows, col_groups, blocks, max_split, blocks_per_split, nsplit;
 };
 // the first node whose rows are computed: inside [0, n), so that a call always has a row
 __device__ __forceinline__ int clamp_first(int first, int n) { return first < 0 ? 0 : (first > n - 1 ? n - 1 : first); }
@@ -176,10 +194,9 @@ __device__ __forceinline__ Split make_split(int n_nodes, int first_node, int kv_
     s.col_groups = (s.rows + ROWS_PER_WG - 1) / ROWS_PER_WG;
     const int L = kv_len > 0 ? kv_len : 0;
     s.blocks = blocks_of(L) + blocks_of(s.n);               // cache blocks, then one or two with the tree's keys
-    int max_split = nslot / s.col_groups;
-    if (max_split < 1) max_split = 1;
-    s.blocks_per_split = max(min_bps, (s.blocks + max_split - 1) / max_split);
-    s.nsplit = (s.blocks + s.blocks_per_split - 1) / s.blocks_per_split;
+    s.max_split = max(1, per_group(nslot, s.col_groups));
+    s.blocks_per_split = max(min_bps, div_ceil(s.blocks, s.max_split));
+    s.nsplit = div_ceil(s.blocks, s.blocks_per_split);
     return s;
 }
 
@@ -209,7 +226,7 @@ __device__ __forceinline__ BatchShape make_batch_shape(const Params& prm, int la
         bs.start_hi = static_cast<int>(st >> 32);
     }
     bs.total = wave_sum_i32((bs.blocks + SEG_COST) * bs.col_groups);   // blocks = 0 in lanes past the batch, so is col_groups
-    bs.q = max(prm.min_blocks_per_split, (bs.total + prm.nrange - 1) / prm.nrange);
+    bs.q = max(prm.min_blocks_per_split, div_ceil(bs.total, prm.nrange));
     return bs;
 }
 
@@ -721,7 +738,7 @@ __device__ __forceinline__ void attention_workgroup(const int* __restrict__ kv_l
     // costs a division
     const int g = blockIdx.x;
     const int id = static_cast<int>(blockIdx.y) - first_slab;   // slabs before first_slab belong to somebody else
-    const int inv_G = (65536 + G_arg - 1) / G_arg;           // (m * inv_G) >> 16 == m / G for the rows of a KV head
+    const int inv_G = prm.inv_G;
 
     auto run_segment = [&](const Segment& v) __attribute__((always_inline)) {
         // every field is wave-uniform; said to the compiler (the batched walk derives them through lane reads), so that
@@ -763,12 +780,12 @@ __device__ __forceinline__ void attention_workgroup(const int* __restrict__ kv_l
         const int L = len_b > 0 ? len_b : 0;
         const Split sp = make_split(n_b, f_b, L, G_arg, nslot_arg, min_bps_arg);
         if (sp.col_groups > nslot_arg) return;              // host guarantees nslot >= the largest group count
-        const int cg = slot % sp.col_groups;
-        const int split = slot / sp.col_groups;
+        const int split = per_group(slot, sp.col_groups);
+        const int cg = slot - split * sp.col_groups;
         if (split >= sp.nsplit) return;
         const int begin = split * sp.blocks_per_split;
         run_segment(Segment{b, g, L, sp.n, sp.first, sp.rows, cg, begin, min(sp.blocks - begin, sp.blocks_per_split), blocks_of(L),
-                            start_b, prm.part + ((static_cast<long>(b) * prm.Hkv + g) * prm.nslot + slot) * PART_SLOT_B});
+                            start_b, prm.part + ((static_cast<long>(b) * prm.Hkv + g) * prm.nslot + cg * sp.max_split + split) * PART_SLOT_B});
     } else {
         const int lane = threadIdx.x & 63;
         const BatchShape bs = make_batch_shape(prm, lane);  // lane b holds sequence b
@@ -870,7 +887,8 @@ constexpr int MERGE_PHASES_BATCH = 32;   // batches: workgroups per (sequence, K
                                          // single sequence gets a wave per possible row (fewer measured no faster)
 template <int MAXS, bool BATCH, int ROWS>
 __global__ __launch_bounds__(64 * ROWS) void tree_attention_merge_kernel(const int* __restrict__ kv_len_arg,
-                                                                         const int* __restrict__ n_nodes_arg, int nslot_arg,
+                                                                         const int* __restrict__ n_nodes_arg,
+                                                                         const int* __restrict__ first_node_arg, int nslot_arg,
                                                                          int min_bps_arg, int G_arg, int phases_arg,
                                                                          const Params prm) {
     static_assert(MAXS <= 64, "one split per lane, one register per split");
@@ -881,16 +899,13 @@ __global__ __launch_bounds__(64 * ROWS) void tree_attention_merge_kernel(const i
     const int g = blockIdx.x;                                // grid = (KV head, phase, sequence), as in the main kernel
     const float c = prm.scale_log2e;
 
-    // one row: `first_row` = the row in the first of its nsplit partials, stride_b = bytes to the next one.  Addresses are
-    // the uniform row pointer plus 32-bit offsets (a launch's partials span far less than 4 GB from any row), which
-    // keeps the address arithmetic of up to 32 loads per lane off the critical path of this latency-bound kernel.
-    auto merge_row = [&](int b, int node, int hg, const unsigned char* first_row, unsigned stride_b, int nsplit_v) __attribute__((always_inline)) {
+    // One row: `first_row` = the row in the first of its nsplit partials, the others one slot after the other.
+    auto merge_row = [&](int b, int node, int hg, const unsigned char* first_row, int nsplit_v) __attribute__((always_inline)) {
         // wave-uniform by construction; said to the compiler, which cannot see it through the lane exchanges of a batch
         const uintptr_t first_v = reinterpret_cast<uintptr_t>(first_row);
         const uintptr_t first =
             (static_cast<uintptr_t>(static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<uint32_t>(first_v >> 32)))) << 32) |
             static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<uint32_t>(first_v)));   // (the builtin returns int)
-        stride_b = __builtin_amdgcn_readfirstlane(stride_b);
         const int nsplit = __builtin_amdgcn_readfirstlane(nsplit_v);
         float2 o = make_float2(0.f, 0.f);
         float m_all = -INFINITY, l_all = 0.f;
@@ -902,10 +917,10 @@ __global__ __launch_bounds__(64 * ROWS) void tree_attention_merge_kernel(const i
             // by the bounds check instead of by memory.  One add and one load instruction per split.
             typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
             const __amdgpu_buffer_rsrc_t rows = __builtin_amdgcn_make_buffer_rsrc(
-                reinterpret_cast<unsigned char*>(first + static_cast<size_t>(s0) * stride_b), 0,
-                static_cast<int>(static_cast<unsigned>(cnt - 1) * stride_b + PART_ROW_B), 0x00020000);
+                reinterpret_cast<unsigned char*>(first + static_cast<size_t>(s0) * PART_SLOT_B), 0,
+                static_cast<int>(static_cast<unsigned>(cnt - 1) * PART_SLOT_B + PART_ROW_B), 0x00020000);
             {
-                const u32x2 pair = __builtin_amdgcn_raw_buffer_load_b64(rows, static_cast<unsigned>(lane) * stride_b + D * 2u, 0, 0);
+                const u32x2 pair = __builtin_amdgcn_raw_buffer_load_b64(rows, static_cast<unsigned>(lane) * PART_SLOT_B + D * 2u, 0, 0);
                 ms = lane < cnt ? __uint_as_float(pair[0]) : -INFINITY;
                 ls = lane < cnt ? __uint_as_float(pair[1]) : 0.f;
             }
@@ -914,7 +929,7 @@ __global__ __launch_bounds__(64 * ROWS) void tree_attention_merge_kernel(const i
 #pragma unroll                                               // bounds-checked, the scalar offset operand is not
             for (int s = 0; s < MAXS; ++s) {
                 v[s] = __builtin_amdgcn_raw_buffer_load_b32(rows, off, 0, 0);
-                off += stride_b;
+                off += PART_SLOT_B;
             }
             __builtin_amdgcn_sched_barrier(0);               // every load is out before the first wait: one round trip
             const float m_blk = sage::wave_max(ms);
@@ -945,15 +960,16 @@ __global__ __launch_bounds__(64 * ROWS) void tree_attention_merge_kernel(const i
     if (!BATCH) {
         int len_b = __builtin_amdgcn_readfirstlane(kv_len_arg[b]);   // requested together, waited for once
         int n_b = __builtin_amdgcn_readfirstlane(n_nodes_arg[b]);
-        int f_b = prm.first_node ? __builtin_amdgcn_readfirstlane(prm.first_node[b]) : 0;
+        int f_b = first_node_arg ? __builtin_amdgcn_readfirstlane(first_node_arg[b]) : 0;
         asm("" : "+s"(len_b), "+s"(n_b), "+s"(f_b));
         const int L = len_b > 0 ? len_b : 0;
         const Split sp = make_split(n_b, f_b, L, G_arg, nslot_arg, min_bps_arg);
-        if (sp.col_groups > nslot_arg) return;
-        const unsigned char* base = prm.part + ((static_cast<long>(b) * prm.Hkv + g) * prm.nslot) * PART_SLOT_B;
-        for (int m = phase * ROWS + wave; m < sp.rows; m += phases * ROWS)
-            merge_row(b, sp.first + m / prm.G, m % prm.G, base + (static_cast<long>(m / ROWS_PER_WG) * ROWS_PER_WG + m % ROWS_PER_WG) * PART_ROW_B,
-                      static_cast<unsigned>(sp.col_groups) * static_cast<unsigned>(PART_SLOT_B), sp.nsplit);
+        const int m = phase * ROWS + wave;                   // a wave per row that a tree can have
+        if (sp.col_groups > nslot_arg || m >= sp.rows) return;
+        const int cg = m / ROWS_PER_WG, node = (m * prm.inv_G) >> 16;
+        merge_row(b, sp.first + node, m - node * prm.G,
+                  prm.part + ((static_cast<long>(b) * prm.Hkv + g) * prm.nslot + cg * sp.max_split) * PART_SLOT_B + (m % ROWS_PER_WG) * PART_ROW_B,
+                  sp.nsplit);
     } else {
         const BatchShape bs = make_batch_shape(prm, lane);
         const int first_b = __builtin_amdgcn_readlane(bs.first, b);
@@ -964,10 +980,10 @@ __global__ __launch_bounds__(64 * ROWS) void tree_attention_merge_kernel(const i
         for (int m = phase * ROWS + wave; m < live; m += phases * ROWS) {
             const int cg = m / ROWS_PER_WG;
             const int u0 = before + cg * (blocks_b + SEG_COST) + SEG_COST;   // first block of segment (b, cg)
-            const int s_first = u0 / bs.q;
-            merge_row(b, first_b + m / prm.G, m % prm.G,
+            const int s_first = div_floor(u0, bs.q), node = (m * prm.inv_G) >> 16;
+            merge_row(b, first_b + node, m - node * prm.G,
                       prm.part + (static_cast<long>(g) * prm.nslot + s_first + groups_before + cg) * PART_SLOT_B + (m % ROWS_PER_WG) * PART_ROW_B,
-                      static_cast<unsigned>(PART_SLOT_B), (u0 + blocks_b - 1) / bs.q - s_first + 1);
+                      div_floor(u0 + blocks_b - 1, bs.q) - s_first + 1);
         }
     }
 }
@@ -1059,7 +1075,7 @@ int tree_attention_bf16(const void* Q, const void* Kc, const void* Vc, const voi
     p.first_node = plan ? nullptr : first_node;
     p.part = static_cast<unsigned char*>(workspace);
     p.kv_token_stride = kv_token_stride; p.kv_head_stride = kv_head_stride;
-    p.B = B; p.Hq = Hq; p.Hkv = Hkv; p.G = G;
+    p.B = B; p.Hq = Hq; p.Hkv = Hkv; p.G = G; p.inv_G = (65536 + G - 1) / G;
     const LaunchShape sh = attention_bf16_shape(B, Hkv, G, max_kv_len);
     p.nslot = sh.nslot;
     p.min_blocks_per_split = sh.min_tiles_per_split * (TILE / BLK);
@@ -1101,22 +1117,22 @@ int tree_attention_bf16(const void* Q, const void* Kc, const void* Vc, const voi
     // keeps more waves resident.  A single sequence has few waves to keep, and a second pass is a second round trip to
     // memory: up to 64 splits in one (41 splits of 7 to 21 rows x 4 KV heads: 4.6 -> 4.1 us).
     if (sh.batch) {
-        if (most <= 8) hipLaunchKernelGGL((tree_attention_merge_kernel<8, true, MERGE_ROWS_BATCH>), mgrid, mblock, 0, stream, kv_len, n_nodes, p.nslot,
+        if (most <= 8) hipLaunchKernelGGL((tree_attention_merge_kernel<8, true, MERGE_ROWS_BATCH>), mgrid, mblock, 0, stream, kv_len, n_nodes, p.first_node, p.nslot,
                                p.min_blocks_per_split, G, p.merge_phases, p);
-        else if (most <= 16) hipLaunchKernelGGL((tree_attention_merge_kernel<16, true, MERGE_ROWS_BATCH>), mgrid, mblock, 0, stream, kv_len, n_nodes, p.nslot,
+        else if (most <= 16) hipLaunchKernelGGL((tree_attention_merge_kernel<16, true, MERGE_ROWS_BATCH>), mgrid, mblock, 0, stream, kv_len, n_nodes, p.first_node, p.nslot,
                                p.min_blocks_per_split, G, p.merge_phases, p);
-        else hipLaunchKernelGGL((tree_attention_merge_kernel<32, true, MERGE_ROWS_BATCH>), mgrid, mblock, 0, stream, kv_len, n_nodes, p.nslot,
+        else hipLaunchKernelGGL((tree_attention_merge_kernel<32, true, MERGE_ROWS_BATCH>), mgrid, mblock, 0, stream, kv_len, n_nodes, p.first_node, p.nslot,
                                p.min_blocks_per_split, G, p.merge_phases, p);
     } else {
-        if (most <= 8) hipLaunchKernelGGL((tree_attention_merge_kernel<8, false, MERGE_ROWS_SINGLE>), mgrid, mblock, 0, stream, kv_len, n_nodes, p.nslot,
+        if (most <= 8) hipLaunchKernelGGL((tree_attention_merge_kernel<8, false, MERGE_ROWS_SINGLE>), mgrid, mblock, 0, stream, kv_len, n_nodes, p.first_node, p.nslot,
                                p.min_blocks_per_split, G, p.merge_phases, p);
-        else if (most <= 16) hipLaunchKernelGGL((tree_attention_merge_kernel<16, false, MERGE_ROWS_SINGLE>), mgrid, mblock, 0, stream, kv_len, n_nodes, p.nslot,
+        else if (most <= 16) hipLaunchKernelGGL((tree_attention_merge_kernel<16, false, MERGE_ROWS_SINGLE>), mgrid, mblock, 0, stream, kv_len, n_nodes, p.first_node, p.nslot,
                                p.min_blocks_per_split, G, p.merge_phases, p);
-        else if (most <= 32) hipLaunchKernelGGL((tree_attention_merge_kernel<32, false, MERGE_ROWS_SINGLE>), mgrid, mblock, 0, stream, kv_len, n_nodes, p.nslot,
+        else if (most <= 32) hipLaunchKernelGGL((tree_attention_merge_kernel<32, false, MERGE_ROWS_SINGLE>), mgrid, mblock, 0, stream, kv_len, n_nodes, p.first_node, p.nslot,
                                p.min_blocks_per_split, G, p.merge_phases, p);
-        else if (most <= 48) hipLaunchKernelGGL((tree_attention_merge_kernel<48, false, MERGE_ROWS_SINGLE>), mgrid, mblock, 0, stream, kv_len, n_nodes, p.nslot,
+        else if (most <= 48) hipLaunchKernelGGL((tree_attention_merge_kernel<48, false, MERGE_ROWS_SINGLE>), mgrid, mblock, 0, stream, kv_len, n_nodes, p.first_node, p.nslot,
                                p.min_blocks_per_split, G, p.merge_phases, p);
-        else hipLaunchKernelGGL((tree_attention_merge_kernel<64, false, MERGE_ROWS_SINGLE>), mgrid, mblock, 0, stream, kv_len, n_nodes, p.nslot,
+        else hipLaunchKernelGGL((tree_attention_merge_kernel<64, false, MERGE_ROWS_SINGLE>), mgrid, mblock, 0, stream, kv_len, n_nodes, p.first_node, p.nslot,
                                p.min_blocks_per_split, G, p.merge_phases, p);
     }
     return launch_status();
