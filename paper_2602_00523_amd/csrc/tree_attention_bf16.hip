@@ -41,11 +41,11 @@
 // What bounds it, and against the kernel before this one (8 waves of 32 rows, softmax and MFMAs of a wave one after the
 // other, sums by two-element dot products, which block the matrix pipe for 16 cycles each); whole call, before -> now:
 //   small trees: the stream, and at short contexts launch, two round trips and the merge launch.  12 nodes, 64/8 heads, 4096
-//   positions 14.2 -> 12.6 us, 32768 positions 33.8 -> 32.8; 15 nodes, 16384 positions 24.2 -> 23.4; three sequences of
-//   301 to 1999 positions 15.5 -> 14.4; eight of 2205 to 12133 56.3 -> 55.0; 28/4 heads, 3 new rows of 12, 2560 positions
-//   10.0 -> 9.25.
-//   64 nodes: power.  32768 positions 79 -> 79.5 us (0.92 PFLOP/s at a clock of 2.0 GHz; 2.3 in the short calls), 16384
-//   positions 47.9 -> 47.3; fewer instructions and waits no longer show.
+//   positions 14.1 -> 12.4 us, 32768 positions 34 -> 33; 15 nodes, 16384 positions 24.3 -> 23.0; three sequences of
+//   301 to 1999 positions 15.5 -> 14.3; eight of 2205 to 12133 56.5 -> 53.5; 28/4 heads, 3 new rows of 12, 2560 positions
+//   10.0 -> 9.0.
+//   64 nodes: power.  32768 positions 78.7 -> 78.7 us (0.9 PFLOP/s at a clock of 2.0 GHz; 2.3 in the short calls); fewer
+//   instructions and waits no longer show.
 #include <type_traits>
 
 #include "plan_device.h"
@@ -61,52 +61,6 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef __attribute__((address_space(3))) unsigned char lds_byte;
 #define LDS_AS __attribute__((address_space(3)))
-
-typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
-
-typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
-
-typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
-
-typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
-
-typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
-
-typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
-
-typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
-
-typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
-
-typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
-
-typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
-
-typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
-
-typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
-
-typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
-
-typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
-
-typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
-
-typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
-
-typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
-
-typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
-
-typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
-
-typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
-
-typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
-
-typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
-
-typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 
 typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 
@@ -527,12 +481,12 @@ __device__ __forceinline__ void attention_pass(const Params& prm, LDS_AS Lds* ld
     };
     // Move the reference maximum of the rows that need it to the row maximum of the current unit (both 32-lane halves of
     // a row decide alike) and rescale what has been accumulated so far.
-    auto rebase = [&](const f32x16& s, int c, bool nothing_yet) __attribute__((always_inline)) {
+    auto rebase = [&](const f32x16& s, int c, bool nothing_yet, float raise_min) __attribute__((always_inline)) {
         float tmax = fmaxf(s[0], s[1]);
 #pragma unroll
         for (int i = 2; i < 16; ++i) tmax = fmaxf(tmax, s[i]);
         tmax = cross_half_max(tmax);
-        const bool raise = (m_ref[c] == -INFINITY) ? (tmax > -INFINITY) : ((tmax - m_ref[c]) * c_log2 > RAISE_MIN);
+        const bool raise = (m_ref[c] == -INFINITY) ? (tmax > -INFINITY) : ((tmax - m_ref[c]) * c_log2 > raise_min);
         const float m_new = raise ? tmax : m_ref[c];
         const float corr = !raise ? 1.f : (m_ref[c] == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f((m_ref[c] - m_new) * c_log2);
         m_ref[c] = m_new;
@@ -557,8 +511,9 @@ __device__ __forceinline__ void attention_pass(const Params& prm, LDS_AS Lds* ld
         f[i + 1] = pb[1];
     };
     // The running sums of the rounded probabilities, four of a lane's 16 at a time: of the 16 products of 4 x 4 matrices that
-    // this MFMA does, a lane's four values are one column, and a matrix of ones adds it up.  8 cycles of the matrix pipe; two
-    // two-element dot products block it for 16 each, and unpacking and adding are eight instructions of a full vector pipe.
+    // this MFMA does, a lane's four values are one column, and a matrix of ones adds it up.  16 cycles of the matrix pipe
+    // (a unit's MFMAs 513 -> 577 cycles with its four); two two-element dot products block it for 16 each, and unpacking and
+    // adding are eight instructions of a full vector pipe.
     auto add_up = [&](f32x4& l, const bf16x8& p, int j) __attribute__((always_inline)) {
         typedef short s16x4 __attribute__((ext_vector_type(4)));
         const s16x4 ones = {0x3F80, 0x3F80, 0x3F80, 0x3F80};
@@ -573,9 +528,22 @@ __device__ __forceinline__ void attention_pass(const Params& prm, LDS_AS Lds* ld
         constexpr int OTHER_C = CT == 2 ? 1 - C : 0;         // column tile of the units before and after
         constexpr bool READ = C == 0;
         f32x16& s = sc[CUR];
-        if (__builtin_expect(h >= full || h == 0, 0)) {
+        if (__builtin_expect(h >= full || h <= 1, 0)) {
             if (h >= full) mask_scores(s, h, C);
-            if (h == 0) rebase(s, C, true);
+            // The reference of a pass is the maximum of its first two blocks (64 tokens), so that the largest probability of a short
+            // pass is exactly one in bf16.  Error against 64 bits, 28/4 heads over 2560 positions: 2.61-2.65e-3 (2.69-2.75e-3 with the
+            // first block's maximum, 2.64-2.68e-3 before); 0.2-0.3 us of a short call, 1-2 of a 64-node one.
+            if (h == 0) rebase(s, C, true, RAISE_MIN);
+            if (h == 1 && CT == 2) rebase(s, C, false, 0.f);
+            if (h == 1 && CT == 1) {                         // (block 0 has not been multiplied yet: its probabilities again)
+                rebase(s, C, true, 0.f);
+                float neg_mc_now = neg_mc[C];
+                PIN(neg_mc_now);
+#pragma unroll
+                for (int i = 0; i < 16; i += 2)
+                    pack2(pf[1 - CUR][i >> 3], i & 7, __builtin_amdgcn_exp2f(fmaf(sc[1 - CUR][i], c_log2, neg_mc_now)),
+                          __builtin_amdgcn_exp2f(fmaf(sc[1 - CUR][i + 1], c_log2, neg_mc_now)));
+            }
         }
         const unsigned k_at = stage_after(KA) + k_lane, v_at = stage + v_lane;
         // The softmax of score m takes three steps, each in a later MFMA's shadow than the one before, so that no instruction
@@ -627,7 +595,7 @@ __device__ __forceinline__ void attention_pass(const Params& prm, LDS_AS Lds* ld
         }
         // A probability that may have overflowed, or a row's first admitted key.
         if (__builtin_expect(__any(most > REBASE_PAST), 0)) {
-            rebase(s, C, false);
+            rebase(s, C, false, RAISE_MIN);
             float neg_mc_now = neg_mc[C];
             PIN(neg_mc_now);                                 // (or the differences above would be kept for the rows that did not move)
 #pragma unroll
@@ -993,7 +961,7 @@ __global__ __launch_bounds__(64 * ROWS) void tree_attention_merge_kernel(const i
 namespace sage {
 
 // Launch shape.  A single sequence (and batches of more than 64): slots = workgroups per (sequence, KV head); a slot is
-// (KV split, column group); the sequence is cut into about one 8-wave workgroup per CU (one round, no tail).
+// (KV split, column group); the sequence is cut into about one workgroup per CU (one round, no tail).
 // Batches of 2..64 sequences: the tile list of all sequences is cut into `nrange` ranges per KV head, about one
 // workgroup per CU in total whatever the lengths turn out to be on the device, and the partial slots of a KV head are one
 // per range plus one per (sequence, column group), the most that range and segment boundaries can produce together.
