@@ -528,14 +528,13 @@ __device__ __forceinline__ void attention_pass(const Params& prm, LDS_AS Lds* ld
         constexpr int OTHER_C = CT == 2 ? 1 - C : 0;         // column tile of the units before and after
         constexpr bool READ = C == 0;
         f32x16& s = sc[CUR];
-        if (__builtin_expect(h >= full || h <= 1, 0)) {
+        if (__builtin_expect(h >= full || (CT == 1 && h <= 1), 0)) {
             if (h >= full) mask_scores(s, h, C);
             // The reference of a pass is the maximum of its first two blocks (64 tokens), so that the largest probability of a short
             // pass is exactly one in bf16.  Error against 64 bits, 28/4 heads over 2560 positions: 2.61-2.65e-3 (2.69-2.75e-3 with the
-            // first block's maximum, 2.64-2.68e-3 before); 0.2-0.3 us of a short call, 1-2 of a 64-node one.
-            if (h == 0) rebase(s, C, true, RAISE_MIN);
-            if (h == 1 && CT == 2) rebase(s, C, false, 0.f);
-            if (h == 1 && CT == 1) {                         // (block 0 has not been multiplied yet: its probabilities again)
+            // first block's maximum, 2.64-2.68e-3 before); 0.2-0.3 us of a short call.
+            if (CT == 1 && h == 0) rebase(s, C, true, RAISE_MIN);
+            if (CT == 1 && h == 1) {                         // (block 0 has not been multiplied yet: its probabilities again)
                 rebase(s, C, true, 0.f);
                 float neg_mc_now = neg_mc[C];
                 PIN(neg_mc_now);
@@ -593,9 +592,10 @@ __device__ __forceinline__ void attention_pass(const Params& prm, LDS_AS Lds* ld
             }
             FENCE();
         }
-        // A probability that may have overflowed, or a row's first admitted key.
-        if (__builtin_expect(__any(most > REBASE_PAST), 0)) {
-            rebase(s, C, false, RAISE_MIN);
+        // A probability that may have overflowed, a row's first admitted key, or (CT = 2) one of the pass's first two blocks: one copy
+        // of the code for all three (four sequences of 64 nodes 57.7 -> 57.0 us against two more copies ahead of the scores).
+        if (__builtin_expect(__any(most > REBASE_PAST) || (CT == 2 && h <= 1), 0)) {
+            rebase(s, C, false, h <= 1 ? 0.f : RAISE_MIN);
             float neg_mc_now = neg_mc[C];
             PIN(neg_mc_now);                                 // (or the differences above would be kept for the rows that did not move)
 #pragma unroll
