@@ -523,7 +523,7 @@ def attention_roofline(w: Workload, name: str, eager: bool = False):
            "frac": (tflops / MFMA_BF16_PEAK_TFLOPS) if mfma_bound else gbps / HBM_PEAK_GBPS,
            "traffic": MEASURED_TRAFFIC_BYTES.get(name),
            "traffic_source": (f"rocprofv3 FETCH_SIZE + WRITE_SIZE per call, profiles/tree_attention_hbm_traffic_by_workload.md, "
-                              f"taken at {TRAFFIC_SPLITS[name]}") if name in TRAFFIC_SPLITS else None,
+                              f"taken with the attention kernel of eight waves, at {TRAFFIC_SPLITS[name]}") if name in TRAFFIC_SPLITS else None,
            "avg_launch_us": us,
            "algorithmic_bytes_per_launch": per_bytes, "hbm_GBps": gbps, "hbm_frac": gbps / HBM_PEAK_GBPS,
            "mfma_TFLOPs": tflops, "mfma_frac": tflops / MFMA_BF16_PEAK_TFLOPS,
