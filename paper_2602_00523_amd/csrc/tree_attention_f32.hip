@@ -129,8 +129,9 @@ __global__ __launch_bounds__(THREADS) void tree_attention_f32_kernel(
         const int f = tile + lane16 * WAVES + wave, j = 4 * (f < cache_fours ? f : f - cache_fours) + row;
         const bool admitted = lane16 < TAKES && (f < cache_fours ? j < L : j < n && ((mask >> j) & 1));
         mine = admitted ? mine : -INFINITY;
-        const float m_new = fmaxf(m, rows_max(row_max(mine)));
-        if (m_new == -INFINITY) continue;                    // nothing admitted so far (uniform across the wave)
+        // A score that is NaN makes the row NaN; the maximum passes over it, and these four keys may be all that the wave has.
+        const float m_new = __any(mine != mine) ? NAN : fmaxf(m, rows_max(row_max(mine)));
+        if (m_new == -INFINITY) continue;                    // no score above -inf so far (uniform across the wave)
         const float corr = m == -INFINITY ? 0.f : expf(m - m_new);
         m = m_new;
         const float p = admitted ? expf(mine - m) : 0.f;

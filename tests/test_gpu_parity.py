@@ -289,6 +289,24 @@ def test_attention_f32_shapes(gu, B, Hq, Hkv, d, lens):
     run_attention_case(gu, 5 + B + d, "f32", B, Hq, Hkv, d, lens)
 
 
+@pytest.mark.parametrize("d,L,at", [(64, 9, 8), (64, 9, 0), (128, 300, 299), (256, 30, 17), (32, 1, 0), (64, 12, "tree"), (128, 28, "tree")])
+def test_attention_f32_nan_key(gu, d, L, at):
+    """A NaN key makes the rows that admit it NaN, also where a wave of the kernel has no other key; other rows do not see it."""
+    inp = wl.attention_inputs(700 + d + L, 1, 2, 2, d, [L], "f32", pad_tokens=1)
+    mask, nn = tree_batch(wl.rng(L), 1, [7], kind="star")
+    if at == "tree":
+        inp["Kt"][0, 6, 0, d // 2] = np.nan                  # a leaf's key: a row of its own admits it
+    else:
+        inp["Kc"][at, 0, d // 2] = np.nan
+    ref = oracle.tree_attention(inp["Q"], inp["Kc"], inp["Vc"], inp["Kt"], inp["Vt"], inp["kv_start"], inp["kv_len"],
+                                inp["kv_token_stride"], inp["kv_head_stride"], mask, nn, 2, 2, d)[0, :7]
+    got = gu.gpu_tree_attention(inp, mask, nn, 2, 2, d)[0][0, :7]
+    np.testing.assert_array_equal(np.isnan(got), np.isnan(ref))
+    assert np.isnan(ref).any() and not np.isnan(ref).all()
+    fine = ~np.isnan(ref)
+    assert np.abs(got[fine] - ref[fine]).max() <= TOL["f32"] * np.abs(ref[fine]).max()
+
+
 @pytest.mark.parametrize("kind,sizes,lens", [
     ("random", [64], [1000]),           # several tiles and a ragged tail, full tree
     ("random", [1], [64]),              # single node, exactly one tile
