@@ -168,18 +168,46 @@ __global__ __launch_bounds__(THREADS) void tree_attention_f32_kernel(
         s_l[wave] = l;
     }
     __syncthreads();
-    if (tid < d) {
-        float m_all = -INFINITY, l_all = 0.f, o = 0.f;
+    if (wave * 64 >= d) return;
+    float m_all = -INFINITY, l_all = 0.f, o = 0.f;
 #pragma unroll
-        for (int w = 0; w < WAVES; ++w) m_all = fmaxf(m_all, s_m[w]);
+    for (int w = 0; w < WAVES; ++w) m_all = fmaxf(m_all, s_m[w]);
 #pragma unroll
-        for (int w = 0; w < WAVES; ++w) {
-            const float weight = s_m[w] == -INFINITY ? 0.f : expf(s_m[w] - m_all);
-            l_all = fmaf(weight, s_l[w], l_all);
-            o = fmaf(weight, s_acc[w][tid], o);
-        }
-        O[q_at + tid] = o / l_all;
+    for (int w = 0; w < WAVES; ++w) {
+        const float weight = s_m[w] == -INFINITY ? 0.f : expf(s_m[w] - m_all);
+        l_all = fmaf(weight, s_l[w], l_all);
+        o = fmaf(weight, s_acc[w][tid], o);
     }
+    o /= l_all;
+    // A value whose weight in the row is zero does not count, whatever it is.  A wave weighs by the maximum of its own keys, so one
+    // that is infinite or NaN may have come in with a weight that other waves' keys make zero: where a result is not finite and
+    // the weights are, the values are summed again, by the row's maximum.
+    const bool again = tid < d && l_all > 0.f && l_all < INFINITY && !(fabsf(o) < INFINITY);
+    if (__builtin_expect(__any(again), 0)) {
+        float sum = 0.f;
+        for (int f = 0; f < fours; ++f) {
+            const bool tree = f >= cache_fours;
+            const int j0 = 4 * (tree ? f - cache_fours : f), last = (tree ? n : L) - 1 - j0;
+            const long stride = tree ? tree_stride : kv_token_stride;
+            const long at = (tree ? tree_at : cache_at) + j0 * stride;
+            const float* kr = (tree ? Kt : Kc) + at + min(row, last) * stride;
+            float a = 0.f;
+            for (int c = 0; c < NC; ++c) {
+                const int dim = min(64 * c + dim0, d - 4);
+                const float4 x = *reinterpret_cast<const float4*>(Q + q_at + dim), y = *reinterpret_cast<const float4*>(kr + dim);
+                const float t = fmaf(x.w, y.w, fmaf(x.z, y.z, fmaf(x.y, y.y, fmaf(x.x, y.x, a))));
+                a = 64 * c + dim0 < d ? t : a;
+            }
+            const bool admitted = row <= last && (!tree || ((mask >> (j0 + row)) & 1));
+            const float p = admitted ? expf(row_sum(a) * scale - m_all) : 0.f;
+            for (int r = 0; r < 4; ++r) {
+                const float pr = sage::lane_value(p, 16 * r);
+                if (pr != 0.f) sum = fmaf(pr, (tree ? Vt : Vc)[at + r * stride + min(tid, d - 1)], sum);
+            }
+        }
+        if (again) o = sum / l_all;
+    }
+    if (tid < d) O[q_at + tid] = o;
 }
 
 }  // namespace

@@ -307,6 +307,29 @@ def test_attention_f32_nan_key(gu, d, L, at):
     assert np.abs(got[fine] - ref[fine]).max() <= TOL["f32"] * np.abs(ref[fine]).max()
 
 
+@pytest.mark.parametrize("value", [np.inf, np.nan])
+@pytest.mark.parametrize("d,L,low", [(64, 9, {8: -200}), (128, 40, {39: -150, 0: -300}), (256, 700, {3: -150, 699: -200}), (60, 0, {"tree": -200}),
+                                     (64, 12, {4: -60, 5: -60, 6: -60, 7: -125})])
+def test_attention_f32_value_without_weight(gu, d, L, low, value):
+    """An infinite or NaN value does not count where its key's weight in the row is zero in fp32 (exp(-105) is), also where that
+    key has the largest score of its wave, or of the wave's weight only a part."""
+    inp = wl.attention_inputs(900 + d + L, 1, 2, 1, d, [L], "f32", pad_tokens=1)
+    mask, nn = tree_batch(wl.rng(L), 1, [7], kind="star")
+    inp["Q"][..., 0] = 1.0
+    for at, score in low.items():
+        k, v = (inp["Kt"][0, 6, 0], inp["Vt"][0, 6, 0]) if at == "tree" else (inp["Kc"][at, 0], inp["Vc"][at, 0])
+        k[:] = 0.0
+        k[0] = score * np.sqrt(d)
+        v[:] = 0.0                                           # what the oracle sees
+    ref = oracle.tree_attention(inp["Q"], inp["Kc"], inp["Vc"], inp["Kt"], inp["Vt"], inp["kv_start"], inp["kv_len"],
+                                inp["kv_token_stride"], inp["kv_head_stride"], mask, nn, 2, 1, d)[0, :7]
+    at = list(low)[-1]
+    v = inp["Vt"][0, 6, 0] if at == "tree" else inp["Vc"][at, 0]
+    v[1::3] = value
+    got = gu.gpu_tree_attention(inp, mask, nn, 2, 1, d)[0][0, :7]
+    assert np.abs(got - ref).max() <= TOL["f32"] * np.abs(ref).max()
+
+
 @pytest.mark.parametrize("kind,sizes,lens", [
     ("random", [64], [1000]),           # several tiles and a ragged tail, full tree
     ("random", [1], [64]),              # single node, exactly one tile
