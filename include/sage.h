@@ -133,6 +133,7 @@ int sage_build_tree(const float* topk_renorm, const float* alpha, const int* top
  * only to size the launch; dtype applies to Q, K, V and O alike.
  * bf16: MFMA path, requires d == 128, Hq / Hkv <= 16, kv_token_stride <= 2^24 elements;
  * fp32: d <= 256, multiple of 4.
+ * bf16: Q, Kc, Vc, Kt, Vt and the workspace at multiples of 16 bytes; fp32: aligned like their elements.
  * Accumulation is fp32; bf16 outputs are rounded to nearest even.
  * first_node [B] i32 (device), nullable = all zero: only the rows of nodes first_node[b] <= i <
  * n_nodes[b] are computed and written; earlier nodes still serve as keys and values through

@@ -22,6 +22,13 @@ namespace {
 constexpr int THREADS = 512;
 constexpr int WAVES = THREADS / 64;
 
+// Four floats that need be aligned like one only: rows of Q, K and V may begin anywhere (16-byte loads either way).
+typedef float float4_any __attribute__((ext_vector_type(4), aligned(4)));
+__device__ __forceinline__ float4 load4(const float* p) {
+    const float4_any x = *reinterpret_cast<const float4_any*>(p);
+    return make_float4(x[0], x[1], x[2], x[3]);
+}
+
 // sum / maximum over the 16 lanes of a row, in each of them
 __device__ __forceinline__ float row_sum(float v) {
     v += sage::f_dpp<0x128>(v); v += sage::f_dpp<0x124>(v); v += sage::f_dpp<0x122>(v); v += sage::f_dpp<0x121>(v);
@@ -100,13 +107,13 @@ __global__ __launch_bounds__(THREADS) void tree_attention_f32_kernel(
             const float* vr = (tree ? Vt : Vc) + at;
 #pragma unroll
             for (int c = 0; c < NC; ++c) {
-                k[u][c] = *reinterpret_cast<const float4*>(kr + off + dims[c]);
-                v[u][c] = *reinterpret_cast<const float4*>(vr + off + dims[c]);
+                k[u][c] = load4(kr + off + dims[c]);
+                v[u][c] = load4(vr + off + dims[c]);
             }
         }
         float4 q[NC];                                        // (here, and not ahead of the loop, whose entry would wait for it)
 #pragma unroll
-        for (int c = 0; c < NC; ++c) q[c] = *reinterpret_cast<const float4*>(Q + q_at + dims[c]);
+        for (int c = 0; c < NC; ++c) q[c] = load4(Q + q_at + dims[c]);
         __builtin_amdgcn_sched_barrier(0);                   // every load is out before the first one is used
         // scores: every lane of a row has all of the row's; lane u keeps the one of take u
         float mine = -INFINITY;
@@ -194,7 +201,7 @@ __global__ __launch_bounds__(THREADS) void tree_attention_f32_kernel(
             float a = 0.f;
             for (int c = 0; c < NC; ++c) {
                 const int dim = min(64 * c + dim0, d - 4);
-                const float4 x = *reinterpret_cast<const float4*>(Q + q_at + dim), y = *reinterpret_cast<const float4*>(kr + dim);
+                const float4 x = load4(Q + q_at + dim), y = load4(kr + dim);
                 const float t = fmaf(x.w, y.w, fmaf(x.z, y.z, fmaf(x.y, y.y, fmaf(x.x, y.x, a))));
                 a = 64 * c + dim0 < d ? t : a;
             }

@@ -330,6 +330,28 @@ def test_attention_f32_value_without_weight(gu, d, L, low, value):
     assert np.abs(got - ref).max() <= TOL["f32"] * np.abs(ref).max()
 
 
+@pytest.mark.parametrize("d,L", [(64, 300), (4, 5), (132, 66), (256, 70)])
+def test_attention_f32_alignment(gu, d, L):
+    """fp32 rows need be aligned like their elements only: the same bits from buffers that begin 4, 8 and 12 bytes past 16."""
+    B, Hq, Hkv = 1, 4, 2
+    inp = wl.attention_inputs(800 + d, B, Hq, Hkv, d, [L], "f32")
+    mask, nn = tree_batch(wl.rng(d), B, [13])
+    want = gu.gpu_tree_attention(inp, mask, nn, Hq, Hkv, d)[0]
+    m, n = gu.to_dev(mask), gu.to_dev(nn)
+    start, length = gu.to_dev(np.asarray(inp["kv_start"], np.int64)), gu.to_dev(np.asarray(inp["kv_len"], np.int32))
+    ws = gu.workspace(gu.sage.sage_tree_attention_workspace_bytes(gu.sage.F32, B, Hq, Hkv, d, L))
+    for off in (1, 2, 3):
+        def moved(a):
+            x = gu.torch.zeros(a.size + 4, device=gu.DEV, dtype=gu.torch.float32)
+            x[off:off + a.size] = gu.to_dev(a.reshape(-1))
+            return x[off:off + a.size].view(a.shape)
+        Q, Kc, Vc, Kt, Vt = (moved(inp[k]) for k in ("Q", "Kc", "Vc", "Kt", "Vt"))
+        O = moved(np.zeros_like(inp["Q"]))
+        gu.sage.sage_tree_attention(Q, Kc, Vc, Kt, Vt, O, start, length, L, inp["kv_token_stride"], inp["kv_head_stride"], m, n,
+                                    1.0 / float(np.sqrt(d)), ws)
+        np.testing.assert_array_equal(gu.to_host(O)[0, :13], want[0, :13])
+
+
 @pytest.mark.parametrize("kind,sizes,lens", [
     ("random", [64], [1000]),           # several tiles and a ragged tail, full tree
     ("random", [1], [64]),              # single node, exactly one tile
