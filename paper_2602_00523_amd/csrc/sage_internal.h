@@ -31,6 +31,9 @@ __device__ __forceinline__ uint16_t float_to_bf16_bits(float f) {
 // loop iteration waits for ALL loads in flight, which drains a prefetch ring.  Kernels that use this keep their own
 // count of loads in flight (s_waitcnt vmcnt(N) plus a barrier); the "memory" clobber keeps LDS reads from moving
 // across an issue.  M0 carries the LDS address of the load; nothing else in these kernels uses it.
+// The compiler does not look for hazards inside such a statement: a vector-memory instruction may read a scalar register no
+// sooner than five wait states after a vector instruction (v_readfirstlane, v_readlane of a spilled value) has written it,
+// so the forms with a scalar base bring five of their own.
 #pragma clang diagnostic push
 #pragma clang diagnostic ignored "-Winline-asm"
 __device__ __forceinline__ void lds_direct_load16(const unsigned char* gptr, __attribute__((address_space(3))) unsigned char* lds) {
@@ -49,7 +52,7 @@ __device__ __forceinline__ void lds_direct_load16(const unsigned char* sbase, un
     const uintptr_t bv = reinterpret_cast<uintptr_t>(sbase);
     const uintptr_t base = (static_cast<uintptr_t>(static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<uint32_t>(bv >> 32)))) << 32) |
                            static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<uint32_t>(bv)));
-    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1"
+    asm volatile("s_mov_b32 m0, %2\n\ts_nop 3\n\tglobal_load_lds_dwordx4 %0, %1"
                  :
                  : "v"(voff), "s"(base), "s"(m0v)
                  : "m0", "memory");
@@ -62,7 +65,7 @@ __device__ __forceinline__ void lds_direct_load16_if(int wanted, const unsigned 
     const uintptr_t bv = reinterpret_cast<uintptr_t>(sbase);     // (uniform: said to the compiler, as above)
     const uintptr_t base = (static_cast<uintptr_t>(static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<uint32_t>(bv >> 32)))) << 32) |
                            static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<uint32_t>(bv)));
-    asm volatile("s_cmp_eq_u32 %3, 0\n\ts_cbranch_scc1 .Lno_load%=\n\ts_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1\n.Lno_load%=:"
+    asm volatile("s_cmp_eq_u32 %3, 0\n\ts_cbranch_scc1 .Lno_load%=\n\ts_mov_b32 m0, %2\n\ts_nop 1\n\tglobal_load_lds_dwordx4 %0, %1\n.Lno_load%=:"
                  :
                  : "v"(voff), "s"(base), "s"(m0v), "s"(__builtin_amdgcn_readfirstlane(wanted))
                  : "m0", "scc", "memory");
