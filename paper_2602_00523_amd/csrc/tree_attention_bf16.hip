@@ -212,6 +212,15 @@ __device__ __forceinline__ void stage_barrier() {
 }
 __device__ __forceinline__ void wait_lds() { __builtin_amdgcn_s_waitcnt(0xc07f); }   // lgkmcnt(0)
 
+// After an MFMA whose result is read past a branch.  Twelve wait states lie between a 32x32x16 MFMA and a vector instruction that
+// reads its result; the compiler sees to them, but where paths join it has been seen to count along a longer one than the
+// shortest (the maximum over the first scores came after nine or ten on the path past the masking).
+__device__ __forceinline__ void mfma_results_ready() {
+    __builtin_amdgcn_sched_barrier(0);
+    asm volatile("s_nop 11");
+    __builtin_amdgcn_sched_barrier(0);
+}
+
 // max / sum of a value with its partner in the other 32-lane half (both halves receive the result)
 __device__ __forceinline__ float cross_half_max(float v) {
     const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
@@ -627,6 +636,7 @@ __device__ __forceinline__ void attention_pass(const Params& prm, LDS_AS Lds* ld
             qk(s, kf, qf[0], kk);
             if (CT == 1) read_k(kf[kk], STAGE_B + k_lane, kk);
         }
+        mfma_results_ready();
     };
     int h = 0;
     if (CT == 1 && (H & 1)) {
