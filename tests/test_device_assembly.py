@@ -128,3 +128,11 @@ def test_early_reads_are_found():
     text[4] = "s_nop 10"
     assert early_reads(text) == []
     assert early_reads([mfma, "v_mfma_f32_32x32x16_bf16 v[32:47], v[4:7], a[0:3], 0", "s_endpgm"])
+
+
+def test_attention_has_no_generic_stores(tmp_path):
+    """A store to a generic address also counts on the LDS counter: reads of LDS between such stores wait for each of them."""
+    name = "tree_attention_bf16.hip"
+    text = assembly(os.path.join(build.CSRC, name), tmp_path / "k.s", build.EXTRA[name])
+    assert any(line.startswith("global_store_dwordx4") for line in text)
+    assert [line for line in text if line.startswith("flat_store")] == []
