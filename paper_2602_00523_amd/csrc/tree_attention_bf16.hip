@@ -537,12 +537,14 @@ __device__ __forceinline__ void attention_pass(const Params& prm, LDS_AS Lds* ld
         constexpr int OTHER_C = CT == 2 ? 1 - C : 0;         // column tile of the units before and after
         constexpr bool READ = C == 0;
         f32x16& s = sc[CUR];
-        if (__builtin_expect(h >= full || (CT == 1 && h <= 1), 0)) {
+        float most = -INFINITY;                              // the largest exponent of a probability
+        if (__builtin_expect(h >= full || h <= 1, 0)) {
             if (h >= full) mask_scores(s, h, C);
             // The reference of a pass is the maximum of its first two blocks (64 tokens), so that the largest probability of a short
             // pass is exactly one in bf16.  Error against 64 bits, 28/4 heads over 2560 positions: 2.61-2.65e-3 (2.69-2.75e-3 with the
             // first block's maximum, 2.64-2.68e-3 before); 0.2-0.3 us of a short call.
-            if (CT == 1 && h == 0) rebase(s, C, true, RAISE_MIN);
+            if (h == 0) rebase(s, C, true, RAISE_MIN);
+            if (CT == 2 && h == 1) most = INFINITY;          // (the reference moves after this unit's MFMAs, below)
             if (CT == 1 && h == 1) {                         // (block 0 has not been multiplied yet: its probabilities again)
                 rebase(s, C, true, 0.f);
                 float neg_mc_now = neg_mc[C];
@@ -556,7 +558,7 @@ __device__ __forceinline__ void attention_pass(const Params& prm, LDS_AS Lds* ld
         const unsigned k_at = stage_after(KA) + k_lane, v_at = stage + v_lane;
         // The softmax of score m takes three steps, each in a later MFMA's shadow than the one before, so that no instruction
         // waits for the result of the one ahead of it.
-        float x[2], e[4], most = -INFINITY;
+        float x[2], e[4];
         x[0] = fmaf(s[0], c_log2, neg_mc[C]);
         x[1] = fmaf(s[1], c_log2, neg_mc[C]);
         PIN(x[0]);
@@ -601,10 +603,12 @@ __device__ __forceinline__ void attention_pass(const Params& prm, LDS_AS Lds* ld
             }
             FENCE();
         }
-        // A probability that may have overflowed, a row's first admitted key, or (CT = 2) one of the pass's first two blocks: one copy
-        // of the code for all three (four sequences of 64 nodes 57.7 -> 57.0 us against two more copies ahead of the scores).
-        if (__builtin_expect(__any(most > REBASE_PAST) || (CT == 2 && h <= 1), 0)) {
-            rebase(s, C, false, h <= 1 ? 0.f : RAISE_MIN);
+        // A probability that may have overflowed, a row's first admitted key, or (CT = 2) the pass's second block: one copy of the
+        // code for all three.  That it is the second block is said by `most`: asked for here, it is a dozen scalar instructions in
+        // every block (80 layers of 64 nodes x 32768 positions 6.38 -> 6.33 ms without them and without the first block here, whose
+        // reference moves ahead of its exponents; four sequences of 64 nodes 49.4 -> 48.3 us, 64 nodes x 300 positions 13.2 -> 12.7).
+        if (__builtin_expect(__any(most > REBASE_PAST), 0)) {
+            rebase(s, C, false, h == 1 ? 0.f : RAISE_MIN);
             float neg_mc_now = neg_mc[C];
             PIN(neg_mc_now);                                 // (or the differences above would be kept for the rows that did not move)
 #pragma unroll
