@@ -50,6 +50,7 @@
 
 #include "plan_device.h"
 #include "sage_internal.h"
+#include "split_divisions.h"
 
 namespace {
 
@@ -121,18 +122,13 @@ __device__ __forceinline__ int blocks_of(int tokens) { return (tokens + BLK - 1)
 // instructions, and there were five of them in the attention kernel's way to its first load and four in the merge's (whole
 // call of 3 new rows over 41 splits 9.3 -> 8.85 us, of 12 nodes over 4096 positions 12.7 -> 12.35, with the merge's first_node
 // and reciprocal brought by the host).
-// x / y for 0 <= x, 1 <= y: below 2^21, x + 1/2 over y is at least 1/2 / y away from an integer, and two roundings and a
-// reciprocal of one ulp move it by less than (x + 1/2) / y * 2^-22.
 __device__ __forceinline__ int div_floor(int x, int y) {
-    if (x < (1 << 21))                                       // (uniform, and what there is: 67 million positions)
-        return __builtin_amdgcn_readfirstlane(static_cast<int>((static_cast<float>(x) + 0.5f) * __builtin_amdgcn_rcpf(static_cast<float>(y))));
-    return x / y;
+    return sage::div_floor(x, y, [](int a, int b) __attribute__((always_inline)) {
+        return __builtin_amdgcn_readfirstlane(sage::by_reciprocal(a, __builtin_amdgcn_rcpf(static_cast<float>(b))));
+    });
 }
 __device__ __forceinline__ int div_ceil(int x, int y) { return div_floor(x + y - 1, y); }
-// x / groups for x <= 256 and up to four column groups
-__device__ __forceinline__ int per_group(int x, int groups) {
-    return groups == 1 ? x : groups == 2 ? x >> 1 : groups == 3 ? (x * 171) >> 9 : x >> 2;
-}
+using sage::per_group;
 
 // How one (sequence, KV head) is cut into workgroups; evaluated identically by both kernels.
 struct Split {

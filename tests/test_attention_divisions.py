@@ -1,25 +1,54 @@
-"""The attention kernels' divisions of small numbers (div_floor, per_group in tree_attention_bf16.hip), with the arithmetic that the
-device does: fp32, and a reciprocal that may be one unit in the last place off either way."""
+"""The divisions with which the attention kernels cut a call (csrc/split_divisions.h), compiled for the host: the code itself, with a
+reciprocal that may be one unit in the last place off either way."""
+import ctypes
+import subprocess
+
 import numpy as np
 import pytest
 
+from paper_2602_00523_amd import build
+
+SOURCE = """
+#include "split_divisions.h"
+extern "C" void quotients(const int* x, const int* y, const float* reciprocal, int n, int* out) {
+    for (int i = 0; i < n; ++i)
+        out[i] = sage::div_floor(x[i], y[i], [&](int a, int) { return sage::by_reciprocal(a, reciprocal[i]); });
+}
+extern "C" int group_share(int x, int groups) { return sage::per_group(x, groups); }
+"""
+
+
+@pytest.fixture(scope="module")
+def lib(tmp_path_factory):
+    try:
+        hipcc = build.hipcc()
+    except RuntimeError:
+        pytest.skip("no hipcc")
+    d = tmp_path_factory.mktemp("divisions")
+    (d / "divisions.hip").write_text(SOURCE)
+    subprocess.run([hipcc, "-O2", "-std=c++20", "-fPIC", "-shared", "--cuda-host-only", "-I", build.CSRC, str(d / "divisions.hip"), "-o",
+                    str(d / "divisions.so")], check=True, capture_output=True)
+    return ctypes.CDLL(str(d / "divisions.so"))
+
 
 @pytest.mark.parametrize("off", [-1, 0, 1])
-def test_division_by_reciprocal(off):
+@pytest.mark.parametrize("most", [(1 << 21) - 1, (1 << 31) - 1])
+def test_division_by_reciprocal(lib, most, off):
     g = np.random.default_rng(7)
     y = np.concatenate([np.arange(1, 600), g.integers(1, 1 << 21, 4000)]).astype(np.int64)
-    for k in (0, 1, 2, 3, 31, 32, 255, 4095):                     # just below, at and above multiples, the largest among them
+    r = np.float32(1) / y.astype(np.float32)
+    if off:
+        r = np.nextafter(r, np.float32(np.inf if off > 0 else 0), dtype=np.float32)
+    for k in (0, 1, 2, 3, 31, 32, 255, 4095, 1 << 20):            # just below, at and above multiples, the largest among them
         for d in (-1, 0, 1):
-            q = np.minimum(k, ((1 << 21) - 2) // y)
-            for x in (q * y + d, ((1 << 21) - 2) // y * y + d):
-                x = np.clip(x, 0, (1 << 21) - 1)
-                r = np.float32(1) / y.astype(np.float32)
-                if off:
-                    r = np.nextafter(r, np.float32(np.inf if off > 0 else 0), dtype=np.float32)
-                got = ((x.astype(np.float32) + np.float32(0.5)) * r).astype(np.int64)
+            q = np.minimum(k, most // y)
+            for x in (q * y + d, most // y * y + d, most + 0 * y, np.clip(q * y + d, 1 << 21, None)):
+                x = np.ascontiguousarray(np.clip(x, 0, most), np.int32)
+                yi, got = y.astype(np.int32), np.empty_like(x)
+                lib.quotients(*(a.ctypes.data_as(ctypes.c_void_p) for a in (x, yi, r)), len(x), got.ctypes.data_as(ctypes.c_void_p))
                 np.testing.assert_array_equal(got, x // y)
 
 
-def test_division_by_column_groups():
-    x = np.arange(257)
-    np.testing.assert_array_equal((x * 171) >> 9, x // 3)
+def test_division_by_column_groups(lib):
+    for groups in (1, 2, 3, 4):
+        assert [lib.group_share(x, groups) for x in range(257)] == [x // groups for x in range(257)]
