@@ -44,8 +44,9 @@
 //   positions 14.1 -> 12.4 us, 32768 positions 34 -> 33; 15 nodes, 16384 positions 24.3 -> 23.0; three sequences of
 //   301 to 1999 positions 15.5 -> 14.3; eight of 2205 to 12133 56.5 -> 53.5; 28/4 heads, 3 new rows of 12, 2560 positions
 //   10.0 -> 9.0.
-//   64 nodes: power.  32768 positions 78.7 -> 78.7 us (0.9 PFLOP/s at a clock of 2.0 GHz; 2.3 in the short calls); fewer
-//   instructions and waits no longer show.
+//   64 nodes: 32768 positions 78.7 -> 78.7 us, 0.9 PFLOP/s.  A unit (below) takes 1016 cycles, at a clock that power keeps at 1.9 GHz
+//   (2.3 in the short calls); its MFMAs take 544, a fifth of the wave's cycles are waits on counters, barriers and instruction
+//   fetch, a fifth waits for taken pipes.
 #include <type_traits>
 
 #include "plan_device.h"
@@ -60,7 +61,6 @@ typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x2 __attribute__((ext_vector_type(2)));
-typedef __attribute__((address_space(3))) unsigned char lds_byte;
 #define LDS_AS __attribute__((address_space(3)))
 
 typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
@@ -206,7 +206,6 @@ __device__ __forceinline__ void stage_barrier() {
     __builtin_amdgcn_s_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
-__device__ __forceinline__ void wait_lds() { __builtin_amdgcn_s_waitcnt(0xc07f); }   // lgkmcnt(0)
 
 // After an MFMA whose result is read past a branch.  Twelve wait states lie between a 32x32x16 MFMA and a vector instruction that
 // reads its result; the compiler sees to them, but where paths join it has been seen to count along a longer one than the
@@ -268,7 +267,7 @@ __device__ __forceinline__ void attention_pass(const Params& prm, LDS_AS Lds* ld
     const int ld_tok = (lane >> 4) * 8 + wave * 2;           // token within the block for i = 0 (i = 1: the next one)
     const unsigned k_chunk_b = ((lane & 15) ^ ((lane >> 4) & 1)) * 16;
     const unsigned v_chunk_b = (lane & 15) * 16;
-    const unsigned cache_row_b = static_cast<unsigned>(prm.kv_token_stride) * 2u;   // host: 64 rows fit 32 bits
+    const unsigned cache_row_b = static_cast<unsigned>(prm.kv_token_stride) * 2u;   // host: 32 rows fit 32 bits
     const unsigned tree_row_b = static_cast<unsigned>(prm.Hkv) * D * 2u;
     const long cache_at = sg.kv_start * prm.kv_token_stride + static_cast<long>(sg.g) * prm.kv_head_stride;
     const long tree_at = (static_cast<long>(sg.b) * SAGE_MAX_NODES * prm.Hkv + sg.g) * D;
@@ -1045,9 +1044,9 @@ int tree_attention_bf16(const void* Q, const void* Kc, const void* Vc, const voi
                         const int* first_node, float scale, void* workspace, size_t workspace_bytes, hipStream_t stream,
                         const PlanArgs* plan) {
     const int G = Hq / Hkv;
-    if (d != D || G < 1 || G > 16) return SAGE_UNSUPPORTED;   // 64 nodes x 16 heads per KV head = 8 groups of 128 rows
+    if (d != D || G < 1 || G > 16) return SAGE_UNSUPPORTED;   // 64 nodes x 16 heads per KV head = 4 groups of 256 rows
     if ((kv_token_stride % 8) != 0 || (kv_head_stride % 8) != 0) return SAGE_INVALID_ARG;
-    if (kv_token_stride > (1L << 24)) return SAGE_UNSUPPORTED;   // the byte offsets inside a 64-token tile are 32-bit
+    if (kv_token_stride > (1L << 24)) return SAGE_UNSUPPORTED;   // the byte offsets inside a 32-token block are 32-bit
     if (!aligned(Q, 16) || !aligned(Kc, 16) || !aligned(Vc, 16) || !aligned(Kt, 16) || !aligned(Vt, 16) || !aligned(workspace, 16))
         return SAGE_INVALID_ARG;
     if (workspace_bytes < attention_bf16_workspace_bytes(B, Hkv, G, max_kv_len)) return SAGE_WORKSPACE_TOO_SMALL;

@@ -228,7 +228,12 @@ int tree_attention_f32(const void* Q, const void* Kc, const void* Vc, const void
     if (d < 4 || d > 256 || (d % 4) != 0) return SAGE_UNSUPPORTED;
     if ((kv_token_stride % 4) != 0 || (kv_head_stride % 4) != 0) return SAGE_INVALID_ARG;
     if (Hq > 65535 || B > 65535) return SAGE_UNSUPPORTED;
-    // as many keys at once as the registers of a wave hold beside each other: 288, 128, 64
+    // Keys of a tile: 288, 128, 64.  A tile takes its time however full it is, and a longer context takes more of them; more takes a
+    // tile need more registers, which leaves fewer workgroups resident.  us per call at these takes, at about twice and at half of them:
+    //   64 dims    72 keys 5.3, 7.2, 4.2     264 keys 5.3, 7.2, 5.6     512 keys 7.9, 7.3, 9.2     1516 keys x 16 nodes 26.7, 16.1, 26.6
+    //   128 dims  108 keys 4.6, 6.0, 4.6     527 keys 16.6, 12.8, 16.3     2064 keys x 64 nodes x 32 heads 163, 216, 171
+    //   256 dims  216 keys 8.9, 9.3, 12.8   1016 keys x 16 nodes 23.1, 21.5, 31.6
+    // The lines lie where contexts of a small model's checks are served best, a few hundred positions of 64 dims.
     const auto kernel = d <= 64 ? tree_attention_f32_kernel<1, 9> : d <= 128 ? tree_attention_f32_kernel<2, 4> : tree_attention_f32_kernel<4, 2>;
     hipLaunchKernelGGL(kernel, dim3(SAGE_MAX_NODES, Hq, B), dim3(THREADS), 0, stream, n_nodes, kv_len, kv_start, first_node, anc_mask, Hq,
                        Hkv, d, static_cast<const float*>(Q), static_cast<const float*>(Kc), static_cast<const float*>(Vc),
