@@ -13,20 +13,19 @@
 // registers of S^T are, as they stand, the B operand of the PV product (the token order inside a 16-token k-block
 // is whatever the accumulator layout says; the V^T reads follow that order).
 //
-// Decomposition (decided on the device from n_nodes/kv_len, so no host round trip): a workgroup of 4 waves, one per SIMD,
-// owns (sequence, KV head, group of up to 256 query rows, KV split); wave w owns one column tile of 32 rows (groups of up
-// to 128 rows) or two (larger ones) and processes every 32-token block of the split for them, so nothing is shared between
-// waves but the K/V stages, and a wave's partial result is complete for its rows.  A block that has been brought into LDS
+// Decomposition (decided on the device from n_nodes/kv_len, so no host round trip): a workgroup of 8 waves, two per SIMD,
+// owns (sequence, KV head, group of up to 256 query rows, KV split); wave w owns one column tile of 32 rows and processes
+// every 32-token block of the split for it, so nothing is shared between waves but the K/V blocks, and a wave's partial result
+// is complete for its rows.  A block that has been brought into LDS
 // serves as many query rows as registers allow: what a CU can pull in (about 24 GB/s from HBM) bounds small trees, and a
-// tree of up to 32 nodes (G = 8) is one group.  With two column tiles a fragment read from LDS feeds two MFMAs, which halves
-// the LDS reads of 64-node trees.  With 2..64 sequences the splits are equal ranges of one list of all sequences' blocks, so
-// ragged lengths leave no CU idle (see the kernel).  The KV head is the fastest grid index, so in launch order the workgroups
-// of one KV head are congruent modulo the KV-head count, which with 8 KV heads pins a head to one XCD and its L2: the two
-// groups of a 64-node tree re-read K/V from that L2, not from HBM.  Each workgroup writes an un-normalised partial (max, sum
+// tree of up to 32 nodes (G = 8) is one group.  With 2..64 sequences the splits are equal ranges of one list of all sequences'
+// blocks, so ragged lengths leave no CU idle (see the kernel).  The KV head is the fastest grid index, so in launch order the
+// workgroups of one KV head are congruent modulo the KV-head count, which with 8 KV heads pins a head to one XCD and its L2: the
+// two groups of a 64-node tree re-read K/V from that L2, not from HBM.  Each workgroup writes an un-normalised partial (max, sum
 // in fp32, O^T in bf16); a second kernel merges the splits in a fixed order (deterministic, no float atomics) and writes bf16.
 //
 // Data movement.  K/V blocks of 32 tokens go from global memory straight into LDS (16-byte LDS-direct loads, no staging
-// registers; issued through inline assembly, see lds_direct_load16) through a ring of four stages.  A wave-level load
+// registers; issued through inline assembly, see lds_direct_load16) through two rings of four blocks.  A wave-level load
 // writes 1 KB of contiguous LDS; it carries four tokens that are 8 apart, and the 1 KB groups are padded so that the reads
 // are free of bank conflicts at compile-time offsets (see the layout constants).  The ancestor masks and the Q rows take
 // the same road ahead of the first blocks, so that no load of the kernel returns into a register and every wait on the
@@ -38,15 +37,20 @@
 // rounded to bf16 (the B operand of PV); their sum is taken over the rounded values, in fp32, by small MFMAs.  The final
 // normalisation uses the same reference for numerator and denominator, so the result does not depend on it.
 //
-// What bounds it, and against the kernel before this one (8 waves of 32 rows, softmax and MFMAs of a wave one after the
-// other, sums by two-element dot products, which block the matrix pipe for 16 cycles each); whole call, before -> now:
+// What bounds it, and against the kernel before this one (4 waves, one per SIMD, of one or two column tiles each, the second of
+// which saved the other's LDS reads; every address and every "is there another block" worked out in every block); whole call, before
+// -> now:
+//   64 nodes: 32768 positions 78.7-81.5 -> 73.3 us, 0.94 PFLOP/s; 300 positions 13.4 -> 11.9; 24 nodes x 32768 41.9 -> 39.3.  A wave alone on
+//   its SIMD issues one instruction at a time: about 600 cycles of a unit's 1016 (below) it issued, 100 of them scalar, and its
+//   MFMAs take 544.  Taking out its LDS reads, its loads or its exponentials made a unit 1-3 % shorter, each by itself: the matrix pipe
+//   waited for the order of the program.  Two waves, of which each fills what the other leaves open: 832 cycles a unit and SIMD (1663
+//   a block); with the scalar work out of the block (the loop once around the rings), 745.  Power then keeps the clock at 1.2-1.9 GHz,
+//   by machine and by how long the calls go on (80 layers in a row 82.4 -> 79.0 us a call); these MFMAs with this softmax and these
+//   LDS reads, and nothing else, take 610 cycles and reach 1.27 PFLOP/s.
 //   small trees: the stream, and at short contexts launch, two round trips and the merge launch.  12 nodes, 64/8 heads, 4096
-//   positions 14.1 -> 12.4 us, 32768 positions 34 -> 33; 15 nodes, 16384 positions 24.3 -> 23.0; three sequences of
-//   301 to 1999 positions 15.5 -> 14.3; eight of 2205 to 12133 56.5 -> 53.5; 28/4 heads, 3 new rows of 12, 2560 positions
-//   10.0 -> 9.0.
-//   64 nodes: 32768 positions 78.7 -> 78.7 us, 0.9 PFLOP/s.  A unit (below) takes 1016 cycles, at a clock that power keeps at 1.9 GHz
-//   (2.3 in the short calls); its MFMAs take 544, a fifth of the wave's cycles are waits on counters, barriers and instruction
-//   fetch, a fifth waits for taken pipes.
+//   positions 12.5 -> 12.0 us, 32768 positions 31.6 -> 31.5; 15 nodes, 16384 positions 21.5 -> 21.4; three sequences of
+//   301 to 1999 positions 15.2 -> 15.0; eight of 2205 to 12133 53.8 -> 53.8; 28/4 heads, 3 new rows of 12, 2560 positions
+//   9.2 -> 8.7.
 #include <type_traits>
 
 #include "plan_device.h"
@@ -64,14 +68,15 @@ typedef float f32x2 __attribute__((ext_vector_type(2)));
 #define LDS_AS __attribute__((address_space(3)))
 
 typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+typedef int i32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int D = 128;                  // head_dim
-constexpr int BLK = 32;                 // tokens per block (one stage of the ring)
-constexpr int THREADS = 256;
-constexpr int WAVES = THREADS / 64;
-constexpr int ROWS_PER_WG = 256;        // query rows of a group: up to 2 column tiles of 32 per wave
+constexpr int BLK = 32;                 // tokens per block
+constexpr int THREADS = 512;
+constexpr int WAVES = THREADS / 64;     // two per SIMD
+constexpr int ROWS_PER_WG = 32 * WAVES; // query rows of a group: a column tile of 32 per wave
 constexpr int ROW_B = 256;              // bytes of one token row (128 bf16)
-// LDS stage layout: token t of a block sits at (t % 8) * GROUP + (t / 8) * ROW_B, where a group is the 1 KB that one
+// LDS layout of a block: token t of a block sits at (t % 8) * GROUP + (t / 8) * ROW_B, where a group is the 1 KB that one
 // wave-level LDS-direct load writes (tokens t, t+8, t+16, t+24) plus padding.  K is read 16 consecutive tokens x one 16-byte
 // chunk at a time: 32 bytes of padding put eight consecutive tokens on eight different even chunk positions, and the rows
 // with t / 8 odd hold their chunks with the lowest index bit flipped, so that the other eight are on the odd ones.  V is
@@ -79,24 +84,23 @@ constexpr int ROW_B = 256;              // bytes of one token row (128 bf16)
 // a compile-time one, and the reads are conflict-free.
 constexpr int K_GROUP = 4 * ROW_B + 32;
 constexpr int V_GROUP = 4 * ROW_B + 64;
-constexpr int K_STAGE_B = 8 * K_GROUP;
-constexpr int V_STAGE_B = 8 * V_GROUP;
-constexpr int STAGE_B = K_STAGE_B + V_STAGE_B;
-// Four stages: one that is read, one that is free for the next loads, two on their way (K a block ahead of V).  More do not
-// help, they cost: of 4, 5, 6, 7 and 9 stages, 32768 positions under 12 nodes take 32.8, 34.4, 34.3, 35.2 and 36.5 us, 4096
-// positions 12.6, 13.0, 13.2, 13.4 and 13.7 (a call that starts by requesting more waits longer for its first block, and
-// workgroups of different KV heads that run further apart read the cache's rows in smaller pieces); 3 stages take 41.1 and 12.8.
-constexpr int STAGES = 4;
-constexpr int END = STAGES * STAGE_B;
-constexpr int AHEAD = STAGES - 2;       // steps (V block t, K block t + 2) requested ahead
-constexpr int Q_TILE_B = K_STAGE_B;     // 32 query rows in the layout of a K block, behind the ring
-constexpr int RING_B = END + ROWS_PER_WG / 32 * Q_TILE_B;
-constexpr int LOADS = 2;                // LDS-direct loads per thread and operand block
+constexpr int K_BLOCK_B = 8 * K_GROUP;
+constexpr int V_BLOCK_B = 8 * V_GROUP;
+// Two rings of four blocks, K and V, K two blocks ahead.  More do not help, they cost: with 4, 5, 6, 7 and 9 blocks (and four waves),
+// 32768 positions under 12 nodes took 32.8, 34.4, 34.3, 35.2 and 36.5 us, 4096 positions 12.6, 13.0, 13.2, 13.4 and 13.7 (a call
+// that starts by requesting more waits longer for its first block, and workgroups of different KV heads that run further apart
+// read the cache's rows in smaller pieces); with 3 blocks 41.1 and 12.8.
+constexpr int SLOTS = 4;
+constexpr int V_AT = SLOTS * K_BLOCK_B;
+constexpr int Q_AT = V_AT + SLOTS * V_BLOCK_B;
+constexpr int Q_TILE_B = K_BLOCK_B;     // 32 query rows in the layout of a K block, behind the rings
+constexpr int ZERO_AT = Q_AT + WAVES * Q_TILE_B;   // 1 KB of zeros: what the first unit reads as the V of the one before it
+constexpr int RING_B = ZERO_AT + 1024;
 // A partial: per query row O^T[128] in bf16, then max and sum in fp32.
 constexpr int PART_ROW_B = D * 2 + 16;   // (8 bytes of padding keep the rows 16-byte aligned)
 constexpr int PART_SLOT_B = ROWS_PER_WG * PART_ROW_B;
 constexpr int EPI_ROW_B = PART_ROW_B;    // a parked row of the epilogue has the layout of a partial row
-static_assert(ROWS_PER_WG * EPI_ROW_B <= RING_B, "the ring holds the epilogue's rows");
+static_assert(ROWS_PER_WG * EPI_ROW_B <= RING_B, "the rings hold the epilogue's rows");
 constexpr float RAISE_MIN = 4.0f;       // rebase() raises a row's reference maximum only past 2^4;
 constexpr float REBASE_PAST = 8.0f;     // it is called when a probability would pass 2^8
 constexpr float NO_REFERENCE = 3e38f;   // stands for -(reference * scale) while a row has none: every admitted key passes 2^8 then
@@ -184,18 +188,16 @@ __device__ __forceinline__ BatchShape make_batch_shape(const Params& prm, int la
 template <int N> __device__ __forceinline__ void wait_vm() {
     __builtin_amdgcn_s_waitcnt((N & 15) | (7 << 4) | (15 << 8) | ((N >> 4) << 14));
 }
-// ... until at most n loads are out (n even, wave-uniform)
+// ... until at most n loads are out (n wave-uniform, at most 4)
 __device__ __forceinline__ void wait_vm_upto(int n) {
-    switch (n >> 1) {
+    switch (n) {
         case 0: wait_vm<0>(); break;
-        case 1: wait_vm<2>(); break;
-        case 2: wait_vm<4>(); break;
-        case 3: wait_vm<6>(); break;
-        case 4: wait_vm<8>(); break;
-        default: wait_vm<10>(); break;
+        case 1: wait_vm<1>(); break;
+        case 2: wait_vm<2>(); break;
+        case 3: wait_vm<3>(); break;
+        default: wait_vm<4>(); break;
     }
 }
-static_assert(LOADS * (AHEAD + AHEAD + 1) <= 10, "the largest count that is asked for");
 
 // Workgroup barrier of the stage ring.  __syncthreads() would also fence, and a workgroup-scope release makes the
 // compiler wait for every LDS-direct load still in flight, which is exactly what the ring must not do: each
@@ -230,6 +232,7 @@ __device__ __forceinline__ float cross_half_sum(float v) {
 struct Lds {
     unsigned char ring[RING_B];
     uint64_t mask[ROWS_PER_WG];          // the rows' ancestor masks
+    i32x4 seq[64];                       // batches: nodes and first node, length, start of each sequence
 };
 
 // What one pass works on; every field is wave-uniform.
@@ -240,118 +243,79 @@ struct Segment {
     unsigned char* out;                  // the partial
 };
 
-// One pass: the blocks of a segment for one column group; CT = column tiles of 32 rows per wave (wave w owns rows
-// 32 CT w .. of the group).
+// One pass: the blocks of a segment for one column group.  Wave w owns column tile w, 32 rows, and processes every block for it
+// (the accumulators of two tiles would leave a wave alone on its SIMD).
 //
-// The loop runs over units, a unit being (block, column tile).  While the vector pipe turns the scores of unit u into
-// probabilities, the matrix pipe computes the scores of unit u + 1 and the PV product of unit u - 1: 16 MFMAs that depend on
-// nothing of unit u, one ahead of each of its 16 scores per lane, in program order (scheduling fences), because one wave per
-// SIMD has no other wave to fill its gaps.  Fragments of K and V are read from LDS into a second set of registers a unit
-// (CT = 1) or a block (CT = 2) before they are used; a fragment read serves CT column tiles.
-template <int CT>
+// The loop runs over units, a unit being one block for the wave's column tile.  While the vector pipe turns the scores of unit
+// h into probabilities, the matrix pipe computes the scores of unit h + 1 and the PV product of unit h - 1: 16 MFMAs that
+// depend on nothing of unit h, one ahead of each of its 16 scores per lane, in program order (scheduling fences).  What one
+// wave leaves open (waits, branches, the end of a unit, scalar instructions), the other wave of its SIMD fills, as far as the
+// barrier of the block lets it.
 __device__ __forceinline__ void attention_pass(const Params& prm, LDS_AS Lds* lds, const Segment& sg, const int inv_G, const int tid) {
-    constexpr int KA = CT == 2 ? 1 : 2;                      // K is read KA blocks ahead of V
     LDS_AS unsigned char* const ring = lds->ring;
     const int lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // wave-uniform, so LDS stage addresses stay scalar
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // wave-uniform, so LDS addresses stay scalar
     const int r32 = lane & 31;           // MFMA row (A) / column (B, C) owned by this lane
     const int half = lane >> 5;
     const int group_rows = min(ROWS_PER_WG, sg.rows - sg.cg * ROWS_PER_WG);
-    const int row0 = wave * 32 * CT;     // this wave's first row within the group
+    const int row0 = wave * 32;          // this wave's first row within the group
     const bool active = row0 < group_rows;
     const int H = sg.count;
+    const int slot0 = H & 1 ? 1 : 2;     // block h lies in slot (h + slot0) % SLOTS of its ring (see the loop)
 
-    // ---- loader: load i of wave w brings tokens t, t+8, t+16, t+24 (t = 2w + i) of a block, 1 KB of LDS: lane l fills
-    // chunk position l % 16 of token t + 8 (l / 16).  Addresses are a wave-uniform block base in scalar registers plus a
-    // 32-bit per-lane offset that is the same for every full block.
-    const int ld_tok = (lane >> 4) * 8 + wave * 2;           // token within the block for i = 0 (i = 1: the next one)
+    // ---- loader: wave w brings tokens w, w+8, w+16, w+24 of a block, 1 KB of LDS: lane l fills chunk position l % 16 of token
+    // w + 8 (l / 16).  Addresses are a wave-uniform block base in scalar registers plus a 32-bit per-lane offset that is the
+    // same for every full block.
+    const int ld_tok = (lane >> 4) * 8 + wave;
     const unsigned k_chunk_b = ((lane & 15) ^ ((lane >> 4) & 1)) * 16;
     const unsigned v_chunk_b = (lane & 15) * 16;
     const unsigned cache_row_b = static_cast<unsigned>(prm.kv_token_stride) * 2u;   // host: 32 rows fit 32 bits
     const unsigned tree_row_b = static_cast<unsigned>(prm.Hkv) * D * 2u;
     const long cache_at = sg.kv_start * prm.kv_token_stride + static_cast<long>(sg.g) * prm.kv_head_stride;
     const long tree_at = (static_cast<long>(sg.b) * SAGE_MAX_NODES * prm.Hkv + sg.g) * D;
-    const unsigned tok_off = static_cast<unsigned>(ld_tok) * cache_row_b;
+    const unsigned k_off = static_cast<unsigned>(ld_tok) * cache_row_b + k_chunk_b;
+    const unsigned v_off = static_cast<unsigned>(ld_tok) * cache_row_b + v_chunk_b;
     const int full = min(H, max(0, sg.L / BLK - sg.begin));  // leading blocks that are whole blocks of the cache
+    const unsigned long block_b = static_cast<unsigned long>(BLK) * cache_row_b;
+    const unsigned char* const k_cache = reinterpret_cast<const unsigned char*>(prm.Kc + cache_at) + static_cast<long>(sg.begin) * static_cast<long>(block_b);
+    const unsigned char* const v_cache = reinterpret_cast<const unsigned char*>(prm.Vc + cache_at) + static_cast<long>(sg.begin) * static_cast<long>(block_b);
 
-    struct Load { const unsigned char* base; unsigned off[2]; LDS_AS unsigned char* dst; int wanted; };
-    // where block h of K or V lies: a uniform base and this lane's offsets for i = 0, 1; wanted = 0 past the last block
-    auto locate = [&](auto is_v, int h, Load& l) __attribute__((always_inline)) {
+    // where block h of K or V lies: a uniform base and this lane's offset
+    struct At { const unsigned char* base; unsigned off; };
+    auto locate = [&](auto is_v, int h) __attribute__((always_inline)) {
         constexpr bool V = decltype(is_v)::value;
-        const unsigned chunk_b = V ? v_chunk_b : k_chunk_b;
         const int blk = sg.begin + h;
         const bool is_tree = blk >= sg.cache_blocks;
         const int tb = is_tree ? blk - sg.cache_blocks : blk;
         const unsigned row_b = is_tree ? tree_row_b : cache_row_b;
-        l.wanted = __builtin_amdgcn_readfirstlane(max(0, H - h));
+        At l;
         l.base = reinterpret_cast<const unsigned char*>(is_tree ? (V ? prm.Vt : prm.Kt) + tree_at : (V ? prm.Vc : prm.Kc) + cache_at) +
                  static_cast<long>(tb) * BLK * row_b;
         // in a ragged tail and in the tree's keys the rows past the end repeat the last one: they are masked later
         const int last = (is_tree ? sg.n : sg.L) - 1 - tb * BLK;
-        l.off[0] = static_cast<unsigned>(min(ld_tok, last)) * row_b + chunk_b;
-        l.off[1] = static_cast<unsigned>(min(ld_tok + 1, last)) * row_b + chunk_b;
+        l.off = static_cast<unsigned>(min(ld_tok, last)) * row_b + (V ? v_chunk_b : k_chunk_b);
+        return l;
     };
-    auto issue = [&](auto is_v, int h) __attribute__((always_inline)) {   // one of the first blocks
+    auto slot_of = [&](int h) __attribute__((always_inline)) { return static_cast<unsigned>(h + slot0) % SLOTS; };
+    auto issue = [&](auto is_v, int h) __attribute__((always_inline)) {
         constexpr bool V = decltype(is_v)::value;
-        constexpr int GROUP = V ? V_GROUP : K_GROUP;
         if (h >= H) return;
-        LDS_AS unsigned char* dst = ring + (h * STAGE_B + (V ? K_STAGE_B : 0) + wave * 2 * GROUP);   // (h < STAGES)
-        Load l;
-        if (h < full) {
-            l.base = reinterpret_cast<const unsigned char*>((V ? prm.Vc : prm.Kc) + cache_at) + static_cast<long>(sg.begin + h) * BLK * cache_row_b;
-            l.off[0] = tok_off + (V ? v_chunk_b : k_chunk_b);
-            l.off[1] = l.off[0] + cache_row_b;
-        } else {
-            locate(is_v, h, l);
-        }
-        sage::lds_direct_load16(l.base, l.off[0], dst);
-        sage::lds_direct_load16(l.base, l.off[1], dst + GROUP);
+        At l;
+        if (h < full) l = At{(V ? v_cache : k_cache) + h * static_cast<long>(block_b), V ? v_off : k_off};
+        else l = locate(is_v, h);
+        sage::lds_direct_load16(l.base, l.off, ring + (V ? V_AT + slot_of(h) * V_BLOCK_B + wave * V_GROUP : slot_of(h) * K_BLOCK_B + wave * K_GROUP));
     };
     using IsK = std::false_type;
     using IsV = std::true_type;
-    // What block h requests on the way, V block h + AHEAD and K block h + AHEAD + 2, as four loads that its units deal out
-    // between their MFMAs (a load occupies the CU's address path for 16 cycles: 16 of them at once would hold up four waves).
-    Load next_k, next_v;
-    auto request = [&](auto is_v, int i) __attribute__((always_inline)) {
-        constexpr bool V = decltype(is_v)::value;
-        const Load& l = V ? next_v : next_k;
-        sage::lds_direct_load16_if(l.wanted, l.base, l.off[i], l.dst + i * (V ? V_GROUP : K_GROUP));
-    };
-    // The usual step: everything that is out and everything that it requests is a whole block of the cache.  Nothing is
-    // computed for it but two running addresses and the two stages.
-    const int usual_end = full - 2 - AHEAD;
-    const unsigned block_b = BLK * cache_row_b;
-    const unsigned char* k_next = reinterpret_cast<const unsigned char*>(prm.Kc + cache_at) + static_cast<long>(sg.begin + AHEAD + 2) * block_b;
-    const unsigned char* v_next = reinterpret_cast<const unsigned char*>(prm.Vc + cache_at) + static_cast<long>(sg.begin + AHEAD) * block_b;
-    unsigned stage = 0;                                      // offset of block h's stage
-    auto stage_after = [&](int n) __attribute__((always_inline)) {       // ... of block h + n's, 0 <= n < STAGES
-        const unsigned at = stage + static_cast<unsigned>(n) * STAGE_B;
-        return at >= END ? at - END : at;
-    };
-    // Before block h's units: K block h + KA and V block h have landed for every wave, and the stages of K block h and V block
-    // h - 2 are free (an MFMA of block h - 1 has used what was read from them).  Loads complete in order, and what was
-    // requested after the two is out at most.
+    // Before unit h: K of block h + 2 and V of block h have landed for every wave, and the slots of K of block h and V of block
+    // h - 2 are free (an MFMA of unit h - 1 has used what was read from them).  Loads complete in order, and what was
+    // requested after the two, V of block h + 1 and K of block h + 3, is out at most.  This is the way of the first and last blocks;
+    // in the middle (see the loop) nothing is left to decide.
     auto arrive = [&](int h) __attribute__((always_inline)) {
-        next_k.dst = ring + (stage + wave * 2 * K_GROUP);
-        next_v.dst = ring + (stage_after(STAGES - 2) + K_STAGE_B + wave * 2 * V_GROUP);
-        if (__builtin_expect(h < usual_end, 1)) {
-            next_k.base = k_next;
-            next_k.off[0] = tok_off + k_chunk_b;
-            next_k.off[1] = next_k.off[0] + cache_row_b;
-            next_v.base = v_next;
-            next_v.off[0] = tok_off + v_chunk_b;
-            next_v.off[1] = next_v.off[0] + cache_row_b;
-            next_k.wanted = next_v.wanted = 1;
-            k_next += block_b;
-            v_next += block_b;
-            wait_vm<LOADS * (AHEAD - 1 + AHEAD + 1 - KA)>();
-        } else {
-            locate(IsK{}, h + AHEAD + 2, next_k);
-            locate(IsV{}, h + AHEAD, next_v);
-            const int r = H - 1 - h;                         // blocks after h
-            wait_vm_upto(LOADS * (min(AHEAD - 1, r) + min(AHEAD + 1 - KA, max(0, r - KA))));
-        }
+        wait_vm_upto((h + 1 < H ? 1 : 0) + (h + 3 < H ? 1 : 0));
         stage_barrier();
+        issue(IsV{}, h + 2);
+        issue(IsK{}, h + 4);
     };
 
     // Everything the prologue needs from memory goes straight into LDS, requested back to back in this order: the wave's
@@ -364,49 +328,40 @@ __device__ __forceinline__ void attention_pass(const Params& prm, LDS_AS Lds* ld
         return make_int2(sg.node0 + nd, mm - nd * prm.G);
     };
     // Q rows as tiles of 32 in the layout of a K block: row q of a tile sits at (q % 8) * K_GROUP + (q / 8) * ROW_B
-    LDS_AS unsigned char* const q_tiles = ring + END + wave * CT * Q_TILE_B;
+    LDS_AS unsigned char* const q_tile = ring + Q_AT + wave * Q_TILE_B;
     if (active) {
-#pragma unroll
-        for (int c = 0; c < CT; ++c) {                       // both words of the masks of rows 32 c + lane / 2
-            const int2 r = row_of(row0 + 32 * c + (lane >> 1));
+        {                                                    // both words of the masks of rows lane / 2
+            const int2 r = row_of(row0 + (lane >> 1));
             sage::lds_direct_load4(reinterpret_cast<const unsigned char*>(prm.anc_mask + static_cast<long>(sg.b) * SAGE_MAX_NODES + r.x) + (lane & 1) * 4,
-                                   (LDS_AS unsigned char*)(&lds->mask[row0 + 32 * c]));
+                                   (LDS_AS unsigned char*)(&lds->mask[row0]));
         }
 #pragma unroll
-        for (int c = 0; c < CT; ++c)
-#pragma unroll
-            for (int i = 0; i < 8; ++i) {
-                const int2 r = row_of(row0 + 32 * c + i + 8 * (lane >> 4));
-                const unsigned char* src = reinterpret_cast<const unsigned char*>(
-                    prm.Q + ((static_cast<long>(sg.b) * SAGE_MAX_NODES + r.x) * prm.Hq + sg.g * prm.G + r.y) * D) + k_chunk_b;
-                sage::lds_direct_load16(src, q_tiles + c * Q_TILE_B + i * K_GROUP);
-            }
+        for (int i = 0; i < 8; ++i) {
+            const int2 r = row_of(row0 + i + 8 * (lane >> 4));
+            const unsigned char* src = reinterpret_cast<const unsigned char*>(
+                prm.Q + ((static_cast<long>(sg.b) * SAGE_MAX_NODES + r.x) * prm.Hq + sg.g * prm.G + r.y) * D) + k_chunk_b;
+            sage::lds_direct_load16(src, q_tile + i * K_GROUP);
+        }
     }
     issue(IsK{}, 0);
     issue(IsK{}, 1);
-#pragma unroll
-    for (int t = 0; t < AHEAD; ++t) {
-        issue(IsV{}, t);
-        issue(IsK{}, t + 2);
-    }
-    // masks, Q and the first KA blocks of K have landed
-    wait_vm_upto(LOADS * (min(AHEAD, H) + min(AHEAD + 2 - KA, max(0, H - KA))));
+    issue(IsV{}, 0);
+    issue(IsK{}, 2);
+    issue(IsV{}, 1);
+    issue(IsK{}, 3);
+    *(LDS_AS u32x4*)(ring + ZERO_AT + lane * 16) = u32x4{0, 0, 0, 0};   // (by every wave, which reads it after its own write)
+    wait_vm_upto(min(2, H) + min(2, max(0, H - 2)));         // masks, Q and the first two blocks of K have landed
     stage_barrier();                                         // ... everyone's have
 
     if (!active) {                                           // no rows: this wave only brings its share of the blocks
-        for (int h = 0; h < H; ++h) {
-            arrive(h);
-            stage = stage_after(1);
-            request(IsV{}, 0);
-            request(IsV{}, 1);
-            request(IsK{}, 0);
-            request(IsK{}, 1);
-        }
+        for (int h = 0; h < H; ++h) arrive(h);
         wait_vm<0>();
         __syncthreads();
         return;
     }
 
+    f32x16 acc[4];                                           // O^T: 4 tiles of 32 dims x this lane's query row
+    float m_ref = -INFINITY;                                 // reference maximum of raw (unscaled) scores
     // ---- per-lane LDS read offsets.  K fragment kk: token r32, chunk 2 kk + half -> k_lane + 32 kk.
     const unsigned k_lane = (r32 & 7) * K_GROUP + (r32 >> 3) * ROW_B + ((half ^ ((r32 >> 3) & 1)) * 16);
     // V^T fragment (dt, jj, u): k-block jj (16 tokens); the 16-lane group q = lane/16 reads tokens 16jj + 8u + 4(q/2) + s/4
@@ -415,44 +370,25 @@ __device__ __forceinline__ void attention_pass(const Params& prm, LDS_AS Lds* ld
     unsigned v_lane;
     {
         const int q = lane >> 4, s16 = lane & 15;
-        v_lane = K_STAGE_B + (4 * (q >> 1) + (s16 >> 2)) * V_GROUP + (2 * (q & 1) + ((s16 & 3) >> 1)) * 16 + 8 * (s16 & 1);
+        v_lane = V_AT + (4 * (q >> 1) + (s16 >> 2)) * V_GROUP + (2 * (q & 1) + ((s16 & 3) >> 1)) * 16 + 8 * (s16 & 1);
     }
     auto read16 = [&](unsigned at) __attribute__((always_inline)) {
         return __builtin_bit_cast(bf16x8, *(const LDS_AS u32x4*)(ring + at));
     };
-
-    bf16x8 qf[CT][8];                                        // this lane's query rows: the B operand of every score MFMA
+    bf16x8 qf[8];                                        // this lane's query row: the B operand of every score MFMA
 #pragma unroll
-    for (int c = 0; c < CT; ++c)
-#pragma unroll
-        for (int kk = 0; kk < 8; ++kk)
-            qf[c][kk] = __builtin_bit_cast(bf16x8, *(const LDS_AS u32x4*)(q_tiles + c * Q_TILE_B + k_lane + kk * 32));
+    for (int kk = 0; kk < 8; ++kk) qf[kk] = read16(Q_AT + wave * Q_TILE_B + k_lane + kk * 32);
 
 #pragma unroll
-    for (int c = 0; c < CT; ++c)
+    for (int dt = 0; dt < 4; ++dt)
 #pragma unroll
-        for (int kk = 0; kk < 8; ++kk) asm volatile("" : "+a"(qf[c][kk]));   // only MFMAs read it: in accumulation registers
-
-    f32x16 acc[CT][4];                                       // O^T: 4 tiles of 32 dims x this lane's query rows
-#pragma unroll
-    for (int c = 0; c < CT; ++c)
-#pragma unroll
-        for (int dt = 0; dt < 4; ++dt)
-#pragma unroll
-            for (int i = 0; i < 16; ++i) acc[c][dt][i] = 0.f;
-    float m_ref[CT], neg_mc[CT];                             // reference maximum of raw (unscaled) scores; -(m_ref * c)
-    f32x4 l_run[CT];                                         // this lane's share of the running sum, four times
-#pragma unroll
-    for (int c = 0; c < CT; ++c) {
-        m_ref[c] = -INFINITY;
-        neg_mc[c] = NO_REFERENCE;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) l_run[c][i] = 0.f;
-    }
+        for (int i = 0; i < 16; ++i) acc[dt][i] = 0.f;
+    float neg_mc = NO_REFERENCE;                         // -(m_ref * c)
+    f32x4 l_run = {0.f, 0.f, 0.f, 0.f};                  // this lane's share of the running sum, four times
     const float c_log2 = prm.scale_log2e;
-    f32x16 sc[2];                                            // scores of the current and of the next unit
-    bf16x8 pf[2][2];                                         // P^T of the current and of the last unit, B operand of PV
-    bf16x8 kf[8], vf[4][2];                                  // fragments of K (by 16 dims) and V^T (by 32 dims and 16 tokens)
+    f32x16 sc[2];                                        // scores of the current and of the next unit
+    bf16x8 pf[2][2];                                     // P^T of the current and of the last unit, B operand of PV
+    bf16x8 kf[4], vf[4];                                 // fragments of K (by 16 dims) and V^T (by 32 dims)
 
     auto read_k = [&](bf16x8& f, unsigned at, int kk) __attribute__((always_inline)) { f = read16(at + kk * 32); };
     auto read_v = [&](bf16x8& f, unsigned at, int dt, int jj) __attribute__((always_inline)) {
@@ -461,21 +397,14 @@ __device__ __forceinline__ void attention_pass(const Params& prm, LDS_AS Lds* ld
         const bf16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((LDS_AS bf16x4*)(p + ROW_B));
         f = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
     };
-    auto qk = [&](f32x16& s, const bf16x8 (&k)[8], const bf16x8 (&q)[8], int kk) __attribute__((always_inline)) {
-        if (kk == 0) {
-#pragma unroll
-            for (int i = 0; i < 16; ++i) s[i] = 0.f;
-        }
-        s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(k[kk], q[kk], s, 0, 0, 0);
-    };
     // admit keys: cache positions below kv_len; tree nodes in this row's ancestor-or-self mask
-    auto mask_scores = [&](f32x16& s, int h, int c) __attribute__((always_inline)) {
+    auto mask_scores = [&](f32x16& s, int h) __attribute__((always_inline)) {
         const int blk = sg.begin + h;
         uint32_t admit;
         if (blk >= sg.cache_blocks) {
-            admit = reinterpret_cast<LDS_AS uint32_t*>(lds->mask)[2 * (row0 + 32 * c + r32) + (blk - sg.cache_blocks)];
+            admit = reinterpret_cast<LDS_AS uint32_t*>(lds->mask)[2 * (row0 + r32) + (blk - sg.cache_blocks)];
         } else {
-            admit = (1u << (sg.L - blk * BLK)) - 1u;         // 1..31 valid tokens
+            admit = (1u << (sg.L - blk * BLK)) - 1u;     // 1..31 valid tokens
         }
         admit >>= 4 * half;
         // token of accumulator register i: 8 (i/4) + 4 half + i%4
@@ -485,31 +414,32 @@ __device__ __forceinline__ void attention_pass(const Params& prm, LDS_AS Lds* ld
     };
     // Move the reference maximum of the rows that need it to the row maximum of the current unit (both 32-lane halves of
     // a row decide alike) and rescale what has been accumulated so far.
-    auto rebase = [&](const f32x16& s, int c, bool nothing_yet, float raise_min) __attribute__((always_inline)) {
+    auto rebase = [&](const f32x16& s, bool nothing_yet, float raise_min) __attribute__((always_inline)) {
         float tmax = fmaxf(s[0], s[1]);
 #pragma unroll
         for (int i = 2; i < 16; ++i) tmax = fmaxf(tmax, s[i]);
         tmax = cross_half_max(tmax);
-        const bool raise = (m_ref[c] == -INFINITY) ? (tmax > -INFINITY) : ((tmax - m_ref[c]) * c_log2 > raise_min);
-        const float m_new = raise ? tmax : m_ref[c];
-        const float corr = !raise ? 1.f : (m_ref[c] == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f((m_ref[c] - m_new) * c_log2);
-        m_ref[c] = m_new;
-        neg_mc[c] = m_new == -INFINITY ? NO_REFERENCE : -m_new * c_log2;
+        const bool raise = (m_ref == -INFINITY) ? (tmax > -INFINITY) : ((tmax - m_ref) * c_log2 > raise_min);
+        const float m_new = raise ? tmax : m_ref;
+        const float corr = !raise ? 1.f : (m_ref == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f((m_ref - m_new) * c_log2);
+        m_ref = m_new;
+        neg_mc = m_new == -INFINITY ? NO_REFERENCE : -m_new * c_log2;
         if (!nothing_yet) {
-            l_run[c][0] *= corr;                             // (the other three are not read)
+            l_run[0] *= corr;                            // (the other three are not read)
 #pragma unroll
             for (int dt = 0; dt < 4; ++dt)
 #pragma unroll
-                for (int i = 0; i < 16; ++i) acc[c][dt][i] *= corr;
+                for (int i = 0; i < 16; ++i) acc[dt][i] *= corr;
         }
     };
     // (the compiler does not move the computation of x past this point)
 #define PIN(x) asm volatile("" : "+v"(x))
+#define FENCE() __builtin_amdgcn_sched_barrier(0)
     // two probabilities to bf16 in place i, i + 1 of f
     auto pack2 = [&](bf16x8& f, int i, float p0, float p1) __attribute__((always_inline)) {
         const f32x2 pp = {p0, p1};
         uint32_t u = __builtin_bit_cast(uint32_t, __builtin_convertvector(pp, bf16x2));
-        PIN(u);                                              // (or it would be computed after the branch that follows)
+        PIN(u);                                          // (or it would be computed after the branch that follows)
         const bf16x2 pb = __builtin_bit_cast(bf16x2, u);
         f[i] = pb[0];
         f[i + 1] = pb[1];
@@ -518,68 +448,88 @@ __device__ __forceinline__ void attention_pass(const Params& prm, LDS_AS Lds* ld
     // this MFMA does, a lane's four values are one column, and a matrix of ones adds it up.  16 cycles of the matrix pipe
     // (a unit's MFMAs 513 -> 577 cycles with its four); two two-element dot products block it for 16 each, and unpacking and
     // adding are eight instructions of a full vector pipe.
-    auto add_up = [&](f32x4& l, const bf16x8& p, int j) __attribute__((always_inline)) {
+    auto add_up = [&](const bf16x8 (&before)[2], int j) __attribute__((always_inline)) {
         typedef short s16x4 __attribute__((ext_vector_type(4)));
         const s16x4 ones = {0x3F80, 0x3F80, 0x3F80, 0x3F80};
-        const bf16x4 part = j == 0 ? __builtin_shufflevector(p, p, 0, 1, 2, 3) : __builtin_shufflevector(p, p, 4, 5, 6, 7);
-        l = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(ones, __builtin_bit_cast(s16x4, part), l, 0, 0, 0);
+        const bf16x8& p = before[j >> 1];
+        const bf16x4 four = (j & 1) == 0 ? __builtin_shufflevector(p, p, 0, 1, 2, 3) : __builtin_shufflevector(p, p, 4, 5, 6, 7);
+        l_run = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(ones, __builtin_bit_cast(s16x4, four), l_run, 0, 0, 0);
     };
-#define FENCE() __builtin_amdgcn_sched_barrier(0)
-    // Unit (h, C); P = h % 2 when CT = 1.
-    auto unit = [&](auto parity, auto cc, const int h) __attribute__((always_inline)) {
-        constexpr int C = decltype(cc)::value;
-        constexpr int CUR = CT == 2 ? C : decltype(parity)::value;   // which of the two score and probability sets
-        constexpr int OTHER_C = CT == 2 ? 1 - C : 0;         // column tile of the units before and after
-        constexpr bool READ = C == 0;
+    // Unit h; CUR = which of the two score and probability sets, its parity counted from the end of the pass.  `usual`: the
+    // blocks in SLOT and around it are whole blocks of the cache, and so are those that are requested.
+    const unsigned k_dst = wave * K_GROUP, v_dst = V_AT + wave * V_GROUP;
+    const unsigned char* k_next;                             // (usual units) K of block h + 4, V of block h + 2
+    const unsigned char* v_next;
+    auto unit = [&](auto is_usual, auto slot, auto cur, const int h) __attribute__((always_inline)) {
+        constexpr bool USUAL = decltype(is_usual)::value;
+        constexpr int SLOT = decltype(slot)::value, CUR = decltype(cur)::value;
         f32x16& s = sc[CUR];
+        f32x16& next = sc[1 - CUR];
         float most = -INFINITY;                              // the largest exponent of a probability
-        if (__builtin_expect(h >= full || h <= 1, 0)) {
-            if (h >= full) mask_scores(s, h, C);
-            // The reference of a pass is the maximum of its first two blocks (64 tokens), so that the largest probability of a short
-            // pass is exactly one in bf16.  Error against 64 bits, 28/4 heads over 2560 positions: 2.61-2.65e-3 (2.69-2.75e-3 with the
-            // first block's maximum, 2.64-2.68e-3 before); 0.2-0.3 us of a short call.
-            if (h == 0) rebase(s, C, true, RAISE_MIN);
-            if (CT == 2 && h == 1) most = INFINITY;          // (the reference moves after this unit's MFMAs, below)
-            if (CT == 1 && h == 1) {                         // (block 0 has not been multiplied yet: its probabilities again)
-                rebase(s, C, true, 0.f);
-                float neg_mc_now = neg_mc[C];
-                PIN(neg_mc_now);
-#pragma unroll
-                for (int i = 0; i < 16; i += 2)
-                    pack2(pf[1 - CUR][i >> 3], i & 7, __builtin_amdgcn_exp2f(fmaf(sc[1 - CUR][i], c_log2, neg_mc_now)),
-                          __builtin_amdgcn_exp2f(fmaf(sc[1 - CUR][i + 1], c_log2, neg_mc_now)));
+        // where this lane reads K of blocks h + 1 (second half) and h + 2 (first half), V of blocks h - 1 (second half) and h
+        unsigned k1, k2, v0, v1;
+        if (USUAL) {
+            k1 = k_lane + (SLOT + 1) % SLOTS * K_BLOCK_B;
+            k2 = k_lane + (SLOT + 2) % SLOTS * K_BLOCK_B;
+            v0 = v_lane + (SLOT + 3) % SLOTS * V_BLOCK_B;
+            v1 = v_lane + SLOT * V_BLOCK_B;
+        } else {
+            k1 = k_lane + slot_of(h + 1) * K_BLOCK_B;
+            k2 = k_lane + slot_of(h + 2) * K_BLOCK_B;
+            v0 = h == 0 ? ZERO_AT : v_lane + slot_of(h + 3) * V_BLOCK_B;
+            v1 = v_lane + slot_of(h) * V_BLOCK_B;
+            if (__builtin_expect(h >= full || h <= 1, 0)) {
+                if (h >= full) mask_scores(s, h);
+                // The reference of a pass is the maximum of its first two blocks (64 tokens), so that the largest probability of a short
+                // pass is exactly one in bf16.  Error against 64 bits, 28/4 heads over 2560 positions: 2.61-2.65e-3 (2.69-2.75e-3 with the
+                // first block's maximum, 2.64-2.68e-3 before); 0.2-0.3 us of a short call.
+                if (h == 0) rebase(s, true, RAISE_MIN);
+                if (h == 1) most = INFINITY;                 // (the reference moves after this unit's MFMAs, below)
             }
         }
-        const unsigned k_at = stage_after(KA) + k_lane, v_at = stage + v_lane;
+        bf16x8 (&p)[2] = pf[CUR];
+        bf16x8 (&before)[2] = pf[1 - CUR];                   // the last unit's
         // The softmax of score m takes three steps, each in a later MFMA's shadow than the one before, so that no instruction
         // waits for the result of the one ahead of it.
         float x[2], e[4];
-        x[0] = fmaf(s[0], c_log2, neg_mc[C]);
-        x[1] = fmaf(s[1], c_log2, neg_mc[C]);
-        PIN(x[0]);
-        PIN(x[1]);
-        e[0] = __builtin_amdgcn_exp2f(x[0]);
-        PIN(e[0]);
-        bf16x8 (&p)[2] = pf[CUR];
-        bf16x8 (&before)[2] = pf[1 - CUR];                   // the last unit's
+        bool over = false;
         FENCE();
 #pragma unroll
         for (int m = 0; m < 16; ++m) {
-            // alternately a score MFMA and a PV MFMA, the last score MFMA third from the end; a fragment's register is
-            // refilled as soon as the last MFMA that needs it has been issued
+            // alternately a score MFMA and a PV MFMA, the last score MFMA third from the end; a fragment's registers take the next
+            // one that they are for as soon as its MFMA has been issued
             const int mm = m == 13 ? 14 : m == 14 ? 13 : m, i = mm >> 1;
             if (mm & 1) {
-                acc[OTHER_C][i & 3] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[i & 3][i >> 2], before[i >> 2], acc[OTHER_C][i & 3], 0, 0, 0);
-                if (READ) read_v(vf[i & 3][i >> 2], v_at, i & 3, i >> 2);
+                acc[i & 3] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[i & 3], before[i >> 2], acc[i & 3], 0, 0, 0);
+                if (i < 4) read_v(vf[i], v0, i, 1);
+                else read_v(vf[i & 3], v1, i & 3, 0);
             } else {
-                qk(sc[1 - CUR], kf, qf[OTHER_C], i);
-                if (READ) read_k(kf[i], k_at, i);
+                if (i == 0) {
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) next[r] = 0.f;
+                }
+                next = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[i & 3], qf[i], next, 0, 0, 0);
+                if (i < 4) read_k(kf[i], k1, i + 4);
+                else read_k(kf[i & 3], k2, i - 4);
             }
-            if ((m & 3) == 2) add_up(l_run[OTHER_C], before[m >> 3], (m >> 2) & 1);
-            if (CT == 2 ? C == 1 && (m & 3) == 1 : (m & 1) && m < 8) {   // m = 1, 5, 9, 13 or 1, 3, 5, 7: V, V, K, K
-                constexpr int STEP = CT == 2 ? 4 : 2;
-                if (m < 2 * STEP) request(IsV{}, m / STEP);
-                else request(IsK{}, m / STEP - 2);
+            if ((m & 3) == 2) add_up(before, m >> 2);
+            // (requested late in the unit: 15 nodes x 16384 positions 23.3, 22.9 and 22.3 us with the two at m = 0, at 1 and 5, at 7 and 11 on
+            // a machine where the kernel before took 22.4; on others the place makes no difference)
+            if (USUAL && m == 13) {
+                sage::lds_direct_load16(v_next, v_off, ring + (v_dst + (SLOT + 2) % SLOTS * V_BLOCK_B));
+                v_next += block_b;
+            }
+            if (USUAL && m == 15) {
+                sage::lds_direct_load16(k_next, k_off, ring + (k_dst + SLOT * K_BLOCK_B));
+                k_next += block_b;
+            }
+            if (m == 0) {
+                x[0] = fmaf(s[0], c_log2, neg_mc);
+                x[1] = fmaf(s[1], c_log2, neg_mc);
+                PIN(x[0]);
+                PIN(x[1]);
+                e[0] = __builtin_amdgcn_exp2f(x[0]);
+                PIN(e[0]);
             }
             if (!(m & 1)) {
                 if (m > 0) pack2(p[(m - 2) >> 3], (m - 2) & 7, e[(m - 2) & 3], e[(m - 1) & 3]);
@@ -593,81 +543,104 @@ __device__ __forceinline__ void attention_pass(const Params& prm, LDS_AS Lds* ld
                 pack2(p[1], 6, e[2], e[3]);
             }
             if (m < 14) {
-                x[m & 1] = fmaf(s[m + 2], c_log2, neg_mc[C]);
+                x[m & 1] = fmaf(s[m + 2], c_log2, neg_mc);
                 PIN(x[m & 1]);
             }
+            if (m == 14) over = __any(most > REBASE_PAST);
             FENCE();
         }
-        // A probability that may have overflowed, a row's first admitted key, or (CT = 2) the pass's second block: one copy of the
-        // code for all three.  That it is the second block is said by `most`: asked for here, it is a dozen scalar instructions in
-        // every block (80 layers of 64 nodes x 32768 positions 6.38 -> 6.33 ms without them and without the first block here, whose
-        // reference moves ahead of its exponents; four sequences of 64 nodes 49.4 -> 48.3 us, 64 nodes x 300 positions 13.2 -> 12.7).
-        if (__builtin_expect(__any(most > REBASE_PAST), 0)) {
-            rebase(s, C, false, h == 1 ? 0.f : RAISE_MIN);
-            float neg_mc_now = neg_mc[C];
+        // A probability that may have overflowed, a row's first admitted key, or (said by `most`) the pass's second block.
+        if (__builtin_expect(over, 0)) {
+            rebase(s, false, !USUAL && h == 1 ? 0.f : RAISE_MIN);
+            float neg_mc_now = neg_mc;
             PIN(neg_mc_now);                                 // (or the differences above would be kept for the rows that did not move)
 #pragma unroll
             for (int i = 0; i < 16; i += 2)
                 pack2(p[i >> 3], i & 7, __builtin_amdgcn_exp2f(fmaf(s[i], c_log2, neg_mc_now)),
                       __builtin_amdgcn_exp2f(fmaf(s[i + 1], c_log2, neg_mc_now)));
         }
-        if (C == CT - 1) stage = stage_after(1);
         FENCE();
     };
 #undef PIN
     using I0 = std::integral_constant<int, 0>;
     using I1 = std::integral_constant<int, 1>;
+    using I2 = std::integral_constant<int, 2>;
+    using I3 = std::integral_constant<int, 3>;
 
-    // The scores of the first unit; what the first unit multiplies as "the last one's" is zero.  With CT = 1 the loop takes two
-    // blocks at a time, for the two sets of scores; of an odd number the first one goes ahead.
+    // The scores of the first unit; what the first unit multiplies as "the last one's" is zero.  Units go in pairs, for the two sets of
+    // scores; of an odd number the first one goes ahead.
+    {
+        const unsigned k0 = k_lane + slot_of(0) * K_BLOCK_B;
 #pragma unroll
-    for (int kk = 0; kk < 8; ++kk) read_k(kf[kk], k_lane, kk);
+        for (int kk = 0; kk < 4; ++kk) read_k(kf[kk], k0, kk);
+    }
 #pragma unroll
-    for (int i = 0; i < 8; ++i)
+    for (int i = 0; i < 4; ++i)
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
-            vf[i & 3][i >> 2][e] = static_cast<__bf16>(0.0f);
-            pf[i & 1][(i >> 1) & 1][e] = static_cast<__bf16>(0.0f);
+            vf[i][e] = static_cast<__bf16>(0.0f);
+            pf[i & 1][i >> 1][e] = static_cast<__bf16>(0.0f);
         }
     auto first_scores = [&](f32x16& s) __attribute__((always_inline)) {
+        const unsigned k0 = k_lane + slot_of(0) * K_BLOCK_B, k1 = k_lane + slot_of(1) * K_BLOCK_B;
+#pragma unroll
+        for (int i = 0; i < 16; ++i) s[i] = 0.f;
 #pragma unroll
         for (int kk = 0; kk < 8; ++kk) {
-            qk(s, kf, qf[0], kk);
-            if (CT == 1) read_k(kf[kk], STAGE_B + k_lane, kk);
+            s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[kk & 3], qf[kk], s, 0, 0, 0);
+            if (kk < 4) read_k(kf[kk], k0, kk + 4);
+            else read_k(kf[kk & 3], k1, kk - 4);
         }
         mfma_results_ready();
     };
+    using Usual = std::true_type;
+    using Any = std::false_type;
     int h = 0;
-    if (CT == 1 && (H & 1)) {
+    if (H & 1) {
         first_scores(sc[1]);
         arrive(0);
-        unit(I1{}, I0{}, 0);
+        unit(Any{}, I0{}, I1{}, 0);
         h = 1;
     } else {
         first_scores(sc[0]);
     }
     while (h < H) {
         arrive(h);
-        unit(I0{}, I0{}, h);
-        if (CT == 2) {
-            unit(I0{}, std::integral_constant<int, CT - 1>{}, h);
-        } else {
-            arrive(++h);
-            unit(I1{}, I0{}, h);
+        unit(Any{}, I0{}, I0{}, h);
+        arrive(h + 1);
+        unit(Any{}, I0{}, I1{}, h + 1);
+        h += 2;
+        // Four units at a time, once around the rings: every address is a compile-time offset.  Block h is in slot 0 now (2 or 3 blocks
+        // are done, and what slot0 is comes from that); past the last of these units this is not reached again with enough blocks left.
+        k_next = k_cache + (h + 4) * static_cast<long>(block_b);
+        v_next = v_cache + (h + 2) * static_cast<long>(block_b);
+        while (h + 7 < full) {
+            wait_vm<2>();
+            stage_barrier();
+            unit(Usual{}, I0{}, I0{}, h);
+            wait_vm<2>();
+            stage_barrier();
+            unit(Usual{}, I1{}, I1{}, h);
+            wait_vm<2>();
+            stage_barrier();
+            unit(Usual{}, I2{}, I0{}, h);
+            wait_vm<2>();
+            stage_barrier();
+            unit(Usual{}, I3{}, I1{}, h);
+            h += 4;
         }
-        ++h;
     }
     // PV of the last unit
+    const unsigned v_last = v_lane + slot_of(H - 1) * V_BLOCK_B;
 #pragma unroll
-    for (int m = 0; m < 8; ++m)
-        acc[CT - 1][m & 3] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[m & 3][m >> 2], pf[1][m >> 2], acc[CT - 1][m & 3], 0, 0, 0);
+    for (int i = 0; i < 8; ++i) {
+        acc[i & 3] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[i & 3], pf[1][i >> 2], acc[i & 3], 0, 0, 0);
+        if (i < 4) read_v(vf[i], v_last, i, 1);
+    }
 #pragma unroll
-    for (int j = 0; j < 4; ++j) add_up(l_run[CT - 1], pf[1][j >> 1], j & 1);
+    for (int j = 0; j < 4; ++j) add_up(pf[1], j);
 #undef FENCE
-
-    float l_tot[CT];
-#pragma unroll
-    for (int c = 0; c < CT; ++c) l_tot[c] = cross_half_sum(l_run[c][0]);
+    const float l_tot = cross_half_sum(l_run[0]);
     wait_vm<0>();
 
     // ---- epilogue: a wave's rows (O^T in bf16, max, sum) are complete.  They go through the wave's own piece of the ring as
@@ -675,28 +648,25 @@ __device__ __forceinline__ void attention_pass(const Params& prm, LDS_AS Lds* ld
     // back and stored to the partial in row order, for the second kernel to merge.
     __syncthreads();                                         // all stages are idle now
     LDS_AS unsigned char* const mine = ring + row0 * EPI_ROW_B;
+    LDS_AS unsigned char* const row = mine + r32 * EPI_ROW_B;
 #pragma unroll
-    for (int c = 0; c < CT; ++c) {
-        LDS_AS unsigned char* row = mine + (32 * c + r32) * EPI_ROW_B;
+    for (int dt = 0; dt < 4; ++dt)
 #pragma unroll
-        for (int dt = 0; dt < 4; ++dt)
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const f32x4 v = {acc[c][dt][4 * q], acc[c][dt][4 * q + 1], acc[c][dt][4 * q + 2], acc[c][dt][4 * q + 3]};
-                *reinterpret_cast<LDS_AS bf16x4*>(row + (dt * 32 + 8 * q + 4 * half) * 2) = __builtin_convertvector(v, bf16x4);
-            }
-        if (half == 0) *reinterpret_cast<LDS_AS f32x2*>(row + D * 2) = f32x2{m_ref[c], l_tot[c]};
-    }
+        for (int q = 0; q < 4; ++q) {
+            const f32x4 v = {acc[dt][4 * q], acc[dt][4 * q + 1], acc[dt][4 * q + 2], acc[dt][4 * q + 3]};
+            *reinterpret_cast<LDS_AS bf16x4*>(row + (dt * 32 + 8 * q + 4 * half) * 2) = __builtin_convertvector(v, bf16x4);
+        }
+    if (half == 0) *reinterpret_cast<LDS_AS f32x2*>(row + D * 2) = f32x2{m_ref, l_tot};
     // (a wave's LDS operations complete in order, and the reads below wait for them: no barrier inside a wave)
     // Parked rows and partial rows have the same pitch, so the wave's rows go out as one contiguous copy of 17 chunks of 16
     // bytes a row (16 of O^T, one of max and sum), 64 chunks per store instruction
-    const int last_chunk = min(32 * CT, group_rows - row0) * (PART_ROW_B / 16);
+    const int last_chunk = min(32, group_rows - row0) * (PART_ROW_B / 16);
     // (said to be global memory: an address that went through lane reads is a generic one to the compiler, and a store to such a one
     // counts as an LDS operation too, so that the 9 or 17 chunks of a lane went out one after the other.  Call, 12 nodes x 4096
     // positions 12.06 -> 11.79 us, 64 x 300 13.5 -> 13.2, 3 new rows over 2560 8.95 -> 8.8)
     typedef __attribute__((address_space(1))) u32x4 global_u32x4;
     global_u32x4* out = (global_u32x4*)(sg.out + static_cast<long>(row0) * PART_ROW_B);
-    constexpr int COPIES = (32 * CT * (PART_ROW_B / 16) + 63) / 64;
+    constexpr int COPIES = (32 * (PART_ROW_B / 16) + 63) / 64;
     u32x4 chunk[COPIES];
 #pragma unroll
     for (int i = 0; i < COPIES; ++i) chunk[i] = *reinterpret_cast<LDS_AS u32x4*>(mine + (lane + 64 * i) * 16);
@@ -743,9 +713,7 @@ __device__ __forceinline__ void attention_workgroup(const int* __restrict__ kv_l
         // The thread index is therefore made opaque per pass, and its derived values are recomputed.
         int tid = static_cast<int>(threadIdx.x);
         if (BATCH) asm volatile("" : "+v"(tid));
-        // up to 128 rows: one column tile per wave, on as many SIMDs as there are tiles; more: two
-        if (sg.rows - sg.cg * ROWS_PER_WG <= WAVES * 32) attention_pass<1>(prm, lds, sg, inv_G, tid);
-        else attention_pass<2>(prm, lds, sg, inv_G, tid);
+        attention_pass(prm, lds, sg, inv_G, tid);
     };
 
     if (!BATCH) {
@@ -772,24 +740,28 @@ __device__ __forceinline__ void attention_workgroup(const int* __restrict__ kv_l
                             start_b, prm.part + ((static_cast<long>(b) * prm.Hkv + g) * prm.nslot + cg * sp.max_split + split) * PART_SLOT_B});
     } else {
         const int lane = threadIdx.x & 63;
-        const BatchShape bs = make_batch_shape(prm, lane);  // lane b holds sequence b
-        const int r0 = id * bs.q;                            // this workgroup's range of the list
-        const int r1 = min(bs.total, r0 + bs.q);
-        if (r0 >= r1) return;
+        int r0, r1, line;                                    // this workgroup's range of the list; lane b: sequence b's positions, column groups
+        {
+            const BatchShape bs = make_batch_shape(prm, lane);   // lane b holds sequence b
+            r0 = id * bs.q;
+            r1 = min(bs.total, r0 + bs.q);
+            if (r0 >= r1) return;
+            // What only a pass needs of its sequence waits in LDS, not in registers, which the passes take all of.  (Every wave writes
+            // all of it and reads what it wrote itself: no barrier.)
+            lds->seq[lane] = i32x4{bs.n << 8 | bs.first, bs.L, bs.start_lo, bs.start_hi};
+            line = (bs.blocks + SEG_COST) << 3 | bs.col_groups;
+        }
         int first = 0, groups_before = 0;                    // first position / number of segments of the sequences before b
         for (int b = 0; b < prm.B && first < r1; ++b) {
-            const int blocks_b = __builtin_amdgcn_readlane(bs.blocks, b);
-            const int cgs_b = __builtin_amdgcn_readlane(bs.col_groups, b);
-            const int seg_len = blocks_b + SEG_COST;
+            const int line_b = __builtin_amdgcn_readlane(line, b);
+            const int seg_len = line_b >> 3, cgs_b = line_b & 7;
             if (first + seg_len * cgs_b > r0) {
-                const int n_b = __builtin_amdgcn_readlane(bs.n, b);
-                const int f_b = __builtin_amdgcn_readlane(bs.first, b);
-                const int L_b = __builtin_amdgcn_readlane(bs.L, b);
-                const long start_b = (static_cast<long>(__builtin_amdgcn_readlane(bs.start_hi, b)) << 32) |
-                                     static_cast<uint32_t>(__builtin_amdgcn_readlane(bs.start_lo, b));
+                const int nf = lds->seq[b].x, L_b = lds->seq[b].y;
+                const int n_b = nf >> 8, f_b = nf & 255;
+                const long start_b = (static_cast<long>(lds->seq[b].w) << 32) | static_cast<uint32_t>(lds->seq[b].z);
                 for (int cg = 0; cg < cgs_b; ++cg) {
                     const int block0 = first + cg * seg_len + SEG_COST;      // position of the segment's first block
-                    const int lo = max(r0, block0), hi = min(r1, block0 + blocks_b);
+                    const int lo = max(r0, block0), hi = min(r1, block0 + seg_len - SEG_COST);
                     if (lo < hi)
                         run_segment(Segment{b, g, L_b, n_b, f_b, (n_b - f_b) * prm.G, cg, lo - block0, hi - lo, blocks_of(L_b), start_b,
                                             prm.part + (static_cast<long>(g) * prm.nslot + id + groups_before + cg) * PART_SLOT_B});
