@@ -661,11 +661,9 @@ __device__ __forceinline__ void attention_pass(const Params& prm, LDS_AS Lds* ld
     // Parked rows and partial rows have the same pitch, so the wave's rows go out as one contiguous copy of 17 chunks of 16
     // bytes a row (16 of O^T, one of max and sum), 64 chunks per store instruction
     const int last_chunk = min(32, group_rows - row0) * (PART_ROW_B / 16);
-    // (said to be global memory: an address that went through lane reads is a generic one to the compiler, and a store to such a one
-    // counts as an LDS operation too, so that the 9 or 17 chunks of a lane went out one after the other.  Call, 12 nodes x 4096
-    // positions 12.06 -> 11.79 us, 64 x 300 13.5 -> 13.2, 3 new rows over 2560 8.95 -> 8.8)
-    typedef __attribute__((address_space(1))) u32x4 global_u32x4;
-    global_u32x4* out = (global_u32x4*)(sg.out + static_cast<long>(row0) * PART_ROW_B);
+    // They are written through the L2 (see store_through16): what a kernel leaves in an L2 is written back at its end, before the merge
+    // may start, and 64 nodes leave 17 MB.
+    unsigned char* const out = sg.out + static_cast<long>(row0) * PART_ROW_B;
     constexpr int COPIES = (32 * (PART_ROW_B / 16) + 63) / 64;
     u32x4 chunk[COPIES];
 #pragma unroll
@@ -673,7 +671,7 @@ __device__ __forceinline__ void attention_pass(const Params& prm, LDS_AS Lds* ld
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int i = 0; i < COPIES; ++i)
-        if (lane + 64 * i < last_chunk) out[lane + 64 * i] = chunk[i];
+        if (lane + 64 * i < last_chunk) sage::store_through16(out + (lane + 64 * i) * 16, chunk[i]);
 }
 
 // BATCH = false: one sequence per launch slot, every (sequence, KV head) cut into equal splits (see make_split).
