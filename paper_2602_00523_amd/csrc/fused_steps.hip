@@ -66,18 +66,26 @@ __global__ __launch_bounds__(64 * ACCEPT_WAVES) void accept_kernel(const int* __
     const int lane = threadIdx.x & 63;
     const int wave = threadIdx.x >> 6;
     const long base = static_cast<long>(b) * SAGE_MAX_NODES;
-    int n = n_nodes[b];
-    n = n < 1 ? 1 : (n > SAGE_MAX_NODES ? SAGE_MAX_NODES : n);
-
-    // wave 0 asks for its node fields now, so they arrive while the reductions run
+    // Wave 0 asks for its node fields now, ahead of the node count (every sequence has the 64 slots), and what the closing needs is
+    // asked for with it: both arrive while the reductions run.
     int par = -1, tok = 0, dep = 0;
     uint64_t am = 0;
-    if (wave == 0 && lane < n) {
+    if (wave == 0) {
         par = parent[base + lane];
         tok = token[base + lane];
         dep = depth[base + lane];
         am = anc_mask[base + lane];
     }
+    int n = n_nodes[b], len_b = 0;
+    int64_t start = 0;
+    sage::closing::HistoryState was{};
+    if (CLOSE) {
+        len_b = cl.kv_len[b];
+        start = cl.kv_start[b];
+        if (wave == 1) was = sage::closing::history_state(b, lane, cl.window, cl.hist, cl.count, cl.d_max_in);
+        asm("" : "+s"(n), "+s"(len_b), "+s"(start));
+    }
+    n = n < 1 ? 1 : (n > SAGE_MAX_NODES ? SAGE_MAX_NODES : n);
 
     // ---- with few lists per lane all of this wave's rows are requested before the first one is reduced (one memory
     //      round trip); with many, a row at a time, to stay within the register file
@@ -131,17 +139,16 @@ __global__ __launch_bounds__(64 * ACCEPT_WAVES) void accept_kernel(const int* __
     if (!CLOSE) return;
     // ---- the accepted path joins the cache, the length advances, the history moves the depth limit: what
     //      sage_close_step does, here with the path still in LDS and all 16 waves copying
-    __syncthreads();
+    __syncthreads();                                 // (by now every thread has read the old length, above)
     const int tau = s_tau;
-    const int len_b = cl.kv_len[b];
-    for (int j = 0; j <= tau && j < path_cap; ++j)
-        sage::closing::commit_row(cl.Kt, cl.Vt, cl.Kc, cl.Vc, cl.esz, cl.Hkv, cl.d, cl.kv_start, len_b, cl.kv_capacity,
-                                  cl.kv_token_stride, cl.kv_head_stride, sh.slot_node[j], j, b);
-    __syncthreads();                                 // every thread has read the old length
+    constexpr int ROW_THREADS = sage::closing::ROW_THREADS;
+    for (int j = threadIdx.x / ROW_THREADS; j <= tau && j < path_cap; j += 64 * ACCEPT_WAVES / ROW_THREADS)   // eight rows at a time
+        sage::closing::commit_row(cl.Kt, cl.Vt, cl.Kc, cl.Vc, cl.esz, cl.Hkv, cl.d, start, len_b, cl.kv_capacity, cl.kv_token_stride,
+                                  cl.kv_head_stride, sh.slot_node[j], j, b, threadIdx.x % ROW_THREADS);
     if (threadIdx.x == 0) cl.kv_len[b] = sage::closing::advanced_len(len_b, tau, cl.kv_capacity);
     if (wave == 1)
-        sage::closing::history_wave(b, lane, tau, cl.window, cl.lo, cl.hi, cl.d_floor, cl.d_cap, cl.hist, cl.count, cl.d_max_in,
-                                    cl.d_max_out, cl.avg_out);
+        sage::closing::history_wave(b, lane, tau, cl.window, cl.lo, cl.hi, cl.d_floor, cl.d_cap, was, cl.hist, cl.count, cl.d_max_out,
+                                    cl.avg_out);
 }
 
 }  // namespace
