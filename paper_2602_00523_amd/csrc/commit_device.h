@@ -9,9 +9,9 @@ namespace closing {
 
 // Closing a step is latency, a chain of round trips to memory: what decides (lengths, state, path), then the rows, all of them at once.
 // Step, before (lengths after the acceptance rule, a row after the other) -> now: one layer over 4096 positions 20.3 -> 19.7 us, over
-// 16384 32.7 -> 32.2, three short sequences of four layers 79.4 -> 78.7.  Code that runs once costs, too, about 0.25 us a KB from a cold
-// instruction cache: copying every piece of all rows in one flat loop, two per thread held, with the divisions that takes, made the
-// steps 0.6 us slower than before.
+// 16384 32.7 -> 32.2, three short sequences of four layers 79.4 -> 78.7.  What is executed costs, too:
+// copying every piece of all rows in one flat loop, two per thread held, with the divisions that takes, made the steps 0.6 us slower
+// than before.
 // 128 threads, of which this one is `t0`, copy the K row and the V row of `node`, path entry j of sequence b (Hkv heads x d elements
 // each), to cache position len_b + j in 16-byte pieces.
 constexpr int ROW_THREADS = 128;

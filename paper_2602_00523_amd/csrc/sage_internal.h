@@ -3,6 +3,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <utility>
+
 #include "sage.h"
 
 namespace sage {
@@ -86,9 +88,12 @@ __device__ __forceinline__ void lds_direct_load4(const unsigned char* gptr, __at
 // 64 nodes x 32768 positions 73.3 -> 72.1, x 4096 21.1 -> 20.8; 12 nodes x 32768 31.9 -> 31.4, x 4096 11.9 -> 12.0; batches and
 // drafting passes 0.5 % faster.  Stores marked as non-temporal take 72.4, 20.6, 31.8 and 11.7, but batches 1 % and drafting passes 4 % more.
 typedef unsigned Store16 __attribute__((ext_vector_type(4)));
-__device__ __forceinline__ void store_through16(unsigned char* p, Store16 v) {
-    asm volatile("global_store_dwordx4 %0, %1, off sc1\n\ts_nop 0" : : "v"(p), "v"(v) : "memory");
+template <int OFFSET>
+__device__ __forceinline__ void store_through16(unsigned char* p, Store16 v) {   // at p + OFFSET, up to 4095
+    asm volatile("global_store_dwordx4 %0, %1, off offset:%2 sc1\n\ts_nop 0" : : "v"(p), "v"(v), "n"(OFFSET) : "memory");
 }
+template <class F, int... I> __device__ __forceinline__ void unrolled(F f, std::integer_sequence<int, I...>) { (f(std::integral_constant<int, I>{}), ...); }
+template <int N, class F> __device__ __forceinline__ void unrolled(F f) { unrolled(f, std::make_integer_sequence<int, N>{}); }
 
 // ---- Wave-wide reductions, result in every lane: four rotations inside each row of 16 lanes, then the 16-lane and
 // 32-lane swaps combine the four rows.  About ten vector instructions and no LDS traffic, where the shuffle intrinsics

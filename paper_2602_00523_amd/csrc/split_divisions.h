@@ -12,12 +12,12 @@ __host__ __device__ __forceinline__ int by_reciprocal(int x, float reciprocal) {
 }
 template <class Quotient>
 __host__ __device__ __forceinline__ int div_floor(int x, int y, Quotient quotient) {
-    if (x < (1 << 21)) return quotient(x, y);                // (uniform, and what there is: 67 million positions)
+    if (__builtin_expect(x < (1 << 21), 1)) return quotient(x, y);   // (uniform, and what there is: 67 million positions)
     return x / y;
 }
 // x / groups for x <= 256 and up to four column groups
 __host__ __device__ __forceinline__ int per_group(int x, int groups) {
-    return groups == 1 ? x : groups == 2 ? x >> 1 : groups == 3 ? (x * 171) >> 9 : x >> 2;
+    return (x * (groups == 1 ? 65536 : groups == 2 ? 32768 : groups == 3 ? 21846 : 16384)) >> 16;   // (no branches)
 }
 
 }  // namespace sage

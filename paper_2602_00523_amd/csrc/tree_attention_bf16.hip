@@ -47,10 +47,12 @@
 //   a block); with the scalar work out of the block (the loop once around the rings), 745.  Power then keeps the clock at 1.2-1.9 GHz,
 //   by machine and by how long the calls go on (80 layers in a row 82.4 -> 79.0 us a call); these MFMAs with this softmax and these
 //   LDS reads, and nothing else, take 610 cycles and reach 1.27 PFLOP/s.
-//   small trees: the stream, and at short contexts launch, two round trips and the merge launch.  12 nodes, 64/8 heads, 4096
-//   positions 12.5 -> 12.0 us, 32768 positions 31.6 -> 31.5; 15 nodes, 16384 positions 21.5 -> 21.4; three sequences of
-//   301 to 1999 positions 15.2 -> 15.0; eight of 2205 to 12133 53.8 -> 53.8; 28/4 heads, 3 new rows of 12, 2560 positions
-//   9.2 -> 8.7.
+//   small trees: the stream, and at short contexts launch, two round trips, the merge launch, and what is executed once: a call over
+//   4096 positions has its sizes after 0.9 us, has requested everything 1.0 us later and has it 0.6 us after that; five blocks take 3.5,
+//   the epilogue 1.2, and the merge ends 4.2 us after the last store.  12 nodes, 64/8 heads, 4096 positions 12.5 -> 11.7 us, 32768
+//   positions 31.6 -> 31.4; 15 nodes, 8192 positions 16.5 -> 15.4, 16384 22.1 -> 21.1 (up to 1.8 us more on some machines, where the
+//   stream is slower the sooner a block is requested); three sequences of 301 to 1999 positions 15.2 -> 14.4; eight of 2205 to 12133
+//   53.8 -> 53.5; 28/4 heads, 3 new rows of 12, 2560 positions 9.2 -> 8.6.
 #include <type_traits>
 
 #include "plan_device.h"
@@ -101,23 +103,33 @@ constexpr int PART_ROW_B = D * 2 + 16;   // (8 bytes of padding keep the rows 16
 constexpr int PART_SLOT_B = ROWS_PER_WG * PART_ROW_B;
 constexpr int EPI_ROW_B = PART_ROW_B;    // a parked row of the epilogue has the layout of a partial row
 static_assert(ROWS_PER_WG * EPI_ROW_B <= RING_B, "the rings hold the epilogue's rows");
+constexpr int TWO_STEP_ROWS = 128;      // groups of more rows take their reference in two steps (see the first two blocks)
 constexpr float RAISE_MIN = 4.0f;       // rebase() raises a row's reference maximum only past 2^4;
 constexpr float REBASE_PAST = 8.0f;     // it is called when a probability would pass 2^8
 constexpr float NO_REFERENCE = 3e38f;   // stands for -(reference * scale) while a row has none: every admitted key passes 2^8 then
 
+// (What the kernels read first stands first, in the fewest cache lines of the argument block.)
 struct Params {
     const uint16_t* Q; const uint16_t* Kc; const uint16_t* Vc; const uint16_t* Kt; const uint16_t* Vt;
-    uint16_t* O;
-    const int64_t* kv_start; const int* kv_len; const uint64_t* anc_mask; const int* n_nodes;
-    const int* first_node;               // nullable: rows are computed for nodes first_node[b] .. n_nodes[b] - 1 only
+    const uint64_t* anc_mask;
     unsigned char* part;                 // [B][Hkv][nslot] slots of PART_SLOT_B bytes; batched launches: [Hkv][nslot]
     long kv_token_stride, kv_head_stride;
-    int B, Hq, Hkv, G, nslot, min_blocks_per_split;
-    int nrange;                          // batched launches: ranges (workgroups) per KV head
+    int Hq, Hkv, G;
     int inv_G;                           // 65536 / G rounded up: (m * inv_G) >> 16 == m / G for the rows of a KV head
-    int merge_phases;                    // merge workgroups per (sequence, KV head)
     float scale_log2e;                   // softmax scale times log2(e): probabilities are exp2 of scaled differences
+    int B, nslot, min_blocks_per_split;
+    int nrange;                          // batched launches: ranges (workgroups) per KV head
+    int merge_phases;                    // merge workgroups per (sequence, KV head)
+    uint16_t* O;
+    const int64_t* kv_start; const int* kv_len; const int* n_nodes;
+    const int* first_node;               // nullable: rows are computed for nodes first_node[b] .. n_nodes[b] - 1 only
 };
+// Has the arguments of an attention workgroup on their way with the first ones (they come from memory, a round trip for every cache
+// line that is first asked for later): the empty statement needs them in registers where it stands.
+__device__ __forceinline__ void arguments_here(const Params& p) {
+    asm volatile("" : : "s"(p.Q), "s"(p.Kc), "s"(p.Vc), "s"(p.anc_mask), "s"(p.part), "s"(p.kv_token_stride), "s"(p.kv_head_stride),
+                 "s"(p.Hq), "s"(p.Hkv), "s"(p.G), "s"(p.inv_G), "s"(p.scale_log2e));
+}
 
 // blocks of the cache and of the tree's own keys
 __device__ __forceinline__ int blocks_of(int tokens) { return (tokens + BLK - 1) / BLK; }
@@ -188,17 +200,6 @@ __device__ __forceinline__ BatchShape make_batch_shape(const Params& prm, int la
 template <int N> __device__ __forceinline__ void wait_vm() {
     __builtin_amdgcn_s_waitcnt((N & 15) | (7 << 4) | (15 << 8) | ((N >> 4) << 14));
 }
-// ... until at most n loads are out (n wave-uniform, at most 4)
-__device__ __forceinline__ void wait_vm_upto(int n) {
-    switch (n) {
-        case 0: wait_vm<0>(); break;
-        case 1: wait_vm<1>(); break;
-        case 2: wait_vm<2>(); break;
-        case 3: wait_vm<3>(); break;
-        default: wait_vm<4>(); break;
-    }
-}
-
 // Workgroup barrier of the stage ring.  __syncthreads() would also fence, and a workgroup-scope release makes the
 // compiler wait for every LDS-direct load still in flight, which is exactly what the ring must not do: each
 // thread has already waited for its own share of the block (wait_vm), LDS needs no cache maintenance, so the bare
@@ -240,7 +241,7 @@ struct Segment {
     int b, g, L, n, node0, rows, cg;     // sequence, KV head, cache length, nodes, first node computed, rows, column group
     int begin, count, cache_blocks;      // blocks begin .. begin + count - 1 (count >= 1); those from cache_blocks on are the tree's
     long kv_start;
-    unsigned char* out;                  // the partial
+    int slot;                            // of the partial
 };
 
 // One pass: the blocks of a segment for one column group.  Wave w owns column tile w, 32 rows, and processes every block for it
@@ -270,9 +271,7 @@ __device__ __forceinline__ void attention_pass(const Params& prm, LDS_AS Lds* ld
     const unsigned k_chunk_b = ((lane & 15) ^ ((lane >> 4) & 1)) * 16;
     const unsigned v_chunk_b = (lane & 15) * 16;
     const unsigned cache_row_b = static_cast<unsigned>(prm.kv_token_stride) * 2u;   // host: 32 rows fit 32 bits
-    const unsigned tree_row_b = static_cast<unsigned>(prm.Hkv) * D * 2u;
     const long cache_at = sg.kv_start * prm.kv_token_stride + static_cast<long>(sg.g) * prm.kv_head_stride;
-    const long tree_at = (static_cast<long>(sg.b) * SAGE_MAX_NODES * prm.Hkv + sg.g) * D;
     const unsigned k_off = static_cast<unsigned>(ld_tok) * cache_row_b + k_chunk_b;
     const unsigned v_off = static_cast<unsigned>(ld_tok) * cache_row_b + v_chunk_b;
     const int full = min(H, max(0, sg.L / BLK - sg.begin));  // leading blocks that are whole blocks of the cache
@@ -287,7 +286,8 @@ __device__ __forceinline__ void attention_pass(const Params& prm, LDS_AS Lds* ld
         const int blk = sg.begin + h;
         const bool is_tree = blk >= sg.cache_blocks;
         const int tb = is_tree ? blk - sg.cache_blocks : blk;
-        const unsigned row_b = is_tree ? tree_row_b : cache_row_b;
+        const long tree_at = (static_cast<long>(sg.b) * SAGE_MAX_NODES * prm.Hkv + sg.g) * D;
+        const unsigned row_b = is_tree ? static_cast<unsigned>(prm.Hkv) * D * 2u : cache_row_b;
         At l;
         l.base = reinterpret_cast<const unsigned char*>(is_tree ? (V ? prm.Vt : prm.Kt) + tree_at : (V ? prm.Vc : prm.Kc) + cache_at) +
                  static_cast<long>(tb) * BLK * row_b;
@@ -297,60 +297,66 @@ __device__ __forceinline__ void attention_pass(const Params& prm, LDS_AS Lds* ld
         return l;
     };
     auto slot_of = [&](int h) __attribute__((always_inline)) { return static_cast<unsigned>(h + slot0) % SLOTS; };
-    auto issue = [&](auto is_v, int h) __attribute__((always_inline)) {
+    auto issue = [&](auto is_v, int h, const unsigned char* in_cache) __attribute__((always_inline)) {   // in_cache: where it is if a whole block of the cache
         constexpr bool V = decltype(is_v)::value;
         if (h >= H) return;
         At l;
-        if (h < full) l = At{(V ? v_cache : k_cache) + h * static_cast<long>(block_b), V ? v_off : k_off};
+        if (h < full) l = At{in_cache, V ? v_off : k_off};
         else l = locate(is_v, h);
         sage::lds_direct_load16(l.base, l.off, ring + (V ? V_AT + slot_of(h) * V_BLOCK_B + wave * V_GROUP : slot_of(h) * K_BLOCK_B + wave * K_GROUP));
     };
     using IsK = std::false_type;
     using IsV = std::true_type;
+    const unsigned char* k_next = k_cache + 4 * block_b;     // block h + 4 of K, block h + 2 of V
+    const unsigned char* v_next = v_cache + 2 * block_b;
     // Before unit h: K of block h + 2 and V of block h have landed for every wave, and the slots of K of block h and V of block
     // h - 2 are free (an MFMA of unit h - 1 has used what was read from them).  Loads complete in order, and what was
     // requested after the two, V of block h + 1 and K of block h + 3, is out at most.  This is the way of the first and last blocks;
     // in the middle (see the loop) nothing is left to decide.
     auto arrive = [&](int h) __attribute__((always_inline)) {
-        wait_vm_upto((h + 1 < H ? 1 : 0) + (h + 3 < H ? 1 : 0));
+        if (h + 3 < H) wait_vm<2>();
+        else if (h + 1 < H) wait_vm<1>();
+        else wait_vm<0>();
         stage_barrier();
-        issue(IsV{}, h + 2);
-        issue(IsK{}, h + 4);
+        issue(IsV{}, h + 2, v_next);
+        issue(IsK{}, h + 4, k_next);
+        v_next += block_b;
+        k_next += block_b;
     };
 
     // Everything the prologue needs from memory goes straight into LDS, requested back to back in this order: the wave's
     // ancestor masks, its Q rows, the first blocks.  No load of the kernel returns into a
     // register, so the compiler never waits on the vector-memory counter here and the only waits are the counted ones.
     // Rows past the group's last one repeat that row (their results are never written).
-    auto row_of = [&](int local) __attribute__((always_inline)) {      // row `local` of this group -> (node, head in group)
-        const int mm = min(sg.cg * ROWS_PER_WG + local, sg.rows - 1);
-        const int nd = (mm * inv_G) >> 16;                               // exact for mm < 64 G, G <= 16
-        return make_int2(sg.node0 + nd, mm - nd * prm.G);
+    auto row_of = [&](int local) __attribute__((always_inline)) {      // row `local` of this group, of the rows of the KV head
+        return static_cast<unsigned>(min(sg.cg * ROWS_PER_WG + local, sg.rows - 1));
     };
+    auto node_of = [&](unsigned m) __attribute__((always_inline)) { return (m * static_cast<unsigned>(inv_G)) >> 16; };   // exact for m < 64 G, G <= 16
     // Q rows as tiles of 32 in the layout of a K block: row q of a tile sits at (q % 8) * K_GROUP + (q / 8) * ROW_B
     LDS_AS unsigned char* const q_tile = ring + Q_AT + wave * Q_TILE_B;
     if (active) {
         {                                                    // both words of the masks of rows lane / 2
-            const int2 r = row_of(row0 + (lane >> 1));
-            sage::lds_direct_load4(reinterpret_cast<const unsigned char*>(prm.anc_mask + static_cast<long>(sg.b) * SAGE_MAX_NODES + r.x) + (lane & 1) * 4,
-                                   (LDS_AS unsigned char*)(&lds->mask[row0]));
+            const unsigned char* masks = reinterpret_cast<const unsigned char*>(prm.anc_mask + static_cast<long>(sg.b) * SAGE_MAX_NODES + sg.node0);
+            sage::lds_direct_load4(masks + (node_of(row_of(row0 + (lane >> 1))) * 8u + (lane & 1) * 4u), (LDS_AS unsigned char*)(&lds->mask[row0]));
         }
+        const unsigned char* q_rows = reinterpret_cast<const unsigned char*>(prm.Q + ((static_cast<long>(sg.b) * SAGE_MAX_NODES + sg.node0) * prm.Hq + sg.g * prm.G) * D);
+        const unsigned node_b = static_cast<unsigned>(prm.Hq - prm.G) * (D * 2u);   // (64 nodes of up to 65535 heads: within 32 bits)
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
-            const int2 r = row_of(row0 + i + 8 * (lane >> 4));
-            const unsigned char* src = reinterpret_cast<const unsigned char*>(
-                prm.Q + ((static_cast<long>(sg.b) * SAGE_MAX_NODES + r.x) * prm.Hq + sg.g * prm.G + r.y) * D) + k_chunk_b;
-            sage::lds_direct_load16(src, q_tile + i * K_GROUP);
+            const unsigned m = row_of(row0 + i + 8 * (lane >> 4));
+            sage::lds_direct_load16(q_rows, node_of(m) * node_b + m * (D * 2u) + k_chunk_b, q_tile + i * K_GROUP);
         }
     }
-    issue(IsK{}, 0);
-    issue(IsK{}, 1);
-    issue(IsV{}, 0);
-    issue(IsK{}, 2);
-    issue(IsV{}, 1);
-    issue(IsK{}, 3);
+    issue(IsK{}, 0, k_cache);
+    issue(IsK{}, 1, k_cache + block_b);
+    issue(IsV{}, 0, v_cache);
+    issue(IsK{}, 2, k_cache + 2 * block_b);
+    issue(IsV{}, 1, v_cache + block_b);
+    issue(IsK{}, 3, k_cache + 3 * block_b);
     *(LDS_AS u32x4*)(ring + ZERO_AT + lane * 16) = u32x4{0, 0, 0, 0};   // (by every wave, which reads it after its own write)
-    wait_vm_upto(min(2, H) + min(2, max(0, H - 2)));         // masks, Q and the first two blocks of K have landed
+    if (H >= 4) wait_vm<4>();                                // masks, Q and the first two blocks of K have landed
+    else if (H == 2) wait_vm<2>();
+    else wait_vm<0>();
     stage_barrier();                                         // ... everyone's have
 
     if (!active) {                                           // no rows: this wave only brings its share of the blocks
@@ -458,8 +464,6 @@ __device__ __forceinline__ void attention_pass(const Params& prm, LDS_AS Lds* ld
     // Unit h; CUR = which of the two score and probability sets, its parity counted from the end of the pass.  `usual`: the
     // blocks in SLOT and around it are whole blocks of the cache, and so are those that are requested.
     const unsigned k_dst = wave * K_GROUP, v_dst = V_AT + wave * V_GROUP;
-    const unsigned char* k_next;                             // (usual units) K of block h + 4, V of block h + 2
-    const unsigned char* v_next;
     auto unit = [&](auto is_usual, auto slot, auto cur, const int h) __attribute__((always_inline)) {
         constexpr bool USUAL = decltype(is_usual)::value;
         constexpr int SLOT = decltype(slot)::value, CUR = decltype(cur)::value;
@@ -482,9 +486,22 @@ __device__ __forceinline__ void attention_pass(const Params& prm, LDS_AS Lds* ld
                 if (h >= full) mask_scores(s, h);
                 // The reference of a pass is the maximum of its first two blocks (64 tokens), so that the largest probability of a short
                 // pass is exactly one in bf16.  Error against 64 bits, 28/4 heads over 2560 positions: 2.61-2.65e-3 (2.69-2.75e-3 with the
-                // first block's maximum, 2.64-2.68e-3 before); 0.2-0.3 us of a short call.
+                // first block's maximum).  In larger groups block 0 keeps its probabilities, and its products are rescaled: 0.2-0.6 % smaller
+                // errors, but 64 instructions more, 0.2 us of a short call.
                 if (h == 0) rebase(s, true, RAISE_MIN);
-                if (h == 1) most = INFINITY;                 // (the reference moves after this unit's MFMAs, below)
+                if (h == 1) {
+                    if (group_rows > TWO_STEP_ROWS) {
+                        most = INFINITY;                     // (the reference moves after this unit's MFMAs, below)
+                    } else {                                 // (block 0 has not been multiplied yet: its probabilities again)
+                        rebase(s, true, 0.f);
+                        float neg_mc_now = neg_mc;
+                        PIN(neg_mc_now);
+#pragma unroll
+                        for (int i = 0; i < 16; i += 2)
+                            pack2(pf[1 - CUR][i >> 3], i & 7, __builtin_amdgcn_exp2f(fmaf(next[i], c_log2, neg_mc_now)),
+                                  __builtin_amdgcn_exp2f(fmaf(next[i + 1], c_log2, neg_mc_now)));
+                    }
+                }
             }
         }
         bf16x8 (&p)[2] = pf[CUR];
@@ -612,8 +629,6 @@ __device__ __forceinline__ void attention_pass(const Params& prm, LDS_AS Lds* ld
         h += 2;
         // Four units at a time, once around the rings: every address is a compile-time offset.  Block h is in slot 0 now (2 or 3 blocks
         // are done, and what slot0 is comes from that); past the last of these units this is not reached again with enough blocks left.
-        k_next = k_cache + (h + 4) * static_cast<long>(block_b);
-        v_next = v_cache + (h + 2) * static_cast<long>(block_b);
         while (h + 7 < full) {
             wait_vm<2>();
             stage_barrier();
@@ -663,15 +678,16 @@ __device__ __forceinline__ void attention_pass(const Params& prm, LDS_AS Lds* ld
     const int last_chunk = min(32, group_rows - row0) * (PART_ROW_B / 16);
     // They are written through the L2 (see store_through16): what a kernel leaves in an L2 is written back at its end, before the merge
     // may start, and 64 nodes leave 17 MB.
-    unsigned char* const out = sg.out + static_cast<long>(row0) * PART_ROW_B;
+    unsigned char* const out = prm.part + static_cast<long>(sg.slot) * PART_SLOT_B + row0 * PART_ROW_B + lane * 16;
     constexpr int COPIES = (32 * (PART_ROW_B / 16) + 63) / 64;
     u32x4 chunk[COPIES];
 #pragma unroll
     for (int i = 0; i < COPIES; ++i) chunk[i] = *reinterpret_cast<LDS_AS u32x4*>(mine + (lane + 64 * i) * 16);
     __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-    for (int i = 0; i < COPIES; ++i)
-        if (lane + 64 * i < last_chunk) sage::store_through16(out + (lane + 64 * i) * 16, chunk[i]);
+    sage::unrolled<COPIES>([&](auto i) __attribute__((always_inline)) {
+        constexpr int I = decltype(i)::value;
+        if (lane + 64 * I < last_chunk) sage::store_through16<I % 4 * 1024>(out + I / 4 * 4096, chunk[I]);
+    });
 }
 
 // BATCH = false: one sequence per launch slot, every (sequence, KV head) cut into equal splits (see make_split).
@@ -704,7 +720,7 @@ __device__ __forceinline__ void attention_workgroup(const int* __restrict__ kv_l
         sg.b = uni(v.b); sg.g = g; sg.L = uni(v.L); sg.n = uni(v.n); sg.node0 = uni(v.node0); sg.rows = uni(v.rows); sg.cg = uni(v.cg);
         sg.begin = uni(v.begin); sg.count = uni(v.count); sg.cache_blocks = uni(v.cache_blocks);
         sg.kv_start = static_cast<long>(uni64(static_cast<uint64_t>(v.kv_start)));
-        sg.out = reinterpret_cast<unsigned char*>(uni64(reinterpret_cast<uint64_t>(v.out)));
+        sg.slot = uni(v.slot);
         if (BATCH) __syncthreads();                          // the previous segment's epilogue has left the ring
         // A batched workgroup calls this in a loop.  Everything that depends only on the thread index would be
         // loop-invariant, and the compiler hoists all of it out of the loop and keeps it alive across the whole pass.
@@ -725,6 +741,7 @@ __device__ __forceinline__ void attention_workgroup(const int* __restrict__ kv_l
         int start_lo = __builtin_amdgcn_readfirstlane(static_cast<int>(static_cast<uint32_t>(start_w)));
         int start_hi = __builtin_amdgcn_readfirstlane(static_cast<int>(start_w >> 32));
         int f_b = first_node_arg ? __builtin_amdgcn_readfirstlane(first_node_arg[b]) : 0;   // (a uniform branch on an argument)
+        arguments_here(prm);
         asm("" : "+s"(len_b), "+s"(n_b), "+s"(start_lo), "+s"(start_hi), "+s"(f_b));
         const long start_b = (static_cast<long>(start_hi) << 32) | static_cast<uint32_t>(start_lo);
         const int L = len_b > 0 ? len_b : 0;
@@ -735,12 +752,13 @@ __device__ __forceinline__ void attention_workgroup(const int* __restrict__ kv_l
         if (split >= sp.nsplit) return;
         const int begin = split * sp.blocks_per_split;
         run_segment(Segment{b, g, L, sp.n, sp.first, sp.rows, cg, begin, min(sp.blocks - begin, sp.blocks_per_split), blocks_of(L),
-                            start_b, prm.part + ((static_cast<long>(b) * prm.Hkv + g) * prm.nslot + cg * sp.max_split + split) * PART_SLOT_B});
+                            start_b, (b * prm.Hkv + g) * prm.nslot + cg * sp.max_split + split});
     } else {
         const int lane = threadIdx.x & 63;
         int r0, r1, line;                                    // this workgroup's range of the list; lane b: sequence b's positions, column groups
         {
             const BatchShape bs = make_batch_shape(prm, lane);   // lane b holds sequence b
+            arguments_here(prm);
             r0 = id * bs.q;
             r1 = min(bs.total, r0 + bs.q);
             if (r0 >= r1) return;
@@ -762,7 +780,7 @@ __device__ __forceinline__ void attention_workgroup(const int* __restrict__ kv_l
                     const int lo = max(r0, block0), hi = min(r1, block0 + seg_len - SEG_COST);
                     if (lo < hi)
                         run_segment(Segment{b, g, L_b, n_b, f_b, (n_b - f_b) * prm.G, cg, lo - block0, hi - lo, blocks_of(L_b), start_b,
-                                            prm.part + (static_cast<long>(g) * prm.nslot + id + groups_before + cg) * PART_SLOT_B});
+                                            g * prm.nslot + id + groups_before + cg});
                 }
             }
             first += seg_len * cgs_b;
