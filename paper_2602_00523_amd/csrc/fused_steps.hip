@@ -66,16 +66,7 @@ __global__ __launch_bounds__(64 * ACCEPT_WAVES) void accept_kernel(const int* __
     const int lane = threadIdx.x & 63;
     const int wave = threadIdx.x >> 6;
     const long base = static_cast<long>(b) * SAGE_MAX_NODES;
-    // Wave 0 asks for its node fields now, ahead of the node count (every sequence has the 64 slots), and what the closing needs is
-    // asked for with it: both arrive while the reductions run.
-    int par = -1, tok = 0, dep = 0;
-    uint64_t am = 0;
-    if (wave == 0) {
-        par = parent[base + lane];
-        tok = token[base + lane];
-        dep = depth[base + lane];
-        am = anc_mask[base + lane];
-    }
+    // (what the closing needs is asked for with the node count)
     int n = n_nodes[b], len_b = 0;
     int64_t start = 0;
     sage::closing::HistoryState was{};
@@ -86,6 +77,16 @@ __global__ __launch_bounds__(64 * ACCEPT_WAVES) void accept_kernel(const int* __
         asm("" : "+s"(n), "+s"(len_b), "+s"(start));
     }
     n = n < 1 ? 1 : (n > SAGE_MAX_NODES ? SAGE_MAX_NODES : n);
+
+    // wave 0 asks for its node fields now, so they arrive while the reductions run
+    int par = -1, tok = 0, dep = 0;
+    uint64_t am = 0;
+    if (wave == 0 && lane < n) {
+        par = parent[base + lane];
+        tok = token[base + lane];
+        dep = depth[base + lane];
+        am = anc_mask[base + lane];
+    }
 
     // ---- with few lists per lane all of this wave's rows are requested before the first one is reduced (one memory
     //      round trip); with many, a row at a time, to stay within the register file
