@@ -2,7 +2,7 @@
 // (Sec. 3.1: Eq. 7 renormalised top-k, Eq. 8 its entropy, Eq. 9 confidence; Eq. 1 softmax) and, with k = 1,
 // the target's greedy token per tree node (Sec. 2.2 / Def. 4.1).
 //
-// HBM-bound: every logit is read exactly once with 16-byte loads.  Candidates are ordered by a 64-bit composite key (value
+// Every logit is read exactly once with 16-byte loads.  Candidates are ordered by a 64-bit composite key (value
 // descending, index ascending).  Pass 1 cuts a row into slices of UNIT logits: with k = 1 each WAVE owns a slice and takes
 // its maximum, done with DPP row rotations and the 16/32-lane swaps (no LDS, no workgroup barrier); with k > 1 a workgroup
 // owns it, each wave finds what its k best logits reach and the survivors are ranked by counting.  Either reduces the
@@ -46,10 +46,11 @@ template <> struct Loader<uint16_t> {
     __device__ static float one(const uint16_t* p) { return sage::bf16_bits_to_float(*p); }
 };
 
-// Pass 1 for k = 1 (many rows, one candidate per slice): one wave per (slice, row), 16 logits per lane.  HBM-bound,
-// so the arithmetic per logit is kept to a compare-and-select for the argmax (strictly greater in index order keeps
-// the lowest index among equals, the same total order as the composite key) and, once the slice maximum is known,
-// one exp2 and two fused multiply-adds for the statistics.  Differences to the maximum are capped at 87, where
+// Pass 1 for k = 1 (many rows, one candidate per slice): one wave per (slice, row), 16 logits per lane.  What bounds it with many
+// rows is what a wave executes, about as long as the stream takes, so that is kept short: the maximum by three-operand maxima,
+// its place by ballots once it is known (a compare and two selects per logit before), both sums through one chain of lane exchanges, and no
+// look at the row's end in whole slices.  512 rows of 152064 bf16 logits, whole call: 38.9 -> 37.8 us.  The statistics are an exp2 and five
+// operations per logit.  Differences to the maximum are capped at 87, where
 // exp is below 2^-125: a -inf logit or a padding slot then adds about 1e-38 instead of 0 to sums that are >= 1.
 //
 // The 16-byte loads of a (row, slice) are requested by request_unit and consumed by reduce_unit, so that a wave that
@@ -58,11 +59,32 @@ template <typename T, int NV>
 __device__ __forceinline__ void request_unit(const T* __restrict__ rowp, int base, int lane, int vocab,
                                              typename Loader<T>::Raw (&raw)[NV]) {
     using L = Loader<T>;
+    if (base + UNIT <= vocab) {                          // a whole slice (wave-uniform)
+#pragma unroll
+        for (int j = 0; j < NV; ++j) raw[j] = L::fetch(rowp + base + (j * 64 + lane) * L::VEC);
+        return;
+    }
 #pragma unroll
     for (int j = 0; j < NV; ++j) {
         const int e0 = base + (j * 64 + lane) * L::VEC;
         if (e0 + L::VEC <= vocab) raw[j] = L::fetch(rowp + e0);      // the ragged end is read element by element later
     }
+}
+// The larger of three numbers, as the instruction has it (fmaxf() would first make every operand that comes from memory canonical).
+__device__ __forceinline__ float max3(float a, float b, float c) {
+    float r;
+    asm("v_max3_f32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
+    return r;
+}
+// Sums of two values over the wave, in every lane: the two share a wave from the first exchange on.
+__device__ __forceinline__ void wave_sums(float& a, float& b) {
+    auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+    float v = __uint_as_float(r[0]) + __uint_as_float(r[1]);   // a in lanes 0 to 31, b in the others
+    r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    v = __uint_as_float(r[0]) + __uint_as_float(r[1]);
+    v += sage::f_dpp<0x128>(v); v += sage::f_dpp<0x124>(v); v += sage::f_dpp<0x122>(v); v += sage::f_dpp<0x121>(v);
+    a = sage::lane_value(v, 0);
+    b = sage::lane_value(v, 32);
 }
 // (returned in every lane, and stored)
 struct Reduced { UnitStats stats; uint64_t key; };
@@ -73,33 +95,36 @@ __device__ __forceinline__ Reduced reduce_unit(const T* __restrict__ rowp, int b
     using L = Loader<T>;
     constexpr int VEC = L::VEC;
     float v[EPT];
-    int first[NV];
+    if (base + UNIT <= vocab) {                          // a whole slice (wave-uniform)
 #pragma unroll
-    for (int j = 0; j < NV; ++j) {
-        const int e0 = base + (j * 64 + lane) * VEC;
-        first[j] = e0;
-        if (e0 + VEC <= vocab) {
-            L::unpack(raw[j], v + j * VEC);
-        } else {
+        for (int j = 0; j < NV; ++j) L::unpack(raw[j], v + j * VEC);
+    } else {
 #pragma unroll
-            for (int e = 0; e < VEC; ++e) v[j * VEC + e] = (e0 + e < vocab) ? L::one(rowp + e0 + e) : -INFINITY;
+        for (int j = 0; j < NV; ++j) {
+            const int e0 = base + (j * 64 + lane) * VEC;
+            if (e0 + VEC <= vocab) {
+                L::unpack(raw[j], v + j * VEC);
+            } else {
+#pragma unroll
+                for (int e = 0; e < VEC; ++e) v[j * VEC + e] = (e0 + e < vocab) ? L::one(rowp + e0 + e) : -INFINITY;
+            }
         }
     }
 
-    // ---- this lane's best candidate, then the slice's
-    float bv = v[0];
-    int bi = first[0];
+    // ---- the slice's best candidate: the largest value, at its lowest index.  Indices ascend by load, lane and element: the first load
+    // that has the value, its first lane, that lane's first element.
+    float most[NV];
 #pragma unroll
-    for (int s = 1; s < EPT; ++s) {
-        const int idx = first[s / VEC] + (s % VEC);
-        const bool better = v[s] > bv;                       // indices ascend with s: equal values keep the earlier one
-        bv = better ? v[s] : bv;
-        bi = better ? idx : bi;
+    for (int j = 0; j < NV; ++j) {
+        most[j] = v[j * VEC];
+#pragma unroll
+        for (int e = 1; e + 1 < VEC; e += 2) most[j] = max3(most[j], v[j * VEC + e], v[j * VEC + e + 1]);
+        most[j] = max3(most[j], v[j * VEC + VEC - 1], v[j * VEC + VEC - 1]);
     }
-    const Key g = wave_max_key(bi < vocab ? make_key(bv, bi) : Key{0, 0});   // a lane past the end starts past the end
-    const float unit_max = key_none(g) ? -INFINITY : key_value(g);
-    if (lane == 0) *key_out = key_pack(g);
-
+    float unit_max = most[0];
+#pragma unroll
+    for (int j = 1; j < NV; ++j) unit_max = max3(unit_max, most[j], most[j]);
+    unit_max = wave_max(unit_max) + 0.f;                 // (-0 is +0, as in the key)
     // ---- softmax statistics of the slice relative to its own maximum
     float Z = 0.f, Tm = 0.f;
     if (unit_max > -INFINITY) {
@@ -111,8 +136,26 @@ __device__ __forceinline__ Reduced reduce_unit(const T* __restrict__ rowp, int b
             Tm = fmaf(e, dlt, Tm);
         }
     }
-    Z = wave_sum(Z);
-    Tm = wave_sum(Tm);
+    int at = base;                                       // (a slice without a number: a token of the row all the same)
+    bool found = false;
+#pragma unroll
+    for (int j = 0; j < NV; ++j) {
+        if (found) continue;                             // (wave-uniform)
+        const uint64_t holders = __ballot(most[j] == unit_max);
+        if (holders == 0) continue;
+        found = true;
+        const int holder = __builtin_ctzll(holders);
+        int element = VEC - 1;
+#pragma unroll
+        for (int e = VEC - 2; e >= 0; --e)
+            if ((__ballot(v[j * VEC + e] == unit_max) >> holder) & 1) element = e;
+        at = base + (j * 64 + holder) * VEC + element;
+    }
+    // (no value is larger than what fills a lane past the end, so that one of those may be the holder only of a value that index `base` has)
+    if (at >= vocab) at = base;
+    const Key g = make_key(unit_max, at);
+    if (lane == 0) *key_out = key_pack(g);
+    wave_sums(Z, Tm);
     if (lane == 0) *stat_out = UnitStats{unit_max, Z, Tm, 0.f};
     return Reduced{UnitStats{unit_max, Z, Tm, 0.f}, key_pack(g)};
 }
@@ -139,8 +182,11 @@ __global__ __launch_bounds__(THREADS) void slice_kernel(const T* __restrict__ lo
 // Phases: with one or two groups every live row may have its workgroups at once (64 live rows of 152064 in one group, first
 // pass 8.4 -> 6.6 us, 40 in each of two 8.9 -> 7.9; 12 rows 3.1 either way).  With more groups 16 of them fill the chip, and the
 // workgroups of dead rows that more would add show (8 x 12 rows 8.5 us at 16, 9.1 at 32, 9.7 at 64).
-inline int row_phases(int groups, int rows_per_group) {
-    const int phases = groups == 1 ? 64 : groups == 2 ? 32 : 16;
+// By themselves the slice passes of more groups take 22, so that a workgroup of a full group walks three rows and not four (512 live rows
+// 38.9 -> 38.5 us, 320 of 512 26.4 -> 25.0, 150 of 320 12.9 -> 12.3); beside a draft row's, in a step, whose trees are seldom full,
+// 16 (eight sequences of 12 nodes 0.5 us a step).
+inline int row_phases(int groups, int rows_per_group, bool in_a_step) {
+    const int phases = groups == 1 ? 64 : groups == 2 ? 32 : in_a_step ? 16 : 22;
     return rows_per_group < phases ? rows_per_group : phases;
 }
 template <typename T>
@@ -696,7 +742,7 @@ static int run_first_pass(const void* logits, int dtype, int rows, int vocab, lo
                                vocab, row_stride, nunits, stats, keys);
     } else if (k == 1) {                             // grouped rows: workgroups walk the live rows of their group
         const int groups = (rows + rows_per_group - 1) / rows_per_group;
-        const dim3 grid((nunits + WAVES - 1) / WAVES, row_phases(groups, rows_per_group), groups);
+        const dim3 grid((nunits + WAVES - 1) / WAVES, row_phases(groups, rows_per_group, false), groups);
         if (dtype == SAGE_F32)
             hipLaunchKernelGGL(slice_rows_kernel<float>, grid, dim3(THREADS), 0, s, static_cast<const float*>(logits), vocab,
                                row_stride, n_valid, rows_per_group, rows, nunits, stats, keys);
@@ -781,7 +827,7 @@ extern "C" int sage_entropy_topk_slices_pair(const void* logits_a, int rows_a, l
     b.stats = static_cast<UnitStats*>(workspace_b);
     b.keys = reinterpret_cast<uint64_t*>(static_cast<char*>(workspace_b) + stats_bytes(rows_b, vocab));
     const int groups = (rows_a + rows_per_group_a - 1) / rows_per_group_a;
-    const int gx = (nunits + WAVES - 1) / WAVES, gy = row_phases(groups, rows_per_group_a);
+    const int gx = (nunits + WAVES - 1) / WAVES, gy = row_phases(groups, rows_per_group_a, true);
     const long blocks_b = static_cast<long>(nunits) * rows_b;
     const long slabs_b = (blocks_b + static_cast<long>(gx) * gy - 1) / (static_cast<long>(gx) * gy);
     if (slabs_b + groups > 65535) return SAGE_UNSUPPORTED;
