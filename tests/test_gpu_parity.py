@@ -180,6 +180,31 @@ def test_entropy_topk_row_groups_k1_shapes(gu, rows, rpg, n_valid, vocab, dtype)
     check_entropy(gu, wl.to_storage(z, dtype), 1, np.array(n_valid, np.int32), rpg)
 
 
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("vocab", [1024, 1025, 2048, 3001, 9000])
+def test_greedy_token_among_equal_maxima(gu, vocab, dtype):
+    """k = 1: the first of equal largest logits, wherever in a slice they are (loads, lanes, elements of a lane, slices), zeros of
+    both signs, slices of -inf only, a row whose only number is its last logit; the two-group and three-group phases of rows."""
+    rng = wl.rng(vocab)
+    rows, pairs = 192, [0, 1, 7, 8, 63, 64, 255, 256, 511, 512, 1023, vocab - 2, vocab - 1]
+    x = rng.standard_normal((rows, vocab)).astype(np.float32)
+    for r in range(rows):
+        if r % 4 == 0:                                    # a pair at places of note
+            x[r, [pairs[r // 4 % 13], pairs[(r // 4 * 5 + 3) % 13]]] = 9.0
+        elif r % 4 == 1:                                  # several anywhere
+            x[r, rng.integers(0, vocab, 5)] = 9.0
+        elif r % 4 == 2:                                  # zeros of either sign are the largest, and equal
+            x[r] = -np.abs(x[r]) - 0.5
+            x[r, rng.integers(0, vocab, 4)] = np.array([0.0, -0.0, 0.0, -0.0], np.float32)
+        else:
+            x[r] = -np.inf
+            x[r, vocab - 1 if r & 4 else rng.integers(0, vocab)] = -3.0
+    x = wl.to_storage(np.pad(x, ((0, 0), (0, -vocab % 16))), dtype)[:, :vocab]
+    for groups in (1, 2, 3):
+        rpg = 64 * 3 // groups
+        check_entropy(gu, x, 1, np.full(groups, rpg, np.int32), rpg)
+
+
 @pytest.mark.parametrize("k", [4, 8, 9, 40])
 @pytest.mark.parametrize("bits", [0x7FFFFFFF, 0xFFFFFFFF])
 def test_topk_of_extreme_nans(gu, bits, k):
@@ -500,6 +525,25 @@ def test_attention_bf16_pass_lengths(gu, nodes, blocks, tail):
     L = max(32 * (splits * blocks - tree) - tail, 0)
     inp = wl.attention_inputs(5000 + nodes + blocks, 1, Hq, Hkv, 128, [L], "bf16", pad_tokens=2)
     if blocks & 1 and L:
+        ramp = np.linspace(0.5, 24.0, L, dtype=np.float32)[:, None, None]
+        inp["Kc"][:L] = wl.f32_to_bf16_bits(wl.bf16_bits_to_f32(inp["Kc"][:L]) * ramp)
+    mask, nn = tree_batch(wl.rng(blocks), 1, [nodes])
+    ref = oracle.tree_attention(inp["Q"], inp["Kc"], inp["Vc"], inp["Kt"], inp["Vt"], inp["kv_start"], inp["kv_len"],
+                                inp["kv_token_stride"], inp["kv_head_stride"], mask, nn, Hq, Hkv, 128)
+    got, _ = gu.gpu_tree_attention(inp, mask, nn, Hq, Hkv, 128, fill=12345.0)
+    gu.assert_attention_close(got, ref, nn, TOL["bf16"])
+
+
+@pytest.mark.parametrize("nodes", [4, 17, 33])
+@pytest.mark.parametrize("blocks,tail", [(8, 0), (9, 1), (10, 31), (11, 0), (12, 16), (13, 1), (14, 0), (15, 31), (19, 1)])
+def test_attention_bf16_long_passes(gu, nodes, blocks, tail):
+    """Passes of `blocks` blocks about the lengths at which the loop takes none, one, two or three rounds of four blocks, full and
+    with a cut last cache block; scores that grow in every other, so that the reference moves inside the rounds."""
+    Hq, Hkv = 512, 64
+    splits, tree = (2 if nodes > 32 else 4), (2 if nodes > 32 else 1)
+    L = 32 * (splits * blocks - tree) - tail
+    inp = wl.attention_inputs(5500 + nodes + blocks, 1, Hq, Hkv, 128, [L], "bf16", pad_tokens=2)
+    if blocks & 1:
         ramp = np.linspace(0.5, 24.0, L, dtype=np.float32)[:, None, None]
         inp["Kc"][:L] = wl.f32_to_bf16_bits(wl.bf16_bits_to_f32(inp["Kc"][:L]) * ramp)
     mask, nn = tree_batch(wl.rng(blocks), 1, [nodes])
