@@ -91,14 +91,15 @@ __device__ __forceinline__ void stage_barrier() {
 // TOPK: k candidates per (row, unit) instead of one (the draft side of Sec. 3.1, whose rows are few), after the fold, at the
 // end of every workgroup's only unit, when no loads are in flight.  Two ways, by the number of live rows and k:
 //   counting: the unit's logits of 32 rows at a time are laid out in the idle ring and a wave per row finds a value that at
-//     least k and at most 64 of them reach (about nine bits of a threshold, a ballot per 64 logits and bit), then ranks those
-//     by counting, four rows side by side: 1.0 us a live row (T = 10; T = 5: 0.3 to 0.45), whatever k;
+//     least k and at most 64 of them reach (the lanes' largest ones give it, a ballot a bit, and rarely too low; a ballot per 64
+//     logits and bit, about nine bits, took twice as long), then ranks those by counting, four rows side by side: 0.52 us a live
+//     row (T = 10; before 1.0), 0.45 (T = 5), whatever k.  16 rows of 3584, k = 10, T = 10, whole call: 217.2 -> 209.8 us;
 //   rounds: every lane scans its 16 T logits for the best one after the previous winner, the four lanes of a row are combined
 //     (lane halves by a swap, vocabulary halves through LDS): 3.1 us each (T = 5: 1.6), whatever the rows.
-// LIST_ROWS_PER_K live rows per candidate is where the two meet, within 1 us of it for every k (us of the call, counting /
-// rounds; vocabulary 152064, hidden 1024, T = 10: 16 rows k = 4 80.8 / 77.3 and k = 8 81.2 / 89.1, 32 rows k = 8 96.5 / 89.2
-// and k = 12 97.0 / 101.0, 64 rows k = 16 132 / 114; vocabulary 32000, hidden 3584, T = 5: 16 rows k = 3 72.1 / 68.3 and k = 6
-// 72.6 / 73.5, 64 rows k = 16 92.6 / 90.6).
+// LIST_ROWS_PER_K live rows per candidate is where the two meet, within 2 us of it for every k (us of the call, counting /
+// rounds; vocabulary 152064, hidden 1024, T = 10: 16 rows k = 4 73.7 / 78.3, 24 rows k = 6 77.5 / 84.0, 32 rows k = 8 81.7 / 90.2,
+// 48 rows k = 10 93.2 / 96.6, 56 rows k = 12 98.1 / 102.6, 64 rows k = 16 104 / 115; vocabulary 32000, hidden 3584, T = 5: 16 rows
+// k = 4 and 24 rows k = 6 the same, 32 rows k = 10 77.9 / 81.5, 40 rows k = 12 83.7 / 84.7, 56 rows k = 16 91.3 / 91.5).
 template <int T, bool TOPK>
 __global__ __launch_bounds__(THREADS) void lm_head_kernel(const Params prm) {
     // The ring position of a step must be a compile-time constant (every stage is its own LDS object, so that loads
@@ -108,7 +109,7 @@ __global__ __launch_bounds__(THREADS) void lm_head_kernel(const Params prm) {
     constexpr int UNROLL = (T % 8 == 0) ? 1 : (T % 4 == 0) ? 2 : (T % 2 == 0) ? 4 : 8;
     static_assert((UNROLL * T) % STAGES == 0, "ring positions must be static");
     constexpr int ROWS = TILE_R;                             // hidden rows of this workgroup
-    constexpr int LIST_ROWS_PER_K = T > 5 ? 3 : 4;           // candidate lists: see above
+    constexpr int LIST_ROWS_PER_K = T > 5 ? 5 : 4;           // candidate lists: see above
     __shared__ __align__(16) unsigned char sW0[STAGE_B];
     __shared__ __align__(16) unsigned char sW1[STAGE_B];
     __shared__ __align__(16) unsigned char sW2[STAGE_B];
@@ -394,7 +395,7 @@ __global__ __launch_bounds__(THREADS) void lm_head_kernel(const Params prm) {
                         present += __builtin_popcountll(__ballot(have[i]));
                     }
                     // at least k candidates and no more than a lane can take each; of equal values the lowest indices
-                    wave_pick<T>(code, have, min(prm.k, present), 64, in);
+                    wave_pick_roughly<T>(code, have, min(prm.k, present), 64, in);
                     int n = 0;
 #pragma unroll
                     for (int i = 0; i < T; ++i) {

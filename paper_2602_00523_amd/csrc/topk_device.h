@@ -191,6 +191,31 @@ __device__ __forceinline__ uint32_t wave_pick(const uint32_t (&code)[N], const b
     return thr;
 }
 
+// The same for a `most` well above `want` (up to 64, both), without a ballot per value and bit: the threshold comes from the
+// lanes' largest values, one ballot a bit.  What `want` of those reach, at least `want` of all values reach, and seldom many more; should
+// too many do (a lane's values are near each other, long runs of equal ones), or fewer than `want` lanes have a value, all values are looked at.
+template <int N>
+__device__ __forceinline__ void wave_pick_roughly(const uint32_t (&code)[N], const bool (&have)[N], int want, int most, bool (&in)[N]) {
+    uint32_t top[1] = {0};
+    bool some[1] = {false}, reached[1];
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+        top[0] = max(top[0], have[i] ? code[i] : 0u);
+        some[0] = some[0] || have[i];
+    }
+    if (__builtin_popcountll(__ballot(some[0])) >= want) {
+        const uint32_t thr = wave_pick<1>(top, some, want, want + want / 2 + 2, reached);
+        int n = 0;
+#pragma unroll
+        for (int i = 0; i < N; ++i) {
+            in[i] = have[i] && code[i] >= thr;
+            n += __builtin_popcountll(__ballot(in[i]));
+        }
+        if (n <= most) return;
+    }
+    wave_pick<N>(code, have, want, most, in);
+}
+
 // Second pass for one row, called by all WG_THREADS threads of a workgroup (at least two waves): combine the slice
 // statistics, merge the per-slice sorted key lists, Eq. 7-9.  OWN = lists per lane of one wave (lane owns lists lane,
 // lane+64, ...).  Writes the row's outputs (null pointers are skipped) and returns true in wave 0, whose lanes receive `out`;

@@ -279,7 +279,7 @@ def test_candidate_lists_of_equal_logits(gu, rows, vocab, k):
     np.testing.assert_allclose(g["topk_renorm"], 1.0 / k, rtol=1e-5)
 
 
-@pytest.mark.parametrize("vocab,per_k", [(2100, 4), (82000, 3)])
+@pytest.mark.parametrize("vocab,per_k", [(2100, 4), (82000, 3), (82000, 5)])
 @pytest.mark.parametrize("k", [2, 7, 16])
 def test_candidate_lists_by_rounds_and_by_counting(gu, vocab, per_k, k):
     """A list is selected by rounds from per_k k live rows on, below by counting (one row alone: by counting): the same
@@ -332,3 +332,34 @@ def test_largest_vocabulary(gu, rows):
     out, ws = torch.zeros(rows, 1, device=hd.device, dtype=torch.int32), gu.workspace(1 << 28)
     with pytest.raises(sage.SageError, match="UNSUPPORTED"):
         sage.sage_lm_head_topk(hd, wd, 1, None, out, None, None, None, None, ws)
+
+
+@pytest.mark.parametrize("kind", ["one lane", "few lanes", "level under a few", "spread", "lane by lane"])
+@pytest.mark.parametrize("vocab", [64, 640, 700, 2100, 82000])
+@pytest.mark.parametrize("k", [2, 10, 16])
+def test_candidate_lists_wherever_the_winners_are(gu, vocab, k, kind):
+    """Logits given one by one (a hidden row with a single 1): all winners in one token of 64, candidates in fewer such places than
+    k, long runs of equal ones, one winner per place, runs of 64 falling ones.  Tokens exact, the lowest index first."""
+    dim, rows = 128, 3
+    rng = wl.rng(vocab + k)
+    x = np.round(rng.standard_normal(vocab) * 16) / 16
+    place = np.arange(vocab) % 64
+    if kind == "one lane":
+        x[place == 37] += 16.0
+    elif kind == "few lanes":
+        x[place >= k // 2] = -np.inf
+    elif kind == "level under a few":
+        x[:] = 1.0
+        x[rng.permutation(vocab)[:max(k // 2, 1)]] = 2.0
+    elif kind == "lane by lane":
+        x = 64.0 - place
+    h = np.zeros((rows, dim), np.float32)
+    h[:, 5] = 1.0
+    w = np.zeros((vocab, dim), np.float32)
+    w[:, 5] = x
+    g = gu.gpu_lm_head_topk(wl.to_storage(h, "bf16"), wl.to_storage(w, "bf16"), k)
+    x = wl.bf16_bits_to_f32(wl.to_storage(x.astype(np.float32)[None], "bf16"))[0]
+    finite = int(np.isfinite(x).sum())
+    want = np.argsort(-x, kind="stable")[:k]
+    for r in range(rows):
+        np.testing.assert_array_equal(g["topk_idx"][r, :min(k, finite)], want[:min(k, finite)])
