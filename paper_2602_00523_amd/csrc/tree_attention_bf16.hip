@@ -969,15 +969,18 @@ namespace sage {
 // Batches of 2..64 sequences: the tile list of all sequences is cut into `nrange` ranges per KV head, about one
 // workgroup per CU in total whatever the lengths turn out to be on the device, and the partial slots of a KV head are one
 // per range plus one per (sequence, column group), the most that range and segment boundaries can produce together.
-// A range is at least MIN_RANGE_TILES positions, less than the pass that it pays anyway: as long as CUs are idle, shorter ranges end
-// sooner.  Attention call, us, at 3 -> 2: three sequences of 301-1999 tokens 14.6 -> 13.5 (1: 13.6), two of 4096 and 3500 16.7 -> 16.5,
-// of 212 and 613, four of 500-1200, eight of 2205-12133 and sixteen of 90-600 the same.  With SEG_COST 7 and 8 and a minimum of 2 the
-// three take 14.0 and 13.7, the eight 54.8 and 54.2 (53.1 with 6), but twelve of 300-5000 with 30 nodes 52.6 (53.1), four of 64 nodes 45.8 (47.2).
+// A range is at least MIN_RANGE_TILES positions, the prologue and epilogue of the pass that it pays anyway: as long as CUs are
+// idle, shorter ranges end sooner until they are about that long.  Attention call with the four-wave kernel before this one, us, at
+// (SEG_COST blocks, MIN_RANGE_TILES) = (8, 4), (6, 3), (5, 2), (4, 2): three sequences of 301-1999 tokens 14.7, 14.3, 14.0, 13.6; two of
+// 212 and 613 13.0, 11.5, 11.7, 12.1; eight of 2205-12133 56.0, 53.4, 54.1, 55.3; six of 500-4000 23.3, 23.5, 22.9, 24.0; twelve of
+// 300-5000 with 30 nodes 58.2, 57.7, 59.1, 59.0.  With this one at (6, 3) and (6, 2): the three 14.6 and 13.8, two
+// of 4096 and 3500 and other batches the same; but a step with four such calls over the three 77.3 and 77.2, and a cut elsewhere gives
+// other bits (0.37 % of the norm).
 // The workspace, of which the size stays, counts CAP_SEGMENT_TILES per segment and CAP_RANGE_TILES per range of the longest
 // lengths allowed.
 constexpr int MAX_BATCH_LANES = 64;      // a lane per sequence in make_batch_shape
 constexpr int TILE = 64;                 // tokens: the unit in which the host counts
-constexpr int MIN_RANGE_TILES = 2;       // 64-token positions of the line, pass cost included
+constexpr int MIN_RANGE_TILES = 3;       // 64-token positions of the line, pass cost included
 constexpr int CAP_RANGE_TILES = 8;
 constexpr int CAP_SEGMENT_TILES = 4;
 struct LaunchShape { int nslot, min_tiles_per_split, nrange; bool batch; };

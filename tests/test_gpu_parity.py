@@ -507,6 +507,29 @@ def test_attention_bf16_many_sequences(gu, B, Hq, Hkv, max_len, seed):
     run_attention_case(gu, 3000 + seed, "bf16", B, Hq, Hkv, 128, lens, sizes)
 
 
+@pytest.mark.parametrize("lens,nodes", [([301, 1999, 1200], 12), ([212, 613], 12), ([4096, 3500], 15), ([301, 1999, 1200], 64), ([90, 0], 3)])
+def test_attention_bf16_cut_of_batches(gu, monkeypatch, lens, nodes):
+    """Where a batch is cut, as the partials that are written say it: the result's bits depend on it.  Every (sequence, group of 256
+    rows) takes 6 positions of a line and one per 32 keys, and the line goes to up to 256 / Hkv workgroups (as many as the workspace
+    has slots for beyond one per segment of 64 nodes), at least 6 positions each."""
+    Hq, Hkv, slot_bytes = 64, 8, 256 * 272
+    kept, workspace = [], gu.workspace
+    monkeypatch.setattr(gu, "workspace", lambda n: kept.append(workspace(n)) or kept[-1])
+    run_attention_case(gu, 3500, "bf16", len(lens), Hq, Hkv, 128, lens, [nodes] * len(lens))
+    slots = kept[-1].numel() // (Hkv * slot_bytes)
+    rows = kept[-1][:Hkv * slots * slot_bytes].view(Hkv, slots, slot_bytes)[:, :, 256:264]     # maximum and sum of a slot's first row
+    groups = -(-nodes * (Hq // Hkv) // 256)
+    segments = [6 + -(-n // 32) + -(-nodes // 32) for n in lens for _ in range(groups)]
+    length = max(6, -(-sum(segments) // (slots - 2 * len(lens))))
+    want, at = set(), 0
+    for i, segment in enumerate(segments):
+        want |= {p // length + i for p in range(at + 6, at + segment)}    # a slot per range and segment, in the order of both
+        at += segment
+    written = (rows != 0xFF).any(-1).cpu().numpy()
+    for head in written:
+        assert set(np.flatnonzero(head)) == want
+
+
 @pytest.mark.parametrize("tiles", [32, 33, 48, 49, 64, 65, 128, 129])
 def test_attention_bf16_split_counts(gu, tiles):
     """One sequence and two KV heads: a split per 64-token tile up to 128, so the merge takes every one of its widths at its
