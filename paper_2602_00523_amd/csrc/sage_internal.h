@@ -83,14 +83,15 @@ __device__ __forceinline__ void lds_direct_load4(const unsigned char* gptr, __at
 #pragma clang diagnostic pop
 
 // A 16-byte store to global memory that is written through the L2 at once (device scope) instead of at the end of the kernel, when
-// the next one waits for it.  There is no builtin for this width.  (The wait state is for the vector instruction that may
-// overwrite the data next, which the compiler sees to only for stores of its own.)  Attention call, plain -> through, us:
+// the next one waits for it.  There is no builtin for this width.  (A vector instruction may overwrite the data of a store of more than 8
+// bytes no sooner than two wait states after it.  The compiler sees to them only for stores of its own, so the statement brings both.)
+// Attention call, plain -> through, us:
 // 64 nodes x 32768 positions 73.3 -> 72.1, x 4096 21.1 -> 20.8; 12 nodes x 32768 31.9 -> 31.4, x 4096 11.9 -> 12.0; batches and
 // drafting passes 0.5 % faster.  Stores marked as non-temporal take 72.4, 20.6, 31.8 and 11.7, but batches 1 % and drafting passes 4 % more.
 typedef unsigned Store16 __attribute__((ext_vector_type(4)));
 template <int OFFSET>
 __device__ __forceinline__ void store_through16(unsigned char* p, Store16 v) {   // at p + OFFSET, up to 4095
-    asm volatile("global_store_dwordx4 %0, %1, off offset:%2 sc1\n\ts_nop 0" : : "v"(p), "v"(v), "n"(OFFSET) : "memory");
+    asm volatile("global_store_dwordx4 %0, %1, off offset:%2 sc1\n\ts_nop 1" : : "v"(p), "v"(v), "n"(OFFSET) : "memory");
 }
 template <class F, int... I> __device__ __forceinline__ void unrolled(F f, std::integer_sequence<int, I...>) { (f(std::integral_constant<int, I>{}), ...); }
 template <int N, class F> __device__ __forceinline__ void unrolled(F f) { unrolled(f, std::make_integer_sequence<int, N>{}); }

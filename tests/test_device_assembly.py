@@ -130,6 +130,67 @@ def test_early_reads_are_found():
     assert early_reads([mfma, "v_mfma_f32_32x32x16_bf16 v[32:47], v[4:7], a[0:3], 0", "s_endpgm"])
 
 
+STORE_SOURCE = """
+#include "sage_internal.h"
+__global__ void overwritten(unsigned char* p, const unsigned* x) {
+    sage::Store16 v = {x[0], x[1], x[2], x[3]};
+    asm volatile("" : "+v"(v));
+    sage::store_through16<0>(p + threadIdx.x * 32, v);
+    v = v * 3u;
+    asm volatile("" : "+v"(v));
+    sage::store_through16<16>(p + threadIdx.x * 32, v);
+}
+"""
+
+
+def early_overwrites(lines):
+    """Pairs of a 16-byte store and a vector instruction that overwrites its data less than two wait states later on some path,
+    and the wait states between them; the number of stores that were looked at."""
+    labels = {line[:-1]: i for i, line in enumerate(lines) if line.endswith(":")}
+    found, checked = [], 0
+    for at, line in enumerate(lines):
+        if not line.startswith("global_store_dwordx4"):
+            continue
+        data = vector_registers(operands(line)[1])
+        assert len(data) == 4, line
+        checked += 1
+        paths = [(at + 1, 0)]
+        while paths:
+            i, states = paths.pop()
+            while i < len(lines) and states < 2 and not lines[i].startswith("s_endpgm"):
+                other = lines[i]
+                i += 1
+                if other.endswith(":"):
+                    continue
+                if other.startswith("s_branch"):
+                    i = labels[operands(other)[0].strip()]
+                elif other.startswith("s_cbranch"):
+                    paths.append((labels[operands(other)[0].strip()], states + 1))
+                elif other.startswith("v_") and vector_registers(operands(other)[0]) & data:
+                    found.append((line, other, states))
+                    break
+                states += wait_states(other)
+    return found, checked
+
+
+def test_data_of_a_store_has_its_wait_states(tmp_path):
+    """Two wait states between a store of more than 8 bytes and a vector instruction that overwrites its data: the statement's own,
+    where nothing else stands between the two, and all of the attention kernels'."""
+    (tmp_path / "k.hip").write_text(STORE_SOURCE)
+    assert early_overwrites(assembly(tmp_path / "k.hip", tmp_path / "k.s")) == ([], 2)
+    name = "tree_attention_bf16.hip"
+    found, checked = early_overwrites(assembly(os.path.join(build.CSRC, name), tmp_path / "a.s", build.EXTRA[name]))
+    assert found == [] and checked >= 36
+
+
+def test_early_overwrites_are_found():
+    store = "global_store_dwordx4 v[4:5], v[0:3], off sc1"
+    assert early_overwrites([store, "s_nop 0", "v_mov_b32_e32 v3, 0", "s_endpgm"])[0][0][2] == 1
+    assert early_overwrites([store, "s_cbranch_scc1 .L1", "s_nop 1", ".L1:", "v_mov_b32_e32 v0, 0", "s_endpgm"])[0][0][2] == 1
+    assert early_overwrites([store, "s_nop 1", "v_mov_b32_e32 v3, 0", "s_endpgm"]) == ([], 1)
+    assert early_overwrites([store, "v_mov_b32_e32 v4, 0", "s_nop 0", "v_mov_b32_e32 v2, 0", "s_endpgm"]) == ([], 1)
+
+
 def test_attention_has_no_generic_stores(tmp_path):
     """A store to a generic address also counts on the LDS counter: reads of LDS between such stores wait for each of them."""
     name = "tree_attention_bf16.hip"
