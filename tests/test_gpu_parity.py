@@ -205,6 +205,29 @@ def test_greedy_token_among_equal_maxima(gu, vocab, dtype):
         check_entropy(gu, x, 1, np.full(groups, rpg, np.int32), rpg)
 
 
+@pytest.mark.parametrize("dtype,bits", [("bf16", 0x7F81), ("bf16", 0xFFA0), ("bf16", 0x7FC0), ("f32", 0x7F800001), ("f32", 0xFFA00000), ("f32", 0x7FC00000)])
+@pytest.mark.parametrize("vocab", [1024, 3001])
+def test_greedy_token_among_nans(gu, vocab, dtype, bits):
+    """k = 1: logits that are no numbers, signalling or quiet, take no number's place, wherever they stand beside the largest one."""
+    rng = wl.rng(vocab + bits)
+    rows = 192
+    x = rng.standard_normal((rows, vocab)).astype(np.float32)
+    best = rng.integers(0, vocab, rows)
+    nan = rng.random((rows, vocab)) < 0.05
+    for r in range(rows):                                 # the largest among its lane's sixteen, one to all of the others NaNs
+        x[r, best[r]] = 9.0
+        lane = best[r] // 8 * 8 + np.arange(8) if dtype == "bf16" else best[r] // 4 * 4 + np.arange(4)
+        lane = np.concatenate([lane, lane ^ (512 if dtype == "bf16" else 256)])
+        nan[r, rng.permutation(lane)[:1 + r % len(lane)].clip(0, vocab - 1)] = True
+        nan[r, best[r]] = False
+    x = wl.to_storage(np.pad(x, ((0, 0), (0, -vocab % 16))), dtype)
+    x.view(np.uint16 if dtype == "bf16" else np.uint32)[:, :vocab][nan] = bits
+    for groups in (0, 1, 2, 3):                           # (0: every row valid, not in groups)
+        rpg = rows // max(groups, 1)
+        got = gu.gpu_entropy_topk(x[:, :vocab], 1, np.full(groups, rpg, np.int32) if groups else None, rpg if groups else 1)["topk_idx"]
+        np.testing.assert_array_equal(got[:, 0], best)
+
+
 @pytest.mark.parametrize("k", [4, 8, 9, 40])
 @pytest.mark.parametrize("bits", [0x7FFFFFFF, 0xFFFFFFFF])
 def test_topk_of_extreme_nans(gu, bits, k):
