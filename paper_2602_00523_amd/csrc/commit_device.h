@@ -12,19 +12,30 @@ namespace closing {
 // 16384 32.7 -> 32.2, three short sequences of four layers 79.4 -> 78.7.  What is executed costs, too:
 // copying every piece of all rows in one flat loop, two per thread held, with the divisions that takes, made the steps 0.6 us slower
 // than before.
-// 128 threads, of which this one is `t0`, copy the K row and the V row of `node`, path entry j of sequence b (Hkv heads x d elements
+// 2^row_shift threads copy a row of `pieces` 16-byte pieces: one piece each while there are threads, so that a short path costs one round
+// trip however wide its rows are, and more rows at a time where they are narrow.  The number of turns of a long path is the same
+// either way.  Calls, us, with 256 threads a row and one row at a time in a workgroup (1024 in the acceptance) -> 128 -> this: a row of 512
+// pieces, path of one, sage_commit_path 2.20 -> 2.33 -> 2.10, sage_close_step 2.61 -> 2.67 -> 2.19, with the acceptance 7.94 -> 7.99 -> 7.50;
+// of three 2.32 -> 2.42 -> 2.24, 3.58 -> 2.89 -> 2.65, 8.87 -> 8.13 -> 7.96; 1024 pieces, path of one 2.51 -> 2.95 -> 2.18, 3.01 -> 3.36 ->
+// 2.39, 8.38 -> 8.74 -> 7.76, of eight 2.63 -> 3.16 -> 2.31, 9.23 -> 6.11 -> 6.24, 12.9 -> 11.4 -> 11.6; rows of up to 128 as with 128.
+constexpr int MIN_ROW_SHIFT = 7;
+inline int row_shift(long pieces, int most) {
+    int s = MIN_ROW_SHIFT;
+    while ((1 << s) < pieces && (2 << s) <= most) ++s;
+    return s;
+}
+// 2^shift threads, of which this one is `t0`, copy the K row and the V row of `node`, path entry j of sequence b (Hkv heads x d elements
 // each), to cache position len_b + j in 16-byte pieces.
-constexpr int ROW_THREADS = 128;
 __device__ __forceinline__ void commit_row(
     const unsigned char* __restrict__ Kt, const unsigned char* __restrict__ Vt, unsigned char* __restrict__ Kc,
     unsigned char* __restrict__ Vc, int esz, int Hkv, int d, int64_t start, int len_b, int kv_capacity, long kv_token_stride,
-    long kv_head_stride, int node, int j, int b, int t0) {
+    long kv_head_stride, int node, int j, int b, int t0, int shift) {
     const long pos = static_cast<long>(len_b) + j;
     if (node < 0 || node >= SAGE_MAX_NODES || pos >= kv_capacity) return;      // never read or write out of range
     const int pieces = d * esz / 16;                                           // 16-byte pieces of one head's row
     const long src_row = (static_cast<long>(b) * SAGE_MAX_NODES + node) * Hkv * d * esz;
     const long dst_tok = (start + pos) * kv_token_stride * esz;
-    for (int t = t0; t < Hkv * pieces; t += ROW_THREADS) {
+    for (int t = t0; t < Hkv * pieces; t += 1 << shift) {
         const int g = t / pieces, c = t % pieces;
         const long src = src_row + (static_cast<long>(g) * d * esz) + c * 16;
         const long dst = dst_tok + static_cast<long>(g) * kv_head_stride * esz + c * 16;

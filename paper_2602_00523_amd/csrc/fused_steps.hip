@@ -45,7 +45,7 @@ struct CloseArgs {
     const unsigned char* Kt; const unsigned char* Vt; unsigned char* Kc; unsigned char* Vc;
     const int64_t* kv_start; int* kv_len; int* hist; int* count; const int* d_max_in; int* d_max_out; float* avg_out;
     long kv_token_stride, kv_head_stride;
-    int esz, Hkv, d, kv_capacity, window, d_floor, d_cap;
+    int esz, Hkv, d, kv_capacity, window, d_floor, d_cap, row_shift;
     float lo, hi;
 };
 template <int OWN, bool CLOSE>
@@ -142,10 +142,10 @@ __global__ __launch_bounds__(64 * ACCEPT_WAVES) void accept_kernel(const int* __
     //      sage_close_step does, here with the path still in LDS and all 16 waves copying
     __syncthreads();                                 // (by now every thread has read the old length, above)
     const int tau = s_tau;
-    constexpr int ROW_THREADS = sage::closing::ROW_THREADS;
-    for (int j = threadIdx.x / ROW_THREADS; j <= tau && j < path_cap; j += 64 * ACCEPT_WAVES / ROW_THREADS)   // eight rows at a time
+    const int shift = cl.row_shift;                  // up to eight rows at a time
+    for (int j = threadIdx.x >> shift; j <= tau && j < path_cap; j += 64 * ACCEPT_WAVES >> shift)
         sage::closing::commit_row(cl.Kt, cl.Vt, cl.Kc, cl.Vc, cl.esz, cl.Hkv, cl.d, start, len_b, cl.kv_capacity, cl.kv_token_stride,
-                                  cl.kv_head_stride, sh.slot_node[j], j, b, threadIdx.x % ROW_THREADS);
+                                  cl.kv_head_stride, sh.slot_node[j], j, b, threadIdx.x & ((1 << shift) - 1), shift);
     if (threadIdx.x == 0) cl.kv_len[b] = sage::closing::advanced_len(len_b, tau, cl.kv_capacity);
     if (wave == 1)
         sage::closing::history_wave(b, lane, tau, cl.window, cl.lo, cl.hi, cl.d_floor, cl.d_cap, was, cl.hist, cl.count, cl.d_max_out,
@@ -268,6 +268,7 @@ extern "C" int sage_verify_accept_close_from_slices(
     cl.avg_out = avg_out; cl.kv_token_stride = kv_token_stride; cl.kv_head_stride = kv_head_stride;
     cl.esz = esz; cl.Hkv = Hkv; cl.d = d; cl.kv_capacity = kv_capacity; cl.window = window; cl.d_floor = d_floor; cl.d_cap = d_cap;
     cl.lo = lo; cl.hi = hi;
+    cl.row_shift = sage::closing::row_shift(static_cast<long>(Hkv) * d * esz / 16, 64 * ACCEPT_WAVES);
     hipStream_t s = sage::as_stream(stream);
     if (nunits <= 256)
         hipLaunchKernelGGL((accept_kernel<4, true>), dim3(B), dim3(64 * ACCEPT_WAVES), 0, s, n_nodes, nunits, stats, keys, token,

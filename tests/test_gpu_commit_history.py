@@ -38,7 +38,7 @@ def _random_paths(g, B, path_cap, max_nodes=24):
 
 
 @pytest.mark.parametrize("dtype,Hkv,d,layout", [("bf16", 8, 128, "thd"), ("bf16", 2, 64, "htd"), ("f32", 1, 64, "thd"),
-                                                 ("f32", 4, 32, "htd")])
+                                                 ("f32", 4, 32, "htd"), ("f32", 8, 128, "htd"), ("bf16", 10, 128, "thd")])
 def test_commit_path_bytes(gu, dtype, Hkv, d, layout):
     g = np.random.default_rng(11)
     B, cap, path_cap = 5, 96, 12
@@ -180,7 +180,7 @@ def test_closed_loop_steps(gu):
     assert (lens > np.array([70, 9])).all()
 
 
-@pytest.mark.parametrize("dtype,Hkv,d,two_limits", [("bf16", 8, 128, True), ("f32", 2, 64, False)])
+@pytest.mark.parametrize("dtype,Hkv,d,two_limits", [("bf16", 8, 128, True), ("f32", 2, 64, False), ("f32", 8, 128, True), ("bf16", 10, 128, False)])
 def test_close_step_equals_commit_advance_history(gu, dtype, Hkv, d, two_limits):
     """sage_close_step over several steps against the oracle's commit, advance and history applied in that order: cache
     bytes, lengths, window, counts, depth limits and averages, all exact; with two depth-limit arrays the input one is
@@ -316,3 +316,61 @@ def test_accept_and_close_in_one_launch(gu, vocab, dtype):
         np.testing.assert_array_equal(one["dm"].cpu().numpy(), dm_o)
         np.testing.assert_array_equal(one["avg"].cpu().numpy(), avg_o)
     assert cnt_o.max() >= 3                                     # enough steps really ran
+
+
+@pytest.mark.parametrize("dtype,Hkv,d", [("bf16", 2, 64), ("bf16", 8, 128), ("bf16", 10, 128), ("f32", 8, 128), ("bf16", 64, 128),
+                                         ("f32", 21, 256)])  # 16, 128, 160, 256, 1024 and 1344 pieces of 16 bytes a row
+def test_rows_of_any_width_along_paths_of_any_length(gu, dtype, Hkv, d):
+    """A path of the root alone, of 8 and 9 rows, and of up to 64 along a chain: sage_commit_path, sage_close_step and the acceptance
+    that closes the step write the same bytes as the oracle, with one row more than there is room for in one sequence."""
+    import torch
+    from paper_2602_00523_amd import sage
+    taus, vocab, path_cap, cap, window = [0, 7, 8, 22, 39, 63], 700, 64, 96, 10
+    B, rows = len(taus), len(taus) * MAX_NODES
+    g = np.random.default_rng(Hkv * d)
+    lens = np.array([3, 0, 30, 17, 40, 33], np.int32)          # the last path has one row more than there is room
+    start = np.arange(B, dtype=np.int64) * cap
+    ts, hs = Hkv * d, d
+    Kc, Vc = wl.gaussian(3, (B * cap, Hkv, d), dtype), wl.gaussian(4, (B * cap, Hkv, d), dtype)
+    Kt, Vt = wl.gaussian(5, (B, MAX_NODES, Hkv, d), dtype), wl.gaussian(6, (B, MAX_NODES, Hkv, d), dtype)
+    p, dd, m, _ = pad_tree(np.arange(-1, MAX_NODES - 1).astype(np.int32))
+    parent, depth, mask = (np.repeat(a, B, 0) for a in (p, dd, m))
+    nn = np.full(B, MAX_NODES, np.int32)
+    tgt = g.integers(0, vocab, (B, MAX_NODES)).astype(np.int32)
+    tok = np.zeros((B, MAX_NODES), np.int32)
+    for b, tau in enumerate(taus):
+        tok[b, 1:] = np.where(np.arange(1, MAX_NODES) <= tau, tgt[b, :-1], (tgt[b, :-1] + 1) % vocab)
+    x = np.zeros((rows, 704), np.float32)
+    x[np.arange(rows), tgt.ravel()] = 4.0
+    o = oracle.verify_accept(tok, tgt, parent, depth, nn, path_cap)
+    np.testing.assert_array_equal(o["accept_len"], taus)
+    Ko, Vo = Kc.copy(), Vc.copy()
+    oracle.commit_path(Kt, Vt, Ko, Vo, start, lens, cap, ts, hs, o["path_nodes"], o["accept_len"], Hkv, d)
+    lens_o = oracle.advance_kv_len(lens, o["accept_len"], cap)
+    hist_o, cnt_o, dm_o = np.zeros((B, window), np.int32), np.zeros(B, np.int32), np.full(B, 6, np.int32)
+    oracle.update_history(o["accept_len"], hist_o, cnt_o, dm_o, window, 2.0, 3.0, 3, 8)
+
+    Kg, Vg, lg = gu.gpu_commit_path(Kt, Vt, Kc, Vc, start, lens, cap, ts, hs, o["path_nodes"], o["accept_len"])
+    assert (Kg == Ko).all() and (Vg == Vo).all()
+    np.testing.assert_array_equal(lg, lens_o)
+    i32 = dict(device="cuda:0", dtype=torch.int32)
+    ktd, vtd, startd = gu.to_dev(Kt), gu.to_dev(Vt), gu.to_dev(start)
+    trees = [gu.to_dev(np.ascontiguousarray(a)) for a in (tok, parent, depth, mask, nn)]
+    for fused in (False, True):
+        kcd, vcd, lend = gu.to_dev(Kc), gu.to_dev(Vc), gu.to_dev(lens)
+        hist, cnt, dm = torch.zeros((B, window), **i32), torch.zeros(B, **i32), torch.full((B,), 6, **i32)
+        acc, best = torch.full((B,), -9, **i32), torch.full((B,), -9, **i32)
+        path, toks = torch.full((B, path_cap), -9, **i32), torch.full((B, path_cap), -9, **i32)
+        if fused:
+            ws = gu.workspace(sage.sage_entropy_topk_workspace_bytes(rows, vocab, 1))
+            sage.sage_entropy_topk_slices(gu.to_dev(wl.to_storage(x, dtype))[:, :vocab], 1, ws, trees[4], MAX_NODES)
+            sage.sage_verify_accept_close_from_slices(ws, vocab, *trees, path_cap, None, torch.zeros(rows, **i32), acc, best, path, toks, ktd,
+                                                      vtd, kcd, vcd, startd, lend, cap, ts, hs, hist, cnt, dm, dm, 2.0, 3.0, 3, 8)
+            np.testing.assert_array_equal(acc.cpu().numpy(), taus)
+        else:
+            sage.sage_close_step(ktd, vtd, kcd, vcd, startd, lend, cap, ts, hs, gu.to_dev(o["path_nodes"]), gu.to_dev(o["accept_len"]),
+                                 hist, cnt, dm, dm, 2.0, 3.0, 3, 8)
+        torch.cuda.synchronize()
+        assert (gu.to_host(kcd) == Ko).all() and (gu.to_host(vcd) == Vo).all(), fused
+        for got, want in ((lend, lens_o), (hist, hist_o), (cnt, cnt_o), (dm, dm_o)):
+            np.testing.assert_array_equal(got.cpu().numpy(), want)
