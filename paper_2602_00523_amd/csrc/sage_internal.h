@@ -35,7 +35,7 @@ __device__ __forceinline__ uint16_t float_to_bf16_bits(float f) {
 // across an issue.  M0 carries the LDS address of the load; nothing else in these kernels uses it.
 // The compiler does not look for hazards inside such a statement: a vector-memory instruction may read a scalar register no
 // sooner than five wait states after a vector instruction (v_readfirstlane, v_readlane of a spilled value) has written it,
-// so the forms with a scalar base bring five of their own.
+// so the form with a scalar base brings five of its own.
 #pragma clang diagnostic push
 #pragma clang diagnostic ignored "-Winline-asm"
 __device__ __forceinline__ void lds_direct_load16(const unsigned char* gptr, __attribute__((address_space(3))) unsigned char* lds) {
@@ -58,19 +58,6 @@ __device__ __forceinline__ void lds_direct_load16(const unsigned char* sbase, un
                  :
                  : "v"(voff), "s"(base), "s"(m0v)
                  : "m0", "memory");
-}
-// The same again, only if `wanted` (wave-uniform) is not zero: the branch is inside the statement, so that a load can stand
-// in the middle of a block of arithmetic whose order is fixed.
-__device__ __forceinline__ void lds_direct_load16_if(int wanted, const unsigned char* sbase, unsigned voff,
-                                                     __attribute__((address_space(3))) unsigned char* lds) {
-    const unsigned m0v = static_cast<unsigned>(reinterpret_cast<uintptr_t>(lds));
-    const uintptr_t bv = reinterpret_cast<uintptr_t>(sbase);     // (uniform: said to the compiler, as above)
-    const uintptr_t base = (static_cast<uintptr_t>(static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<uint32_t>(bv >> 32)))) << 32) |
-                           static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<uint32_t>(bv)));
-    asm volatile("s_cmp_eq_u32 %3, 0\n\ts_cbranch_scc1 .Lno_load%=\n\ts_mov_b32 m0, %2\n\ts_nop 1\n\tglobal_load_lds_dwordx4 %0, %1\n.Lno_load%=:"
-                 :
-                 : "v"(voff), "s"(base), "s"(m0v), "s"(__builtin_amdgcn_readfirstlane(wanted))
-                 : "m0", "scc", "memory");
 }
 // The 4-byte form: lane l lands at lds + 4 l.
 __device__ __forceinline__ void lds_direct_load4(const unsigned char* gptr, __attribute__((address_space(3))) unsigned char* lds) {

@@ -9,14 +9,9 @@ from paper_2602_00523_amd import build
 
 SOURCE = """
 #include "sage_internal.h"
-__global__ void unconditional(const unsigned char* const* p, unsigned char* out) {
+__global__ void load(const unsigned char* const* p, unsigned char* out) {
     __shared__ unsigned char lds[1024];
     sage::lds_direct_load16(p[threadIdx.x], threadIdx.x * 16u, (__attribute__((address_space(3))) unsigned char*)lds);
-    out[threadIdx.x] = lds[threadIdx.x];
-}
-__global__ void conditional(const unsigned char* const* p, unsigned char* out) {
-    __shared__ unsigned char lds[1024];
-    sage::lds_direct_load16_if(out[threadIdx.x], p[threadIdx.x], threadIdx.x * 16u, (__attribute__((address_space(3))) unsigned char*)lds);
     out[threadIdx.x] = lds[threadIdx.x];
 }
 """
@@ -56,7 +51,7 @@ def test_scalar_base_of_a_load_has_its_wait_states(tmp_path):
             checked += 1
         else:
             states += wait_states(line)
-    assert checked == 2
+    assert checked == 1
 
 
 def vector_registers(operand):
