@@ -24,8 +24,8 @@ COMMON = ["--offload-arch=gfx950", "-O3", "-std=c++20", "-fPIC", "-Xclang", "-ta
           # these kernels are short and launched in dependent chains, where that round trip is a visible share
           "-mllvm", "-amdgpu-kernarg-preload-count=16"]
 EXTRA = {"build_tree.hip": ["-ffp-contract=off"],
-         # MFMA results in ordinary vector registers: the softmax reads scores and rescales accumulators where they lie, and the
-         # operands that only MFMAs read take the accumulation registers
+         # MFMA results in ordinary vector registers, where the softmax reads scores and rescales accumulators.  All 256 registers of a
+         # wave are ordinary ones: an operand pinned to the accumulation half would make the compiler split the file in two
          "tree_attention_bf16.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"]}
 # Kernels that keep their own count of vector-memory operations in flight (s_waitcnt vmcnt(N) around LDS-direct loads):
 # a register spill adds scratch loads and stores to that counter and silently breaks the count, so these translation

@@ -46,11 +46,12 @@ template <> struct Loader<uint16_t> {
     __device__ static float one(const uint16_t* p) { return sage::bf16_bits_to_float(*p); }
 };
 
-// Pass 1 for k = 1 (many rows, one candidate per slice): one wave per (slice, row), 16 logits per lane.  What bounds it with many
-// rows is what a wave executes, about as long as the stream takes, so that is kept short: the maximum by three-operand maxima,
-// its place by ballots once it is known (a compare and two selects per logit before), both sums through one chain of lane exchanges, and no
-// look at the row's end in whole slices.  512 rows of 152064 bf16 logits, whole call: 38.9 -> 37.8 us.  The statistics are an exp2 and five
-// operations per logit.  Differences to the maximum are capped at 87, where
+// Pass 1 for k = 1 (many rows, one candidate per slice): one wave per (slice, row), 16 logits per lane.  With many rows the stream
+// bounds it (512 rows, all valid: 156 MB in 30.4 us, 5.1 TB/s, where a copy reaches 5.15; in full groups, three rows a workgroup one after
+// the other, 35.7), and what a wave executes takes nearly as long, so that is kept short: the maximum by three-operand maxima, its place by ballots once it is known (a compare and two selects per logit before),
+// both sums through one chain of lane exchanges, and no look at the row's end in whole slices.  Whole call, 152064 bf16 logits, groups of
+// 64: 512 live rows 39.1 -> 37.9 us on one machine, 38.5 -> 38.4 on another, 256 of 256 23.5 -> 22.9, 192 of 1024 16.5 -> 16.0, up to 64
+// rows the same.  The statistics are an exp2 and five operations per logit.  Differences to the maximum are capped at 87, where
 // exp is below 2^-125: a -inf logit or a padding slot then adds about 1e-38 instead of 0 to sums that are >= 1.
 //
 // The 16-byte loads of a (row, slice) are requested by request_unit and consumed by reduce_unit, so that a wave that
@@ -194,9 +195,12 @@ __global__ __launch_bounds__(THREADS) void slice_kernel(const T* __restrict__ lo
 // Phases: with one or two groups every live row may have its workgroups at once (64 live rows of 152064 in one group, first
 // pass 8.4 -> 6.6 us, 40 in each of two 8.9 -> 7.9; 12 rows 3.1 either way).  With more groups 16 of them fill the chip, and the
 // workgroups of dead rows that more would add show (8 x 12 rows 8.5 us at 16, 9.1 at 32, 9.7 at 64).
-// By themselves the slice passes of more groups take 22, so that a workgroup of a full group walks three rows and not four (512 live rows
-// 38.9 -> 38.5 us, 320 of 512 26.4 -> 25.0, 150 of 320 12.9 -> 12.3); beside a draft row's, in a step, whose trees are seldom full,
-// 16 (eight sequences of 12 nodes 0.5 us a step).
+// By themselves the slice passes of more groups take 22, so that a workgroup walks one or two rows of a group of 20 to 40 and three of a
+// full one.  Calls, us, at 16 -> 22: 20 rows in each of eight 15.1 -> 14.0, 30 in each of five 15.5 -> 14.9, 40 in each of eight 25.3 ->
+// 24.0, 64 in each of three 20.0 -> 19.2, of four and of eight the same; 12 in each of three, eight, twelve and sixteen the same within 0.1,
+// in each of five 8.8 -> 9.1.  Beside a draft row's, in a step, whose trees are seldom full, 16: 12 rows in each of three 5.65 us (22: 5.9),
+// of eight 10.6 (10.8), of twelve 14.7 (14.9), 15 in each of eight 11.8 (12.0), though full groups would be faster with 22 (three 17.2
+// and 16.3, four 20.6 and 19.8, eight 36.1 and 35.6).
 inline int row_phases(int groups, int rows_per_group, bool in_a_step) {
     const int phases = groups == 1 ? 64 : groups == 2 ? 32 : in_a_step ? 16 : 22;
     return rows_per_group < phases ? rows_per_group : phases;

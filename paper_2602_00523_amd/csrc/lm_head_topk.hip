@@ -92,14 +92,15 @@ __device__ __forceinline__ void stage_barrier() {
 // end of every workgroup's only unit, when no loads are in flight.  Two ways, by the number of live rows and k:
 //   counting: the unit's logits of 32 rows at a time are laid out in the idle ring and a wave per row finds a value that at
 //     least k and at most 64 of them reach (the lanes' largest ones give it, a ballot a bit, and rarely too low; a ballot per 64
-//     logits and bit, about nine bits, took twice as long), then ranks those by counting, four rows side by side: 0.52 us a live
+//     logits and bit, about nine bits, took twice as long), then ranks those by counting, four rows side by side: 0.45 to 0.5 us a live
 //     row (T = 10; before 1.0), 0.45 (T = 5), whatever k.  16 rows of 3584, k = 10, T = 10, whole call: 217.2 -> 209.8 us;
 //   rounds: every lane scans its 16 T logits for the best one after the previous winner, the four lanes of a row are combined
 //     (lane halves by a swap, vocabulary halves through LDS): 3.1 us each (T = 5: 1.6), whatever the rows.
-// LIST_ROWS_PER_K live rows per candidate is where the two meet, within 2 us of it for every k (us of the call, counting /
-// rounds; vocabulary 152064, hidden 1024, T = 10: 16 rows k = 4 73.7 / 78.3, 24 rows k = 6 77.5 / 84.0, 32 rows k = 8 81.7 / 90.2,
-// 48 rows k = 10 93.2 / 96.6, 56 rows k = 12 98.1 / 102.6, 64 rows k = 16 104 / 115; vocabulary 32000, hidden 3584, T = 5: 16 rows
-// k = 4 and 24 rows k = 6 the same, 32 rows k = 10 77.9 / 81.5, 40 rows k = 12 83.7 / 84.7, 56 rows k = 16 91.3 / 91.5).
+// LIST_ROWS_PER_K live rows per candidate is about where the two meet (us of the call, counting / rounds; vocabulary 152064, hidden
+// 1024, T = 10, at 4, 5 and 6 rows per k: k = 4 74.7 / 79.7, 76.8 / 79.9, 78.4 / 79.5; k = 6 78.9 / 85.6, 82.5 / 85.8, 87.8 / 85.8; k = 8
+// 83.1 / 91.4, 90.1 / 91.9, 93.7 / 92.1; k = 12 95.9 / 104.2 and 101.5 / 104.4; 64 rows k = 16 104 / 115.  Vocabulary 32000, hidden 3584,
+// T = 5, just below 4 and at 5: k = 4 72.7 / 74.3, 74.2 / 74.3; k = 8 79.0 / 80.3, 83.9 / 80.4; k = 12 88.5 / 86.9 and k = 16 96.0 / 92.9).
+// So the rule loses up to 3.4 us (k = 6, 30 rows, T = 10) or 3.1 (k = 16, 63 rows, T = 5) next to the line, and nothing away from it.
 template <int T, bool TOPK>
 __global__ __launch_bounds__(THREADS) void lm_head_kernel(const Params prm) {
     // The ring position of a step must be a compile-time constant (every stage is its own LDS object, so that loads

@@ -193,7 +193,9 @@ __device__ __forceinline__ uint32_t wave_pick(const uint32_t (&code)[N], const b
 
 // The same for a `most` well above `want` (up to 64, both), without a ballot per value and bit: the threshold comes from the
 // lanes' largest values, one ballot a bit.  What `want` of those reach, at least `want` of all values reach, and seldom many more; should
-// too many do (a lane's values are near each other, long runs of equal ones), or fewer than `want` lanes have a value, all values are looked at.
+// too many do (a lane's values are near each other, long runs of equal ones), or fewer than `want` lanes have a value, all values are looked at
+// as well: with nothing but equal logits a projection of 8, 16 and 33 rows takes 1.0, 1.8 and 4 us more than with the ballots alone (k = 10 or
+// 16; 78, 81 and 98 us), with others 1.5 to 13 less.
 template <int N>
 __device__ __forceinline__ void wave_pick_roughly(const uint32_t (&code)[N], const bool (&have)[N], int want, int most, bool (&in)[N]) {
     uint32_t top[1] = {0};

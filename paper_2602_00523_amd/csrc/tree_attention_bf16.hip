@@ -42,7 +42,7 @@
 // -> now:
 //   64 nodes: 32768 positions 78.7-81.5 -> 73.3 us, 0.94 PFLOP/s; 300 positions 13.4 -> 11.9; 24 nodes x 32768 41.9 -> 39.3.  A wave alone on
 //   its SIMD issues one instruction at a time: about 600 cycles of a unit's 1016 (below) it issued, 100 of them scalar, and its
-//   MFMAs take 544.  Taking out its LDS reads, its loads or its exponentials made a unit 1-3 % shorter, each by itself: the matrix pipe
+//   MFMAs take 577.  Taking out its LDS reads, its loads or its exponentials made a unit 1-3 % shorter, each by itself: the matrix pipe
 //   waited for the order of the program.  Two waves, of which each fills what the other leaves open: 832 cycles a unit and SIMD (1663
 //   a block); with the scalar work out of the block (the loop once around the rings), 745.  Power then keeps the clock at 1.2-1.9 GHz,
 //   by machine and by how long the calls go on (80 layers in a row 82.4 -> 79.0 us a call); these MFMAs with this softmax and these
@@ -452,8 +452,8 @@ __device__ __forceinline__ void attention_pass(const Params& prm, LDS_AS Lds* ld
     };
     // The running sums of the rounded probabilities, four of a lane's 16 at a time: of the 16 products of 4 x 4 matrices that
     // this MFMA does, a lane's four values are one column, and a matrix of ones adds it up.  16 cycles of the matrix pipe
-    // (a unit's MFMAs 513 -> 577 cycles with its four); two two-element dot products block it for 16 each, and unpacking and
-    // adding are eight instructions of a full vector pipe.
+    // (a loop of a unit's MFMAs takes 513 cycles without its four and 577 with them; the counter of busy cycles advances by 8 for each);
+    // two two-element dot products block it for 16 each, and unpacking and adding are eight instructions of a full vector pipe.
     auto add_up = [&](const bf16x8 (&before)[2], int j) __attribute__((always_inline)) {
         typedef short s16x4 __attribute__((ext_vector_type(4)));
         const s16x4 ones = {0x3F80, 0x3F80, 0x3F80, 0x3F80};
