@@ -50,9 +50,9 @@
 //   small trees: the stream, and at short contexts launch, two round trips, the merge launch, and what is executed once: a call over
 //   4096 positions has its sizes after 0.9 us, has requested everything 1.0 us later and has it 0.6 us after that; five blocks take 3.5,
 //   the epilogue 1.2, and the merge ends 4.2 us after the last store.  12 nodes, 64/8 heads, 4096 positions 12.5 -> 11.7 us, 32768
-//   positions 31.6 -> 31.4; 15 nodes, 8192 positions 16.5 -> 15.4, 16384 22.1 -> 21.1 (up to 1.8 us more on some machines, where the
-//   stream is slower the sooner a block is requested); three sequences of 301 to 1999 positions 15.2 -> 14.4; eight of 2205 to 12133
-//   53.8 -> 53.5; 28/4 heads, 3 new rows of 12, 2560 positions 9.2 -> 8.6.
+//   positions 31.6 -> 31.4; 15 nodes, 8192 positions 16.5 -> 15.4, 16384 22.1 -> 20.8 (1.8 us more in one run, on a machine where the
+//   stream was slower the sooner a block was requested; in five later ones not); three sequences of 301 to 1999 positions 15.2 -> 14.5; eight of
+//   2205 to 12133 53.8 -> 53.5; 28/4 heads, 3 new rows of 12, 2560 positions 9.2 -> 8.6.
 #include <type_traits>
 
 #include "plan_device.h"
@@ -200,7 +200,7 @@ __device__ __forceinline__ BatchShape make_batch_shape(const Params& prm, int la
 template <int N> __device__ __forceinline__ void wait_vm() {
     __builtin_amdgcn_s_waitcnt((N & 15) | (7 << 4) | (15 << 8) | ((N >> 4) << 14));
 }
-// Workgroup barrier of the stage ring.  __syncthreads() would also fence, and a workgroup-scope release makes the
+// Workgroup barrier of the rings.  __syncthreads() would also fence, and a workgroup-scope release makes the
 // compiler wait for every LDS-direct load still in flight, which is exactly what the ring must not do: each
 // thread has already waited for its own share of the block (wait_vm), LDS needs no cache maintenance, so the bare
 // barrier is enough; the wavefront-scope fences only pin the order of memory operations around it.
@@ -661,7 +661,7 @@ __device__ __forceinline__ void attention_pass(const Params& prm, LDS_AS Lds* ld
     // ---- epilogue: a wave's rows (O^T in bf16, max, sum) are complete.  They go through the wave's own piece of the ring as
     // rows of EPI_ROW_B bytes, transposed on the way: written 8 bytes (4 dims) at a time from the accumulator layout, read
     // back and stored to the partial in row order, for the second kernel to merge.
-    __syncthreads();                                         // all stages are idle now
+    __syncthreads();                                         // the rings are idle now
     LDS_AS unsigned char* const mine = ring + row0 * EPI_ROW_B;
     LDS_AS unsigned char* const row = mine + r32 * EPI_ROW_B;
 #pragma unroll

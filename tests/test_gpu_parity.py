@@ -564,7 +564,7 @@ def test_attention_bf16_split_counts(gu, tiles):
 @pytest.mark.parametrize("blocks,tail", [(1, 0), (1, 31), (2, 1), (3, 16), (4, 0), (5, 31), (7, 1)])
 def test_attention_bf16_pass_lengths(gu, nodes, blocks, tail):
     """One sequence, many KV heads and so few splits: passes of `blocks` 32-token blocks, of which the cache's last holds
-    32 - tail tokens, at the row counts between one and two column tiles per wave and between one and two groups.  Half of the
+    32 - tail tokens, at the row counts on either side of 128 (the reference in one step or in two) and of one and two groups.  Half of the
     lengths with scores that grow along the cache, so that the reference maximum has to move in every block."""
     Hq, Hkv = 512, 64                                     # four splits of a KV head (two where there are two groups)
     splits, tree = (2 if nodes > 32 else 4), (2 if nodes > 32 else 1)
