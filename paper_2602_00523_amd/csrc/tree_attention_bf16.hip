@@ -857,6 +857,11 @@ constexpr int MERGE_ROWS_SINGLE = 4;     // one sequence: many small workgroups 
 constexpr int MERGE_ROWS_BATCH = 4;      // (16 rows per workgroup measured 6 % slower on the ragged batch of 8)
 constexpr int MERGE_PHASES_BATCH = 32;   // batches: workgroups per (sequence, KV head), each walking the live rows; a
                                          // single sequence gets a wave per possible row (fewer measured no faster)
+// A pass asks for as many splits as there are, in steps of MERGE_STEP, where it takes up to MERGE_STEP_UPTO: a batch has 5 to 13 of the 32
+// that its instantiation is for, a tree of 64 nodes 16 (whole call: three sequences of 301 to 1999 positions 13.3 -> 12.8 us, seven of
+// 300 to 1300 17.1 -> 16.3, seven of 2500 to 8700 with 64 nodes 104 -> 98; 80 layers of 64 nodes 5.94 -> 5.91 ms).  Beyond that the choice
+// costs what it saves (41 of 48 splits, ten calls of a drafting pass: 79.4 -> 80.2 us).
+constexpr int MERGE_STEP = 8, MERGE_STEP_UPTO = 32;
 template <int MAXS, bool BATCH, int ROWS>
 __global__ __launch_bounds__(64 * ROWS) void tree_attention_merge_kernel(const int* __restrict__ kv_len_arg,
                                                                          const int* __restrict__ n_nodes_arg,
@@ -881,8 +886,9 @@ __global__ __launch_bounds__(64 * ROWS) void tree_attention_merge_kernel(const i
         const int nsplit = __builtin_amdgcn_readfirstlane(nsplit_v);
         float2 o = make_float2(0.f, 0.f);
         float m_all = -INFINITY, l_all = 0.f;
-        for (int s0 = 0; s0 < nsplit; s0 += MAXS) {           // MAXS splits at a time
-            const int cnt = min(MAXS, nsplit - s0);
+        // The splits from s0 on, `cnt` of them, in N registers.
+        auto pass = [&](auto n, int s0, int cnt) __attribute__((always_inline)) {
+            constexpr int N = decltype(n)::value;
             float ms = -INFINITY, ls = 0.f;
             // The row's partials of this pass as one buffer: uniform base (partial s0), 32-bit offsets, and a size that ends
             // with the row's extent in its last split, so that a load for a split past the last one is answered with zeros
@@ -896,10 +902,11 @@ __global__ __launch_bounds__(64 * ROWS) void tree_attention_merge_kernel(const i
                 ms = lane < cnt ? __uint_as_float(pair[0]) : -INFINITY;
                 ls = lane < cnt ? __uint_as_float(pair[1]) : 0.f;
             }
-            unsigned v[MAXS];                                // two bf16 output dims of split s
+            unsigned v[N];                                   // two bf16 output dims of split s
             unsigned off = 4u * lane;                        // the whole offset goes through the per-lane operand: that one is
-#pragma unroll                                               // bounds-checked, the scalar offset operand is not
-            for (int s = 0; s < MAXS; ++s) {
+            asm volatile("" : "+v"(off));                    // bounds-checked, the scalar offset operand is not.  (Opaque, or the
+#pragma unroll                                               // offsets are kept in a register each for all the passes below.)
+            for (int s = 0; s < N; ++s) {
                 v[s] = __builtin_amdgcn_raw_buffer_load_b32(rows, off, 0, 0);
                 off += PART_SLOT_B;
             }
@@ -912,11 +919,24 @@ __global__ __launch_bounds__(64 * ROWS) void tree_attention_merge_kernel(const i
             o.x *= keep; o.y *= keep;
             m_all = m_new;
 #pragma unroll
-            for (int s = 0; s < MAXS; ++s) {
+            for (int s = 0; s < N; ++s) {
                 const float ws = sage::lane_value(w, s);        // split s's weight, through a scalar register
                 o.x += ws * __uint_as_float(v[s] << 16);
                 o.y += ws * __uint_as_float(v[s] & 0xFFFF0000u);
             }
+        };
+        for (int s0 = 0; s0 < nsplit; s0 += MAXS) {           // MAXS splits at a time
+            const int cnt = min(MAXS, nsplit - s0);          // (uniform)
+            bool done = false;
+            if constexpr (MAXS <= MERGE_STEP_UPTO)
+                sage::unrolled<(MAXS - 1) / MERGE_STEP>([&](auto i) __attribute__((always_inline)) {
+                    constexpr int N = (decltype(i)::value + 1) * MERGE_STEP;
+                    if (!done && cnt <= N) {
+                        pass(std::integral_constant<int, N>{}, s0, cnt);
+                        done = true;
+                    }
+                });
+            if (!done) pass(std::integral_constant<int, MAXS>{}, s0, cnt);
         }
         const float inv = 1.0f / l_all;
         const uint32_t packed = static_cast<uint32_t>(sage::float_to_bf16_bits(o.x * inv)) |

@@ -560,6 +560,15 @@ def test_attention_bf16_split_counts(gu, tiles):
     run_attention_case(gu, 4000 + tiles, "bf16", 1, 4, 2, 128, [64 * (tiles - 1) - 3], sizes=[3])
 
 
+@pytest.mark.parametrize("B", [1, 2])
+@pytest.mark.parametrize("splits", [7, 8, 9, 16, 17, 24, 25, 32])
+def test_attention_bf16_merge_widths(gu, splits, B):
+    """Splits of a row about the steps of 8 in which the merge asks for them: two blocks of 32 keys a split with one sequence, six beside
+    an empty sequence."""
+    lens = [64 * splits - 32] if B == 1 else [192 * splits - 40, 0]
+    run_attention_case(gu, 4200 + splits, "bf16", B, 8, 8, 128, lens, sizes=[5, 3][:B])
+
+
 @pytest.mark.parametrize("nodes", [4, 16, 17, 32, 33])
 @pytest.mark.parametrize("blocks,tail", [(1, 0), (1, 31), (2, 1), (3, 16), (4, 0), (5, 31), (7, 1)])
 def test_attention_bf16_pass_lengths(gu, nodes, blocks, tail):
