@@ -176,23 +176,31 @@ struct BatchShape {
     int total, q;                                            // wave-uniform
 };
 __device__ __forceinline__ int wave_sum_i32(int v) { return static_cast<int>(sage::wave_sum_u32(static_cast<uint32_t>(v))); }
-__device__ __forceinline__ BatchShape make_batch_shape(const Params& prm, int lane) {
+// What it needs of the arguments comes in scalars that are preloaded at wave launch, see the kernels, and its loads are the first thing
+// that a wave does: from the argument block in memory they were two round trips later, in the attention's workgroups and in the merge's
+// (whole call, three sequences of 301 to 1999 positions 12.8 -> 12.4 us, seven of 300 to 1300 16.3 -> 15.6, eight of 2800 to 11000 64.3 ->
+// 62.8).  `others_here`: what else is to be on its way before they are waited for.
+template <bool WITH_START, class F>
+__device__ __forceinline__ BatchShape make_batch_shape(const int* __restrict__ kv_len, const int* __restrict__ n_nodes, const int* __restrict__ first_node,
+                                                       const int64_t* __restrict__ kv_start, int B, int nrange, int min_bps, int G, int lane, F others_here) {
     BatchShape bs;
-    bs.n = 1; bs.first = 0; bs.L = 0; bs.blocks = 0; bs.col_groups = 0; bs.start_lo = 0; bs.start_hi = 0;
-    if (lane < prm.B) {
-        const int nn = prm.n_nodes[lane];
-        const int len = prm.kv_len[lane];
-        const int64_t st = prm.kv_start[lane];
-        bs.n = nn < 1 ? 1 : (nn > SAGE_MAX_NODES ? SAGE_MAX_NODES : nn);
-        bs.first = prm.first_node ? clamp_first(prm.first_node[lane], bs.n) : 0;
-        bs.L = len > 0 ? len : 0;
-        bs.blocks = blocks_of(bs.L) + blocks_of(bs.n);       // cache blocks, then one or two with the tree's keys
-        bs.col_groups = ((bs.n - bs.first) * prm.G + ROWS_PER_WG - 1) / ROWS_PER_WG;
+    const int seq = min(lane, B - 1);
+    int nn = n_nodes[seq], len = kv_len[seq], f = first_node ? first_node[seq] : 0;
+    bs.start_lo = 0; bs.start_hi = 0;
+    if (WITH_START) {
+        const int64_t st = kv_start[seq];
         bs.start_lo = static_cast<int>(static_cast<uint32_t>(st));
         bs.start_hi = static_cast<int>(st >> 32);
     }
-    bs.total = wave_sum_i32((bs.blocks + SEG_COST) * bs.col_groups);   // blocks = 0 in lanes past the batch, so is col_groups
-    bs.q = max(prm.min_blocks_per_split, div_ceil(bs.total, prm.nrange));
+    others_here();
+    asm volatile("" : "+v"(nn), "+v"(len), "+v"(f), "+v"(bs.start_lo), "+v"(bs.start_hi));
+    bs.n = nn < 1 ? 1 : (nn > SAGE_MAX_NODES ? SAGE_MAX_NODES : nn);
+    bs.first = clamp_first(f, bs.n);
+    bs.L = len > 0 ? len : 0;
+    bs.blocks = blocks_of(bs.L) + blocks_of(bs.n);           // cache blocks, then one or two with the tree's keys
+    bs.col_groups = lane < B ? ((bs.n - bs.first) * G + ROWS_PER_WG - 1) / ROWS_PER_WG : 0;   // (none in lanes past the batch)
+    bs.total = wave_sum_i32((bs.blocks + SEG_COST) * bs.col_groups);
+    bs.q = max(min_bps, div_ceil(bs.total, nrange));
     return bs;
 }
 
@@ -701,7 +709,7 @@ template <bool BATCH>
 __device__ __forceinline__ void attention_workgroup(const int* __restrict__ kv_len_arg, const int* __restrict__ n_nodes_arg,
                                                     const int* __restrict__ first_node_arg,
                                                     const int64_t* __restrict__ kv_start_arg, int nslot_arg, int min_bps_arg,
-                                                    int G_arg, const Params& prm, const int first_slab, LDS_AS Lds* lds) {
+                                                    int G_arg, int B_arg, int nrange_arg, const Params& prm, const int first_slab, LDS_AS Lds* lds) {
     // grid = (KV head, slot or range, sequence): the KV head is the fastest index of the launch order, and no index
     // costs a division
     const int g = blockIdx.x;
@@ -757,8 +765,8 @@ __device__ __forceinline__ void attention_workgroup(const int* __restrict__ kv_l
         const int lane = threadIdx.x & 63;
         int r0, r1, line;                                    // this workgroup's range of the list; lane b: sequence b's positions, column groups
         {
-            const BatchShape bs = make_batch_shape(prm, lane);   // lane b holds sequence b
-            arguments_here(prm);
+            const BatchShape bs = make_batch_shape<true>(kv_len_arg, n_nodes_arg, first_node_arg, kv_start_arg, B_arg, nrange_arg, min_bps_arg, G_arg,
+                                                         lane, [&]() __attribute__((always_inline)) { arguments_here(prm); });
             r0 = id * bs.q;
             r1 = min(bs.total, r0 + bs.q);
             if (r0 >= r1) return;
@@ -768,7 +776,7 @@ __device__ __forceinline__ void attention_workgroup(const int* __restrict__ kv_l
             line = (bs.blocks + SEG_COST) << 3 | bs.col_groups;
         }
         int first = 0, groups_before = 0;                    // first position / number of segments of the sequences before b
-        for (int b = 0; b < prm.B && first < r1; ++b) {
+        for (int b = 0; b < B_arg && first < r1; ++b) {
             const int line_b = __builtin_amdgcn_readlane(line, b);
             const int seg_len = line_b >> 3, cgs_b = line_b & 7;
             if (first + seg_len * cgs_b > r0) {
@@ -780,7 +788,7 @@ __device__ __forceinline__ void attention_workgroup(const int* __restrict__ kv_l
                     const int lo = max(r0, block0), hi = min(r1, block0 + seg_len - SEG_COST);
                     if (lo < hi)
                         run_segment(Segment{b, g, L_b, n_b, f_b, (n_b - f_b) * prm.G, cg, lo - block0, hi - lo, blocks_of(L_b), start_b,
-                                            g * prm.nslot + id + groups_before + cg});
+                                            g * nslot_arg + id + groups_before + cg});
                 }
             }
             first += seg_len * cgs_b;
@@ -794,9 +802,9 @@ __global__ __launch_bounds__(THREADS) void tree_attention_bf16_kernel(const int*
                                                                       const int* __restrict__ n_nodes_arg,
                                                                       const int* __restrict__ first_node_arg,
                                                                       const int64_t* __restrict__ kv_start_arg, int nslot_arg,
-                                                                      int min_bps_arg, int G_arg, const Params prm) {
+                                                                      int min_bps_arg, int G_arg, int B_arg, int nrange_arg, const Params prm) {
     __shared__ __align__(256) Lds lds;
-    attention_workgroup<BATCH>(kv_len_arg, n_nodes_arg, first_node_arg, kv_start_arg, nslot_arg, min_bps_arg, G_arg, prm, 0,
+    attention_workgroup<BATCH>(kv_len_arg, n_nodes_arg, first_node_arg, kv_start_arg, nslot_arg, min_bps_arg, G_arg, B_arg, nrange_arg, prm, 0,
                                (LDS_AS Lds*)&lds);
 }
 
@@ -827,7 +835,7 @@ template <bool BATCH>
 __global__ __launch_bounds__(THREADS) void tree_attention_plan_kernel(const int* __restrict__ kv_len_arg,
                                                                       const int* __restrict__ n_nodes_arg,
                                                                       const int64_t* __restrict__ kv_start_arg, int nslot_arg,
-                                                                      int min_bps_arg, int G_arg, int plan_slabs,
+                                                                      int min_bps_arg, int G_arg, int plan_slabs, int B_arg, int nrange_arg,
                                                                       const Params prm, const sage::PlanArgs pl) {
     __shared__ __align__(256) union Both {
         Lds attention;
@@ -843,7 +851,7 @@ __global__ __launch_bounds__(THREADS) void tree_attention_plan_kernel(const int*
         sage::plan_sequence<PLAN_OWN, THREADS>(b, pl, sh);
         return;
     }
-    attention_workgroup<BATCH>(kv_len_arg, n_nodes_arg, nullptr, kv_start_arg, nslot_arg, min_bps_arg, G_arg, prm, plan_slabs,
+    attention_workgroup<BATCH>(kv_len_arg, n_nodes_arg, nullptr, kv_start_arg, nslot_arg, min_bps_arg, G_arg, B_arg, nrange_arg, prm, plan_slabs,
                                (LDS_AS Lds*)&lds.attention);   // a verify pass: every node
 }
 
@@ -866,7 +874,7 @@ template <int MAXS, bool BATCH, int ROWS>
 __global__ __launch_bounds__(64 * ROWS) void tree_attention_merge_kernel(const int* __restrict__ kv_len_arg,
                                                                          const int* __restrict__ n_nodes_arg,
                                                                          const int* __restrict__ first_node_arg, int nslot_arg,
-                                                                         int min_bps_arg, int G_arg, int phases_arg,
+                                                                         int min_bps_arg, int G_arg, int phases_arg, int B_arg, int nrange_arg,
                                                                          const Params prm) {
     static_assert(MAXS <= 64, "one split per lane, one register per split");
     // As in the main kernel, a KV head's blocks are congruent modulo the KV-head count, so with 8 KV heads they run on
@@ -963,7 +971,8 @@ __global__ __launch_bounds__(64 * ROWS) void tree_attention_merge_kernel(const i
                   prm.part + ((static_cast<long>(b) * prm.Hkv + g) * prm.nslot + cg * sp.max_split) * PART_SLOT_B + (m % ROWS_PER_WG) * PART_ROW_B,
                   sp.nsplit);
     } else {
-        const BatchShape bs = make_batch_shape(prm, lane);
+        const BatchShape bs = make_batch_shape<false>(kv_len_arg, n_nodes_arg, first_node_arg, nullptr, B_arg, nrange_arg, min_bps_arg, G_arg, lane,
+                                                      [&]() __attribute__((always_inline)) { asm volatile("" : : "s"(prm.part), "s"(prm.O), "s"(prm.Hq), "s"(prm.inv_G), "s"(prm.scale_log2e)); });
         const int first_b = __builtin_amdgcn_readlane(bs.first, b);
         const int live = (__builtin_amdgcn_readlane(bs.n, b) - first_b) * prm.G;
         const int blocks_b = __builtin_amdgcn_readlane(bs.blocks, b);
@@ -974,7 +983,7 @@ __global__ __launch_bounds__(64 * ROWS) void tree_attention_merge_kernel(const i
             const int u0 = before + cg * (blocks_b + SEG_COST) + SEG_COST;   // first block of segment (b, cg)
             const int s_first = div_floor(u0, bs.q), node = (m * prm.inv_G) >> 16;
             merge_row(b, first_b + node, m - node * prm.G,
-                      prm.part + (static_cast<long>(g) * prm.nslot + s_first + groups_before + cg) * PART_SLOT_B + (m % ROWS_PER_WG) * PART_ROW_B,
+                      prm.part + (static_cast<long>(g) * nslot_arg + s_first + groups_before + cg) * PART_SLOT_B + (m % ROWS_PER_WG) * PART_ROW_B,
                       div_floor(u0 + blocks_b - 1, bs.q) - s_first + 1);
         }
     }
@@ -1086,18 +1095,18 @@ int tree_attention_bf16(const void* Q, const void* Kc, const void* Vc, const voi
         const dim3 grid(Hkv, plan_slabs + own_slabs, sh.batch ? 1 : B);
         if (sh.batch)
             hipLaunchKernelGGL(tree_attention_plan_kernel<true>, grid, block, 0, stream, kv_len, n_nodes, kv_start, p.nslot,
-                               p.min_blocks_per_split, G, plan_slabs, p, *plan);
+                               p.min_blocks_per_split, G, plan_slabs, B, p.nrange, p, *plan);
         else
             hipLaunchKernelGGL(tree_attention_plan_kernel<false>, grid, block, 0, stream, kv_len, n_nodes, kv_start, p.nslot,
-                               p.min_blocks_per_split, G, plan_slabs, p, *plan);
+                               p.min_blocks_per_split, G, plan_slabs, B, p.nrange, p, *plan);
     } else {
         const dim3 grid(Hkv, own_slabs, sh.batch ? 1 : B);
         if (sh.batch)
             hipLaunchKernelGGL(tree_attention_bf16_kernel<true>, grid, block, 0, stream, kv_len, n_nodes, first_node, kv_start, p.nslot,
-                               p.min_blocks_per_split, G, p);
+                               p.min_blocks_per_split, G, B, p.nrange, p);
         else
             hipLaunchKernelGGL(tree_attention_bf16_kernel<false>, grid, block, 0, stream, kv_len, n_nodes, first_node, kv_start, p.nslot,
-                               p.min_blocks_per_split, G, p);
+                               p.min_blocks_per_split, G, B, p.nrange, p);
     }
     if (hipGetLastError() != hipSuccess) return SAGE_LAUNCH_FAILED;
     const int mrows = sh.batch ? MERGE_ROWS_BATCH : MERGE_ROWS_SINGLE;
@@ -1113,22 +1122,22 @@ int tree_attention_bf16(const void* Q, const void* Kc, const void* Vc, const voi
     // memory: up to 64 splits in one (41 splits of 7 to 21 rows x 4 KV heads: 4.6 -> 4.1 us).
     if (sh.batch) {
         if (most <= 8) hipLaunchKernelGGL((tree_attention_merge_kernel<8, true, MERGE_ROWS_BATCH>), mgrid, mblock, 0, stream, kv_len, n_nodes, p.first_node, p.nslot,
-                               p.min_blocks_per_split, G, p.merge_phases, p);
+                               p.min_blocks_per_split, G, p.merge_phases, B, p.nrange, p);
         else if (most <= 16) hipLaunchKernelGGL((tree_attention_merge_kernel<16, true, MERGE_ROWS_BATCH>), mgrid, mblock, 0, stream, kv_len, n_nodes, p.first_node, p.nslot,
-                               p.min_blocks_per_split, G, p.merge_phases, p);
+                               p.min_blocks_per_split, G, p.merge_phases, B, p.nrange, p);
         else hipLaunchKernelGGL((tree_attention_merge_kernel<32, true, MERGE_ROWS_BATCH>), mgrid, mblock, 0, stream, kv_len, n_nodes, p.first_node, p.nslot,
-                               p.min_blocks_per_split, G, p.merge_phases, p);
+                               p.min_blocks_per_split, G, p.merge_phases, B, p.nrange, p);
     } else {
         if (most <= 8) hipLaunchKernelGGL((tree_attention_merge_kernel<8, false, MERGE_ROWS_SINGLE>), mgrid, mblock, 0, stream, kv_len, n_nodes, p.first_node, p.nslot,
-                               p.min_blocks_per_split, G, p.merge_phases, p);
+                               p.min_blocks_per_split, G, p.merge_phases, B, p.nrange, p);
         else if (most <= 16) hipLaunchKernelGGL((tree_attention_merge_kernel<16, false, MERGE_ROWS_SINGLE>), mgrid, mblock, 0, stream, kv_len, n_nodes, p.first_node, p.nslot,
-                               p.min_blocks_per_split, G, p.merge_phases, p);
+                               p.min_blocks_per_split, G, p.merge_phases, B, p.nrange, p);
         else if (most <= 32) hipLaunchKernelGGL((tree_attention_merge_kernel<32, false, MERGE_ROWS_SINGLE>), mgrid, mblock, 0, stream, kv_len, n_nodes, p.first_node, p.nslot,
-                               p.min_blocks_per_split, G, p.merge_phases, p);
+                               p.min_blocks_per_split, G, p.merge_phases, B, p.nrange, p);
         else if (most <= 48) hipLaunchKernelGGL((tree_attention_merge_kernel<48, false, MERGE_ROWS_SINGLE>), mgrid, mblock, 0, stream, kv_len, n_nodes, p.first_node, p.nslot,
-                               p.min_blocks_per_split, G, p.merge_phases, p);
+                               p.min_blocks_per_split, G, p.merge_phases, B, p.nrange, p);
         else hipLaunchKernelGGL((tree_attention_merge_kernel<64, false, MERGE_ROWS_SINGLE>), mgrid, mblock, 0, stream, kv_len, n_nodes, p.first_node, p.nslot,
-                               p.min_blocks_per_split, G, p.merge_phases, p);
+                               p.min_blocks_per_split, G, p.merge_phases, B, p.nrange, p);
     }
     return launch_status();
 }
