@@ -167,22 +167,60 @@ __device__ __forceinline__ Split make_split(int n_nodes, int first_node, int kv_
 }
 
 // Batched decomposition: lane b of a wave holds the shape of sequence b.  Every (sequence, column group) segment
-// occupies SEG_COST + blocks positions of one line per KV head (the first SEG_COST stand for the prologue and
-// epilogue a pass costs, about that many block steps); the line of `total` positions is cut into ranges of q, so a
-// workgroup whose range starts several segments gets fewer blocks.  Evaluated identically by both kernels.
+// occupies SEG_COST + blocks times the cost of a block positions of one line per KV head (the SEG_COST stand for the prologue
+// and epilogue a pass costs, about that many block steps); the line of `total` positions is cut into ranges of q, so a
+// workgroup whose range starts several segments gets fewer blocks.  A block belongs to the range that its first position lies
+// in.  Evaluated identically by both kernels.
+// Cost of a block: a group of up to LIGHT_ROWS rows is four waves, one per SIMD, and waits for the stream; with more rows two waves share a SIMD.
+// Among seven sequences of 12 nodes over 8192 positions, a workgroup of one with 4, 8, 12 and 16 nodes took 0.50, 0.51, 0.54 and 0.55 us a block,
+// with 17, 20, 24, 28 and 32 nodes 0.69, 0.68, 0.69, 0.69 and 0.70: the ranges of that sequence ended at 49 us, the others at 37.5; with 3 and
+// 4 positions a block the last ends at 44.7.  A batch of one kind only keeps one position a block.
+// In such mixed batches the last range is TAIL_BLOCKS shorter: where ranges fill the CUs, it is the one that waits for the workgroups that plan
+// (see tree_attention_plan_kernel).  Whole call, at 0, 8 and 12, planning along: two sequences of 12 and 24 nodes over 16096 and 13000 34.5, 32.3 and 32.7
+// us, eight of 9 to 19 nodes over 2800 to 11000 68.9, 65.9 and 66.0; attention alone 32.7, 32.5 and 32.5, 67.8, 67.4 and 67.1.
+// Whole call, equal costs before -> now: three sequences of 12, 18 and 12 nodes over 301, 1900 and 1200 positions 15.4 -> 14.3 us, twelve of 9 to 40
+// nodes over 400 to 5000 43.3 -> 42.1, five of 9 to 25 over 14000 to 20000 76.2 -> 72.0, the eight 67.7 -> 64.8.  Batches of one kind: forty of 12
+// nodes 38.8 -> 37.2 (positions by a scan of the lanes, where every workgroup walked the sequences before its own), twelve 17.0 -> 16.8, three 12.15 ->
+// 12.25, two 26.5 -> 26.9.
 constexpr int SEG_COST = 6;
+constexpr int LIGHT_ROWS = 128, LIGHT_COST = 3, HEAVY_COST = 4;
+constexpr int TAIL_BLOCKS = 8;
 struct BatchShape {
-    int n, first, L, blocks, col_groups, start_lo, start_hi; // per lane (sequence)
+    int n, first, L, start_lo, start_hi;                     // per lane (sequence)
+    int seg, col_groups;                                     // SEG_COST + blocks, and column groups (0 in lanes past the batch)
+    int cost, last_cost;                                     // positions of a block: of a full group of rows, of the last one
+    int length, at, groups_before;                           // its length on the line; position and segments of the sequences before it
     int total, q;                                            // wave-uniform
 };
-__device__ __forceinline__ int wave_sum_i32(int v) { return static_cast<int>(sage::wave_sum_u32(static_cast<uint32_t>(v))); }
+// how many blocks of `cost` positions begin before position x, counted from the first one's: x / cost, rounded up
+__device__ __forceinline__ int blocks_until(int x, int cost) {
+    static_assert(LIGHT_COST == 3 && HEAVY_COST == 4, "the factors are 2^31 over 1, 3 and 4, rounded up: exact below 2^31");
+    const unsigned up = static_cast<unsigned>(max(x, 0) + cost - 1);
+    return static_cast<int>(__umulhi(2 * up, cost == 1 ? 0x80000000u : cost == LIGHT_COST ? 0x2AAAAAABu : 0x20000000u));
+}
+// Sums over the lanes up to and including a lane's own, of two values at a time (the steps of one fill the wait states of the other's).
+__device__ __forceinline__ void wave_scan2(int& a, int& b) {
+    auto step = [&](auto ctrl, auto rows) __attribute__((always_inline)) {
+        const int x = __builtin_amdgcn_update_dpp(0, a, decltype(ctrl)::value, decltype(rows)::value, 0xF, false);
+        const int y = __builtin_amdgcn_update_dpp(0, b, decltype(ctrl)::value, decltype(rows)::value, 0xF, false);
+        a += x;
+        b += y;
+    };
+    using All = std::integral_constant<int, 0xF>;
+    step(std::integral_constant<int, 0x111>{}, All{});       // row_shr:1
+    step(std::integral_constant<int, 0x112>{}, All{});       // row_shr:2
+    step(std::integral_constant<int, 0x114>{}, All{});       // row_shr:4
+    step(std::integral_constant<int, 0x118>{}, All{});       // row_shr:8
+    step(std::integral_constant<int, 0x142>{}, std::integral_constant<int, 0xA>{});   // row_bcast:15 into rows 1 and 3
+    step(std::integral_constant<int, 0x143>{}, std::integral_constant<int, 0xC>{});   // row_bcast:31 into rows 2 and 3
+}
 // What it needs of the arguments comes in scalars that are preloaded at wave launch, see the kernels, and its loads are the first thing
 // that a wave does: from the argument block in memory they were two round trips later, in the attention's workgroups and in the merge's
 // (whole call, three sequences of 301 to 1999 positions 12.8 -> 12.4 us, seven of 300 to 1300 16.3 -> 15.6, eight of 2800 to 11000 64.3 ->
 // 62.8).  `others_here`: what else is to be on its way before they are waited for.
 template <bool WITH_START, class F>
 __device__ __forceinline__ BatchShape make_batch_shape(const int* __restrict__ kv_len, const int* __restrict__ n_nodes, const int* __restrict__ first_node,
-                                                       const int64_t* __restrict__ kv_start, int B, int nrange, int min_bps, int G, int lane, F others_here) {
+                                                       const int64_t* __restrict__ kv_start, int B, int nrange, int min_bps, int G, int light_rows, int lane, F others_here) {
     BatchShape bs;
     const int seq = min(lane, B - 1);
     int nn = n_nodes[seq], len = kv_len[seq], f = first_node ? first_node[seq] : 0;
@@ -197,10 +235,22 @@ __device__ __forceinline__ BatchShape make_batch_shape(const int* __restrict__ k
     bs.n = nn < 1 ? 1 : (nn > SAGE_MAX_NODES ? SAGE_MAX_NODES : nn);
     bs.first = clamp_first(f, bs.n);
     bs.L = len > 0 ? len : 0;
-    bs.blocks = blocks_of(bs.L) + blocks_of(bs.n);           // cache blocks, then one or two with the tree's keys
-    bs.col_groups = lane < B ? ((bs.n - bs.first) * G + ROWS_PER_WG - 1) / ROWS_PER_WG : 0;   // (none in lanes past the batch)
-    bs.total = wave_sum_i32((bs.blocks + SEG_COST) * bs.col_groups);
-    bs.q = max(min_bps, div_ceil(bs.total, nrange));
+    bs.seg = blocks_of(bs.L) + blocks_of(bs.n) + SEG_COST;   // cache blocks, then one or two with the tree's keys
+    const int last = (bs.n - bs.first) * G - 1;              // its last row (there is at least one)
+    static_assert(ROWS_PER_WG == 256 && LIGHT_ROWS == 128, "bits of a row's number");
+    // (lanes past the batch repeat its last sequence here)
+    const bool mixed = __ballot(last >= light_rows) != 0 && __ballot(!(last & 128)) != 0;
+    bs.cost = mixed ? HEAVY_COST : 1;
+    bs.last_cost = mixed ? LIGHT_COST + (static_cast<unsigned>(last) >> 7 & 1) : 1;
+    const int groups_before_last = last >> 8;
+    bs.length = lane < B ? bs.seg * (bs.cost * groups_before_last + bs.last_cost) : 0;
+    bs.col_groups = lane < B ? groups_before_last + 1 : 0;
+    int at = bs.length, groups = bs.col_groups;
+    wave_scan2(at, groups);
+    bs.total = __builtin_amdgcn_readlane(at, 63);
+    bs.at = at - bs.length;
+    bs.groups_before = groups - bs.col_groups;
+    bs.q = max(mixed ? min_bps * LIGHT_COST : min_bps, div_ceil(bs.total + (mixed ? TAIL_BLOCKS * LIGHT_COST : 0), nrange));
     return bs;
 }
 
@@ -242,6 +292,7 @@ struct Lds {
     unsigned char ring[RING_B];
     uint64_t mask[ROWS_PER_WG];          // the rows' ancestor masks
     i32x4 seq[64];                       // batches: nodes and first node, length, start of each sequence
+    i32x4 line[64];                      // ... its position on the line, SEG_COST + blocks, costs and column groups, segments before it
 };
 
 // What one pass works on; every field is wave-uniform.
@@ -709,7 +760,7 @@ template <bool BATCH>
 __device__ __forceinline__ void attention_workgroup(const int* __restrict__ kv_len_arg, const int* __restrict__ n_nodes_arg,
                                                     const int* __restrict__ first_node_arg,
                                                     const int64_t* __restrict__ kv_start_arg, int nslot_arg, int min_bps_arg,
-                                                    int G_arg, int B_arg, int nrange_arg, const Params& prm, const int first_slab, LDS_AS Lds* lds) {
+                                                    int G_arg, int B_arg, int nrange_arg, int light_rows_arg, const Params& prm, const int first_slab, LDS_AS Lds* lds) {
     // grid = (KV head, slot or range, sequence): the KV head is the fastest index of the launch order, and no index
     // costs a division
     const int g = blockIdx.x;
@@ -763,36 +814,43 @@ __device__ __forceinline__ void attention_workgroup(const int* __restrict__ kv_l
                             start_b, (b * prm.Hkv + g) * prm.nslot + cg * sp.max_split + split});
     } else {
         const int lane = threadIdx.x & 63;
-        int r0, r1, line;                                    // this workgroup's range of the list; lane b: sequence b's positions, column groups
+        int r0, r1;                                          // this workgroup's range of the line
+        uint64_t todo;                                       // the sequences that it touches
+        struct { int nodes, L, start_lo, start_hi, at, seg, costs, groups_before; } now;
         {
             const BatchShape bs = make_batch_shape<true>(kv_len_arg, n_nodes_arg, first_node_arg, kv_start_arg, B_arg, nrange_arg, min_bps_arg, G_arg,
-                                                         lane, [&]() __attribute__((always_inline)) { arguments_here(prm); });
+                                                         light_rows_arg, lane, [&]() __attribute__((always_inline)) { arguments_here(prm); });
             r0 = id * bs.q;
             r1 = min(bs.total, r0 + bs.q);
             if (r0 >= r1) return;
-            // What only a pass needs of its sequence waits in LDS, not in registers, which the passes take all of.  (Every wave writes
+            todo = __ballot(bs.at < r1 && bs.at + bs.length > r0);
+            // What a pass needs of its sequence waits in LDS, not in registers, which the passes take all of.  (Every wave writes
             // all of it and reads what it wrote itself: no barrier.)
-            lds->seq[lane] = i32x4{bs.n << 8 | bs.first, bs.L, bs.start_lo, bs.start_hi};
-            line = (bs.blocks + SEG_COST) << 3 | bs.col_groups;
+            const int nodes = bs.n << 8 | bs.first, costs = bs.cost << 8 | bs.last_cost << 4 | bs.col_groups;
+            lds->seq[lane] = i32x4{nodes, bs.L, bs.start_lo, bs.start_hi};
+            lds->line[lane] = i32x4{bs.at, bs.seg, costs, bs.groups_before};
+            const int b = __builtin_ctzll(todo);             // (the first pass does not wait for LDS)
+            auto of = [b](int x) __attribute__((always_inline)) { return __builtin_amdgcn_readlane(x, b); };
+            now = {of(nodes), of(bs.L), of(bs.start_lo), of(bs.start_hi), of(bs.at), of(bs.seg), of(costs), of(bs.groups_before)};
         }
-        int first = 0, groups_before = 0;                    // first position / number of segments of the sequences before b
-        for (int b = 0; b < B_arg && first < r1; ++b) {
-            const int line_b = __builtin_amdgcn_readlane(line, b);
-            const int seg_len = line_b >> 3, cgs_b = line_b & 7;
-            if (first + seg_len * cgs_b > r0) {
-                const int nf = lds->seq[b].x, L_b = lds->seq[b].y;
-                const int n_b = nf >> 8, f_b = nf & 255;
-                const long start_b = (static_cast<long>(lds->seq[b].w) << 32) | static_cast<uint32_t>(lds->seq[b].z);
-                for (int cg = 0; cg < cgs_b; ++cg) {
-                    const int block0 = first + cg * seg_len + SEG_COST;      // position of the segment's first block
-                    const int lo = max(r0, block0), hi = min(r1, block0 + seg_len - SEG_COST);
-                    if (lo < hi)
-                        run_segment(Segment{b, g, L_b, n_b, f_b, (n_b - f_b) * prm.G, cg, lo - block0, hi - lo, blocks_of(L_b), start_b,
-                                            g * nslot_arg + id + groups_before + cg});
-                }
+        while (true) {                                       // (todo is not empty: a range has positions)
+            const int b = __builtin_ctzll(todo);
+            const int n_b = now.nodes >> 8, f_b = now.nodes & 255, L_b = now.L, seg = now.seg, cgs_b = now.costs & 15;
+            const long start_b = (static_cast<long>(now.start_hi) << 32) | static_cast<uint32_t>(now.start_lo);
+            int at = now.at, slot_b = g * nslot_arg + id + now.groups_before;
+            for (int cg = 0; cg < cgs_b; ++cg) {
+                const int cost = cg + 1 == cgs_b ? now.costs >> 4 & 15 : now.costs >> 8;
+                const int block0 = at + SEG_COST * cost;     // position of the segment's first block
+                const int lo = blocks_until(r0 - block0, cost), hi = min(seg - SEG_COST, blocks_until(r1 - block0, cost));
+                if (lo < hi)
+                    run_segment(Segment{b, g, L_b, n_b, f_b, (n_b - f_b) * G_arg, cg, lo, hi - lo, blocks_of(L_b), start_b, slot_b + cg});
+                at += seg * cost;
             }
-            first += seg_len * cgs_b;
-            groups_before += cgs_b;
+            todo &= todo - 1;
+            if (todo == 0) break;
+            const i32x4 s = lds->seq[__builtin_ctzll(todo)], l = lds->line[__builtin_ctzll(todo)];
+            auto uni = [](int x) __attribute__((always_inline)) { return __builtin_amdgcn_readfirstlane(x); };
+            now = {uni(s.x), uni(s.y), uni(s.z), uni(s.w), uni(l.x), uni(l.y), uni(l.z), uni(l.w)};
         }
     }
 }
@@ -802,9 +860,9 @@ __global__ __launch_bounds__(THREADS) void tree_attention_bf16_kernel(const int*
                                                                       const int* __restrict__ n_nodes_arg,
                                                                       const int* __restrict__ first_node_arg,
                                                                       const int64_t* __restrict__ kv_start_arg, int nslot_arg,
-                                                                      int min_bps_arg, int G_arg, int B_arg, int nrange_arg, const Params prm) {
+                                                                      int min_bps_arg, int G_arg, int B_arg, int nrange_arg, int light_rows_arg, const Params prm) {
     __shared__ __align__(256) Lds lds;
-    attention_workgroup<BATCH>(kv_len_arg, n_nodes_arg, first_node_arg, kv_start_arg, nslot_arg, min_bps_arg, G_arg, B_arg, nrange_arg, prm, 0,
+    attention_workgroup<BATCH>(kv_len_arg, n_nodes_arg, first_node_arg, kv_start_arg, nslot_arg, min_bps_arg, G_arg, B_arg, nrange_arg, light_rows_arg, prm, 0,
                                (LDS_AS Lds*)&lds);
 }
 
@@ -835,7 +893,7 @@ template <bool BATCH>
 __global__ __launch_bounds__(THREADS) void tree_attention_plan_kernel(const int* __restrict__ kv_len_arg,
                                                                       const int* __restrict__ n_nodes_arg,
                                                                       const int64_t* __restrict__ kv_start_arg, int nslot_arg,
-                                                                      int min_bps_arg, int G_arg, int plan_slabs, int B_arg, int nrange_arg,
+                                                                      int min_bps_arg, int G_arg, int plan_slabs, int B_arg, int nrange_arg, int light_rows_arg,
                                                                       const Params prm, const sage::PlanArgs pl) {
     __shared__ __align__(256) union Both {
         Lds attention;
@@ -851,7 +909,7 @@ __global__ __launch_bounds__(THREADS) void tree_attention_plan_kernel(const int*
         sage::plan_sequence<PLAN_OWN, THREADS>(b, pl, sh);
         return;
     }
-    attention_workgroup<BATCH>(kv_len_arg, n_nodes_arg, nullptr, kv_start_arg, nslot_arg, min_bps_arg, G_arg, B_arg, nrange_arg, prm, plan_slabs,
+    attention_workgroup<BATCH>(kv_len_arg, n_nodes_arg, nullptr, kv_start_arg, nslot_arg, min_bps_arg, G_arg, B_arg, nrange_arg, light_rows_arg, prm, plan_slabs,
                                (LDS_AS Lds*)&lds.attention);   // a verify pass: every node
 }
 
@@ -874,7 +932,7 @@ template <int MAXS, bool BATCH, int ROWS>
 __global__ __launch_bounds__(64 * ROWS) void tree_attention_merge_kernel(const int* __restrict__ kv_len_arg,
                                                                          const int* __restrict__ n_nodes_arg,
                                                                          const int* __restrict__ first_node_arg, int nslot_arg,
-                                                                         int min_bps_arg, int G_arg, int phases_arg, int B_arg, int nrange_arg,
+                                                                         int min_bps_arg, int G_arg, int phases_arg, int B_arg, int nrange_arg, int light_rows_arg,
                                                                          const Params prm) {
     static_assert(MAXS <= 64, "one split per lane, one register per split");
     // As in the main kernel, a KV head's blocks are congruent modulo the KV-head count, so with 8 KV heads they run on
@@ -971,20 +1029,20 @@ __global__ __launch_bounds__(64 * ROWS) void tree_attention_merge_kernel(const i
                   prm.part + ((static_cast<long>(b) * prm.Hkv + g) * prm.nslot + cg * sp.max_split) * PART_SLOT_B + (m % ROWS_PER_WG) * PART_ROW_B,
                   sp.nsplit);
     } else {
-        const BatchShape bs = make_batch_shape<false>(kv_len_arg, n_nodes_arg, first_node_arg, nullptr, B_arg, nrange_arg, min_bps_arg, G_arg, lane,
+        const BatchShape bs = make_batch_shape<false>(kv_len_arg, n_nodes_arg, first_node_arg, nullptr, B_arg, nrange_arg, min_bps_arg, G_arg, light_rows_arg, lane,
                                                       [&]() __attribute__((always_inline)) { asm volatile("" : : "s"(prm.part), "s"(prm.O), "s"(prm.Hq), "s"(prm.inv_G), "s"(prm.scale_log2e)); });
         const int first_b = __builtin_amdgcn_readlane(bs.first, b);
-        const int live = (__builtin_amdgcn_readlane(bs.n, b) - first_b) * prm.G;
-        const int blocks_b = __builtin_amdgcn_readlane(bs.blocks, b);
-        const int before = wave_sum_i32(lane < b ? (bs.blocks + SEG_COST) * bs.col_groups : 0);
-        const int groups_before = wave_sum_i32(lane < b ? bs.col_groups : 0);
+        const int live = (__builtin_amdgcn_readlane(bs.n, b) - first_b) * G_arg;
+        const int seg = __builtin_amdgcn_readlane(bs.seg, b), at = __builtin_amdgcn_readlane(bs.at, b);
+        const int last_cost = __builtin_amdgcn_readlane(bs.last_cost, b);
+        const int slot_b = g * nslot_arg + __builtin_amdgcn_readlane(bs.groups_before, b);
         for (int m = phase * ROWS + wave; m < live; m += phases * ROWS) {
             const int cg = m / ROWS_PER_WG;
-            const int u0 = before + cg * (blocks_b + SEG_COST) + SEG_COST;   // first block of segment (b, cg)
+            const int cost = m - m % ROWS_PER_WG + ROWS_PER_WG < live ? bs.cost : last_cost;
+            const int u0 = at + cg * seg * bs.cost + SEG_COST * cost;   // first block of segment (b, cg)
             const int s_first = div_floor(u0, bs.q), node = (m * prm.inv_G) >> 16;
-            merge_row(b, first_b + node, m - node * prm.G,
-                      prm.part + (static_cast<long>(g) * nslot_arg + s_first + groups_before + cg) * PART_SLOT_B + (m % ROWS_PER_WG) * PART_ROW_B,
-                      div_floor(u0 + blocks_b - 1, bs.q) - s_first + 1);
+            merge_row(b, first_b + node, m - node * G_arg, prm.part + static_cast<long>(slot_b + s_first + cg) * PART_SLOT_B + (m % ROWS_PER_WG) * PART_ROW_B,
+                      div_floor(u0 + (seg - SEG_COST - 1) * cost, bs.q) - s_first + 1);
         }
     }
 }
@@ -1086,6 +1144,9 @@ int tree_attention_bf16(const void* Q, const void* Kc, const void* Vc, const voi
     p.scale_log2e = scale * 1.4426950408889634f;
 
     p.nrange = sh.nrange;
+    // (blocks of different costs only where the line has less than 2^31 positions whatever the lengths are)
+    const int light_rows = max_kv_len < (1 << 25) ? LIGHT_ROWS : 1 << 30;
+    static_assert(MAX_BATCH_LANES * 4L * ((1L << 25) / BLK + 2 + SEG_COST) * HEAVY_COST + TAIL_BLOCKS * LIGHT_COST < (1L << 31), "64 sequences of four groups");
     const int own_slabs = sh.batch ? p.nrange : p.nslot;
     const dim3 block(THREADS);
     if (plan) {
@@ -1095,18 +1156,18 @@ int tree_attention_bf16(const void* Q, const void* Kc, const void* Vc, const voi
         const dim3 grid(Hkv, plan_slabs + own_slabs, sh.batch ? 1 : B);
         if (sh.batch)
             hipLaunchKernelGGL(tree_attention_plan_kernel<true>, grid, block, 0, stream, kv_len, n_nodes, kv_start, p.nslot,
-                               p.min_blocks_per_split, G, plan_slabs, B, p.nrange, p, *plan);
+                               p.min_blocks_per_split, G, plan_slabs, B, p.nrange, light_rows, p, *plan);
         else
             hipLaunchKernelGGL(tree_attention_plan_kernel<false>, grid, block, 0, stream, kv_len, n_nodes, kv_start, p.nslot,
-                               p.min_blocks_per_split, G, plan_slabs, B, p.nrange, p, *plan);
+                               p.min_blocks_per_split, G, plan_slabs, B, p.nrange, light_rows, p, *plan);
     } else {
         const dim3 grid(Hkv, own_slabs, sh.batch ? 1 : B);
         if (sh.batch)
             hipLaunchKernelGGL(tree_attention_bf16_kernel<true>, grid, block, 0, stream, kv_len, n_nodes, first_node, kv_start, p.nslot,
-                               p.min_blocks_per_split, G, B, p.nrange, p);
+                               p.min_blocks_per_split, G, B, p.nrange, light_rows, p);
         else
             hipLaunchKernelGGL(tree_attention_bf16_kernel<false>, grid, block, 0, stream, kv_len, n_nodes, first_node, kv_start, p.nslot,
-                               p.min_blocks_per_split, G, B, p.nrange, p);
+                               p.min_blocks_per_split, G, B, p.nrange, light_rows, p);
     }
     if (hipGetLastError() != hipSuccess) return SAGE_LAUNCH_FAILED;
     const int mrows = sh.batch ? MERGE_ROWS_BATCH : MERGE_ROWS_SINGLE;
@@ -1122,22 +1183,22 @@ int tree_attention_bf16(const void* Q, const void* Kc, const void* Vc, const voi
     // memory: up to 64 splits in one (41 splits of 7 to 21 rows x 4 KV heads: 4.6 -> 4.1 us).
     if (sh.batch) {
         if (most <= 8) hipLaunchKernelGGL((tree_attention_merge_kernel<8, true, MERGE_ROWS_BATCH>), mgrid, mblock, 0, stream, kv_len, n_nodes, p.first_node, p.nslot,
-                               p.min_blocks_per_split, G, p.merge_phases, B, p.nrange, p);
+                               p.min_blocks_per_split, G, p.merge_phases, B, p.nrange, light_rows, p);
         else if (most <= 16) hipLaunchKernelGGL((tree_attention_merge_kernel<16, true, MERGE_ROWS_BATCH>), mgrid, mblock, 0, stream, kv_len, n_nodes, p.first_node, p.nslot,
-                               p.min_blocks_per_split, G, p.merge_phases, B, p.nrange, p);
+                               p.min_blocks_per_split, G, p.merge_phases, B, p.nrange, light_rows, p);
         else hipLaunchKernelGGL((tree_attention_merge_kernel<32, true, MERGE_ROWS_BATCH>), mgrid, mblock, 0, stream, kv_len, n_nodes, p.first_node, p.nslot,
-                               p.min_blocks_per_split, G, p.merge_phases, B, p.nrange, p);
+                               p.min_blocks_per_split, G, p.merge_phases, B, p.nrange, light_rows, p);
     } else {
         if (most <= 8) hipLaunchKernelGGL((tree_attention_merge_kernel<8, false, MERGE_ROWS_SINGLE>), mgrid, mblock, 0, stream, kv_len, n_nodes, p.first_node, p.nslot,
-                               p.min_blocks_per_split, G, p.merge_phases, B, p.nrange, p);
+                               p.min_blocks_per_split, G, p.merge_phases, B, p.nrange, light_rows, p);
         else if (most <= 16) hipLaunchKernelGGL((tree_attention_merge_kernel<16, false, MERGE_ROWS_SINGLE>), mgrid, mblock, 0, stream, kv_len, n_nodes, p.first_node, p.nslot,
-                               p.min_blocks_per_split, G, p.merge_phases, B, p.nrange, p);
+                               p.min_blocks_per_split, G, p.merge_phases, B, p.nrange, light_rows, p);
         else if (most <= 32) hipLaunchKernelGGL((tree_attention_merge_kernel<32, false, MERGE_ROWS_SINGLE>), mgrid, mblock, 0, stream, kv_len, n_nodes, p.first_node, p.nslot,
-                               p.min_blocks_per_split, G, p.merge_phases, B, p.nrange, p);
+                               p.min_blocks_per_split, G, p.merge_phases, B, p.nrange, light_rows, p);
         else if (most <= 48) hipLaunchKernelGGL((tree_attention_merge_kernel<48, false, MERGE_ROWS_SINGLE>), mgrid, mblock, 0, stream, kv_len, n_nodes, p.first_node, p.nslot,
-                               p.min_blocks_per_split, G, p.merge_phases, B, p.nrange, p);
+                               p.min_blocks_per_split, G, p.merge_phases, B, p.nrange, light_rows, p);
         else hipLaunchKernelGGL((tree_attention_merge_kernel<64, false, MERGE_ROWS_SINGLE>), mgrid, mblock, 0, stream, kv_len, n_nodes, p.first_node, p.nslot,
-                               p.min_blocks_per_split, G, p.merge_phases, B, p.nrange, p);
+                               p.min_blocks_per_split, G, p.merge_phases, B, p.nrange, light_rows, p);
     }
     return launch_status();
 }

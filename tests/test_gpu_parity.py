@@ -553,6 +553,33 @@ def test_attention_bf16_cut_of_batches(gu, monkeypatch, lens, nodes):
         assert set(np.flatnonzero(head)) == want
 
 
+@pytest.mark.parametrize("lens,nodes", [([301, 1900, 1200], [16, 17, 12]), ([6000, 2500], [32, 4]), ([900, 2100, 0, 5000], [33, 64, 1, 48]),
+                                        ([4000, 2000, 3000], [49, 20, 64]), ([90, 10], [3, 40])])
+def test_attention_bf16_cut_of_mixed_batches(gu, monkeypatch, lens, nodes):
+    """The same for batches in which some groups have more than 128 rows and others do not: a block takes 4 positions there and 3 here,
+    belongs to the range that its first one lies in, and the line is cut as if it were 24 positions longer."""
+    Hq, Hkv, slot_bytes = 64, 8, 256 * 272
+    kept, workspace = [], gu.workspace
+    monkeypatch.setattr(gu, "workspace", lambda n: kept.append(workspace(n)) or kept[-1])
+    run_attention_case(gu, 3600, "bf16", len(lens), Hq, Hkv, 128, lens, nodes)
+    slots = kept[-1].numel() // (Hkv * slot_bytes)
+    rows = kept[-1][:Hkv * slots * slot_bytes].view(Hkv, slots, slot_bytes)[:, :, 256:264]
+    groups = [(min(256, n * (Hq // Hkv) - first), 6 + -(-L // 32) + -(-n // 32)) for L, n in zip(lens, nodes) for first in range(0, n * (Hq // Hkv), 256)]
+    costs = [4 if rows_of > 128 else 3 for rows_of, _ in groups]
+    mixed = len(set(costs)) == 2
+    assert mixed == (lens != [4000, 2000, 3000])
+    costs = costs if mixed else [1] * len(groups)
+    total = sum(c * segment for c, (_, segment) in zip(costs, groups))
+    length = max(18 if mixed else 6, -(-(total + (24 if mixed else 0)) // (slots - 2 * len(lens))))
+    want, at = set(), 0
+    for i, (c, (_, segment)) in enumerate(zip(costs, groups)):
+        want |= {(at + c * block) // length + i for block in range(6, segment)}
+        at += c * segment
+    written = (rows != 0xFF).any(-1).cpu().numpy()
+    for head in written:
+        assert set(np.flatnonzero(head)) == want
+
+
 @pytest.mark.parametrize("tiles", [32, 33, 48, 49, 64, 65, 128, 129])
 def test_attention_bf16_split_counts(gu, tiles):
     """One sequence and two KV heads: a split per 64-token tile up to 128, so the merge takes every one of its widths at its
