@@ -3,9 +3,9 @@
 // the target's greedy token per tree node (Sec. 2.2 / Def. 4.1).
 //
 // Every logit is read exactly once with 16-byte loads.  Candidates are ordered by a 64-bit composite key (value
-// descending, index ascending).  Pass 1 cuts a row into slices of UNIT logits: with k = 1 each WAVE owns a slice and takes
-// its maximum, done with DPP row rotations and the 16/32-lane swaps (no LDS, no workgroup barrier); with k > 1 a workgroup
-// owns it, each wave finds what its k best logits reach and the survivors are ranked by counting.  Either reduces the
+// descending, index ascending).  Pass 1 cuts a row into slices of UNIT logits, which a WAVE owns up to k = 48: with k = 1 it takes
+// the maximum (DPP row rotations and the 16/32-lane swaps, no LDS, no workgroup barrier), with more it finds what its k best
+// logits reach and ranks by counting what reaches that; longer lists are found by a workgroup per slice.  Either reduces the
 // slice's softmax statistics
 //   Z = sum exp(x - m),  T = sum exp(x - m) (m - x)   so that   H = ln Z + T / Z   (both terms >= 0).
 // Pass 2 combines the slice statistics by log-sum-exp, finds the k winners of the sorted per-slice lists (k = 1: a wave per
@@ -89,15 +89,12 @@ __device__ __forceinline__ void wave_sums(float& a, float& b) {
     a = sage::lane_value(v, 0);
     b = sage::lane_value(v, 32);
 }
-// (returned in every lane, and stored)
-struct Reduced { UnitStats stats; uint64_t key; };
+// The 16 logits of a lane, -inf past the row's end.
 template <typename T, int NV>
-__device__ __forceinline__ Reduced reduce_unit(const T* __restrict__ rowp, int base, int lane, int vocab,
-                                               const typename Loader<T>::Raw (&raw)[NV], UnitStats* __restrict__ stat_out,
-                                               uint64_t* __restrict__ key_out) {
+__device__ __forceinline__ void unpack_unit(const T* __restrict__ rowp, int base, int lane, int vocab,
+                                            const typename Loader<T>::Raw (&raw)[NV], float (&v)[EPT]) {
     using L = Loader<T>;
     constexpr int VEC = L::VEC;
-    float v[EPT];
     if (base + UNIT <= vocab) {                          // a whole slice (wave-uniform)
 #pragma unroll
         for (int j = 0; j < NV; ++j) L::unpack(raw[j], v + j * VEC);
@@ -109,10 +106,40 @@ __device__ __forceinline__ Reduced reduce_unit(const T* __restrict__ rowp, int b
                 L::unpack(raw[j], v + j * VEC);
             } else {
 #pragma unroll
-                for (int e = 0; e < VEC; ++e) v[j * VEC + e] = (e0 + e < vocab) ? L::one(rowp + e0 + e) : -INFINITY;
+                for (int e = 0; e < VEC; ++e) v[j * VEC + e] = -INFINITY;
+                if (e0 < vocab) {                        // (one lane of the row; where there is none, no questions)
+#pragma unroll
+                    for (int e = 0; e + 1 < VEC; ++e)
+                        if (e0 + e < vocab) v[j * VEC + e] = L::one(rowp + e0 + e);
+                }
             }
         }
     }
+}
+// Softmax statistics of the slice relative to its maximum: a lane's share of the sums.  (EXACT: a -inf logit adds exactly 0, not 1e-38.)
+template <bool EXACT>
+__device__ __forceinline__ void unit_sums(const float (&v)[EPT], float unit_max, float& Z, float& Tm) {
+    Z = 0.f;
+    Tm = 0.f;
+    if (unit_max > -INFINITY) {
+#pragma unroll
+        for (int s = 0; s < EPT; ++s) {
+            const float dlt = EXACT ? unit_max - v[s] : fminf(unit_max - v[s], 87.0f);
+            const float e = __builtin_amdgcn_exp2f(dlt * -1.4426950408889634f);
+            Z += e;
+            Tm = fmaf(e, EXACT && !(e > 0.f) ? 0.f : dlt, Tm);
+        }
+    }
+}
+// (returned in every lane, and stored)
+struct Reduced { UnitStats stats; uint64_t key; };
+template <typename T, int NV>
+__device__ __forceinline__ Reduced reduce_unit(const T* __restrict__ rowp, int base, int lane, int vocab,
+                                               const typename Loader<T>::Raw (&raw)[NV], UnitStats* __restrict__ stat_out,
+                                               uint64_t* __restrict__ key_out) {
+    constexpr int VEC = Loader<T>::VEC;
+    float v[EPT];
+    unpack_unit<T, NV>(rowp, base, lane, vocab, raw, v);
 
     // ---- the slice's best candidate: the largest value, at its lowest index.  Indices ascend by load, lane and element: the first load
     // that has the value, its first lane, that lane's first element.
@@ -138,17 +165,8 @@ __device__ __forceinline__ Reduced reduce_unit(const T* __restrict__ rowp, int b
         }
     }
     unit_max = wave_max(unit_max) + 0.f;                 // (-0 is +0, as in the key)
-    // ---- softmax statistics of the slice relative to its own maximum
-    float Z = 0.f, Tm = 0.f;
-    if (unit_max > -INFINITY) {
-#pragma unroll
-        for (int s = 0; s < EPT; ++s) {
-            const float dlt = fminf(unit_max - v[s], 87.0f);
-            const float e = __builtin_amdgcn_exp2f(dlt * -1.4426950408889634f);
-            Z += e;
-            Tm = fmaf(e, dlt, Tm);
-        }
-    }
+    float Z, Tm;
+    unit_sums<false>(v, unit_max, Z, Tm);
     int at = base;                                       // (a slice without a number: a token of the row all the same)
     bool found = false;
 #pragma unroll
@@ -240,124 +258,210 @@ __global__ __launch_bounds__(THREADS) void slice_rows_kernel(const T* __restrict
                         gridDim.y, blockIdx.z);
 }
 
-// Pass 1 for bf16 logits and 1 < k <= 16 (the draft row of a step; pure latency, so the serial selection rounds are
-// kept as short as they can be): the same decomposition as the generic kernel below, but the rounds run on ONE
-// 32-bit word per candidate, (16-bit value code << 16) | (1024 - position in the slice), whose order is the total
-// order (value descending, index ascending) inside a slice; 0 = no candidate.  Each wave selects the k best of its
-// 256 logits, wave 0 then ranks the 4k survivors by counting.
-constexpr int FAST_MAX_K = 16;
-__device__ __forceinline__ void slice_topk_bf16_block(const uint16_t* __restrict__ logits, int vocab, long row_stride, int k,
-                                                      const int* __restrict__ n_valid, int rows_per_group, int nunits,
-                                                      UnitStats* __restrict__ stats, uint64_t* __restrict__ keys, int unit,
-                                                      int row) {
-    __shared__ __align__(16) uint32_t s_list[WAVES * FAST_MAX_K];
-    __shared__ float s_red[3][WAVES];
-    if (!row_is_valid(row, n_valid, rows_per_group)) return;
-    const int lane = threadIdx.x & 63;
-    const int wave = threadIdx.x >> 6;
-    const uint16_t* rowp = logits + static_cast<long>(row) * row_stride;
-    const int local0 = threadIdx.x * 4;
-    const int e0 = unit * UNIT + local0;
-
-    float v[4];
-    if (e0 + 4 <= vocab) {
-        const uint2 q = *reinterpret_cast<const uint2*>(rowp + e0);
-        v[0] = __uint_as_float(q.x << 16); v[1] = __uint_as_float(q.x & 0xFFFF0000u);
-        v[2] = __uint_as_float(q.y << 16); v[3] = __uint_as_float(q.y & 0xFFFF0000u);
-    } else {
+// Pass 1 for 1 < k <= WAVE_MAX_K (draft rows): a wave per slice, 16 logits per lane, as with k = 1.  The k best of the slice reach what k of the
+// lanes' largest logits reach, and few others do: that threshold is found bit by bit, a ballot a bit, from the first bit in which those 64
+// differ; what reaches it goes to LDS, a logit of every lane at a time, and a lane per entry counts the entries above its own, which is its place.
+// Where that does not hold (more logits reach the threshold than the list has room for, fewer than k lanes have a logit above -inf, or some are
+// no numbers) the threshold is settled among all 1024 codes, and of those that equal it the first are taken.
+// What bounds it is what is executed: 149 slices of a row are 149 waves on 1024 SIMDs, so that with few rows the chain counts and with many the
+// instructions.  Against a workgroup per slice (four waves that each selected k of 256 logits, by k rounds of a maximum for bf16 and k <= 16, by
+// ballots over all values otherwise, and a fifth selection among theirs), whole call, 152064 logits: fp32 k = 10, one row 8.95 -> 8.15 us,
+// eight 12.0 -> 8.9, a hundred 46 -> 18.5; bf16 k = 10, one row 8.45 -> 8.1, eight 10.9 -> 8.9, forty 21.6 -> 11.6, three hundred 103 -> 35; k = 16, twelve rows 14.4
+// -> 9.8; k = 40, eight rows 18.7 -> 14.5.  Beside the rows of trees of 12 nodes, in a step: one sequence 4.7 -> 4.5, three 5.9 -> 5.6, eight 10.9 -> 9.4.
+// Of the odd ones, eight rows: all logits equal 15.3 -> 15.7 (fp32 19.5 -> 15.7), bf16 in steps of one 13.5 -> 14.2, all but 1000 logits -inf 11.6 -> 12.3 (fp32
+// 15.7 -> 13.2), rising bf16 logits 13.3 -> 16.1 (fp32 15.9 -> 12.9).
+// MOST_LANES: with k near 64 a threshold that nearly all lanes reach lets too many logits through (k = 40, eight fp32 rows: 14.4 us with 44 lanes at
+// most, 15.3 with 52).  Beyond k = 48 a workgroup per slice is the faster one (one row, k = 56, 15.1 us and 18.0; k = 48, 14.7 and 14.4).
+constexpr int WAVE_MAX_K = 48;
+constexpr int WAVE_LIST = 128;
+constexpr int MOST_LANES = 44;
+struct SliceTop { UnitStats stats; uint64_t key[2]; int place[2]; };   // a lane's entries and their places in the slice's list (none: WAVE_LIST)
+template <typename T, int NV>
+__device__ __forceinline__ SliceTop slice_topk_wave(const T* __restrict__ rowp, int base, int lane, int vocab, int k,
+                                                    const typename Loader<T>::Raw (&raw)[NV], uint64_t* list) {
+    constexpr int VEC = Loader<T>::VEC;
+    // the codes of different bf16 values differ in their upper halves
+    constexpr uint32_t LAST_BIT = sizeof(T) == 4 ? 1u : 0x10000u, REST = LAST_BIT - 1;
+    float v[EPT];
+    unpack_unit<T, NV>(rowp, base, lane, vocab, raw, v);
+    auto index = [&](int i) __attribute__((always_inline)) { return base + ((i / VEC) * 64 + lane) * VEC + i % VEC; };
+    const int present = vocab - base, want = min(k, present);
+    float top = v[0];                                    // (a NaN if the lane has one, see maximum3)
 #pragma unroll
-        for (int e = 0; e < 4; ++e) v[e] = (e0 + e < vocab) ? Loader<uint16_t>::one(rowp + e0 + e) : -INFINITY;
-    }
-    uint32_t cand[4];
-#pragma unroll
-    for (int e = 0; e < 4; ++e)
-        cand[e] = (e0 + e < vocab) ? ((sortable(v[e]) & 0xFFFF0000u) | static_cast<uint32_t>(UNIT - (local0 + e))) : 0u;
-
-    uint32_t mine = 0, top = 0;                      // lane j keeps the wave's winner of round j
-    for (int round = 0; round < k; ++round) {
-        const uint32_t g = wave_max_u32(max(max(cand[0], cand[1]), max(cand[2], cand[3])));
-        if (round == 0) top = g;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) cand[e] = (cand[e] == g) ? 0u : cand[e];
-        if (lane == round) mine = g;
-    }
-    if (lane < k) s_list[wave * k + lane] = mine;
-    else if (wave == WAVES - 1 && WAVES * k + lane - k < ((WAVES * k + 15) & ~15)) s_list[WAVES * k + lane - k] = 0;
-    // a bf16 value's 32-bit code is its 16-bit code followed by sixteen zeros (non-negative) or ones (negative)
-    auto full_code = [](uint32_t key) { return (key & 0xFFFF0000u) | ((key & 0x80000000u) ? 0u : 0xFFFFu); };
-    const float wmax = top ? unsortable(full_code(top)) : -INFINITY;
-    float Z = 0.f, Tm = 0.f;
-    if (wmax > -INFINITY) {
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const float dlt = wmax - v[e];
-            const float ex = __builtin_amdgcn_exp2f(dlt * -1.4426950408889634f);   // exactly 0 for a -inf logit
-            Z += ex;
-            Tm += (ex > 0.f) ? ex * dlt : 0.f;
+    for (int i = 1; i + 1 < EPT; i += 2) top = maximum3(top, v[i], v[i + 1]);
+    top = maximum3(top, v[EPT - 1], v[EPT - 1]);
+    const uint32_t code = sortable(top);
+    uint32_t hi = __builtin_amdgcn_readfirstlane(wave_max_u32(code));
+    const uint32_t lo = __builtin_amdgcn_readfirstlane(~wave_max_u32(~code));
+    uint32_t bit = hi == lo ? 0u : 0x80000000u >> __builtin_clz(hi ^ lo);
+    uint32_t thr = bit ? hi & ~(2u * bit - 1u) : hi;     // what all lanes have in common (2 bit wraps to 0: nothing)
+    int got = 64;
+    auto search = [&](int most) __attribute__((always_inline)) {       // until at most that many lanes reach it, or it is a lane's value
+        while ((bit >= LAST_BIT) & (got > most)) {
+            const int n = __builtin_popcountll(__ballot(code >= (thr | bit)));
+            thr = n >= want ? thr | bit : thr;
+            got = n >= want ? n : got;
+            bit >>= 1;
         }
+    };
+    bool tail = present <= WAVE_LIST && present <= VEC * (want - 1);   // a last slice that fits the list whole, with logits in too few lanes
+    if (!tail) search(min(want + want / 2 + 2, max(want, MOST_LANES)));
+    const float floor = unsortable(thr);
+    const bool nan = __any(top != top);
+    const bool clear = !tail && !nan && floor > -INFINITY;   // (a number then: thr lies between two lanes' codes, or is what they share)
+    tail = !clear && present <= WAVE_LIST;
+    const bool usual = clear || tail;
+    uint32_t mine = 0;                                   // which of its logits the lane has yet to put on the list
+#pragma unroll
+    for (int i = EPT - 1; i >= 0; --i) mine = mine + mine + (v[i] >= floor ? 1u : 0u);
+    if (tail) {
+        mine = 0;
+#pragma unroll
+        for (int j = 0; j < NV; ++j) mine |= ((1u << min(max(present - (j * 64 + lane) * VEC, 0), VEC)) - 1u) << (j * VEC);
     }
-    Z = wave_sum(Z);
-    Tm = wave_sum(Tm);
-    if (lane == 0) { s_red[0][wave] = wmax; s_red[1][wave] = Z; s_red[2][wave] = Tm; }
-    __syncthreads();
-    if (wave != 0) return;
-
-    // ---- wave 0: a lane per survivor finds its place in the slice's list (distinct words, 0 = none), by counting the survivors
-    // above it (about 600 cycles) or, for very short lists, by k rounds of a maximum (about 110 each)
-    const uint32_t key = lane < WAVES * k ? s_list[lane] : 0u;
-    int above = 0;
-    if (k <= 5) {
-        uint32_t rest = key;
-        above = k;
-        for (int round = 0; round < k; ++round) {
-            const uint32_t g = wave_max_u32(rest);
-            // (0 marks the lanes without a candidate and those ranked already: fewer than k candidates are not matched again)
-            if (g != 0 && rest == g) { above = round; rest = 0u; }
-        }
-    } else {
-        for (int o = 0; o < WAVES * k; o += 16) {            // (the list is padded with zeros to whole pieces of 16)
-            uint4 q[4];
+    int n = 0;
+    uint64_t b = usual ? __ballot(mine != 0) : 0;
+    while (b != 0) {                                     // one by every lane at a time, seldom more than two
+        const int i = __builtin_ctz(mine | 0x10000u);
+        float x[EPT];
 #pragma unroll
-            for (int u = 0; u < 4; ++u) q[u] = *reinterpret_cast<const uint4*>(s_list + o + 4 * u);
+        for (int e = 0; e < EPT; ++e) x[e] = v[e];
 #pragma unroll
-            for (int u = 0; u < 4; ++u)
-                above += (q[u].x > key ? 1 : 0) + (q[u].y > key ? 1 : 0) + (q[u].z > key ? 1 : 0) + (q[u].w > key ? 1 : 0);
-        }
-    }
-    uint64_t* const kout = keys + (static_cast<long>(row) * nunits + unit) * k;
-    if (key != 0 && above < k)
-        kout[above] = key_pack(Key{full_code(key), 0xFFFFFFFFu - static_cast<uint32_t>(unit * UNIT + UNIT - static_cast<int>(key & 0xFFFFu))});
-    const int present = vocab - unit * UNIT;                 // a short last slice has no more candidates than logits
-    if (lane < k && lane >= present) kout[lane] = 0;
-    if (lane == 0) {
-        float m = fmaxf(fmaxf(s_red[0][0], s_red[0][1]), fmaxf(s_red[0][2], s_red[0][3]));
-        float z = 0.f, t = 0.f;
+        for (int w = 1; w < EPT; w *= 2) {
+            const bool upper = (i & w) != 0;
 #pragma unroll
-        for (int w = 0; w < WAVES; ++w) {
-            if (s_red[0][w] > -INFINITY) {
-                const float dlt = m - s_red[0][w];
-                const float sc = expf(-dlt);
-                z += sc * s_red[1][w];
-                t += sc * (s_red[2][w] + s_red[1][w] * dlt);
+            for (int e = 0; e < EPT; e += 2 * w) {
+                const float a = x[e], b = x[e + w];      // (of two array elements the compiler would choose the address)
+                x[e] = upper ? b : a;
             }
         }
-        stats[static_cast<long>(row) * nunits + unit] = UnitStats{m, z, t, 0.f};
+        const int to = n + static_cast<int>(__builtin_amdgcn_mbcnt_hi(static_cast<uint32_t>(b >> 32), __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(b), 0u)));
+        const int at = base + ((i / VEC) * 64 + lane) * VEC + i % VEC;
+        if (mine != 0 && to < WAVE_LIST) list[to] = key_pack(make_key(x[0], at));
+        mine &= mine - 1;
+        n += __builtin_popcountll(b);
+        b = n <= WAVE_LIST ? __ballot(mine != 0) : 0;
     }
+    if (__builtin_expect(!usual || n > WAVE_LIST, 0)) {
+        uint32_t all[EPT];
+        bool have[EPT];
+#pragma unroll
+        for (int i = 0; i < EPT; ++i) {
+            have[i] = index(i) < vocab;
+            all[i] = sortable(v[i]);
+        }
+        search(want);
+        auto count = [&](uint32_t t) __attribute__((always_inline)) {  // how many reach t
+            int a = 0;
+#pragma unroll
+            for (int i = 0; i < EPT; ++i) a += __builtin_popcountll(__ballot(have[i] && all[i] >= t));
+            return a;
+        };
+        auto above = [&]() __attribute__((always_inline)) { return (thr | REST) == 0xFFFFFFFFu ? 0 : count((thr | REST) + 1u); };
+        int more = above();
+        if (nan || more > WAVE_LIST) {                   // the threshold of all values, which is above that of the lanes'
+            hi = 0;
+#pragma unroll
+            for (int i = 0; i < EPT; ++i) hi = max(hi, have[i] ? all[i] : 0u);
+            hi = __builtin_amdgcn_readfirstlane(wave_max_u32(hi));
+            const uint32_t low = nan ? 0u : thr;
+            bit = hi == low ? 0u : 0x80000000u >> __builtin_clz(hi ^ low);
+            thr = bit ? hi & ~(2u * bit - 1u) : hi;
+            for (got = EPT * 64; (bit >= LAST_BIT) & (got > WAVE_LIST); bit >>= 1) {
+                const int reach = count(thr | bit);
+                thr = reach >= want ? thr | bit : thr;
+                got = reach >= want ? reach : got;
+            }
+            more = got > WAVE_LIST ? above() : got;      // (what reaches it fits the list: nothing is left to choose)
+            thr = got > WAVE_LIST ? thr : thr - 1;
+        }
+        int left = max(want - more, 0);                  // so many of those that equal it, by index: by load, lane, element
+        n = 0;
+#pragma unroll
+        for (int j = 0; j < NV; ++j) {
+            int own = 0, before = 0, all_of = 0;
+#pragma unroll
+            for (int e = 0; e < VEC; ++e) own += have[j * VEC + e] && (all[j * VEC + e] | REST) == (thr | REST) ? 1 : 0;
+#pragma unroll
+            for (int w = 1; w <= VEC; w *= 2) {          // (own is at most VEC)
+                const uint64_t b = __ballot((own & w) != 0);
+                before += w * static_cast<int>(__builtin_amdgcn_mbcnt_hi(static_cast<uint32_t>(b >> 32), __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(b), 0u)));
+                all_of += w * __builtin_popcountll(b);
+            }
+#pragma unroll
+            for (int e = 0; e < VEC; ++e) {
+                const int i = j * VEC + e;
+                const bool equal = have[i] && (all[i] | REST) == (thr | REST);
+                const bool in = have[i] && (all[i] > (thr | REST) || (equal && before < left));
+                const uint64_t b = __ballot(in);
+                if (b != 0) {
+                    const int to = n + static_cast<int>(__builtin_amdgcn_mbcnt_hi(static_cast<uint32_t>(b >> 32), __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(b), 0u)));
+                    if (in) list[to] = key_pack(Key{all[i], 0xFFFFFFFFu - static_cast<uint32_t>(index(i))});
+                    n += __builtin_popcountll(b);
+                }
+                before += equal ? 1 : 0;
+            }
+            left -= all_of;
+        }
+#pragma unroll
+        for (int i = 0; i < EPT; ++i) v[i] = have[i] ? unsortable(all[i]) : -INFINITY;   // (so that only one of the two is kept meanwhile)
+    }
+    if (lane < (-n & 15)) list[n + lane] = 0;
+    const float unit_max = unsortable(hi);
+    float Z, Tm;
+    unit_sums<true>(v, unit_max, Z, Tm);
+    wave_sums(Z, Tm);
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    SliceTop out;
+    out.stats = UnitStats{unit_max, Z, Tm, 0.f};
+    const int padded = (n + 15) & ~15;
+    out.key[0] = lane < n ? list[lane] : 0;
+    out.place[0] = count_above(list, padded, out.key[0]);
+    out.place[0] = lane < n ? out.place[0] : WAVE_LIST;
+    out.key[1] = 0;
+    out.place[1] = WAVE_LIST;
+    if (n > 64) {                                        // (uniform)
+        out.key[1] = 64 + lane < n ? list[64 + lane] : 0;
+        const int above = count_above(list, padded, out.key[1]);
+        out.place[1] = 64 + lane < n ? above : WAVE_LIST;
+    }
+    return out;
 }
-__global__ __launch_bounds__(THREADS) void slice_topk_bf16_kernel(const uint16_t* __restrict__ logits, int vocab, long row_stride,
-                                                                  int k, const int* __restrict__ n_valid, int rows_per_group,
-                                                                  int nunits, UnitStats* __restrict__ stats,
-                                                                  uint64_t* __restrict__ keys) {
-    slice_topk_bf16_block(logits, vocab, row_stride, k, n_valid, rows_per_group, nunits, stats, keys, blockIdx.x, blockIdx.y);
+// One (slice, row) by every wave of a workgroup: the four slices from 4 block_x on.
+template <typename T>
+__device__ __forceinline__ void slice_topk_wave_block(const T* __restrict__ logits, int vocab, long row_stride, int k,
+                                                      const int* __restrict__ n_valid, int rows_per_group, int nunits,
+                                                      UnitStats* __restrict__ stats, uint64_t* __restrict__ keys, int block_x, int row) {
+    constexpr int NV = EPT / Loader<T>::VEC;
+    __shared__ __align__(16) uint64_t s_list[WAVES][WAVE_LIST];
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int unit = block_x * WAVES + wave;
+    if (unit >= nunits || !row_is_valid(row, n_valid, rows_per_group)) return;
+    const int lane = threadIdx.x & 63;
+    const T* rowp = logits + static_cast<long>(row) * row_stride;
+    typename Loader<T>::Raw raw[NV];
+    request_unit<T, NV>(rowp, unit * UNIT, lane, vocab, raw);
+    const SliceTop r = slice_topk_wave<T, NV>(rowp, unit * UNIT, lane, vocab, k, raw, s_list[wave]);
+    const long o = static_cast<long>(row) * nunits + unit;
+#pragma unroll
+    for (int e = 0; e < 2; ++e)
+        if (r.place[e] < k) keys[o * k + r.place[e]] = r.key[e];
+    if (lane < k && lane >= vocab - unit * UNIT) keys[o * k + lane] = 0;   // a short last slice has no more candidates than logits
+    if (lane == 0) stats[o] = r.stats;
+}
+template <typename T>
+__global__ __launch_bounds__(THREADS) void slice_topk_wave_kernel(const T* __restrict__ logits, int vocab, long row_stride, int k,
+                                                                  const int* __restrict__ n_valid, int rows_per_group, int nunits,
+                                                                  UnitStats* __restrict__ stats, uint64_t* __restrict__ keys) {
+    slice_topk_wave_block<T>(logits, vocab, row_stride, k, n_valid, rows_per_group, nunits, stats, keys, blockIdx.x, blockIdx.y);
 }
 
-// Pass 1 for k > 1 in general (few rows, latency matters more than bandwidth): one WORKGROUP per slice, 4 logits per lane.
-// Each wave finds the value that exactly k of its 256 logits reach, for short lists by stepping down from the maximum, for
-// long ones bit by bit from the top, each bit one ballot per logit (about 20 of the 32 bits on Gaussian logits).  Equal
+// Pass 1 for longer lists: one WORKGROUP per slice, 4 logits per lane.  Each wave finds the value that exactly k of its 256 logits reach,
+// bit by bit from the top, each bit one ballot per logit (about 20 of the 32 bits on Gaussian logits).  Equal
 // values at the threshold are admitted lowest index first.  The survivors of the four waves, in any order, are then ranked
-// by counting.
-// Selecting by k rounds of a wave-wide maximum of 64-bit keys, some 60 instructions each, made this pass arithmetic-bound:
-// 8 rows of 152064 fp32 logits took 11.6 us at k = 10, one row 36 us at k = 64.
+// by counting.  (Selecting by k rounds of a wave-wide maximum of 64-bit keys took one row 36 us at k = 64.)
 template <typename T>
 __device__ __forceinline__ void slice_topk_block(const T* __restrict__ logits, int vocab, long row_stride, int k,
                                                  const int* __restrict__ n_valid, int rows_per_group, int nunits,
@@ -401,18 +505,7 @@ __device__ __forceinline__ void slice_topk_block(const T* __restrict__ logits, i
     const int want = min(k, present);
     uint32_t thr = 1u;
     int got = present;
-    if (got > want && k <= 8) {                      // the next smaller value, round by round (about 400 cycles each)
-        thr = 0xFFFFFFFFu;
-        got = 0;
-        while (got < want) {
-            uint32_t best = 0;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) best = max(best, code[e] < thr ? code[e] : 0u);
-            thr = __builtin_amdgcn_readfirstlane(wave_max_u32(best));
-#pragma unroll
-            for (int e = 0; e < 4; ++e) got += __builtin_popcountll(__ballot(code[e] == thr));
-        }
-    } else if (got > want) {                         // the threshold bit by bit (about 170 cycles each, 20 of them)
+    if (got > want) {                                // the threshold bit by bit (about 170 cycles each, 20 of them)
         thr = 0u;
         for (uint32_t bit = 0x80000000u; bit != 0; bit >>= 1) {
             const int n = reach(thr | bit);
@@ -506,32 +599,37 @@ __global__ __launch_bounds__(THREADS) void slice_topk_kernel(const T* __restrict
 }
 
 // Two first passes in one launch (sage_entropy_topk_slices_pair): the k = 1 pass over grouped rows (job A, the grid
-// of slice_rows_kernel) with the k > 1 pass over a few rows (job B) in slabs of workgroups ahead of it.  A step is a
+// of slice_rows_kernel) with the k > 1 pass over a few rows (job B) in workgroups ahead of it.  A step is a
 // chain of dependent launches, each a few microseconds whatever it computes; two passes that do not depend on each
-// other share one.  FAST: job B takes the 32-bit rounds (bf16, k <= 16).
+// other share one.  Job B comes first, because its chain is the longer one (behind job A: 0.5 to 1 us more).  BY_WAVES: a wave per slice
+// in job B (k <= WAVE_MAX_K).
 struct PairJob {
     const void* logits; long row_stride; int rows, k, nunits;
     UnitStats* stats; uint64_t* keys;
 };
-template <typename T, bool FAST>
+template <typename T, bool BY_WAVES>
 __global__ __launch_bounds__(THREADS) void slice_pair_kernel(const T* __restrict__ logits_a, int vocab, long row_stride_a,
                                                              const int* __restrict__ n_valid_a, int rows_per_group_a,
                                                              int rows_a, int nunits, UnitStats* __restrict__ stats_a,
                                                              uint64_t* __restrict__ keys_a, int slabs_b, const PairJob b) {
-    if (static_cast<int>(blockIdx.z) < slabs_b) {            // workgroup-uniform
-        const int lin = (blockIdx.z * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x;
-        if (lin >= b.nunits * b.rows) return;
-        const int row = lin / b.nunits, unit = lin - row * b.nunits;
-        if constexpr (FAST)
-            slice_topk_bf16_block(static_cast<const uint16_t*>(b.logits), vocab, b.row_stride, b.k, nullptr, 1, b.nunits, b.stats,
-                                  b.keys, unit, row);
-        else
+    // one group: the rows of job B come ahead of the phases of job A; several: in slabs ahead of theirs
+    const int y = blockIdx.y, z = blockIdx.z, ahead = slabs_b == 0 ? b.rows : 0;
+    if (z < slabs_b || y < ahead) {                          // workgroup-uniform
+        if constexpr (BY_WAVES) {
+            const int row = z * static_cast<int>(gridDim.y) + y;
+            if (row < b.rows)
+                slice_topk_wave_block<T>(static_cast<const T*>(b.logits), vocab, b.row_stride, b.k, nullptr, 1, b.nunits, b.stats, b.keys, blockIdx.x, row);
+        } else {
+            const int lin = (z * gridDim.y + y) * gridDim.x + blockIdx.x;
+            if (lin >= b.nunits * b.rows) return;
+            const int row = lin / b.nunits, unit = lin - row * b.nunits;
             slice_topk_block<T>(static_cast<const T*>(b.logits), vocab, b.row_stride, b.k, nullptr, 1, b.nunits, b.stats, b.keys,
                                 unit, row);
+        }
         return;
     }
     slice_rows_block<T>(logits_a, vocab, row_stride_a, n_valid_a, rows_per_group_a, rows_a, nunits, stats_a, keys_a, blockIdx.x,
-                        blockIdx.y, gridDim.y, static_cast<int>(blockIdx.z) - slabs_b);
+                        y - ahead, static_cast<int>(gridDim.y) - ahead, z - slabs_b);
 }
 
 // Pass 2 for k = 1 (the target rows): a wave per row, no LDS and no barrier.  Statistics and candidates of the row's slices
@@ -630,8 +728,49 @@ __global__ __launch_bounds__(THREADS) void rows_in_one_kernel(const T* __restric
     MergedRow r;
     finish_row(row, 1, lane, g, m, Z, topk_idx, topk_prob, topk_renorm, topk_entropy, alpha, r);
 }
-// k > 1: a workgroup per row of one slice (fp32, k = 8: 6.8 -> 6.0 us; two slices one after the other are slower, 7.0 -> 8.9).
-template <typename T, bool FAST>
+// k > 1, one slice: up to WAVE_MAX_K by a wave per row, which finishes the row (fp32, k = 8, 1000 logits: 6.5 -> 4.3 us, k = 33 10.8 -> 4.8;
+// the list is the row's, and nothing goes through memory); longer lists by a workgroup per row, which merges the one list (two slices one
+// after the other are slower than two launches).
+template <typename T>
+__global__ __launch_bounds__(THREADS) void row_topk_by_wave_kernel(const T* __restrict__ logits, int vocab, long row_stride, int k,
+                                                                   const int* __restrict__ n_valid, int rows_per_group, int rows,
+                                                                   UnitStats* __restrict__ stats, uint64_t* __restrict__ keys,
+                                                                   float* __restrict__ entropy, int* __restrict__ topk_idx,
+                                                                   float* __restrict__ topk_prob, float* __restrict__ topk_renorm,
+                                                                   float* __restrict__ topk_entropy, float* __restrict__ alpha) {
+    constexpr int NV = EPT / Loader<T>::VEC;
+    __shared__ __align__(16) uint64_t s_list[WAVES][WAVE_LIST];
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int row = blockIdx.x * WAVES + wave;
+    if (row >= rows || !row_is_valid(row, n_valid, rows_per_group)) return;
+    const int lane = threadIdx.x & 63;
+    const T* rowp = logits + static_cast<long>(row) * row_stride;
+    typename Loader<T>::Raw raw[NV];
+    request_unit<T, NV>(rowp, 0, lane, vocab, raw);
+    const SliceTop r = slice_topk_wave<T, NV>(rowp, 0, lane, vocab, k, raw, s_list[wave]);
+    uint64_t* const kout = keys + static_cast<long>(row) * k;
+#pragma unroll
+    for (int e = 0; e < 2; ++e)
+        if (r.place[e] < k) kout[r.place[e]] = r.key[e];
+    if (lane == 0) stats[row] = r.stats;
+    // the list in order: every lane has read its entry and counted
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+#pragma unroll
+    for (int e = 0; e < 2; ++e)
+        if (r.place[e] < k) s_list[wave][r.place[e]] = r.key[e];
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    const UnitStats u[1] = {r.stats};
+    float m, Z, Tm;
+    combine_unit_stats<1>(u, lane, 1, m, Z, Tm);
+    if (lane == 0 && entropy) entropy[row] = logf(Z) + Tm / Z;
+    MergedRow out;
+    finish_row(row, k, lane, lane < k ? key_unpack(s_list[wave][lane]) : Key{0, 0}, m, Z, topk_idx, topk_prob, topk_renorm, topk_entropy, alpha, out);
+}
+template <typename T>
 __global__ __launch_bounds__(THREADS) void row_topk_in_one_kernel(const T* __restrict__ logits, int vocab, long row_stride, int k,
                                                                   const int* __restrict__ n_valid, int rows_per_group,
                                                                   UnitStats* __restrict__ stats, uint64_t* __restrict__ keys,
@@ -642,8 +781,7 @@ __global__ __launch_bounds__(THREADS) void row_topk_in_one_kernel(const T* __res
     __shared__ MergeShared<1> sh;
     const int row = blockIdx.x;
     if (!row_is_valid(row, n_valid, rows_per_group)) return;
-    if constexpr (FAST) slice_topk_bf16_block(logits, vocab, row_stride, k, n_valid, rows_per_group, 1, stats, keys, 0, row);
-    else slice_topk_block<T>(logits, vocab, row_stride, k, n_valid, rows_per_group, 1, stats, keys, 0, row);
+    slice_topk_block<T>(logits, vocab, row_stride, k, n_valid, rows_per_group, 1, stats, keys, 0, row);
     __syncthreads();                                         // what it stored is there for the workgroup
     MergedRow r;
     merge_row<1>(row, k, 1, stats, keys, sh, entropy, topk_idx, topk_prob, topk_renorm, topk_entropy, alpha, r);
@@ -661,11 +799,12 @@ void launch_in_one(const T* logits, int rows, int vocab, long row_stride, int k,
                            rows_per_group, rows, nunits, stats, keys, entropy, topk_idx, topk_prob, topk_renorm, topk_entropy, alpha);
         return;
     }
-    auto kernel = row_topk_in_one_kernel<T, false>;
-    if constexpr (sizeof(T) == 2)
-        if (k <= FAST_MAX_K) kernel = row_topk_in_one_kernel<T, true>;
-    hipLaunchKernelGGL(kernel, dim3(rows), dim3(THREADS), 0, s, logits, vocab, row_stride, k, n_valid, rows_per_group, stats, keys, entropy,
-                       topk_idx, topk_prob, topk_renorm, topk_entropy, alpha);
+    if (k <= WAVE_MAX_K)
+        hipLaunchKernelGGL(row_topk_by_wave_kernel<T>, dim3((rows + WAVES - 1) / WAVES), dim3(THREADS), 0, s, logits, vocab, row_stride, k, n_valid,
+                           rows_per_group, rows, stats, keys, entropy, topk_idx, topk_prob, topk_renorm, topk_entropy, alpha);
+    else
+        hipLaunchKernelGGL(row_topk_in_one_kernel<T>, dim3(rows), dim3(THREADS), 0, s, logits, vocab, row_stride, k, n_valid, rows_per_group, stats,
+                           keys, entropy, topk_idx, topk_prob, topk_renorm, topk_entropy, alpha);
 }
 
 inline int num_units(int vocab) { return (vocab + UNIT - 1) / UNIT; }
@@ -765,13 +904,18 @@ static int run_first_pass(const void* logits, int dtype, int rows, int vocab, lo
         else
             hipLaunchKernelGGL(slice_rows_kernel<uint16_t>, grid, dim3(THREADS), 0, s, static_cast<const uint16_t*>(logits),
                                vocab, row_stride, n_valid, rows_per_group, rows, nunits, stats, keys);
-    } else {                                         // k rounds: a workgroup per slice, 4 logits per lane
+    } else if (k <= WAVE_MAX_K) {                    // few rows, short lists: a wave per slice
+        const dim3 grid((nunits + WAVES - 1) / WAVES, rows);
+        if (dtype == SAGE_F32)
+            hipLaunchKernelGGL(slice_topk_wave_kernel<float>, grid, dim3(THREADS), 0, s, static_cast<const float*>(logits), vocab,
+                               row_stride, k, n_valid, rows_per_group, nunits, stats, keys);
+        else
+            hipLaunchKernelGGL(slice_topk_wave_kernel<uint16_t>, grid, dim3(THREADS), 0, s, static_cast<const uint16_t*>(logits), vocab,
+                               row_stride, k, n_valid, rows_per_group, nunits, stats, keys);
+    } else {                                         // a workgroup per slice, 4 logits per lane
         const dim3 grid(nunits, rows);
         if (dtype == SAGE_F32)
             hipLaunchKernelGGL(slice_topk_kernel<float>, grid, dim3(THREADS), 0, s, static_cast<const float*>(logits), vocab,
-                               row_stride, k, n_valid, rows_per_group, nunits, stats, keys);
-        else if (k <= FAST_MAX_K)
-            hipLaunchKernelGGL(slice_topk_bf16_kernel, grid, dim3(THREADS), 0, s, static_cast<const uint16_t*>(logits), vocab,
                                row_stride, k, n_valid, rows_per_group, nunits, stats, keys);
         else
             hipLaunchKernelGGL(slice_topk_kernel<uint16_t>, grid, dim3(THREADS), 0, s, static_cast<const uint16_t*>(logits),
@@ -844,20 +988,19 @@ extern "C" int sage_entropy_topk_slices_pair(const void* logits_a, int rows_a, l
     b.keys = reinterpret_cast<uint64_t*>(static_cast<char*>(workspace_b) + stats_bytes(rows_b, vocab));
     const int groups = (rows_a + rows_per_group_a - 1) / rows_per_group_a;
     const int gx = (nunits + WAVES - 1) / WAVES, gy = row_phases(groups, rows_per_group_a, true);
-    const long blocks_b = static_cast<long>(nunits) * rows_b;
-    const long slabs_b = (blocks_b + static_cast<long>(gx) * gy - 1) / (static_cast<long>(gx) * gy);
+    const bool by_waves = k_b <= WAVE_MAX_K;                 // workgroups of job B, in rows of the grid
+    const long rows_of_b = by_waves ? rows_b : (static_cast<long>(nunits) * rows_b + gx - 1) / gx;
+    const bool ahead = groups == 1 && by_waves && rows_b + gy <= 65535;
+    const long slabs_b = ahead ? 0 : (rows_of_b + gy - 1) / gy;
     if (slabs_b + groups > 65535) return SAGE_UNSUPPORTED;
-    const dim3 grid(gx, gy, static_cast<unsigned>(slabs_b + groups));
+    const dim3 grid(gx, ahead ? gy + rows_b : gy, static_cast<unsigned>(slabs_b + groups));
+    auto launch = [&](auto kernel, auto* logits) {
+        hipLaunchKernelGGL(kernel, grid, dim3(THREADS), 0, s, logits, vocab, row_stride_a, n_valid_a, rows_per_group_a, rows_a, nunits, stats_a,
+                           keys_a, static_cast<int>(slabs_b), b);
+    };
     if (dtype == SAGE_F32)
-        hipLaunchKernelGGL((slice_pair_kernel<float, false>), grid, dim3(THREADS), 0, s, static_cast<const float*>(logits_a), vocab,
-                           row_stride_a, n_valid_a, rows_per_group_a, rows_a, nunits, stats_a, keys_a, static_cast<int>(slabs_b), b);
-    else if (k_b <= FAST_MAX_K)
-        hipLaunchKernelGGL((slice_pair_kernel<uint16_t, true>), grid, dim3(THREADS), 0, s, static_cast<const uint16_t*>(logits_a),
-                           vocab, row_stride_a, n_valid_a, rows_per_group_a, rows_a, nunits, stats_a, keys_a,
-                           static_cast<int>(slabs_b), b);
+        launch(by_waves ? slice_pair_kernel<float, true> : slice_pair_kernel<float, false>, static_cast<const float*>(logits_a));
     else
-        hipLaunchKernelGGL((slice_pair_kernel<uint16_t, false>), grid, dim3(THREADS), 0, s, static_cast<const uint16_t*>(logits_a),
-                           vocab, row_stride_a, n_valid_a, rows_per_group_a, rows_a, nunits, stats_a, keys_a,
-                           static_cast<int>(slabs_b), b);
+        launch(by_waves ? slice_pair_kernel<uint16_t, true> : slice_pair_kernel<uint16_t, false>, static_cast<const uint16_t*>(logits_a));
     return sage::launch_status();
 }

@@ -169,6 +169,38 @@ def test_topk_short_last_slice(gu, dtype, k):
         np.testing.assert_array_equal(idx.cpu().numpy(), want, err_msg=f"vocab {vocab}, pair")
 
 
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("k", [2, 10, 33, 48])
+@pytest.mark.parametrize("vocab", [700, 1024 + 63, 2048 + 64, 1024 + 65, 3072 + 127, 1024 + 130, 4000])
+def test_topk_by_waves(gu, vocab, k, dtype):
+    """Lists of up to 48 candidates, which a wave finds in a slice: winners that share lanes (rising and falling rows, runs of eight and sixteen
+    at the top, one lane's sixteen logits alone above the rest), more equal values at the threshold than the list has room for, few logits above
+    -inf, the last slice about the size of the list, and all of it below zero."""
+    rng = wl.rng(vocab * 31 + k)
+    x = rng.standard_normal((12, vocab)).astype(np.float32)
+    x[0] = np.sort(x[0])
+    x[1] = np.sort(x[1])[::-1]
+    x[2] = np.linspace(-3.0, 3.0, vocab)
+    x[3, 40:40 + 16] += 9.0
+    lane = 5 * (8 if dtype == "bf16" else 4)             # one lane's logits of a slice, in its loads of 64 lanes each
+    per_load = 512 if dtype == "bf16" else 256
+    for first in range(0, min(vocab, 1024), per_load):
+        x[4, first + lane:first + lane + per_load // 64] += 9.0
+    x[5] = np.round(x[5] * 2.0)                          # few levels
+    x[6] = np.where(rng.random(vocab) < 0.2, 1.5, -2.0)  # two
+    x[7] = -np.inf
+    x[7, rng.permutation(vocab)[:6]] = rng.standard_normal(6)
+    x[8] -= 100.0
+    x[9, -70:] += 5.0
+    x[10] = 0.0
+    x[11, ::3] = -np.inf
+    x = wl.to_storage(np.pad(x, ((0, 0), (0, -vocab % 16))), dtype)[:, :vocab]
+    g1, o1 = gu.gpu_entropy_topk(x, k), oracle.entropy_topk(x, k)
+    np.testing.assert_array_equal(g1["topk_idx"], o1["topk_idx"])
+    np.testing.assert_allclose(g1["topk_prob"], o1["topk_prob"], rtol=1e-5, atol=1e-7)
+    np.testing.assert_allclose(g1["entropy"], o1["entropy"], rtol=1e-5, atol=1e-5)
+
+
 @pytest.mark.parametrize("rows,rpg,n_valid,vocab,dtype", [
     (150, 64, [64, 33, 22], 5000, "f32"),            # a short last group (22 rows): every one of its rows counts
     (150, 64, [17, 0, 99], 70008, "bf16"),           # n_valid beyond the group's rows is clamped
