@@ -311,6 +311,7 @@ struct Segment {
 // depend on nothing of unit h, one ahead of each of its 16 scores per lane, in program order (scheduling fences).  What one
 // wave leaves open (waits, branches, the end of a unit, scalar instructions), the other wave of its SIMD fills, as far as the
 // barrier of the block lets it.
+template <bool KEYS_FIRST>
 __device__ __forceinline__ void attention_pass(const Params& prm, LDS_AS Lds* lds, const Segment& sg, const int inv_G, const int tid) {
     LDS_AS unsigned char* const ring = lds->ring;
     const int lane = tid & 63;
@@ -383,7 +384,7 @@ __device__ __forceinline__ void attention_pass(const Params& prm, LDS_AS Lds* ld
         k_next += block_b;
     };
 
-    // Everything the prologue needs from memory goes straight into LDS, requested back to back in this order: the wave's
+    // Everything the prologue needs from memory goes straight into LDS, requested back to back: the wave's
     // ancestor masks, its Q rows, the first blocks.  No load of the kernel returns into a
     // register, so the compiler never waits on the vector-memory counter here and the only waits are the counted ones.
     // Rows past the group's last one repeat that row (their results are never written).
@@ -391,6 +392,14 @@ __device__ __forceinline__ void attention_pass(const Params& prm, LDS_AS Lds* ld
         return static_cast<unsigned>(min(sg.cg * ROWS_PER_WG + local, sg.rows - 1));
     };
     auto node_of = [&](unsigned m) __attribute__((always_inline)) { return (m * static_cast<unsigned>(inv_G)) >> 16; };   // exact for m < 64 G, G <= 16
+    // Addresses of Q rows take 0.4 us of instructions, those of whole blocks few: where the stream is what a pass waits for, the first two blocks of K go
+    // ahead of them (15 nodes x 16384 positions 19.2 -> 18.5 us, 12 x 4096 10.97 -> 10.83, 12 x 32768 27.3 -> 27.0).  With more than 128 rows (64
+    // nodes x 2000 15.7 -> 15.8, 32 x 2000 14.3 -> 14.45) and in batches, whose first passes begin later (three sequences 12.45 -> 12.65), they do not.
+    const bool keys_first = KEYS_FIRST && group_rows <= LIGHT_ROWS;
+    if (keys_first) {
+        issue(IsK{}, 0, k_cache);
+        issue(IsK{}, 1, k_cache + block_b);
+    }
     // Q rows as tiles of 32 in the layout of a K block: row q of a tile sits at (q % 8) * K_GROUP + (q / 8) * ROW_B
     LDS_AS unsigned char* const q_tile = ring + Q_AT + wave * Q_TILE_B;
     if (active) {
@@ -406,8 +415,10 @@ __device__ __forceinline__ void attention_pass(const Params& prm, LDS_AS Lds* ld
             sage::lds_direct_load16(q_rows, node_of(m) * node_b + m * (D * 2u) + k_chunk_b, q_tile + i * K_GROUP);
         }
     }
-    issue(IsK{}, 0, k_cache);
-    issue(IsK{}, 1, k_cache + block_b);
+    if (!keys_first) {
+        issue(IsK{}, 0, k_cache);
+        issue(IsK{}, 1, k_cache + block_b);
+    }
     issue(IsV{}, 0, v_cache);
     issue(IsK{}, 2, k_cache + 2 * block_b);
     issue(IsV{}, 1, v_cache + block_b);
@@ -786,7 +797,7 @@ __device__ __forceinline__ void attention_workgroup(const int* __restrict__ kv_l
         // The thread index is therefore made opaque per pass, and its derived values are recomputed.
         int tid = static_cast<int>(threadIdx.x);
         if (BATCH) asm volatile("" : "+v"(tid));
-        attention_pass(prm, lds, sg, inv_G, tid);
+        attention_pass<!BATCH>(prm, lds, sg, inv_G, tid);
     };
 
     if (!BATCH) {
