@@ -101,6 +101,8 @@ constexpr int RING_B = ZERO_AT + 1024;
 // A partial: per query row O^T[128] in bf16, then max and sum in fp32.
 constexpr int PART_ROW_B = D * 2 + 16;   // (8 bytes of padding keep the rows 16-byte aligned)
 constexpr int PART_SLOT_B = ROWS_PER_WG * PART_ROW_B;
+// (a slot's number is an int: what memory there is holds a few million of them)
+__device__ __forceinline__ size_t slot_at(int slot) { return static_cast<size_t>(static_cast<unsigned>(slot)) * PART_SLOT_B; }
 constexpr int EPI_ROW_B = PART_ROW_B;    // a parked row of the epilogue has the layout of a partial row
 static_assert(ROWS_PER_WG * EPI_ROW_B <= RING_B, "the rings hold the epilogue's rows");
 constexpr int TWO_STEP_ROWS = 128;      // groups of more rows take their reference in two steps (see the first two blocks)
@@ -148,21 +150,32 @@ using sage::per_group;
 
 // How one (sequence, KV head) is cut into workgroups; evaluated identically by both kernels.
 struct Split {
-    int n, first, rows, col_groups, blocks, max_split, blocks_per_split, nsplit;
+    int n, first, rows, col_groups, blocks, max_split, blocks_per_split;
+    __device__ __forceinline__ int count() const { return __builtin_amdgcn_readfirstlane(div_ceil(blocks, blocks_per_split)); }   // of splits
 };
 // the first node whose rows are computed: inside [0, n), so that a call always has a row
 __device__ __forceinline__ int clamp_first(int first, int n) { return first < 0 ? 0 : (first > n - 1 ? n - 1 : first); }
-__device__ __forceinline__ Split make_split(int n_nodes, int first_node, int kv_len, int G, int nslot, int min_bps) {
+// inv_nslot: sage::inverse(nslot), or 0 where a division is needed (see the host).
+// One or two groups, which is what there is at 8 heads a KV head, then need neither a division nor a branch each.
+// (Whole call, by divisions -> so, and with the merge's arguments on their way with the sizes: 12 nodes x 4096 positions 10.83 -> 10.64 us, x 300
+// 7.95 -> 7.75, 64 nodes x 2000 15.7 -> 15.5, 28/4 heads, 3 new rows of 12 over 2560, 8.0 -> 7.83.)
+__device__ __forceinline__ Split make_split(int n_nodes, int first_node, int kv_len, int G, int nslot, unsigned inv_nslot, int min_bps) {
     Split s;
     s.n = n_nodes < 1 ? 1 : (n_nodes > SAGE_MAX_NODES ? SAGE_MAX_NODES : n_nodes);
     s.first = clamp_first(first_node, s.n);
     s.rows = (s.n - s.first) * G;
-    s.col_groups = (s.rows + ROWS_PER_WG - 1) / ROWS_PER_WG;
     const int L = kv_len > 0 ? kv_len : 0;
     s.blocks = blocks_of(L) + blocks_of(s.n);               // cache blocks, then one or two with the tree's keys
-    s.max_split = max(1, per_group(nslot, s.col_groups));
-    s.blocks_per_split = max(min_bps, div_ceil(s.blocks, s.max_split));
-    s.nsplit = div_ceil(s.blocks, s.blocks_per_split);
+    if (s.rows <= 2 * ROWS_PER_WG && inv_nslot != 0) {       // (uniform)
+        const int second = s.rows > ROWS_PER_WG ? 1 : 0;
+        s.col_groups = 1 + second;
+        s.max_split = nslot >> second;                       // (nslot is even then)
+        s.blocks_per_split = max(min_bps, sage::by_product((s.blocks + s.max_split - 1) << second, inv_nslot));
+    } else {
+        s.col_groups = (s.rows + ROWS_PER_WG - 1) / ROWS_PER_WG;
+        s.max_split = max(1, per_group(nslot, s.col_groups));
+        s.blocks_per_split = max(min_bps, __builtin_amdgcn_readfirstlane(div_ceil(s.blocks, s.max_split)));   // (or the other branch's is per lane, too)
+    }
     return s;
 }
 
@@ -192,11 +205,10 @@ struct BatchShape {
     int length, at, groups_before;                           // its length on the line; position and segments of the sequences before it
     int total, q;                                            // wave-uniform
 };
-// how many blocks of `cost` positions begin before position x, counted from the first one's: x / cost, rounded up
+// how many blocks of `cost` positions begin before position x, counted from the first one's
 __device__ __forceinline__ int blocks_until(int x, int cost) {
-    static_assert(LIGHT_COST == 3 && HEAVY_COST == 4, "the factors are 2^31 over 1, 3 and 4, rounded up: exact below 2^31");
-    const unsigned up = static_cast<unsigned>(max(x, 0) + cost - 1);
-    return static_cast<int>(__umulhi(2 * up, cost == 1 ? 0x80000000u : cost == LIGHT_COST ? 0x2AAAAAABu : 0x20000000u));
+    static_assert(LIGHT_COST == 3 && HEAVY_COST == 4, "the costs that it divides by");
+    return sage::div_up_by_cost(max(x, 0), cost);
 }
 // Sums over the lanes up to and including a lane's own, of two values at a time (the steps of one fill the wait states of the other's).
 __device__ __forceinline__ void wave_scan2(int& a, int& b) {
@@ -748,7 +760,7 @@ __device__ __forceinline__ void attention_pass(const Params& prm, LDS_AS Lds* ld
     const int last_chunk = min(32, group_rows - row0) * (PART_ROW_B / 16);
     // They are written through the L2 (see store_through16): what a kernel leaves in an L2 is written back at its end, before the merge
     // may start, and 64 nodes leave 17 MB.
-    unsigned char* const out = prm.part + static_cast<long>(sg.slot) * PART_SLOT_B + row0 * PART_ROW_B + lane * 16;
+    unsigned char* const out = prm.part + slot_at(sg.slot) + row0 * PART_ROW_B + lane * 16;
     constexpr int COPIES = (32 * (PART_ROW_B / 16) + 63) / 64;
     u32x4 chunk[COPIES];
 #pragma unroll
@@ -771,7 +783,7 @@ template <bool BATCH>
 __device__ __forceinline__ void attention_workgroup(const int* __restrict__ kv_len_arg, const int* __restrict__ n_nodes_arg,
                                                     const int* __restrict__ first_node_arg,
                                                     const int64_t* __restrict__ kv_start_arg, int nslot_arg, int min_bps_arg,
-                                                    int G_arg, int B_arg, int nrange_arg, int light_rows_arg, const Params& prm, const int first_slab, LDS_AS Lds* lds) {
+                                                    int G_arg, int B_arg, int cut_arg, int light_rows_arg, const Params& prm, const int first_slab, LDS_AS Lds* lds) {
     // grid = (KV head, slot or range, sequence): the KV head is the fastest index of the launch order, and no index
     // costs a division
     const int g = blockIdx.x;
@@ -815,21 +827,27 @@ __device__ __forceinline__ void attention_workgroup(const int* __restrict__ kv_l
         asm("" : "+s"(len_b), "+s"(n_b), "+s"(start_lo), "+s"(start_hi), "+s"(f_b));
         const long start_b = (static_cast<long>(start_hi) << 32) | static_cast<uint32_t>(start_lo);
         const int L = len_b > 0 ? len_b : 0;
-        const Split sp = make_split(n_b, f_b, L, G_arg, nslot_arg, min_bps_arg);
+        const Split sp = make_split(n_b, f_b, L, G_arg, nslot_arg, static_cast<unsigned>(cut_arg), min_bps_arg);
+        int split = slot >> 1, cg = slot & 1;
+        if (sp.col_groups == 1) {
+            split = slot;
+            cg = 0;
+        } else if (sp.col_groups != 2) {
+            split = per_group(slot, sp.col_groups);
+            cg = slot - split * sp.col_groups;
+        }
         if (sp.col_groups > nslot_arg) return;              // host guarantees nslot >= the largest group count
-        const int split = per_group(slot, sp.col_groups);
-        const int cg = slot - split * sp.col_groups;
-        if (split >= sp.nsplit) return;
         const int begin = split * sp.blocks_per_split;
+        if (begin >= sp.blocks) return;
         run_segment(Segment{b, g, L, sp.n, sp.first, sp.rows, cg, begin, min(sp.blocks - begin, sp.blocks_per_split), blocks_of(L),
-                            start_b, (b * prm.Hkv + g) * prm.nslot + cg * sp.max_split + split});
+                            start_b, (b * prm.Hkv + g) * nslot_arg + cg * sp.max_split + split});
     } else {
         const int lane = threadIdx.x & 63;
         int r0, r1;                                          // this workgroup's range of the line
         uint64_t todo;                                       // the sequences that it touches
         struct { int nodes, L, start_lo, start_hi, at, seg, costs, groups_before; } now;
         {
-            const BatchShape bs = make_batch_shape<true>(kv_len_arg, n_nodes_arg, first_node_arg, kv_start_arg, B_arg, nrange_arg, min_bps_arg, G_arg,
+            const BatchShape bs = make_batch_shape<true>(kv_len_arg, n_nodes_arg, first_node_arg, kv_start_arg, B_arg, cut_arg, min_bps_arg, G_arg,
                                                          light_rows_arg, lane, [&]() __attribute__((always_inline)) { arguments_here(prm); });
             r0 = id * bs.q;
             r1 = min(bs.total, r0 + bs.q);
@@ -871,9 +889,9 @@ __global__ __launch_bounds__(THREADS) void tree_attention_bf16_kernel(const int*
                                                                       const int* __restrict__ n_nodes_arg,
                                                                       const int* __restrict__ first_node_arg,
                                                                       const int64_t* __restrict__ kv_start_arg, int nslot_arg,
-                                                                      int min_bps_arg, int G_arg, int B_arg, int nrange_arg, int light_rows_arg, const Params prm) {
+                                                                      int min_bps_arg, int G_arg, int B_arg, int cut_arg, int light_rows_arg, const Params prm) {
     __shared__ __align__(256) Lds lds;
-    attention_workgroup<BATCH>(kv_len_arg, n_nodes_arg, first_node_arg, kv_start_arg, nslot_arg, min_bps_arg, G_arg, B_arg, nrange_arg, light_rows_arg, prm, 0,
+    attention_workgroup<BATCH>(kv_len_arg, n_nodes_arg, first_node_arg, kv_start_arg, nslot_arg, min_bps_arg, G_arg, B_arg, cut_arg, light_rows_arg, prm, 0,
                                (LDS_AS Lds*)&lds);
 }
 
@@ -904,7 +922,7 @@ template <bool BATCH>
 __global__ __launch_bounds__(THREADS) void tree_attention_plan_kernel(const int* __restrict__ kv_len_arg,
                                                                       const int* __restrict__ n_nodes_arg,
                                                                       const int64_t* __restrict__ kv_start_arg, int nslot_arg,
-                                                                      int min_bps_arg, int G_arg, int plan_slabs, int B_arg, int nrange_arg, int light_rows_arg,
+                                                                      int min_bps_arg, int G_arg, int plan_slabs, int B_arg, int cut_arg, int light_rows_arg,
                                                                       const Params prm, const sage::PlanArgs pl) {
     __shared__ __align__(256) union Both {
         Lds attention;
@@ -920,7 +938,7 @@ __global__ __launch_bounds__(THREADS) void tree_attention_plan_kernel(const int*
         sage::plan_sequence<PLAN_OWN, THREADS>(b, pl, sh);
         return;
     }
-    attention_workgroup<BATCH>(kv_len_arg, n_nodes_arg, nullptr, kv_start_arg, nslot_arg, min_bps_arg, G_arg, B_arg, nrange_arg, light_rows_arg, prm, plan_slabs,
+    attention_workgroup<BATCH>(kv_len_arg, n_nodes_arg, nullptr, kv_start_arg, nslot_arg, min_bps_arg, G_arg, B_arg, cut_arg, light_rows_arg, prm, plan_slabs,
                                (LDS_AS Lds*)&lds.attention);   // a verify pass: every node
 }
 
@@ -943,7 +961,7 @@ template <int MAXS, bool BATCH, int ROWS>
 __global__ __launch_bounds__(64 * ROWS) void tree_attention_merge_kernel(const int* __restrict__ kv_len_arg,
                                                                          const int* __restrict__ n_nodes_arg,
                                                                          const int* __restrict__ first_node_arg, int nslot_arg,
-                                                                         int min_bps_arg, int G_arg, int phases_arg, int B_arg, int nrange_arg, int light_rows_arg,
+                                                                         int min_bps_arg, int G_arg, int phases_arg, int B_arg, int cut_arg, int light_rows_arg,
                                                                          const Params prm) {
     static_assert(MAXS <= 64, "one split per lane, one register per split");
     // As in the main kernel, a KV head's blocks are congruent modulo the KV-head count, so with 8 KV heads they run on
@@ -1026,33 +1044,37 @@ __global__ __launch_bounds__(64 * ROWS) void tree_attention_merge_kernel(const i
     const int phases = phases_arg;
     const int phase = blockIdx.y;
     const int b = blockIdx.z;
+    auto arguments = [&]() __attribute__((always_inline)) {  // on their way with the sizes
+        asm volatile("" : : "s"(prm.part), "s"(prm.O), "s"(prm.Hq), "s"(prm.Hkv), "s"(prm.inv_G), "s"(prm.scale_log2e));
+    };
     if (!BATCH) {
         int len_b = __builtin_amdgcn_readfirstlane(kv_len_arg[b]);   // requested together, waited for once
         int n_b = __builtin_amdgcn_readfirstlane(n_nodes_arg[b]);
         int f_b = first_node_arg ? __builtin_amdgcn_readfirstlane(first_node_arg[b]) : 0;
+        arguments();
         asm("" : "+s"(len_b), "+s"(n_b), "+s"(f_b));
         const int L = len_b > 0 ? len_b : 0;
-        const Split sp = make_split(n_b, f_b, L, G_arg, nslot_arg, min_bps_arg);
+        const Split sp = make_split(n_b, f_b, L, G_arg, nslot_arg, static_cast<unsigned>(cut_arg), min_bps_arg);
         const int m = phase * ROWS + wave;                   // a wave per row that a tree can have
         if (sp.col_groups > nslot_arg || m >= sp.rows) return;
-        const int cg = m / ROWS_PER_WG, node = (m * prm.inv_G) >> 16;
-        merge_row(b, sp.first + node, m - node * prm.G,
-                  prm.part + ((static_cast<long>(b) * prm.Hkv + g) * prm.nslot + cg * sp.max_split) * PART_SLOT_B + (m % ROWS_PER_WG) * PART_ROW_B,
-                  sp.nsplit);
+        const int cg = static_cast<int>(static_cast<unsigned>(m) / ROWS_PER_WG), node = (m * prm.inv_G) >> 16;
+        merge_row(b, sp.first + node, m - node * G_arg,
+                  prm.part + slot_at((b * prm.Hkv + g) * nslot_arg + cg * sp.max_split) + static_cast<unsigned>(m) % ROWS_PER_WG * PART_ROW_B,
+                  sp.count());
     } else {
-        const BatchShape bs = make_batch_shape<false>(kv_len_arg, n_nodes_arg, first_node_arg, nullptr, B_arg, nrange_arg, min_bps_arg, G_arg, light_rows_arg, lane,
-                                                      [&]() __attribute__((always_inline)) { asm volatile("" : : "s"(prm.part), "s"(prm.O), "s"(prm.Hq), "s"(prm.inv_G), "s"(prm.scale_log2e)); });
+        const BatchShape bs = make_batch_shape<false>(kv_len_arg, n_nodes_arg, first_node_arg, nullptr, B_arg, cut_arg, min_bps_arg, G_arg, light_rows_arg, lane,
+                                                      arguments);
         const int first_b = __builtin_amdgcn_readlane(bs.first, b);
         const int live = (__builtin_amdgcn_readlane(bs.n, b) - first_b) * G_arg;
         const int seg = __builtin_amdgcn_readlane(bs.seg, b), at = __builtin_amdgcn_readlane(bs.at, b);
         const int last_cost = __builtin_amdgcn_readlane(bs.last_cost, b);
         const int slot_b = g * nslot_arg + __builtin_amdgcn_readlane(bs.groups_before, b);
         for (int m = phase * ROWS + wave; m < live; m += phases * ROWS) {
-            const int cg = m / ROWS_PER_WG;
+            const int cg = static_cast<int>(static_cast<unsigned>(m) / ROWS_PER_WG);
             const int cost = m - m % ROWS_PER_WG + ROWS_PER_WG < live ? bs.cost : last_cost;
             const int u0 = at + cg * seg * bs.cost + SEG_COST * cost;   // first block of segment (b, cg)
             const int s_first = div_floor(u0, bs.q), node = (m * prm.inv_G) >> 16;
-            merge_row(b, first_b + node, m - node * G_arg, prm.part + static_cast<long>(slot_b + s_first + cg) * PART_SLOT_B + (m % ROWS_PER_WG) * PART_ROW_B,
+            merge_row(b, first_b + node, m - node * G_arg, prm.part + slot_at(slot_b + s_first + cg) + static_cast<unsigned>(m) % ROWS_PER_WG * PART_ROW_B,
                       div_floor(u0 + (seg - SEG_COST - 1) * cost, bs.q) - s_first + 1);
         }
     }
@@ -1155,6 +1177,9 @@ int tree_attention_bf16(const void* Q, const void* Kc, const void* Vc, const voi
     p.scale_log2e = scale * 1.4426950408889634f;
 
     p.nrange = sh.nrange;
+    // what the kernels need to cut a sequence or a batch (see make_split and make_batch_shape)
+    const bool by_product = max_kv_len < (1 << 27) && (p.nslot % 2 == 0 || (SAGE_MAX_NODES * G <= ROWS_PER_WG && p.nslot > 1));
+    const int cut = sh.batch ? sh.nrange : by_product ? static_cast<int>(inverse(p.nslot)) : 0;
     // (blocks of different costs only where the line has less than 2^31 positions whatever the lengths are)
     const int light_rows = max_kv_len < (1 << 25) ? LIGHT_ROWS : 1 << 30;
     static_assert(MAX_BATCH_LANES * 4L * ((1L << 25) / BLK + 2 + SEG_COST) * HEAVY_COST + TAIL_BLOCKS * LIGHT_COST < (1L << 31), "64 sequences of four groups");
@@ -1167,18 +1192,18 @@ int tree_attention_bf16(const void* Q, const void* Kc, const void* Vc, const voi
         const dim3 grid(Hkv, plan_slabs + own_slabs, sh.batch ? 1 : B);
         if (sh.batch)
             hipLaunchKernelGGL(tree_attention_plan_kernel<true>, grid, block, 0, stream, kv_len, n_nodes, kv_start, p.nslot,
-                               p.min_blocks_per_split, G, plan_slabs, B, p.nrange, light_rows, p, *plan);
+                               p.min_blocks_per_split, G, plan_slabs, B, cut, light_rows, p, *plan);
         else
             hipLaunchKernelGGL(tree_attention_plan_kernel<false>, grid, block, 0, stream, kv_len, n_nodes, kv_start, p.nslot,
-                               p.min_blocks_per_split, G, plan_slabs, B, p.nrange, light_rows, p, *plan);
+                               p.min_blocks_per_split, G, plan_slabs, B, cut, light_rows, p, *plan);
     } else {
         const dim3 grid(Hkv, own_slabs, sh.batch ? 1 : B);
         if (sh.batch)
             hipLaunchKernelGGL(tree_attention_bf16_kernel<true>, grid, block, 0, stream, kv_len, n_nodes, first_node, kv_start, p.nslot,
-                               p.min_blocks_per_split, G, B, p.nrange, light_rows, p);
+                               p.min_blocks_per_split, G, B, cut, light_rows, p);
         else
             hipLaunchKernelGGL(tree_attention_bf16_kernel<false>, grid, block, 0, stream, kv_len, n_nodes, first_node, kv_start, p.nslot,
-                               p.min_blocks_per_split, G, B, p.nrange, light_rows, p);
+                               p.min_blocks_per_split, G, B, cut, light_rows, p);
     }
     if (hipGetLastError() != hipSuccess) return SAGE_LAUNCH_FAILED;
     const int mrows = sh.batch ? MERGE_ROWS_BATCH : MERGE_ROWS_SINGLE;
@@ -1194,22 +1219,22 @@ int tree_attention_bf16(const void* Q, const void* Kc, const void* Vc, const voi
     // memory: up to 64 splits in one (41 splits of 7 to 21 rows x 4 KV heads: 4.6 -> 4.1 us).
     if (sh.batch) {
         if (most <= 8) hipLaunchKernelGGL((tree_attention_merge_kernel<8, true, MERGE_ROWS_BATCH>), mgrid, mblock, 0, stream, kv_len, n_nodes, p.first_node, p.nslot,
-                               p.min_blocks_per_split, G, p.merge_phases, B, p.nrange, light_rows, p);
+                               p.min_blocks_per_split, G, p.merge_phases, B, cut, light_rows, p);
         else if (most <= 16) hipLaunchKernelGGL((tree_attention_merge_kernel<16, true, MERGE_ROWS_BATCH>), mgrid, mblock, 0, stream, kv_len, n_nodes, p.first_node, p.nslot,
-                               p.min_blocks_per_split, G, p.merge_phases, B, p.nrange, light_rows, p);
+                               p.min_blocks_per_split, G, p.merge_phases, B, cut, light_rows, p);
         else hipLaunchKernelGGL((tree_attention_merge_kernel<32, true, MERGE_ROWS_BATCH>), mgrid, mblock, 0, stream, kv_len, n_nodes, p.first_node, p.nslot,
-                               p.min_blocks_per_split, G, p.merge_phases, B, p.nrange, light_rows, p);
+                               p.min_blocks_per_split, G, p.merge_phases, B, cut, light_rows, p);
     } else {
         if (most <= 8) hipLaunchKernelGGL((tree_attention_merge_kernel<8, false, MERGE_ROWS_SINGLE>), mgrid, mblock, 0, stream, kv_len, n_nodes, p.first_node, p.nslot,
-                               p.min_blocks_per_split, G, p.merge_phases, B, p.nrange, light_rows, p);
+                               p.min_blocks_per_split, G, p.merge_phases, B, cut, light_rows, p);
         else if (most <= 16) hipLaunchKernelGGL((tree_attention_merge_kernel<16, false, MERGE_ROWS_SINGLE>), mgrid, mblock, 0, stream, kv_len, n_nodes, p.first_node, p.nslot,
-                               p.min_blocks_per_split, G, p.merge_phases, B, p.nrange, light_rows, p);
+                               p.min_blocks_per_split, G, p.merge_phases, B, cut, light_rows, p);
         else if (most <= 32) hipLaunchKernelGGL((tree_attention_merge_kernel<32, false, MERGE_ROWS_SINGLE>), mgrid, mblock, 0, stream, kv_len, n_nodes, p.first_node, p.nslot,
-                               p.min_blocks_per_split, G, p.merge_phases, B, p.nrange, light_rows, p);
+                               p.min_blocks_per_split, G, p.merge_phases, B, cut, light_rows, p);
         else if (most <= 48) hipLaunchKernelGGL((tree_attention_merge_kernel<48, false, MERGE_ROWS_SINGLE>), mgrid, mblock, 0, stream, kv_len, n_nodes, p.first_node, p.nslot,
-                               p.min_blocks_per_split, G, p.merge_phases, B, p.nrange, light_rows, p);
+                               p.min_blocks_per_split, G, p.merge_phases, B, cut, light_rows, p);
         else hipLaunchKernelGGL((tree_attention_merge_kernel<64, false, MERGE_ROWS_SINGLE>), mgrid, mblock, 0, stream, kv_len, n_nodes, p.first_node, p.nslot,
-                               p.min_blocks_per_split, G, p.merge_phases, B, p.nrange, light_rows, p);
+                               p.min_blocks_per_split, G, p.merge_phases, B, cut, light_rows, p);
     }
     return launch_status();
 }

@@ -15,6 +15,12 @@ extern "C" void quotients(const int* x, const int* y, const float* reciprocal, i
         out[i] = sage::div_floor(x[i], y[i], [&](int a, int) { return sage::by_reciprocal(a, reciprocal[i]); });
 }
 extern "C" int group_share(int x, int groups) { return sage::per_group(x, groups); }
+extern "C" void products(const int* x, int n, int y, int* out) {
+    for (int i = 0; i < n; ++i) out[i] = sage::by_product(x[i], sage::inverse(y));
+}
+extern "C" void up_by_cost(const int* x, int n, int cost, int* out) {
+    for (int i = 0; i < n; ++i) out[i] = sage::div_up_by_cost(x[i], cost);
+}
 """
 
 
@@ -52,3 +58,22 @@ def test_division_by_reciprocal(lib, most, off):
 def test_division_by_column_groups(lib):
     for groups in (1, 2, 3, 4):
         assert [lib.group_share(x, groups) for x in range(257)] == [x // groups for x in range(257)]
+
+
+def test_division_by_product(lib):
+    k = np.random.default_rng(8).integers(0, 1 << 24, 20000)
+    for y in range(2, 257):
+        x = np.concatenate([np.arange(1025), (k // y)[:, None].repeat(3, 1).ravel() * y + np.tile([-1, 0, 1], len(k)), (1 << 24) - 1 - np.arange(300)])
+        x = np.ascontiguousarray(np.clip(x, 0, (1 << 24) - 1), np.int32)
+        got = np.empty_like(x)
+        lib.products(*(a.ctypes.data_as(ctypes.c_void_p) if isinstance(a, np.ndarray) else a for a in (x, len(x), y, got)))
+        np.testing.assert_array_equal(got, x // y)
+
+
+def test_division_by_cost(lib):
+    top = (1 << 31) - 8
+    x = np.concatenate([np.arange(5000), top - np.arange(5000), np.random.default_rng(9).integers(0, top, 200000)]).astype(np.int32)
+    for cost in (1, 3, 4):
+        got = np.empty_like(x)
+        lib.up_by_cost(*(a.ctypes.data_as(ctypes.c_void_p) if isinstance(a, np.ndarray) else a for a in (x, len(x), cost, got)))
+        np.testing.assert_array_equal(got, -(-x.astype(np.int64) // cost))
