@@ -8,6 +8,14 @@
 namespace sage {
 namespace lmhead {
 
+// A weight matrix of more bytes than the memory-side cache holds (256 MB) is read with loads that leave nothing there: it would have pushed itself out
+// before the next call came, and to place it costs memory bandwidth.  Whole call, us, plain / so, k = 10 with 16 rows and greedy with 40 of 64: 389 MB 95.1 /
+// 83.7 and 79.2 / 69.5, 623 MB 162 / 147 and 160 / 147, 1.09 GB 210 / 184, 2.49 GB (greedy, 64 rows) 433 / 397; at the line 272 MB 68.9 / 66.6 and 53.1 / 52.0,
+// 262 MB 79.9 / 79.5 and 68.5 / 70.0.  A smaller matrix stays there from one call to the next: 246 MB, 48 rows, k = 4, 55 / 70 (though not in a
+// program that reads more than the cache holds between two calls).
+constexpr long READ_ONCE_BYTES = 256L << 20;
+inline bool read_once(int vocab, int dim) { return static_cast<long>(vocab) * dim * 2 > READ_ONCE_BYTES; }
+
 struct Fold { float m, Z, T; uint64_t key; };
 
 // This lane's 16 N logits of one row: logit(a, i, left) is logit i of tile a if fewer than `left` rows precede it and -inf

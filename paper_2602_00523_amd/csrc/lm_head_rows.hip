@@ -28,12 +28,13 @@
 // consecutive items of one XCD and share the unit's weights through that XCD's L2 as far as they stay together (1.21 fetches
 // of the matrix at 512 rows).  Up to 128 live rows the weight stream is the bound, and what counts is that every CU has the same
 // share of it: the cut for one block, three units of at most 4 tiles on each of 256 CUs (152064 tokens), whatever the number of
-// rows; cut for the blocks of 1024 rows, 64 live ones take 459 us instead of 446, 128 of 512 470 instead of 456.  With more
+// rows; cut for the blocks of 1024 rows, 64 live ones take 459 us instead of 446, 128 of 512 470 instead of 456 (before READ_ONCE_BYTES).  With more
 // live rows the larger units of the rows' own cut are as good or better (256 of 512: 622 us, 645 with the cut for one block).
 //
 // Measured (hidden 8192, vocabulary 152064; before = 4 waves on 320 vocabulary rows x 128 hidden rows): 512 live rows
 // 1690 -> 1045 us (1.22 PFLOP/s), 256 live 880 -> 620, 160 live 920 -> 500, 128 live 505 -> 453, 1024 live 3140 -> 1975; 64 live
-// of 512 443 -> 442.  At 512 rows the matrix pipe is busy 74 % of the cycles and the chip clocks down to 1.48 GHz (2.19 in the
+// of 512 443 -> 442; since then calls of one block with weights past the memory-side cache, 64 live rows 431 -> 397, 160 535 -> 516,
+// 240 (hidden 5120) 426 -> 413 (see READ_ONCE_BYTES).  At 512 rows the matrix pipe is busy 74 % of the cycles and the chip clocks down to 1.48 GHz (2.19 in the
 // 64-row call): what is left is power, so bytes moved per flop are what counts.
 #include <type_traits>
 
@@ -66,6 +67,7 @@ struct Params {
     const unsigned char* hidden; const unsigned char* weight;
     long hidden_stride_b, weight_stride_b;
     int rows, vocab, nsteps, ntiles;
+    int read_once;                       // the weights are more than stays in memory-side cache (see lm_head_device.h)
     Cut few, all;                        // for up to FEW_LIVE live rows; for more
     const int* n_valid; int rows_per_group;
     UnitStats* stats; uint64_t* keys;    // [rows][units]
@@ -84,7 +86,7 @@ __device__ __forceinline__ void bare_barrier() {
 
 // One unit x row block: NV tiles = 2 NV strips of vocabulary rows (those at or past v_end repeat the last one and are masked) times
 // 64 NR hidden rows.  s_row[0 .. 64 NR) at the start of LDS holds the hidden row behind each slot (-1 = none).
-template <int NV, int NR>
+template <int NV, int NR, bool ONCE>
 __device__ __forceinline__ void pass(const Params& prm, unsigned char* lds, int units, int unit, int v_begin, int v_end) {
     // Stages of the weight and of the hidden ring: as many as fit (small units would otherwise have too little in flight),
     // the same number unless only two hidden stages fit beside three weight stages.
@@ -131,7 +133,8 @@ __device__ __forceinline__ void pass(const Params& prm, unsigned char* lds, int 
     // stay and the loads repeat it (an L2 hit, into a stage nobody reads any more), so that every step issues the same
     // number of loads, the waits are fixed counts, and the block of MFMAs around them has no branch.
     auto issue_w1 = [&](int i, unsigned stage_off, int next) __attribute__((always_inline)) {
-        sage::lds_direct_load16(w_ptr[i], lds3 + (stage_off + (wave * W_LOADS + i) * 1024));
+        if constexpr (ONCE) sage::lds_direct_load16_once(w_ptr[i], lds3 + (stage_off + (wave * W_LOADS + i) * 1024));
+        else sage::lds_direct_load16(w_ptr[i], lds3 + (stage_off + (wave * W_LOADS + i) * 1024));
         w_ptr[i] += next;
     };
     auto issue_h1 = [&](int i, unsigned stage_off, int next) __attribute__((always_inline)) {
@@ -330,17 +333,23 @@ __global__ __launch_bounds__(THREADS) void lm_head_rows_kernel(const Params prm)
         map_rows(rb);
         const int v_begin = t_begin * TILE_V, v_end = min(prm.vocab, t_end * TILE_V);
         const int nv = t_end - t_begin, nr = (rows_here + 63) / 64;
-#define SAGE_PASS(V, R) pass<V, R>(prm, lds, units, u, v_begin, v_end)
-        if (nv == 4) {
-            if (nr == 4) SAGE_PASS(4, 4); else if (nr == 3) SAGE_PASS(4, 3); else if (nr == 2) SAGE_PASS(4, 2); else SAGE_PASS(4, 1);
-        } else if (nv == 3) {
-            if (nr == 4) SAGE_PASS(3, 4); else if (nr == 3) SAGE_PASS(3, 3); else if (nr == 2) SAGE_PASS(3, 2); else SAGE_PASS(3, 1);
-        } else if (nv == 2) {
-            if (nr == 4) SAGE_PASS(2, 4); else if (nr == 3) SAGE_PASS(2, 3); else if (nr == 2) SAGE_PASS(2, 2); else SAGE_PASS(2, 1);
-        } else {
-            if (nr == 4) SAGE_PASS(1, 4); else if (nr == 3) SAGE_PASS(1, 3); else if (nr == 2) SAGE_PASS(1, 2); else SAGE_PASS(1, 1);
-        }
+        auto one = [&](auto once) __attribute__((always_inline)) {
+            constexpr bool ONCE = decltype(once)::value;
+#define SAGE_PASS(V, R) pass<V, R, ONCE>(prm, lds, units, u, v_begin, v_end)
+            if (nv == 4) {
+                if (nr == 4) SAGE_PASS(4, 4); else if (nr == 3) SAGE_PASS(4, 3); else if (nr == 2) SAGE_PASS(4, 2); else SAGE_PASS(4, 1);
+            } else if (nv == 3) {
+                if (nr == 4) SAGE_PASS(3, 4); else if (nr == 3) SAGE_PASS(3, 3); else if (nr == 2) SAGE_PASS(3, 2); else SAGE_PASS(3, 1);
+            } else if (nv == 2) {
+                if (nr == 4) SAGE_PASS(2, 4); else if (nr == 3) SAGE_PASS(2, 3); else if (nr == 2) SAGE_PASS(2, 2); else SAGE_PASS(2, 1);
+            } else {
+                if (nr == 4) SAGE_PASS(1, 4); else if (nr == 3) SAGE_PASS(1, 3); else if (nr == 2) SAGE_PASS(1, 2); else SAGE_PASS(1, 1);
+            }
 #undef SAGE_PASS
+        };
+        // (the blocks of several share the weights through an L2, and are as fast or faster if these stay there: 512 live rows 1044 us, read so 1053)
+        if (blocks == 1 && prm.read_once) one(std::true_type{});
+        else one(std::false_type{});
     }
 }
 
@@ -385,6 +394,7 @@ int launch_lm_head_rows(const void* hidden, const void* weight, int rows, int di
     p.hidden_stride_b = hidden_stride * 2;
     p.weight_stride_b = weight_stride * 2;
     p.rows = rows; p.vocab = vocab; p.nsteps = dim / 64;
+    p.read_once = sage::lmhead::read_once(vocab, dim) ? 1 : 0;
     p.ntiles = (vocab + TILE_V - 1) / TILE_V;
     p.few = cut_vocabulary(vocab, n_valid ? 1 : rows);
     p.all = cut_vocabulary(vocab, rows);

@@ -93,7 +93,8 @@ __device__ __forceinline__ void stage_barrier() {
 //   counting: the unit's logits of 32 rows at a time are laid out in the idle ring and a wave per row finds a value that at
 //     least k and at most 64 of them reach (the lanes' largest ones give it, a ballot a bit, and rarely too low; a ballot per 64
 //     logits and bit, about nine bits, took twice as long), then ranks those by counting, four rows side by side: 0.45 to 0.5 us a live
-//     row (T = 10; before 1.0), 0.45 (T = 5), whatever k.  16 rows of 3584, k = 10, T = 10, whole call: 217.2 -> 209.8 us;
+//     row (T = 10; before 1.0), 0.45 (T = 5), whatever k.  16 rows of 3584, k = 10, T = 10, whole call: 217.2 -> 209.8 us
+//     (184.5 since the weights are read past the memory-side cache);
 //   rounds: every lane scans its 16 T logits for the best one after the previous winner, the four lanes of a row are combined
 //     (lane halves by a swap, vocabulary halves through LDS): 3.1 us each (T = 5: 1.6), whatever the rows.
 // LIST_ROWS_PER_K live rows per candidate is about where the two meet (us of the call, counting / rounds; vocabulary 152064, hidden
@@ -101,7 +102,7 @@ __device__ __forceinline__ void stage_barrier() {
 // 83.1 / 91.4, 90.1 / 91.9, 93.7 / 92.1; k = 12 95.9 / 104.2 and 101.5 / 104.4; 64 rows k = 16 104 / 115.  Vocabulary 32000, hidden 3584,
 // T = 5, just below 4 and at 5: k = 4 72.7 / 74.3, 74.2 / 74.3; k = 8 79.0 / 80.3, 83.9 / 80.4; k = 12 88.5 / 86.9 and k = 16 96.0 / 92.9).
 // So the rule loses up to 3.4 us (k = 6, 30 rows, T = 10) or 3.1 (k = 16, 63 rows, T = 5) next to the line, and nothing away from it.
-template <int T, bool TOPK>
+template <int T, bool TOPK, bool ONCE>
 __global__ __launch_bounds__(THREADS) void lm_head_kernel(const Params prm) {
     // The ring position of a step must be a compile-time constant (every stage is its own LDS object, so that loads
     // in flight into one stage are known not to alias reads of another): step t of chunk kc uses stage
@@ -207,7 +208,10 @@ __global__ __launch_bounds__(THREADS) void lm_head_kernel(const Params prm) {
             long off = static_cast<long>(t) * TILE_V * prm.weight_stride_b + static_cast<long>(kc) * ROW_B;
             asm volatile("" : "+s"(off));
 #pragma unroll
-            for (int i = 0; i < 4; ++i) sage::lds_direct_load16(reinterpret_cast<const unsigned char*>(w_ptr[i] + off), dst + i * GROUP);
+            for (int i = 0; i < 4; ++i) {
+                if constexpr (ONCE) sage::lds_direct_load16_once(w_ptr[i] + off, dst + i * GROUP);
+                else sage::lds_direct_load16(w_ptr[i] + off, dst + i * GROUP);
+            }
         } else {
             const unsigned char* wb = w_base + static_cast<long>(kc) * ROW_B;
 #pragma unroll
@@ -499,10 +503,14 @@ extern "C" int sage_lm_head_topk(const void* hidden, const void* weight, int dty
         p.n_valid = n_valid; p.rows_per_group = rows_per_group;
         p.stats = stats; p.keys = keys;
         const dim3 grid(nunits < CUS ? nunits : CUS);        // a workgroup fills a CU's LDS: one resident workgroup per CU
-        if (k > 1 && sh.tiles_per_unit == 5) hipLaunchKernelGGL((lm_head_kernel<5, true>), grid, dim3(THREADS), 0, s, p);
-        else if (k > 1) hipLaunchKernelGGL((lm_head_kernel<10, true>), grid, dim3(THREADS), 0, s, p);
-        else if (sh.tiles_per_unit == 5) hipLaunchKernelGGL((lm_head_kernel<5, false>), grid, dim3(THREADS), 0, s, p);
-        else hipLaunchKernelGGL((lm_head_kernel<10, false>), grid, dim3(THREADS), 0, s, p);
+        auto launch = [&](auto once) {
+            constexpr bool ONCE = decltype(once)::value;
+            const auto kernel = k > 1 ? (sh.tiles_per_unit == 5 ? lm_head_kernel<5, true, ONCE> : lm_head_kernel<10, true, ONCE>)
+                                      : (sh.tiles_per_unit == 5 ? lm_head_kernel<5, false, ONCE> : lm_head_kernel<10, false, ONCE>);
+            hipLaunchKernelGGL(kernel, grid, dim3(THREADS), 0, s, p);
+        };
+        if (sage::lmhead::read_once(vocab, dim)) launch(std::true_type{});
+        else launch(std::false_type{});
         if (hipGetLastError() != hipSuccess) return SAGE_LAUNCH_FAILED;
     }
     sage::topk_merge(rows, k, n_valid, rows_per_group, nunits, stats, keys, entropy, topk_idx, topk_prob, topk_renorm,

@@ -45,6 +45,15 @@ __device__ __forceinline__ void lds_direct_load16(const unsigned char* gptr, __a
                  : "v"(gptr), "s"(m0v)
                  : "m0", "memory");
 }
+// The same for data that is read once: marked as non-temporal, it does not take the place of anything
+// in the memory-side cache, and no bandwidth to be placed there.
+__device__ __forceinline__ void lds_direct_load16_once(const unsigned char* gptr, __attribute__((address_space(3))) unsigned char* lds) {
+    const unsigned m0v = static_cast<unsigned>(reinterpret_cast<uintptr_t>(lds));
+    asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off nt"
+                 :
+                 : "v"(gptr), "s"(m0v)
+                 : "m0", "memory");
+}
 // The same load with the address split into a wave-uniform base (scalar register pair) and a 32-bit per-lane byte
 // offset: a stream whose per-lane offsets repeat from tile to tile then advances with scalar arithmetic only.
 __device__ __forceinline__ void lds_direct_load16(const unsigned char* sbase, unsigned voff,

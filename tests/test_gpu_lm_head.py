@@ -207,6 +207,36 @@ def test_full_size_72b_projection_sampled_rows(gu, rows, n_valid, sampled):
         assert abs(ge[r] - o["entropy"][0]) <= 1e-3 * max(1.0, o["entropy"][0])
 
 
+@pytest.mark.parametrize("rows,vocab,k,below,above", [(1, 152064, 1, 768, 896), (64, 152064, 1, 768, 896), (12, 152064, 10, 768, 896),
+                                                      (9, 40000, 4, 3328, 3456), (130, 40000, 1, 3328, 3456), (256, 81900, 1, 1536, 1664),
+                                                      (300, 81900, 1, 1536, 1664)])
+def test_weights_past_the_memory_side_cache(gu, rows, vocab, k, below, above):
+    """Weights of more than 256 MB are read with other loads (one block of rows; with 300 the blocks keep the usual ones).  Columns of
+    zeros take a matrix past the line and add nothing: every output keeps its bits, which the other tests hold to the oracle."""
+    import torch
+    from paper_2602_00523_amd import sage
+    assert vocab * below * 2 <= 256 << 20 < vocab * above * 2
+    g = torch.Generator(device="cuda:0")
+    g.manual_seed(rows * 1000 + k)
+    W = torch.zeros(vocab, above, device="cuda:0", dtype=torch.bfloat16)
+    H = torch.zeros(rows, above, device="cuda:0", dtype=torch.bfloat16)
+    W[:, :below] = torch.randn(vocab, below, generator=g, device="cuda:0") * (3.0 / np.sqrt(below))
+    H[:, :below] = torch.randn(rows, below, generator=g, device="cuda:0")
+    ws = torch.empty(sage.sage_lm_head_topk_workspace_bytes(rows, vocab, k), device="cuda:0", dtype=torch.uint8)
+
+    def run(dim):
+        ent, tent, alpha = (torch.full((rows,), float("nan"), device="cuda:0") for _ in range(3))
+        idx = torch.full((rows, k), -1, device="cuda:0", dtype=torch.int32)
+        prob, renorm = (torch.full((rows, k), float("nan"), device="cuda:0") for _ in range(2))
+        sage.sage_lm_head_topk(H[:, :dim].contiguous(), W[:, :dim].contiguous(), k, ent, idx, prob, renorm, tent, alpha, ws, None, 1)
+        torch.cuda.synchronize()
+        return ent, idx, prob, renorm, tent, alpha
+
+    for name, a, b in zip(("entropy", "idx", "prob", "renorm", "topk_entropy", "alpha"), run(below), run(above)):
+        assert not torch.isnan(a.float()).any() and (a >= 0).all(), name
+        assert torch.equal(a, b), name
+
+
 @pytest.mark.parametrize("rows,dim,vocab,k", [(5, 256, 1000, 10), (64, 512, 4096, 16), (1, 1024, 130, 8), (33, 128, 70, 16),
                                               (3, 128, 152064, 10), (16, 3584, 152064, 10), (2, 384, 81900, 2)])
 def test_candidate_lists_of_a_draft_row(gu, rows, dim, vocab, k):
