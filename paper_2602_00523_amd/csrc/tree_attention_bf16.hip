@@ -105,6 +105,14 @@ constexpr int PART_SLOT_B = ROWS_PER_WG * PART_ROW_B;
 __device__ __forceinline__ size_t slot_at(int slot) { return static_cast<size_t>(static_cast<unsigned>(slot)) * PART_SLOT_B; }
 constexpr int EPI_ROW_B = PART_ROW_B;    // a parked row of the epilogue has the layout of a partial row
 static_assert(ROWS_PER_WG * EPI_ROW_B <= RING_B, "the rings hold the epilogue's rows");
+// A sequence of which B have more keys and values than this is read with loads that leave nothing in the memory-side cache
+// (256 MB), if its rows are one group: a decoding step has read other layers and weights by the time they
+// come up again, and to place them there costs memory bandwidth.  Whole call, 12 nodes, us, plain / so, over enough buffers in turn that none is still
+// there: 32768 positions (134 MB) 30.0 / 27.8, 49152 41.2 / 37.5, 65536 53.1 / 49.3; eight of 4000 33.1 / 30.7, of 7000 53.2 / 48.3, of 12000 78.3 /
+// 71.3.  What has stayed there is faster to read from there, so the line lies where few such buffers could: three of 67 MB in turn
+// 17.3 / 18.8 (eight in turn 20.1 / 18.3), of 82 MB 19.4 / 21.2, of 101 MB 23.0 / 22.8; one of 134 MB again and again 25.8 / 27.2.
+// Two row groups share a block through their L2 and lose it to these loads: 64 nodes, 32768 positions, 2 to 4 % slower.
+constexpr long READ_ONCE_BYTES = 96L << 20;
 constexpr int TWO_STEP_ROWS = 128;      // groups of more rows take their reference in two steps (see the first two blocks)
 constexpr float RAISE_MIN = 4.0f;       // rebase() raises a row's reference maximum only past 2^4;
 constexpr float REBASE_PAST = 8.0f;     // it is called when a probability would pass 2^8
@@ -119,6 +127,7 @@ struct Params {
     int Hq, Hkv, G;
     int inv_G;                           // 65536 / G rounded up: (m * inv_G) >> 16 == m / G for the rows of a KV head
     float scale_log2e;                   // softmax scale times log2(e): probabilities are exp2 of scaled differences
+    int once_past;                       // sequences of more positions and one row group are read past the memory-side cache
     int B, nslot, min_blocks_per_split;
     int nrange;                          // batched launches: ranges (workgroups) per KV head
     int merge_phases;                    // merge workgroups per (sequence, KV head)
@@ -323,7 +332,8 @@ struct Segment {
 // depend on nothing of unit h, one ahead of each of its 16 scores per lane, in program order (scheduling fences).  What one
 // wave leaves open (waits, branches, the end of a unit, scalar instructions), the other wave of its SIMD fills, as far as the
 // barrier of the block lets it.
-template <bool KEYS_FIRST>
+// ONCE: the cache is read past the memory-side cache (see READ_ONCE_BYTES).
+template <bool KEYS_FIRST, bool ONCE>
 __device__ __forceinline__ void attention_pass(const Params& prm, LDS_AS Lds* lds, const Segment& sg, const int inv_G, const int tid) {
     LDS_AS unsigned char* const ring = lds->ring;
     const int lane = tid & 63;
@@ -375,7 +385,7 @@ __device__ __forceinline__ void attention_pass(const Params& prm, LDS_AS Lds* ld
         At l;
         if (h < full) l = At{in_cache, V ? v_off : k_off};
         else l = locate(is_v, h);
-        sage::lds_direct_load16(l.base, l.off, ring + (V ? V_AT + slot_of(h) * V_BLOCK_B + wave * V_GROUP : slot_of(h) * K_BLOCK_B + wave * K_GROUP));
+        sage::lds_direct_load16<ONCE>(l.base, l.off, ring + (V ? V_AT + slot_of(h) * V_BLOCK_B + wave * V_GROUP : slot_of(h) * K_BLOCK_B + wave * K_GROUP));
     };
     using IsK = std::false_type;
     using IsV = std::true_type;
@@ -615,11 +625,11 @@ __device__ __forceinline__ void attention_pass(const Params& prm, LDS_AS Lds* ld
             // (requested late in the unit: 15 nodes x 16384 positions 23.3, 22.9 and 22.3 us with the two at m = 0, at 1 and 5, at 7 and 11 on
             // a machine where the kernel before took 22.4; on others the place makes no difference)
             if (USUAL && m == 13) {
-                sage::lds_direct_load16(v_next, v_off, ring + (v_dst + (SLOT + 2) % SLOTS * V_BLOCK_B));
+                sage::lds_direct_load16<ONCE>(v_next, v_off, ring + (v_dst + (SLOT + 2) % SLOTS * V_BLOCK_B));
                 v_next += block_b;
             }
             if (USUAL && m == 15) {
-                sage::lds_direct_load16(k_next, k_off, ring + (k_dst + SLOT * K_BLOCK_B));
+                sage::lds_direct_load16<ONCE>(k_next, k_off, ring + (k_dst + SLOT * K_BLOCK_B));
                 k_next += block_b;
             }
             if (m == 0) {
@@ -779,7 +789,7 @@ __device__ __forceinline__ void attention_pass(const Params& prm, LDS_AS Lds* ld
 // The leading arguments repeat fields of prm: explicit scalar arguments are preloaded into registers at wave launch
 // (the library is built with kernel-argument preloading), so the first thing a workgroup does, fetching its sequence's
 // length and node count, does not wait for a fetch of the argument block first.
-template <bool BATCH>
+template <bool BATCH, bool ONCE>
 __device__ __forceinline__ void attention_workgroup(const int* __restrict__ kv_len_arg, const int* __restrict__ n_nodes_arg,
                                                     const int* __restrict__ first_node_arg,
                                                     const int64_t* __restrict__ kv_start_arg, int nslot_arg, int min_bps_arg,
@@ -809,7 +819,9 @@ __device__ __forceinline__ void attention_workgroup(const int* __restrict__ kv_l
         // The thread index is therefore made opaque per pass, and its derived values are recomputed.
         int tid = static_cast<int>(threadIdx.x);
         if (BATCH) asm volatile("" : "+v"(tid));
-        attention_pass<!BATCH>(prm, lds, sg, inv_G, tid);
+        // (a kernel without ONCE has one pass only: both behind a flag cost 0.15 us of 10.6 at 4096 positions, 3 % of the short batches)
+        if (ONCE && sg.L > prm.once_past && sg.rows <= ROWS_PER_WG) attention_pass<!BATCH, true>(prm, lds, sg, inv_G, tid);
+        else attention_pass<!BATCH, false>(prm, lds, sg, inv_G, tid);
     };
 
     if (!BATCH) {
@@ -884,14 +896,14 @@ __device__ __forceinline__ void attention_workgroup(const int* __restrict__ kv_l
     }
 }
 
-template <bool BATCH>
+template <bool BATCH, bool ONCE>
 __global__ __launch_bounds__(THREADS) void tree_attention_bf16_kernel(const int* __restrict__ kv_len_arg,
                                                                       const int* __restrict__ n_nodes_arg,
                                                                       const int* __restrict__ first_node_arg,
                                                                       const int64_t* __restrict__ kv_start_arg, int nslot_arg,
                                                                       int min_bps_arg, int G_arg, int B_arg, int cut_arg, int light_rows_arg, const Params prm) {
     __shared__ __align__(256) Lds lds;
-    attention_workgroup<BATCH>(kv_len_arg, n_nodes_arg, first_node_arg, kv_start_arg, nslot_arg, min_bps_arg, G_arg, B_arg, cut_arg, light_rows_arg, prm, 0,
+    attention_workgroup<BATCH, ONCE>(kv_len_arg, n_nodes_arg, first_node_arg, kv_start_arg, nslot_arg, min_bps_arg, G_arg, B_arg, cut_arg, light_rows_arg, prm, 0,
                                (LDS_AS Lds*)&lds);
 }
 
@@ -918,7 +930,7 @@ struct PlanShared {
     float& row_m;
     float& row_Z;
 };
-template <bool BATCH>
+template <bool BATCH, bool ONCE>
 __global__ __launch_bounds__(THREADS) void tree_attention_plan_kernel(const int* __restrict__ kv_len_arg,
                                                                       const int* __restrict__ n_nodes_arg,
                                                                       const int64_t* __restrict__ kv_start_arg, int nslot_arg,
@@ -938,7 +950,7 @@ __global__ __launch_bounds__(THREADS) void tree_attention_plan_kernel(const int*
         sage::plan_sequence<PLAN_OWN, THREADS>(b, pl, sh);
         return;
     }
-    attention_workgroup<BATCH>(kv_len_arg, n_nodes_arg, nullptr, kv_start_arg, nslot_arg, min_bps_arg, G_arg, B_arg, cut_arg, light_rows_arg, prm, plan_slabs,
+    attention_workgroup<BATCH, ONCE>(kv_len_arg, n_nodes_arg, nullptr, kv_start_arg, nslot_arg, min_bps_arg, G_arg, B_arg, cut_arg, light_rows_arg, prm, plan_slabs,
                                (LDS_AS Lds*)&lds.attention);   // a verify pass: every node
 }
 
@@ -1175,6 +1187,7 @@ int tree_attention_bf16(const void* Q, const void* Kc, const void* Vc, const voi
     p.nslot = sh.nslot;
     p.min_blocks_per_split = sh.min_tiles_per_split * (TILE / BLK);
     p.scale_log2e = scale * 1.4426950408889634f;
+    p.once_past = static_cast<int>(READ_ONCE_BYTES / (static_cast<long>(B) * Hkv * (2 * ROW_B)));
 
     p.nrange = sh.nrange;
     // what the kernels need to cut a sequence or a batch (see make_split and make_batch_shape)
@@ -1185,26 +1198,31 @@ int tree_attention_bf16(const void* Q, const void* Kc, const void* Vc, const voi
     static_assert(MAX_BATCH_LANES * 4L * ((1L << 25) / BLK + 2 + SEG_COST) * HEAVY_COST + TAIL_BLOCKS * LIGHT_COST < (1L << 31), "64 sequences of four groups");
     const int own_slabs = sh.batch ? p.nrange : p.nslot;
     const dim3 block(THREADS);
-    if (plan) {
-        // planning workgroups in slabs of their own ahead of the attention's: one slab whose first workgroup of every
-        // sequence plans (one sequence per launch slot), or as many slabs as B workgroups need (batches)
-        const int plan_slabs = sh.batch ? (B + Hkv - 1) / Hkv : 1;
-        const dim3 grid(Hkv, plan_slabs + own_slabs, sh.batch ? 1 : B);
-        if (sh.batch)
-            hipLaunchKernelGGL(tree_attention_plan_kernel<true>, grid, block, 0, stream, kv_len, n_nodes, kv_start, p.nslot,
-                               p.min_blocks_per_split, G, plan_slabs, B, cut, light_rows, p, *plan);
-        else
-            hipLaunchKernelGGL(tree_attention_plan_kernel<false>, grid, block, 0, stream, kv_len, n_nodes, kv_start, p.nslot,
-                               p.min_blocks_per_split, G, plan_slabs, B, cut, light_rows, p, *plan);
-    } else {
-        const dim3 grid(Hkv, own_slabs, sh.batch ? 1 : B);
-        if (sh.batch)
-            hipLaunchKernelGGL(tree_attention_bf16_kernel<true>, grid, block, 0, stream, kv_len, n_nodes, first_node, kv_start, p.nslot,
-                               p.min_blocks_per_split, G, B, cut, light_rows, p);
-        else
-            hipLaunchKernelGGL(tree_attention_bf16_kernel<false>, grid, block, 0, stream, kv_len, n_nodes, first_node, kv_start, p.nslot,
-                               p.min_blocks_per_split, G, B, cut, light_rows, p);
-    }
+    auto launch = [&](auto once) {
+        constexpr bool ONCE = decltype(once)::value;
+        if (plan) {
+            // planning workgroups in slabs of their own ahead of the attention's: one slab whose first workgroup of every
+            // sequence plans (one sequence per launch slot), or as many slabs as B workgroups need (batches)
+            const int plan_slabs = sh.batch ? (B + Hkv - 1) / Hkv : 1;
+            const dim3 grid(Hkv, plan_slabs + own_slabs, sh.batch ? 1 : B);
+            if (sh.batch)
+                hipLaunchKernelGGL((tree_attention_plan_kernel<true, ONCE>), grid, block, 0, stream, kv_len, n_nodes, kv_start, p.nslot,
+                                   p.min_blocks_per_split, G, plan_slabs, B, cut, light_rows, p, *plan);
+            else
+                hipLaunchKernelGGL((tree_attention_plan_kernel<false, ONCE>), grid, block, 0, stream, kv_len, n_nodes, kv_start, p.nslot,
+                                   p.min_blocks_per_split, G, plan_slabs, B, cut, light_rows, p, *plan);
+        } else {
+            const dim3 grid(Hkv, own_slabs, sh.batch ? 1 : B);
+            if (sh.batch)
+                hipLaunchKernelGGL((tree_attention_bf16_kernel<true, ONCE>), grid, block, 0, stream, kv_len, n_nodes, first_node, kv_start, p.nslot,
+                                   p.min_blocks_per_split, G, B, cut, light_rows, p);
+            else
+                hipLaunchKernelGGL((tree_attention_bf16_kernel<false, ONCE>), grid, block, 0, stream, kv_len, n_nodes, first_node, kv_start, p.nslot,
+                                   p.min_blocks_per_split, G, B, cut, light_rows, p);
+        }
+    };
+    if (max_kv_len > p.once_past) launch(std::true_type{});
+    else launch(std::false_type{});
     if (hipGetLastError() != hipSuccess) return SAGE_LAUNCH_FAILED;
     const int mrows = sh.batch ? MERGE_ROWS_BATCH : MERGE_ROWS_SINGLE;
     const int row_blocks = (SAGE_MAX_NODES * G + mrows - 1) / mrows;

@@ -628,6 +628,20 @@ def test_attention_bf16_merge_widths(gu, splits, B):
     run_attention_case(gu, 4200 + splits, "bf16", B, 8, 8, 128, lens, sizes=[5, 3][:B])
 
 
+@pytest.mark.parametrize("lens,sizes", [([24576], [9]), ([24577], [9]), ([24700], [33]), ([8193, 8192, 8300], [9, 20, 40])])
+def test_attention_bf16_of_long_caches(gu, lens, sizes):
+    """Sequences at and past the length from which the cache is read with other loads (24576 positions of 8 KV heads, by the number of
+    sequences), of one and of two row groups, alone and beside shorter ones; the launch that carries planning along gives the same bits."""
+    B, Hq, Hkv, d = len(lens), 64, 8, 128
+    run_attention_case(gu, 4400 + lens[0], "bf16", B, Hq, Hkv, d, lens, sizes=sizes)
+    inp = wl.attention_inputs(4400 + lens[0], B, Hq, Hkv, d, lens, "bf16", pad_tokens=3)
+    mask, nn = tree_batch(wl.rng(4400 + lens[0]), B, sizes)
+    _, raw = gu.gpu_tree_attention(inp, mask, nn, Hq, Hkv, d)
+    x = wl.gaussian(4400, (B, 5000), "bf16", 3.0)
+    O, _, _ = gu.gpu_attention_with_plan(inp, mask, nn, Hq, Hkv, d, x, 8, wl.CONFIGS["toy"]["tree"])
+    assert (gu.to_host(raw) == O).all()
+
+
 @pytest.mark.parametrize("nodes", [4, 16, 17, 32, 33])
 @pytest.mark.parametrize("blocks,tail", [(1, 0), (1, 31), (2, 1), (3, 16), (4, 0), (5, 31), (7, 1)])
 def test_attention_bf16_pass_lengths(gu, nodes, blocks, tail):
