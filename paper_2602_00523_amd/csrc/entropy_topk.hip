@@ -20,21 +20,39 @@ namespace {
 
 constexpr int THREADS = 256;
 constexpr int EPT = 16;                  // logits per lane
+// The greedy first pass over rows that are more than this, live or not, reads them with loads that leave nothing in the memory-side cache (256 MB):
+// nobody reads the logits again.  Whole call, 152064 logits, us, plain / so: 512 live rows in groups of 64 38.6 / 36.5 (with the 156 MB
+// written just before, copy included, 92.6 / 86.9), 512 rows 33.0 / 31.8 (86.7 / 80.1), fp32 58.9 / 54.3, fp32 30 rows in each of eight groups 29.9 / 27.8, 1024
+// rows 60.3 / 59.6.  What has stayed in that cache from a call before is read faster from there: 384 rows (117 MB), three buffers in turn, 24.5 /
+// 25.0; past the line, of groups mostly dead: 30 live in each of eight, two buffers in turn, 19.4 / 20.1, 12 live 11.15 / 11.2, fp32 14.1 / 14.5.  (To
+// decide by the live rows of a group, in the kernel, cost 12 live rows 0.4 us.)
+constexpr long READ_ONCE_BYTES = 128L << 20;
 constexpr int UNIT = 64 * EPT;           // logits per wave
 constexpr int WAVES = THREADS / 64;
 
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+template <typename Raw>
+__device__ __forceinline__ Raw load_once(const void* p) { return __builtin_bit_cast(Raw, __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(p))); }
 template <typename T> struct Loader;
 template <> struct Loader<float> {
     static constexpr int VEC = 4;   // elements per 16-byte load
     using Raw = float4;
-    __device__ static Raw fetch(const float* p) { return *reinterpret_cast<const float4*>(p); }
+    template <bool ONCE>
+    __device__ static Raw fetch(const float* p) {
+        if constexpr (ONCE) return load_once<Raw>(p);
+        else return *reinterpret_cast<const Raw*>(p);
+    }
     __device__ static void unpack(Raw v, float* out) { out[0] = v.x; out[1] = v.y; out[2] = v.z; out[3] = v.w; }
     __device__ static float one(const float* p) { return *p; }
 };
 template <> struct Loader<uint16_t> {
     static constexpr int VEC = 8;
     using Raw = uint4;
-    __device__ static Raw fetch(const uint16_t* p) { return *reinterpret_cast<const uint4*>(p); }
+    template <bool ONCE>
+    __device__ static Raw fetch(const uint16_t* p) {
+        if constexpr (ONCE) return load_once<Raw>(p);
+        else return *reinterpret_cast<const Raw*>(p);
+    }
     __device__ static void unpack(Raw v, float* out) {
         const uint32_t w[4] = {v.x, v.y, v.z, v.w};
 #pragma unroll
@@ -56,19 +74,19 @@ template <> struct Loader<uint16_t> {
 //
 // The 16-byte loads of a (row, slice) are requested by request_unit and consumed by reduce_unit, so that a wave that
 // walks several rows can have the next row's loads in flight while it reduces the current one.
-template <typename T, int NV>
+template <typename T, int NV, bool ONCE = false>
 __device__ __forceinline__ void request_unit(const T* __restrict__ rowp, int base, int lane, int vocab,
                                              typename Loader<T>::Raw (&raw)[NV]) {
     using L = Loader<T>;
     if (base + UNIT <= vocab) {                          // a whole slice (wave-uniform)
 #pragma unroll
-        for (int j = 0; j < NV; ++j) raw[j] = L::fetch(rowp + base + (j * 64 + lane) * L::VEC);
+        for (int j = 0; j < NV; ++j) raw[j] = L::template fetch<ONCE>(rowp + base + (j * 64 + lane) * L::VEC);
         return;
     }
 #pragma unroll
     for (int j = 0; j < NV; ++j) {
         const int e0 = base + (j * 64 + lane) * L::VEC;
-        if (e0 + L::VEC <= vocab) raw[j] = L::fetch(rowp + e0);      // the ragged end is read element by element later
+        if (e0 + L::VEC <= vocab) raw[j] = L::template fetch<ONCE>(rowp + e0);      // the ragged end is read element by element later
     }
 }
 // The largest of three numbers, a NaN if one of them is none, so that one compare a slice says whether its maximum is to be taken again
@@ -192,7 +210,7 @@ __device__ __forceinline__ Reduced reduce_unit(const T* __restrict__ rowp, int b
 }
 
 // Every row is valid (n_valid == null): grid (slices / 4, rows).
-template <typename T>
+template <typename T, bool ONCE>
 __global__ __launch_bounds__(THREADS) void slice_kernel(const T* __restrict__ logits, int vocab, long row_stride, int nunits,
                                                         UnitStats* __restrict__ stats, uint64_t* __restrict__ keys) {
     constexpr int NV = EPT / Loader<T>::VEC;
@@ -202,7 +220,7 @@ __global__ __launch_bounds__(THREADS) void slice_kernel(const T* __restrict__ lo
     const int lane = threadIdx.x & 63;
     const T* rowp = logits + static_cast<long>(row) * row_stride;
     typename Loader<T>::Raw raw[NV];
-    request_unit<T, NV>(rowp, unit * UNIT, lane, vocab, raw);
+    request_unit<T, NV, ONCE>(rowp, unit * UNIT, lane, vocab, raw);
     const long o = static_cast<long>(row) * nunits + unit;
     reduce_unit<T, NV>(rowp, unit * UNIT, lane, vocab, raw, stats + o, keys + o);
 }
@@ -223,7 +241,7 @@ inline int row_phases(int groups, int rows_per_group, bool in_a_step) {
     const int phases = groups == 1 ? 64 : groups == 2 ? 32 : in_a_step ? 16 : 22;
     return rows_per_group < phases ? rows_per_group : phases;
 }
-template <typename T>
+template <typename T, bool ONCE>
 __device__ __forceinline__ void slice_rows_block(const T* __restrict__ logits, int vocab, long row_stride,
                                                  const int* __restrict__ n_valid, int rows_per_group, int rows, int nunits,
                                                  UnitStats* __restrict__ stats, uint64_t* __restrict__ keys, int block_x,
@@ -237,11 +255,11 @@ __device__ __forceinline__ void slice_rows_block(const T* __restrict__ logits, i
     const int base = unit * UNIT;
     const long row0 = static_cast<long>(group) * rows_per_group;
     typename Loader<T>::Raw cur[NV], nxt[NV];
-    request_unit<T, NV>(logits + (row0 + r) * row_stride, base, lane, vocab, cur);
+    request_unit<T, NV, ONCE>(logits + (row0 + r) * row_stride, base, lane, vocab, cur);
     while (true) {
         const int rn = r + phases;
         const bool more = rn < n;                            // wave-uniform
-        if (more) request_unit<T, NV>(logits + (row0 + rn) * row_stride, base, lane, vocab, nxt);
+        if (more) request_unit<T, NV, ONCE>(logits + (row0 + rn) * row_stride, base, lane, vocab, nxt);
         const long o = (row0 + r) * nunits + unit;
         reduce_unit<T, NV>(logits + (row0 + r) * row_stride, base, lane, vocab, cur, stats + o, keys + o);
         if (!more) break;
@@ -249,12 +267,12 @@ __device__ __forceinline__ void slice_rows_block(const T* __restrict__ logits, i
         r = rn;
     }
 }
-template <typename T>
+template <typename T, bool ONCE>
 __global__ __launch_bounds__(THREADS) void slice_rows_kernel(const T* __restrict__ logits, int vocab, long row_stride,
                                                              const int* __restrict__ n_valid, int rows_per_group, int rows,
                                                              int nunits, UnitStats* __restrict__ stats,
                                                              uint64_t* __restrict__ keys) {
-    slice_rows_block<T>(logits, vocab, row_stride, n_valid, rows_per_group, rows, nunits, stats, keys, blockIdx.x, blockIdx.y,
+    slice_rows_block<T, ONCE>(logits, vocab, row_stride, n_valid, rows_per_group, rows, nunits, stats, keys, blockIdx.x, blockIdx.y,
                         gridDim.y, blockIdx.z);
 }
 
@@ -628,7 +646,7 @@ __global__ __launch_bounds__(THREADS) void slice_pair_kernel(const T* __restrict
         }
         return;
     }
-    slice_rows_block<T>(logits_a, vocab, row_stride_a, n_valid_a, rows_per_group_a, rows_a, nunits, stats_a, keys_a, blockIdx.x,
+    slice_rows_block<T, false>(logits_a, vocab, row_stride_a, n_valid_a, rows_per_group_a, rows_a, nunits, stats_a, keys_a, blockIdx.x,
                         y - ahead, static_cast<int>(gridDim.y) - ahead, z - slabs_b);
 }
 
@@ -879,6 +897,12 @@ static int check_first_pass(const void* logits, int dtype, int rows, int vocab, 
     return SAGE_OK;
 }
 
+template <typename F>
+static void with_loads(const void* logits, int dtype, bool once, F launch) {
+    auto of = [&](auto* x) { if (once) launch(x, std::true_type{}); else launch(x, std::false_type{}); };
+    if (dtype == SAGE_F32) of(static_cast<const float*>(logits));
+    else of(static_cast<const uint16_t*>(logits));
+}
 // Argument checks and the first pass, common to sage_entropy_topk and sage_entropy_topk_slices.
 static int run_first_pass(const void* logits, int dtype, int rows, int vocab, long row_stride, int k, const int* n_valid,
                           int rows_per_group, void* workspace, size_t workspace_bytes, hipStream_t s) {
@@ -887,23 +911,23 @@ static int run_first_pass(const void* logits, int dtype, int rows, int vocab, lo
     const int nunits = num_units(vocab);
     UnitStats* stats = static_cast<UnitStats*>(workspace);
     uint64_t* keys = reinterpret_cast<uint64_t*>(static_cast<char*>(workspace) + stats_bytes(rows, vocab));
+    const bool once = static_cast<long>(rows) * vocab * (dtype == SAGE_F32 ? 4 : 2) > READ_ONCE_BYTES;
     if (k == 1 && !n_valid) {                        // many rows, one round: a wave per slice, 16 logits per lane
         const dim3 grid((nunits + WAVES - 1) / WAVES, rows);
-        if (dtype == SAGE_F32)
-            hipLaunchKernelGGL(slice_kernel<float>, grid, dim3(THREADS), 0, s, static_cast<const float*>(logits), vocab,
-                               row_stride, nunits, stats, keys);
-        else
-            hipLaunchKernelGGL(slice_kernel<uint16_t>, grid, dim3(THREADS), 0, s, static_cast<const uint16_t*>(logits),
-                               vocab, row_stride, nunits, stats, keys);
+        auto launch = [&](auto* x, auto once) {
+            using T = std::remove_const_t<std::remove_pointer_t<decltype(x)>>;
+            hipLaunchKernelGGL((slice_kernel<T, decltype(once)::value>), grid, dim3(THREADS), 0, s, x, vocab, row_stride, nunits, stats, keys);
+        };
+        with_loads(logits, dtype, once, launch);
     } else if (k == 1) {                             // grouped rows: workgroups walk the live rows of their group
         const int groups = (rows + rows_per_group - 1) / rows_per_group;
         const dim3 grid((nunits + WAVES - 1) / WAVES, row_phases(groups, rows_per_group, false), groups);
-        if (dtype == SAGE_F32)
-            hipLaunchKernelGGL(slice_rows_kernel<float>, grid, dim3(THREADS), 0, s, static_cast<const float*>(logits), vocab,
-                               row_stride, n_valid, rows_per_group, rows, nunits, stats, keys);
-        else
-            hipLaunchKernelGGL(slice_rows_kernel<uint16_t>, grid, dim3(THREADS), 0, s, static_cast<const uint16_t*>(logits),
-                               vocab, row_stride, n_valid, rows_per_group, rows, nunits, stats, keys);
+        auto launch = [&](auto* x, auto once) {
+            using T = std::remove_const_t<std::remove_pointer_t<decltype(x)>>;
+            hipLaunchKernelGGL((slice_rows_kernel<T, decltype(once)::value>), grid, dim3(THREADS), 0, s, x, vocab, row_stride, n_valid, rows_per_group, rows,
+                               nunits, stats, keys);
+        };
+        with_loads(logits, dtype, once, launch);
     } else if (k <= WAVE_MAX_K) {                    // few rows, short lists: a wave per slice
         const dim3 grid((nunits + WAVES - 1) / WAVES, rows);
         if (dtype == SAGE_F32)

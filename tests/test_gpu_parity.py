@@ -201,6 +201,34 @@ def test_topk_by_waves(gu, vocab, k, dtype):
     np.testing.assert_allclose(g1["entropy"], o1["entropy"], rtol=1e-5, atol=1e-5)
 
 
+@pytest.mark.parametrize("rows,vocab,dtype", [(448, 152061, "bf16"), (224, 152061, "f32"), (900, 80000, "bf16")])
+@pytest.mark.parametrize("grouped", [False, True])
+def test_greedy_rows_of_many_logits(gu, rows, vocab, dtype, grouped):
+    """More than 128 MB of logits are read with other loads: every row has the bits that it has in a call over half of the rows, which the
+    other tests hold to the oracle."""
+    import torch
+    from paper_2602_00523_amd import sage
+    half, esz, rpg = rows // 2, 4 if dtype == "f32" else 2, 56 if rows < 900 else 50
+    assert half * vocab * esz <= 128 << 20 < rows * vocab * esz
+    g = torch.Generator(device="cuda:0")
+    g.manual_seed(vocab + rows)
+    x = (torch.randn(rows, -(-vocab // 8) * 8, generator=g, device="cuda:0") * 3.0).to(torch.float32 if dtype == "f32" else torch.bfloat16)[:, :vocab]
+    live = torch.tensor([1 + 11 * i % rpg for i in range(rows // rpg)], device="cuda:0", dtype=torch.int32) if grouped else None
+    ws = torch.empty(sage.sage_entropy_topk_workspace_bytes(rows, vocab, 1), device="cuda:0", dtype=torch.uint8)
+
+    def run(n):
+        ent = torch.full((n,), -1.0, device="cuda:0")
+        idx = torch.full((n, 1), -1, device="cuda:0", dtype=torch.int32)
+        sage.sage_entropy_topk(x[:n], 1, ent, idx, None, None, None, None, ws, live, rpg if grouped else 1)
+        torch.cuda.synchronize()
+        return ent, idx
+
+    (e, i), (eh, ih) = run(rows), run(half)
+    assert torch.equal(e[:half], eh) and torch.equal(i[:half], ih) and (ih >= 0).any()
+    counted = torch.ones(rows, dtype=torch.bool, device="cuda:0") if live is None else torch.arange(rows, device="cuda:0") % rpg < live.repeat_interleave(rpg)
+    assert (i[~counted] == -1).all() and (i[counted, 0].long() == x[counted].max(-1).values[:, None].eq(x[counted]).int().argmax(-1)).all()
+
+
 @pytest.mark.parametrize("rows,rpg,n_valid,vocab,dtype", [
     (150, 64, [64, 33, 22], 5000, "f32"),            # a short last group (22 rows): every one of its rows counts
     (150, 64, [17, 0, 99], 70008, "bf16"),           # n_valid beyond the group's rows is clamped
